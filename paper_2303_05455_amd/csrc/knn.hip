@@ -1,9 +1,5 @@
-// Exact brute-force k nearest neighbours on gfx950: the input preparation
-// of the loop (the thesis builds its kNN graphs with an approximate GPU
-// library; here the graph is exact).
-//
-// Order: squared Euclidean distance, ties to the lower index, the query
-// itself excluded.
+// Inverted-file (approximate) k nearest neighbours on gfx950, and the
+// operand scale and scans shared with the exact search (knn_filter.hip).
 //
 // Dot products on the FP16 matrix cores with FP32 accumulation, at close to
 // FP32 accuracy: every coordinate, scaled by a power of two so the largest
@@ -11,24 +7,20 @@
 // lo = fp16(x - hi) (22 significant bits together), and
 //     q.x ~= hi_q.hi_x + hi_q.lo_x + lo_q.hi_x
 // (the dropped lo.lo term is below 2^-22 of |q_k x_k|; each fp16 product is
-// exact in FP32).  Three v_mfma_f32_16x16x32_f16 per product block give
-// about 5x the throughput of the FP32 matrix path.
+// exact in FP32).
 //
-// A block of 256 threads (4 waves) owns 128 queries and sweeps all
-// candidates: for padded widths up to 128 in tiles of 64 with the queries'
-// operands held in registers (knn_small_kernel), above that in tiles of 128,
-// K in steps of 32 staged in LDS (knn_kernel); K is contiguous per LDS row,
-// so one lane's operand, 8 consecutive k, is one 16-byte read.  The
-// ranking score |x_c|^2 - 2 q.x_c (|q|^2 is the same for the whole row) goes
-// to an LDS score tile, where two threads per query row keep running top-KP
-// lists in registers.  At the end
-// the two lists are merged and the KP survivors are re-ranked by their exact
-// FP32 distance sum_k (q_k - x_k)^2, which removes the cancellation error of
-// the expanded form; KP >= k + 4 leaves room for candidates the score
-// misranks.
+// Tiles of 128 queries x 128 points, K in steps of 32 staged in LDS; K is
+// contiguous per LDS row, so one lane's operand, 8 consecutive k, is one
+// 16-byte read.  The ranking score |x_c|^2 - 2 q.x_c (|q|^2 is the same for
+// the whole row) goes to an LDS score tile, where two threads per query row
+// keep running top-KP lists in registers.  At the end the two lists are
+// merged and the KP survivors are re-ranked by their exact FP32 distance
+// sum_k (q_k - x_k)^2, which removes the cancellation error of the expanded
+// form; KP >= k + 4 leaves room for candidates the score misranks.
 #include <cfloat>
 
 #include "ivhd_internal.h"
+#include "knn_rank.h"
 
 namespace ivhd {
 namespace {
@@ -37,16 +29,12 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
 
 constexpr int QB = 128;        // queries per block
-constexpr int CB = 64;         // candidates per tile
 constexpr int TKK = 32;        // features per staged step
 constexpr int HP = TKK + 8;    // LDS row pitch in halves (80 bytes, 16-byte aligned rows)
-constexpr int SP = CB + 4;     // score tile pitch (floats; rows 16-byte aligned)
+constexpr int CBW = 128;       // points per tile
+constexpr int SPW = CBW + 4;   // score tile pitch (floats; rows 16-byte aligned)
 constexpr int kKnnThreads = 256;
 constexpr int kSplitMaxExp = 14;   // scaled magnitudes stay below 2^14
-
-__device__ __forceinline__ bool pair_less(float a, int32_t ia, float b, int32_t ib) {
-  return a < b || (a == b && ia < ib);
-}
 
 template <int KP>
 __device__ __forceinline__ void list_insert(float (&ks)[KP], int32_t (&ki)[KP], float s, int32_t j) {
@@ -76,17 +64,35 @@ __global__ void __launch_bounds__(256) row_norms_kernel(const float *__restrict_
 }
 
 // largest |x| (as the bits of a non-negative float, so integer max is float
-// max); NaN sets the top bits and is reported by the host
+// max); NaN sets the top bits and is reported by the host.  16-byte loads
+// over the aligned middle, four in flight: 103 -> 40 us for 400,000 x 100.
 __global__ void __launch_bounds__(256) absmax_kernel(const float *__restrict__ X, int64_t n, uint32_t *out) {
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x, t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  int64_t head = (4 - (int64_t)(reinterpret_cast<uintptr_t>(X) / 4 & 3)) & 3;
+  if (head > n) head = n;
+  const u32x4 *V = reinterpret_cast<const u32x4 *>(X + head);
+  const int64_t nv = (n - head) / 4;
   uint32_t m = 0;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
-    const uint32_t u = __float_as_uint(X[e]) & 0x7fffffffu;
+  auto take = [&](uint32_t u) {
+    u &= 0x7fffffffu;
     m = u > m ? u : m;
+  };
+#pragma unroll 4
+  for (int64_t e = t; e < nv; e += stride) {
+    const u32x4 v = V[e];
+    take(v.x);
+    take(v.y);
+    take(v.z);
+    take(v.w);
   }
+  if (t < head) take(__float_as_uint(X[t]));
+  const int64_t tail = head + 4 * nv + t;
+  if (tail < n) take(__float_as_uint(X[tail]));
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
-    const uint32_t t = __shfl_xor(m, o, 64);
-    m = t > m ? t : m;
+    const uint32_t w = __shfl_xor(m, o, 64);
+    m = w > m ? w : m;
   }
   if ((threadIdx.x & 63) == 0) atomicMax(out, m);
 }
@@ -104,31 +110,6 @@ __global__ void split_kernel(const float *__restrict__ X, int64_t M, int N, int 
   lo[e] = (_Float16)(x - (float)h);
 }
 
-// Ranks the CW scores of one thread's half row (sS row `row`, candidates
-// cbase..cbase+CW-1, in order) into its list.  A group of four whose
-// smallest score lies above the list's last entry is passed over at once:
-// none of them could enter the list, so the list ends as if each had been
-// offered.  (Lists of 32 keep a one-by-one scan of alternate columns: the
-// group test costs registers they do not have.)
-template <int KP, int CW>
-__device__ __forceinline__ void scan_half_row(const float *__restrict__ row, int64_t cbase, int64_t M,
-                                              int64_t my_self, float (&ks)[KP], int32_t (&ki)[KP]) {
-#pragma unroll 1
-  for (int m = 0; m < CW; m += 4) {
-    floatx4 v = *reinterpret_cast<const floatx4 *>(row + m);
-    const float lo = fminf(fminf(v.x, v.y), fminf(v.z, v.w));
-    if (lo > ks[KP - 1]) continue;
-#pragma unroll 1
-    for (int e = 0; e < 4; ++e) {   // one insertion body, the group rotated through it
-      const float se = v.x;
-      v = v.yzwx;
-      const int64_t c = cbase + m + e;
-      if (c >= M || c == my_self) continue;
-      list_insert<KP>(ks, ki, se, (int32_t)c);
-    }
-  }
-}
-
 // Exact FP32 squared distances of a block's (row, survivor) pairs: mI
 // [QB][KP] holds the survivors' ids (INT32_MAX: none), mS receives the
 // distances; the pairs are spread over the whole block, the features taken in
@@ -138,35 +119,12 @@ template <int KP, typename QRowOf>
 __device__ __forceinline__ void rerank_pairs(float *__restrict__ mS, const int32_t *__restrict__ mI,
                                              const float *__restrict__ Q, const float *__restrict__ X, int N,
                                              QRowOf qrow_of) {
-  const bool vec4 = N % 4 == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0 &&
-                    (reinterpret_cast<uintptr_t>(Q) & 15) == 0;
+  const bool vec4 = rows_are_vec4(X, Q, N);
 #pragma unroll 1
   for (int t = threadIdx.x; t < QB * KP; t += kKnnThreads) {
     const int32_t id = mI[t];
     float d = FLT_MAX;
-    if (id != INT32_MAX) {
-      const float *qr = Q + qrow_of(t / KP) * N, *xr = X + (int64_t)id * N;
-      d = 0.f;
-      if (vec4) {
-        for (int kk = 0; kk < N; kk += 4) {
-          const float4 u = *reinterpret_cast<const float4 *>(qr + kk);
-          const float4 v = *reinterpret_cast<const float4 *>(xr + kk);
-          float e = u.x - v.x;
-          d += e * e;
-          e = u.y - v.y;
-          d += e * e;
-          e = u.z - v.z;
-          d += e * e;
-          e = u.w - v.w;
-          d += e * e;
-        }
-      } else {
-        for (int kk = 0; kk < N; ++kk) {
-          const float e = qr[kk] - xr[kk];
-          d += e * e;
-        }
-      }
-    }
+    if (id != INT32_MAX) d = exact_distance(Q + qrow_of(t / KP) * N, X + (int64_t)id * N, N, vec4);
     mS[t] = d;
   }
 }
@@ -189,332 +147,14 @@ __device__ __forceinline__ void sort_row(float *__restrict__ rs, int32_t *__rest
   }
 }
 
-// End of a query block: the two running lists of each row are merged
-// (through LDS, sS holding at least 2 QB KP words), the survivors are
-// re-ranked by their exact FP32 distances (the whole block computing them)
-// and the best k written out.
-template <int KP>
-__device__ __forceinline__ void finish_rows(float *sS, float (&ks)[KP], int32_t (&ki)[KP], int my_row, int half,
-                                            int64_t my_q, int64_t nq, const float *__restrict__ Q,
-                                            const float *__restrict__ X, int N, int k,
-                                            int32_t *__restrict__ out_idx, float *__restrict__ out_dist) {
-  __syncthreads();
-  float *mS = sS;                                // [QB][KP] scores
-  int32_t *mI = (int32_t *)(sS + QB * KP);       // [QB][KP] indices
-  if (half == 1) {
-#pragma unroll
-    for (int p = 0; p < KP; ++p) { mS[my_row * KP + p] = ks[p]; mI[my_row * KP + p] = ki[p]; }
-  }
-  __syncthreads();
-  if (half == 0 && my_q < nq) {
-#pragma unroll
-    for (int p = 0; p < KP; ++p) list_insert<KP>(ks, ki, mS[my_row * KP + p], mI[my_row * KP + p]);
-  }
-  __syncthreads();   // the other half's list has been read
-  if (half == 0) {
-#pragma unroll
-    for (int p = 0; p < KP; ++p) mI[my_row * KP + p] = my_q < nq ? ki[p] : INT32_MAX;
-  }
-  __syncthreads();
-  const int64_t q0 = my_q - my_row;
-  rerank_pairs<KP>(mS, mI, Q, X, N, [&](int r) { return q0 + r; });
-  __syncthreads();
-  if (half == 0 && my_q < nq) {
-    float *rs = mS + my_row * KP;
-    int32_t *ri = mI + my_row * KP;
-    sort_row<KP>(rs, ri);
-#pragma unroll 1
-    for (int p = 0; p < k; ++p) {
-      out_idx[my_q * k + p] = ri[p] == INT32_MAX ? -1 : ri[p];
-      if (out_dist) out_dist[my_q * k + p] = rs[p];
-    }
-  }
-}
-
-// Wide data: a block owns 128 queries and sweeps the candidates in tiles of
-// CBW = 128; wave (wq, wc) computes the 64 x 64 quarter rows 64 wq.., columns
-// 64 wc.. of each tile, so every staged operand byte feeds twice the MFMAs
-// of a 64-candidate tile.  The operand rows of K step s + 1 are loaded into
-// registers during the MFMAs of step s.
-constexpr int CBW = 128;        // candidates per tile (wide kernel)
-constexpr int SPW = CBW + 4;    // its score tile pitch (floats; rows 16-byte aligned)
-
-struct WideFrag {
-  halfx8 qh[2], ql[2], ch[2], cl[2];   // 128 query and 128 candidate rows x 8 features per thread
-};
-
-__device__ __forceinline__ void load_wide(WideFrag &F, const _Float16 *__restrict__ Qh,
-                                          const _Float16 *__restrict__ Ql, int64_t nq, int64_t q0,
-                                          const _Float16 *__restrict__ Xh, const _Float16 *__restrict__ Xl,
-                                          int64_t M, int64_t c0, int Np, int k0) {
-  const int kc = (threadIdx.x & 3) * 8;
-#pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    const int r = (threadIdx.x + kKnnThreads * c) >> 2;
-    const bool okq = q0 + r < nq, okc = c0 + r < M;
-    F.qh[c] = okq ? *reinterpret_cast<const halfx8 *>(Qh + (q0 + r) * Np + k0 + kc) : halfx8{};
-    F.ql[c] = okq ? *reinterpret_cast<const halfx8 *>(Ql + (q0 + r) * Np + k0 + kc) : halfx8{};
-    F.ch[c] = okc ? *reinterpret_cast<const halfx8 *>(Xh + (c0 + r) * Np + k0 + kc) : halfx8{};
-    F.cl[c] = okc ? *reinterpret_cast<const halfx8 *>(Xl + (c0 + r) * Np + k0 + kc) : halfx8{};
-  }
-}
-
-__device__ __forceinline__ void store_wide(const WideFrag &F, _Float16 *sQh, _Float16 *sQl, _Float16 *sCh,
-                                           _Float16 *sCl) {
-  const int kc = (threadIdx.x & 3) * 8;
-#pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    const int r = (threadIdx.x + kKnnThreads * c) >> 2;
-    *reinterpret_cast<halfx8 *>(sQh + r * HP + kc) = F.qh[c];
-    *reinterpret_cast<halfx8 *>(sQl + r * HP + kc) = F.ql[c];
-    *reinterpret_cast<halfx8 *>(sCh + r * HP + kc) = F.ch[c];
-    *reinterpret_cast<halfx8 *>(sCl + r * HP + kc) = F.cl[c];
-  }
-}
-
-// self_mode: 0 = no exclusion, 1 = query q excludes candidate q, 2 = self[q]
-template <int KP>
-__global__ void __launch_bounds__(kKnnThreads, 2)
-knn_kernel(const float *__restrict__ X, int64_t M, int N, const float *__restrict__ Q, int64_t nq,
-           const _Float16 *__restrict__ Xh, const _Float16 *__restrict__ Xl, const _Float16 *__restrict__ Qh,
-           const _Float16 *__restrict__ Ql, int Np, float inv_scale2, int self_mode,
-           const int32_t *__restrict__ self, const float *__restrict__ cnorm, int k,
-           int32_t *__restrict__ out_idx, float *__restrict__ out_dist) {
-  // one LDS area: the operand tiles during the K loop, then the score tile
-  __shared__ __attribute__((aligned(16))) float smem[QB * SPW];
-  static_assert((2 * QB + 2 * CBW) * HP * 2 <= QB * SPW * 4, "operand tiles must fit in the score tile");
-  static_assert(2 * QB * 32 <= QB * SPW, "merge buffers must fit in the score tile");
-  _Float16 *sQh = reinterpret_cast<_Float16 *>(smem);
-  _Float16 *sQl = sQh + QB * HP;
-  _Float16 *sCh = sQl + QB * HP;
-  _Float16 *sCl = sCh + CBW * HP;
-  float *sS = smem;
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int wq = 64 * (wave >> 1), wc = 64 * (wave & 1);
-  const int64_t q0 = (int64_t)blockIdx.x * QB;
-
-  // scan ownership: two threads per query row (halves of the columns, or
-  // alternate columns for 32-entry lists)
-  const int my_row = tid >> 1;
-  const int half = tid & 1;
-  const int64_t my_q = q0 + my_row;
-  int64_t my_self = -1;
-  if (my_q < nq) my_self = self_mode == 1 ? my_q : (self_mode == 2 ? (int64_t)self[my_q] : -1);
-
-  float ks[KP];
-  int32_t ki[KP];
-#pragma unroll
-  for (int p = 0; p < KP; ++p) { ks[p] = FLT_MAX; ki[p] = INT32_MAX; }
-
-  const int kq = (lane >> 4) * 8;
-  static_assert(QB * (TKK / 8) == 2 * kKnnThreads && CBW * (TKK / 8) == 2 * kKnnThreads, "fragment shape");
-  WideFrag F;
-  load_wide(F, Qh, Ql, nq, q0, Xh, Xl, M, 0, Np, 0);
-  for (int64_t c0 = 0; c0 < M; c0 += CBW) {
-    floatx4 acc[4][4];
-#pragma unroll
-    for (int rb = 0; rb < 4; ++rb)
-#pragma unroll
-      for (int cb = 0; cb < 4; ++cb) acc[rb][cb] = floatx4{0.f, 0.f, 0.f, 0.f};
-
-    for (int k0 = 0; k0 < Np; k0 += TKK) {
-      __syncthreads();   // the previous step's operands, or the previous tile's scores, are consumed
-      store_wide(F, sQh, sQl, sCh, sCl);
-      __syncthreads();
-      {  // prefetch the next step: the next K slice, or the first of the next tile
-        int64_t nc0 = c0;
-        int nk0 = k0 + TKK;
-        if (nk0 >= Np) {
-          nk0 = 0;
-          nc0 = c0 + CBW;
-        }
-        if (nc0 < M) load_wide(F, Qh, Ql, nq, q0, Xh, Xl, M, nc0, Np, nk0);
-      }
-      halfx8 ah[4], al[4];
-#pragma unroll
-      for (int rb = 0; rb < 4; ++rb) {
-        const int r = wq + 16 * rb + (lane & 15);
-        ah[rb] = *reinterpret_cast<const halfx8 *>(sQh + r * HP + kq);
-        al[rb] = *reinterpret_cast<const halfx8 *>(sQl + r * HP + kq);
-      }
-#pragma unroll
-      for (int cb = 0; cb < 4; ++cb) {
-        const int r = wc + 16 * cb + (lane & 15);
-        const halfx8 bh = *reinterpret_cast<const halfx8 *>(sCh + r * HP + kq);
-        const halfx8 bl = *reinterpret_cast<const halfx8 *>(sCl + r * HP + kq);
-#pragma unroll
-        for (int rb = 0; rb < 4; ++rb) {
-          acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[rb], bh, acc[rb][cb], 0, 0, 0);
-          acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[rb], bl, acc[rb][cb], 0, 0, 0);
-          acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al[rb], bh, acc[rb][cb], 0, 0, 0);
-        }
-      }
-    }
-    __syncthreads();   // operands dead: the area becomes the score tile
-
-    // scores: D[i][j] of a 16x16 block sits in lane j + 16 (i / 4), register i % 4
-#pragma unroll
-    for (int cb = 0; cb < 4; ++cb) {
-      const int col = wc + 16 * cb + (lane & 15);
-      const int64_t c = c0 + col;
-      const float cn = c < M ? cnorm[c] : 0.f;
-#pragma unroll
-      for (int rb = 0; rb < 4; ++rb)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int row = wq + 16 * rb + 4 * (lane >> 4) + r;
-          sS[row * SPW + col] = cn - 2.f * (acc[rb][cb][r] * inv_scale2);
-        }
-    }
-    __syncthreads();
-    if (my_q < nq) {
-      if constexpr (KP >= 32) {
-        for (int m = 0; m < CBW / 2; ++m) {
-          const int col = 2 * m + half;
-          const int64_t c = c0 + col;
-          if (c >= M || c == my_self) continue;
-          list_insert<KP>(ks, ki, sS[my_row * SPW + col], (int32_t)c);
-        }
-      } else
-        scan_half_row<KP, CBW / 2>(sS + my_row * SPW + half * (CBW / 2), c0 + half * (CBW / 2), M, my_self, ks,
-                                   ki);
-    }
-  }
-  finish_rows<KP>(sS, ks, ki, my_row, half, my_q, nq, Q, X, N, k, out_idx, out_dist);
-}
-
-// Narrow data (padded width Np = 32 NS <= 128): each wave keeps its 32
-// query rows' hi / lo fragments for all NS K steps in registers for the whole
-// sweep, so only the candidate tile is staged, once per tile: its rows for
-// the next tile are loaded into registers while this tile is multiplied and
-// ranked, and a tile costs two barriers instead of two per K step.  Same
-// MFMA sequence per score (K steps in order, hi.hi, hi.lo, lo.hi), so the
-// scores, and the answers, are those of knn_kernel.
-constexpr int kSmallPitch = 4 * TKK + 8;   // candidate tile pitch in halves (NS <= 4)
-
-template <int KP, int NS>
-__global__ void __launch_bounds__(kKnnThreads, 2)
-knn_small_kernel(const float *__restrict__ X, int64_t M, int N, const float *__restrict__ Q, int64_t nq,
-                 const _Float16 *__restrict__ Xh, const _Float16 *__restrict__ Xl,
-                 const _Float16 *__restrict__ Qh, const _Float16 *__restrict__ Ql, float inv_scale2,
-                 int self_mode, const int32_t *__restrict__ self, const float *__restrict__ cnorm, int k,
-                 int32_t *__restrict__ out_idx, float *__restrict__ out_dist) {
-  constexpr int Np = NS * TKK;
-  __shared__ __attribute__((aligned(16))) float sS[QB * SP];
-  __shared__ __attribute__((aligned(16))) _Float16 sCh[CB * kSmallPitch];
-  __shared__ __attribute__((aligned(16))) _Float16 sCl[CB * kSmallPitch];
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int64_t q0 = (int64_t)blockIdx.x * QB;
-  const int my_row = tid >> 1;
-  const int half = tid & 1;
-  const int64_t my_q = q0 + my_row;
-  int64_t my_self = -1;
-  if (my_q < nq) my_self = self_mode == 1 ? my_q : (self_mode == 2 ? (int64_t)self[my_q] : -1);
-
-  float ks[KP];
-  int32_t ki[KP];
-#pragma unroll
-  for (int p = 0; p < KP; ++p) { ks[p] = FLT_MAX; ki[p] = INT32_MAX; }
-
-  const int kq = (lane >> 4) * 8;
-  // this wave's query operands: rows 32 wave + 16 rb + lane % 16
-  halfx8 ah[NS][2], al[NS][2];
-#pragma unroll
-  for (int rb = 0; rb < 2; ++rb) {
-    const int64_t q = q0 + 32 * wave + 16 * rb + (lane & 15);
-#pragma unroll
-    for (int t = 0; t < NS; ++t) {
-      ah[t][rb] = q < nq ? *reinterpret_cast<const halfx8 *>(Qh + q * Np + TKK * t + kq) : halfx8{};
-      al[t][rb] = q < nq ? *reinterpret_cast<const halfx8 *>(Ql + q * Np + TKK * t + kq) : halfx8{};
-    }
-  }
-  // candidate rows: thread holds row tid / 4, features 8 (tid % 4) + 32 t
-  const int cr = tid >> 2, ckc = (tid & 3) * 8;
-  halfx8 ch[NS], cl[NS];
-  auto load_cand = [&](int64_t c0) {
-    const bool ok = c0 + cr < M;
-#pragma unroll
-    for (int t = 0; t < NS; ++t) {
-      ch[t] = ok ? *reinterpret_cast<const halfx8 *>(Xh + (c0 + cr) * Np + TKK * t + ckc) : halfx8{};
-      cl[t] = ok ? *reinterpret_cast<const halfx8 *>(Xl + (c0 + cr) * Np + TKK * t + ckc) : halfx8{};
-    }
-  };
-  load_cand(0);
-  for (int64_t c0 = 0; c0 < M; c0 += CB) {
-#pragma unroll
-    for (int t = 0; t < NS; ++t) {
-      *reinterpret_cast<halfx8 *>(sCh + cr * kSmallPitch + TKK * t + ckc) = ch[t];
-      *reinterpret_cast<halfx8 *>(sCl + cr * kSmallPitch + TKK * t + ckc) = cl[t];
-    }
-    __syncthreads();   // tile staged; every thread has finished ranking the previous tile
-    if (c0 + CB < M) load_cand(c0 + CB);
-    floatx4 acc[2][4];
-#pragma unroll
-    for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-      for (int cb = 0; cb < 4; ++cb) acc[rb][cb] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int t = 0; t < NS; ++t) {
-      halfx8 bh[4], bl[4];
-#pragma unroll
-      for (int cb = 0; cb < 4; ++cb) {
-        const int r = 16 * cb + (lane & 15);
-        bh[cb] = *reinterpret_cast<const halfx8 *>(sCh + r * kSmallPitch + TKK * t + kq);
-        bl[cb] = *reinterpret_cast<const halfx8 *>(sCl + r * kSmallPitch + TKK * t + kq);
-      }
-#pragma unroll
-      for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-        for (int cb = 0; cb < 4; ++cb) {
-          acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[t][rb], bh[cb], acc[rb][cb], 0, 0, 0);
-          acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[t][rb], bl[cb], acc[rb][cb], 0, 0, 0);
-          acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al[t][rb], bh[cb], acc[rb][cb], 0, 0, 0);
-        }
-    }
-    // scores: D[i][j] of a 16x16 block sits in lane j + 16 (i / 4), register i % 4
-#pragma unroll
-    for (int cb = 0; cb < 4; ++cb) {
-      const int col = 16 * cb + (lane & 15);
-      const int64_t c = c0 + col;
-      const float cn = c < M ? cnorm[c] : 0.f;
-#pragma unroll
-      for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int row = 32 * wave + 16 * rb + 4 * (lane >> 4) + r;
-          sS[row * SP + col] = cn - 2.f * (acc[rb][cb][r] * inv_scale2);
-        }
-    }
-    __syncthreads();   // scores complete; every wave has finished reading the candidate tile
-    if (my_q < nq) {
-      if constexpr (KP >= 32) {
-        for (int m = 0; m < CB / 2; ++m) {
-          const int col = 2 * m + half;
-          const int64_t c = c0 + col;
-          if (c >= M || c == my_self) continue;
-          list_insert<KP>(ks, ki, sS[my_row * SP + col], (int32_t)c);
-        }
-      } else
-        scan_half_row<KP, CB / 2>(sS + my_row * SP + half * (CB / 2), c0 + half * (CB / 2), M, my_self, ks, ki);
-    }
-  }
-  finish_rows<KP>(sS, ks, ki, my_row, half, my_q, nq, Q, X, N, k, out_idx, out_dist);
-}
-
 // ---- inverted-file (approximate) search ------------------------------------
 // The index: nlist centroids and the points' list assignment.  The points are
 // reordered by list (sorted position p holds point pos_id[p]; list c is
 // positions [lptr[c], lptr[c+1])), split into hi / lo FP16 rows in that
 // order.  The work is list-major: each block takes up to 128 of the queries
 // that probe one list (query ids pq[qbeg..qend)) and sweeps that list's
-// points with the same MFMA tiles, score tile and top-KP lists as the exact
-// kernel, then re-ranks its survivors exactly and writes them to the query's
+// points with MFMA tiles, an LDS score tile and top-KP lists,
+// then re-ranks its survivors exactly and writes them to the query's
 // probe slot.  A merge kernel then takes each query's best k over its slots.
 
 __global__ void gather_f32_kernel(const float *__restrict__ src, const int32_t *__restrict__ idx, int64_t n,
@@ -575,8 +215,7 @@ __device__ __forceinline__ void store_ivf(const IvfFrag &F, _Float16 *sQh, _Floa
   }
 }
 
-// the list kernel tiles like knn_kernel: 128 queries x 128 list points per
-// tile, each wave a 64 x 64 quarter
+// 128 queries x 128 list points per tile, each wave a 64 x 64 quarter
 template <int KP>
 __global__ void __launch_bounds__(kKnnThreads, 2)
 ivf_list_kernel(const float *__restrict__ X, int N, const float *__restrict__ Q, const _Float16 *__restrict__ Xh,
@@ -773,33 +412,6 @@ __global__ void centroid_mean_kernel(const float *__restrict__ X, int N, const i
   }
 }
 
-template <int KP>
-hipError_t launch_knn_kp(const float *X, int64_t M, int N, const float *Q, int64_t nq, const _Float16 *Xh,
-                         const _Float16 *Xl, const _Float16 *Qh, const _Float16 *Ql, int Np, float inv_scale2,
-                         int self_mode, const int32_t *self, const float *cnorm, int k, int32_t *idx, float *dist,
-                         hipStream_t s) {
-  static_assert(2 * QB * KP <= QB * SP, "merge buffers must fit in the score tile");
-  const unsigned grid = (unsigned)((nq + QB - 1) / QB);
-#define IVHD_SMALL_ARGS X, M, N, Q, nq, Xh, Xl, Qh, Ql, inv_scale2, self_mode, self, cnorm, k, idx, dist
-  // (KP = 32 with four K steps would spill registers: the general kernel)
-  if (Np == TKK) {
-    knn_small_kernel<KP, 1><<<grid, kKnnThreads, 0, s>>>(IVHD_SMALL_ARGS);
-  } else if (Np == 2 * TKK) {
-    knn_small_kernel<KP, 2><<<grid, kKnnThreads, 0, s>>>(IVHD_SMALL_ARGS);
-  } else if (Np == 3 * TKK) {
-    knn_small_kernel<KP, 3><<<grid, kKnnThreads, 0, s>>>(IVHD_SMALL_ARGS);
-  } else if constexpr (KP < 32) {
-    if (Np == 4 * TKK) knn_small_kernel<KP, 4><<<grid, kKnnThreads, 0, s>>>(IVHD_SMALL_ARGS);
-    else knn_kernel<KP><<<grid, kKnnThreads, 0, s>>>(X, M, N, Q, nq, Xh, Xl, Qh, Ql, Np, inv_scale2, self_mode,
-                                                      self, cnorm, k, idx, dist);
-  } else {
-    knn_kernel<KP><<<grid, kKnnThreads, 0, s>>>(X, M, N, Q, nq, Xh, Xl, Qh, Ql, Np, inv_scale2, self_mode, self,
-                                                 cnorm, k, idx, dist);
-  }
-#undef IVHD_SMALL_ARGS
-  return hipGetLastError();
-}
-
 }  // namespace
 
 int knn_max_k() { return 28; }
@@ -832,18 +444,6 @@ hipError_t launch_split(const float *X, int64_t M, int N, int Np, float scale, _
                         hipStream_t s) {
   split_kernel<<<grid_for(M * Np), kBlock, 0, s>>>(X, M, N, Np, scale, hi, lo);
   return hipGetLastError();
-}
-
-hipError_t launch_knn(const float *X, int64_t M, int N, const float *Q, int64_t nq, const _Float16 *Xh,
-                      const _Float16 *Xl, const _Float16 *Qh, const _Float16 *Ql, int Np, float scale,
-                      int self_mode, const int32_t *self, const float *cnorm, int k, int32_t *idx, float *dist,
-                      hipStream_t s) {
-  const float inv2 = 1.f / (scale * scale);
-  if (k + 4 <= 8)
-    return launch_knn_kp<8>(X, M, N, Q, nq, Xh, Xl, Qh, Ql, Np, inv2, self_mode, self, cnorm, k, idx, dist, s);
-  if (k + 4 <= 16)
-    return launch_knn_kp<16>(X, M, N, Q, nq, Xh, Xl, Qh, Ql, Np, inv2, self_mode, self, cnorm, k, idx, dist, s);
-  return launch_knn_kp<32>(X, M, N, Q, nq, Xh, Xl, Qh, Ql, Np, inv2, self_mode, self, cnorm, k, idx, dist, s);
 }
 
 hipError_t launch_gather_f32(const float *src, const int32_t *idx, int64_t n, float *dst, hipStream_t s) {

@@ -1,0 +1,1117 @@
+// Exact k nearest neighbours on gfx950 as a filtered matrix product.
+//
+// Order: squared Euclidean distance in FP32 (sum_k (q_k - x_k)^2, features in
+// order), ties to the lower index, the query itself excluded.
+//
+// Every coordinate, scaled by a power of two so the largest magnitude sits
+// below 2^14, is split into hi = fp16(x) and lo = fp16(x - hi) (22
+// significant bits together).  The matrix cores compute the ranking value
+//     a(q, c) = q.c - |c|^2 / 2          (the distance is |q|^2 - 2 a)
+// with FP32 accumulation, started at -|c|^2 / 2, from one of
+//     1 segment    hi.hi
+//     3 segments   hi.hi + hi.lo + lo.hi  (close to FP32 accuracy)
+// and each query keeps its KP best candidates by (a, id).  These survivors
+// are then ranked by their exact FP32 distances, so the answer does not carry
+// the rounding of a as long as the true neighbours are among them.
+//   * One segment: every answer is certified.  With E a bound on the error
+//     of a (Cauchy-Schwarz on the rows' actual rounding residuals, plus the
+//     accumulation), a candidate that was dropped has a <= a_last + E, hence
+//     a distance of at least |q|^2 - 2 (a_last + E); the answer stands when
+//     its k-th distance lies below that.  Queries that fail are run again
+//     with three segments.
+//   * Three segments: the same certificate with a smaller E.  What fails it
+//     (points whose offsets are thousands of times their distances, more
+//     equal distances than the list holds) is ranked over all candidates by
+//     the FP32 distances themselves (knn_brute_kernel).
+// One segment costs a third of the matrix work; which one a call starts with
+// is decided by a pilot of a few query tiles (see KnnSearch::run).
+//
+// knn_filter_kernel: a block of 16 waves owns 256 queries and a range of
+// candidate tiles of 256; wave (wc, wq) computes 64 candidates x 64 queries
+// with v_mfma_f32_32x32x16_f16 (candidates on the rows, so a lane's 32
+// values of a query column stay in its registers).  Operands are laid out by
+// the split kernel as the LDS stage images themselves: 256 rows x 32 features
+// = 16 KB, in slot order, so a stage is filled by global_load_lds_dwordx4
+// from consecutive addresses, without bounds checks (rows past the end are
+// zero, their start value -3e38).  The values never leave the registers: a
+// lane compares the maximum of 16 of them with its query's threshold (the
+// KP-th best so far), and only hits go to the query's list in LDS, which is
+// cut to its KP best when it fills up.  A sweep starts with a short run over
+// its first tiles that only tracks the maxima of KP groups of candidates per
+// query: their minimum is a threshold that at least KP candidates reach, so
+// the lists never see the flood of a cold start.  After it a query has about
+// KP ln(M / 4096) hits in a sweep.
+// What bounds it: the matrix cores, at the clock that the power limit leaves
+// them (1.7 GHz instead of 2.4 in these loops): per K step of 32 a CU spends
+// 1,024 cycles in MFMAs, beside 768 of operand reads and 256 of stage writes.
+// Measured (whole call, exact graph): 400,000 x 100, k = 2 149.6 -> 54.3 ms
+// (the sweep 49 ms, 45 of them without any hit: 0.83 PFLOP/s of products);
+// 70,000 x 784, k = 5 52.4 -> 18.3 ms; 48,600 x 128, k = 20 24.8 -> 7.3 ms.
+// Before, three segments always, each score through LDS to two threads per
+// query row with a register list.  Waves of 64 x 64 (16 per block), rings of
+// two and three stages and per-register ballots measured the same or slower:
+// what a hit costs (about 0.2 us of its wave) is what is left above the
+// products.
+#include <cfloat>
+
+#include "ivhd_internal.h"
+#include "knn_rank.h"
+
+namespace ivhd {
+namespace {
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
+typedef __attribute__((address_space(3))) void lds_void;
+
+constexpr int FT = 256;                  // rows per tile (queries and candidates)
+constexpr int FK = 32;                   // features per stage
+constexpr int kTileHalves = FT * FK;     // one operand's share of a stage (16 KB)
+constexpr int kFilterWaves = 8;
+constexpr int kCandWaves = kFilterWaves / 4;   // waves along the candidates of a tile
+constexpr int NI = FT / kCandWaves / 32;       // 32 x 32 blocks of a wave along the candidates
+constexpr int kFilterThreads = 64 * kFilterWaves;
+constexpr int64_t kCus = 256;
+constexpr int kRing = 2;                 // stages in LDS
+constexpr int kListPlaces = 44;          // places of a query's list (LDS: 64 KB ring + 88 KB lists)
+constexpr float kNoValue = -2.9e38f;     // threshold of a list that is not full
+constexpr float kPadStart = -3.0e38f;    // start value of rows past the end (below kNoValue)
+
+// slot of 16-byte chunk `chunk` (8 features) of row `row` in a stage image:
+// an operand read touches rows r..r+31 at chunk c (lanes 0-31) and c + 1
+// (lanes 32-63); any eight consecutive rows at one chunk, and any four at
+// both, fall on distinct 16-byte bank groups
+__device__ __forceinline__ int tile_slot(int row, int chunk) {
+  return row * 4 + (chunk ^ ((row & 2) | ((row >> 2) & 1)));
+}
+
+// A candidate of a list: the value's bits made monotone above, the
+// complement of its id below, so that a larger key is a better candidate
+// (larger a, then lower id).  0: none.
+__device__ __forceinline__ uint64_t cand_key(float a, int32_t id) {
+  const uint32_t u = __float_as_uint(a);
+  return (uint64_t)(u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u)) << 32 | (uint32_t)~id;
+}
+__device__ __forceinline__ int32_t key_id(uint64_t k) { return (int32_t)~(uint32_t)k; }
+__device__ __forceinline__ float key_value(uint64_t k) {
+  const uint32_t u = (uint32_t)(k >> 32);
+  return __uint_as_float(u ^ (~(uint32_t)((int32_t)u >> 31) | 0x80000000u));
+}
+
+// ---- operands ---------------------------------------------------------------
+
+// Column means in two fixed-order steps: partial sums over row ranges, then
+// their sum.  Centred data have smaller norms, hence smaller error bounds.
+constexpr int kMeanParts = 256;
+
+__global__ void __launch_bounds__(256) knn_mean_parts_kernel(const float *__restrict__ X, int64_t M, int N,
+                                                             float *__restrict__ part) {
+  const int64_t per = (M + kMeanParts - 1) / kMeanParts, r0 = blockIdx.x * per, r1 = r0 + per < M ? r0 + per : M;
+  __shared__ float red[4][64];
+  const int c = threadIdx.x & 63, w = threadIdx.x >> 6;
+  for (int n0 = 0; n0 < N; n0 += 64) {
+    float t = 0.f;
+    if (n0 + c < N) {
+#pragma unroll 8
+      for (int64_t r = r0 + w; r < r1; r += 4) t += X[r * N + n0 + c];
+    }
+    red[w][c] = t;
+    __syncthreads();
+    if (w == 0 && n0 + c < N)
+      part[(int64_t)blockIdx.x * N + n0 + c] = ((red[0][c] + red[1][c]) + red[2][c]) + red[3][c];
+    __syncthreads();
+  }
+}
+
+__global__ void __launch_bounds__(256) knn_mean_kernel(const float *__restrict__ part, int64_t M, int N,
+                                                       float *__restrict__ mean) {
+  const int c = blockIdx.x * 256 + threadIdx.x;
+  if (c >= N) return;
+  float t = 0.f;
+#pragma unroll 8
+  for (int p = 0; p < kMeanParts; ++p) t += part[(int64_t)p * N + c];
+  mean[c] = t / (float)M;
+}
+
+// Stage images of scale * (X - mean) (mean NULL: 0; rows taken through `map` when given),
+// the rows' squared norms, start values and the largest norm and residual.
+// 16 lanes per row, 8 features per lane and step; a block walks rows 16 at a
+// time so that the two maxima cost a block one atomic each.
+__global__ void __launch_bounds__(256) knn_split_kernel(const float *__restrict__ X, int64_t M, int N, int nk,
+                                                        const int32_t *__restrict__ map,
+                                                        const float *__restrict__ mean, float scale,
+                                                        _Float16 *__restrict__ hi, _Float16 *__restrict__ lo,
+                                                        float *__restrict__ norms, float *__restrict__ start,
+                                                        KnnStats *__restrict__ stats, bool vec) {
+  __shared__ float smax[2][4];
+  const int g = threadIdx.x & 15;
+  const int64_t rows = (M + FT - 1) / FT * FT;
+  float top_s = 0.f, top_e = 0.f;
+  for (int64_t row = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4); row < rows; row += (int64_t)gridDim.x * 16) {
+    const bool real = row < M;
+    const int64_t src = real ? (map ? (int64_t)map[row] : row) : 0;
+    const float *x = X + src * N;
+    const int64_t base = row / FT * nk * kTileHalves;
+    const int r = (int)(row % FT);
+    float s = 0.f, e = 0.f;
+    for (int c = g; c < nk * 4; c += 16) {
+      float v[8];
+      if (vec && 8 * c + 8 <= N) {
+        floatx4 m0 = {}, m1 = {};
+        if (mean) {
+          m0 = *reinterpret_cast<const floatx4 *>(mean + 8 * c);
+          m1 = *reinterpret_cast<const floatx4 *>(mean + 8 * c + 4);
+        }
+        const floatx4 u = *reinterpret_cast<const floatx4 *>(x + 8 * c) - m0;
+        const floatx4 w = *reinterpret_cast<const floatx4 *>(x + 8 * c + 4) - m1;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          v[j] = real ? u[j] : 0.f;
+          v[j + 4] = real ? w[j] : 0.f;
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = real && 8 * c + j < N ? x[8 * c + j] - (mean ? mean[8 * c + j] : 0.f) : 0.f;
+      }
+      halfx8 h, l;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        s += v[j] * v[j];
+        const float t = v[j] * scale;
+        h[j] = (_Float16)t;
+        const float d = t - (float)h[j];
+        e += d * d;
+        l[j] = (_Float16)d;
+      }
+      const int64_t at = base + (int64_t)(c >> 2) * kTileHalves + tile_slot(r, c & 3) * 8;
+      if (hi) *reinterpret_cast<halfx8 *>(hi + at) = h;
+      if (lo) *reinterpret_cast<halfx8 *>(lo + at) = l;
+    }
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) {
+      s += __shfl_xor(s, o, 64);
+      e += __shfl_xor(e, o, 64);
+    }
+    if (g == 0) {
+      if (norms && real) norms[row] = s;
+      if (start) start[row] = real ? -0.5f * s * scale * scale : kPadStart;
+    }
+    top_s = fmaxf(top_s, s);
+    top_e = fmaxf(top_e, e);
+  }
+  if (!stats) return;
+#pragma unroll
+  for (int o = 32; o >= 16; o >>= 1) {
+    top_s = fmaxf(top_s, __shfl_xor(top_s, o, 64));
+    top_e = fmaxf(top_e, __shfl_xor(top_e, o, 64));
+  }
+  if ((threadIdx.x & 63) == 0) {
+    smax[0][threadIdx.x >> 6] = top_s;
+    smax[1][threadIdx.x >> 6] = top_e;
+  }
+  __syncthreads();
+  if (threadIdx.x < 2) {   // non-negative floats compare as integers
+    const float *m = smax[threadIdx.x];
+    const float t = fmaxf(fmaxf(m[0], m[1]), fmaxf(m[2], m[3]));
+    atomicMax(threadIdx.x == 0 ? &stats->norm2 : &stats->res2, __float_as_uint(t));
+  }
+}
+
+// ---- the filter -------------------------------------------------------------
+
+struct FilterArgs {
+  const _Float16 *Qh, *Ql, *Ch, *Cl;   // stage images; the lo ones only with nseg = 3
+  const float *start;                  // [tiles * FT]
+  int nk, nseg;                        // stages per segment, segments
+  int64_t nq, M;
+  int64_t qb0, qb_step;                // query tile of item row r: qb0 + r qb_step
+  int64_t nqb;                         // query tiles of this launch
+  int splits;                          // candidate ranges
+  int64_t tiles, tiles_per_split;
+  int lead;                            // tiles that set the starting thresholds
+  int self_mode;                       // 0 none, 1 the query's own row, 2 self[]
+  const int32_t *self, *map;           // map: original row of query q (NULL: q)
+  uint64_t *part;                      // [launch query][splits][KP]
+};
+
+// block barrier that waits for this wave's LDS operations only: the stage
+// loads in flight stay in flight
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// LDS writes as single instructions: the compiler would wait for every stage
+// load in flight before each of them, since those write LDS too
+__device__ __forceinline__ uint32_t lds_at(const void *p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char *)p;
+}
+__device__ __forceinline__ void lds_put(uint64_t *p, uint64_t v) {
+  asm volatile("ds_write_b64 %0, %1" ::"v"(lds_at(p)), "v"(v) : "memory");
+}
+template <typename T>
+__device__ __forceinline__ void lds_put(T *p, T v) {
+  static_assert(sizeof(T) == 4, "one dword");
+  asm volatile("ds_write_b32 %0, %1" ::"v"(lds_at(p)), "v"(v) : "memory");
+}
+__device__ __forceinline__ void lds_put2(uint64_t *p, uint32_t lo, uint32_t hi) {
+  asm volatile("ds_write2_b32 %0, %1, %2 offset0:0 offset1:1" ::"v"(lds_at(p)), "v"(lo), "v"(hi) : "memory");
+}
+__device__ __forceinline__ void lds_max(float *p, float v) {
+  asm volatile("ds_max_f32 %0, %1" ::"v"(lds_at(p)), "v"(v) : "memory");
+}
+__device__ __forceinline__ void lds_put(uint8_t *p, uint32_t v) {
+  asm volatile("ds_write_b8 %0, %1" ::"v"(lds_at(p)), "v"(v) : "memory");
+}
+
+// A query's list: KP places for its best so far (sorted once cut), then one
+// area of (C - KP) / kOwners places for each of the lanes that hold its
+// values: two lane halves x the waves along the candidates.  A lane appends to
+// its own area without asking anybody; empty places hold 0.
+constexpr int kOwners = 2 * kCandWaves;
+
+// The list cut to its KP best, in place and sorted, the areas emptied; one
+// lane per place.
+template <int KP, int C>
+__device__ __forceinline__ void cut_list(uint64_t *list, uint8_t *cnt, float *thr, int32_t *thr_id, int lane) {
+  constexpr int AREA = (C - KP) / kOwners;
+  uint64_t mine = 0;
+  if (lane < C) {
+    const int o = lane - KP;
+    if (o < 0) {
+      mine = list[lane];
+    } else if (o % AREA < (int)cnt[o / AREA]) {   // as appended: id below, value above
+      const uint64_t e = list[lane];
+      mine = cand_key(__uint_as_float((uint32_t)(e >> 32)), (int32_t)(uint32_t)e);
+    }
+    lds_put(list + lane, mine);   // what is not counted is 0 from here on
+  }
+  int rank = 0;
+#pragma unroll 11
+  for (int j = 0; j < C; j += 2) {
+    const uint64_t o0 = list[j], o1 = list[j + 1];
+    rank += (o0 > mine ? 1 : 0) + (o1 > mine ? 1 : 0);
+  }
+  // the first KP places: the KP best, 0 where there are fewer
+  if (lane < KP) lds_put(list + lane, (uint64_t)0);
+  if (mine && rank < KP) lds_put(list + rank, mine);
+  if (mine && rank == KP - 1) {
+    lds_put(thr, key_value(mine));
+    lds_put(thr_id, key_id(mine));
+  }
+  if (lane < kOwners) lds_put(cnt + lane, 0u);
+}
+
+// cuts the lists of the set bits, list q0 + bit each
+template <int KP, int C>
+__device__ __forceinline__ void cut_lists(uint32_t todo, int q0, uint64_t *lists, uint8_t *cnt, float *thr,
+                                          int32_t *thr_id, int lane) {
+  while (todo) {
+    const int q = q0 + __builtin_ctz(todo);
+    todo &= todo - 1;
+    cut_list<KP, C>(lists + q * C, cnt + q * kOwners, thr + q, thr_id + q, lane);
+  }
+}
+
+template <int KP>
+__global__ void __launch_bounds__(kFilterThreads, kFilterWaves / 4) knn_filter_kernel(FilterArgs A) {
+  constexpr int C = kListPlaces, RING = kRing;
+  constexpr int AREA = (C - KP) / kOwners;
+  static_assert(C <= 64 && (C - KP) % kOwners == 0 && C % 2 == 0 && KP <= 32, "list shape");
+  constexpr int kTrigger = AREA - (AREA > 4 ? 2 : 1);   // an area this full has the lists cut
+  constexpr int SUB = 32 / (NI * kOwners);   // candidate groups per 32 x 32 block and lane: 32 per query
+  // separate LDS objects: the compiler then knows that the lists are not what
+  // the stage loads write, and does not wait for those at every list access
+  __shared__ __attribute__((aligned(16))) _Float16 ring[RING * 2 * kTileHalves];   // [candidates 16 KB | queries 16 KB]
+  __shared__ __attribute__((aligned(16))) float sStart[3 * FT];
+  __shared__ __attribute__((aligned(16))) uint64_t sList[FT * C];
+  __shared__ uint8_t sCnt[FT * kOwners];
+  __shared__ float sThr[FT];
+  __shared__ int32_t sThrId[FT];
+  __shared__ int32_t sSelf[FT];
+  __shared__ int32_t sFlag[2];           // [0] offer after which lists are to be cut, [1] one that left values over
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wc = 32 * NI * (wave >> 2), wq = 64 * (wave & 3);
+  // XCD-aware items: blocks go to XCD b % 8; each XCD gets a contiguous run
+  // of items, ordered by groups of four query tiles, then candidate range,
+  // then query tile, so the blocks that run together on one L2 share query
+  // panels and candidate tiles
+  int64_t item;
+  {
+    const int64_t nb = gridDim.x, b = blockIdx.x, q = nb / kXcds, rem = nb % kXcds, x = b % kXcds, i = b / kXcds;
+    item = x < rem ? x * (q + 1) + i : rem * (q + 1) + (x - rem) * q + i;
+  }
+  const int64_t full = A.nqb / 4 * 4 * A.splits;
+  const int64_t gw = item < full ? 4 : A.nqb % 4, in_group = item < full ? item % (4 * A.splits) : item - full;
+  const int64_t qrow = (item < full ? item / (4 * A.splits) * 4 : A.nqb / 4 * 4) + in_group % gw;
+  const int split = (int)(in_group / gw);
+  const int64_t qb = A.qb0 + qrow * A.qb_step;
+  const int64_t q0 = qb * FT;
+  const int t0 = (int)(split * A.tiles_per_split);
+  const int t1 = (int)(t0 + A.tiles_per_split < A.tiles ? t0 + A.tiles_per_split : A.tiles);
+  const int per_tile = A.nk * A.nseg;
+  // the tiles of this block in order: `lead` of them for the starting
+  // thresholds, then all
+  const int lead = t1 > t0 ? min(A.lead, t1 - t0) : 0;
+  const int ntiles = t1 > t0 ? lead + (t1 - t0) : 0;
+  const int64_t nstages = (int64_t)ntiles * per_tile;
+
+  // lead tiles: the maxima of 32 groups of candidates per query, each kept by
+  // one lane, in the place of the lists (which are still empty)
+  float *gm = reinterpret_cast<float *>(sList);
+  constexpr int GP = FT + 1;   // pitch of a group's values
+
+  if (tid < FT) {
+    const int64_t q = q0 + tid;
+    const int64_t orig = q < A.nq ? (A.map ? (int64_t)A.map[q] : q) : 0;
+    sThr[tid] = q < A.nq ? kNoValue : INFINITY;   // padding queries keep nothing
+    sThrId[tid] = INT32_MAX;
+    sSelf[tid] = A.self_mode == 1 ? (int32_t)orig : (A.self_mode == 2 && q < A.nq ? A.self[orig] : -1);
+  }
+  if (tid < 2) sFlag[tid] = -1;
+  for (int e = tid; e < FT * kOwners; e += kFilterThreads) sCnt[e] = 0;
+  for (int e = tid; e < FT * C; e += kFilterThreads) sList[e] = 0;
+  __syncthreads();
+  if (lead > 0)
+    for (int e = tid; e < 32 * GP; e += kFilterThreads) gm[e] = kNoValue;
+
+  // stage issue: counters of the next stage to load
+  int i_seq = 0, i_seg = 0, i_k = 0, i_slot = 0, i_start = 0;
+  const uint32_t load_at = tid * 16;
+  auto issue = [&]() __attribute__((always_inline)) {
+    const int64_t i_tile = i_seq < lead ? t0 + i_seq : t0 + i_seq - lead;
+    const _Float16 *c = (i_seg == 1 ? A.Cl : A.Ch) + (i_tile * A.nk + i_k) * kTileHalves;
+    const _Float16 *q = (i_seg == 2 ? A.Ql : A.Qh) + (qb * A.nk + i_k) * kTileHalves;
+    _Float16 *dst = ring + i_slot * 2 * kTileHalves;
+    if (i_seg == 0 && i_k == 0) {   // the tile's start values, ahead of its first stage
+      if (wave == 0)
+        __builtin_amdgcn_global_load_lds((const void *)(reinterpret_cast<const char *>(A.start + i_tile * FT) + load_at),
+                                         (lds_void *)(sStart + i_start * FT), 16, 0, 0);
+      i_start = i_start == 2 ? 0 : i_start + 1;
+    }
+    // 64 lanes x 16 bytes per wave, load and operand
+    unsigned char *at = reinterpret_cast<unsigned char *>(dst) + wave * 1024;
+#pragma unroll
+    for (int u = 0; u < 16 / kFilterWaves; ++u) {
+      __builtin_amdgcn_global_load_lds((const void *)(reinterpret_cast<const char *>(c) + load_at + u * kFilterThreads * 16),
+                                       (lds_void *)(at + u * kFilterThreads * 16), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((const void *)(reinterpret_cast<const char *>(q) + load_at + u * kFilterThreads * 16),
+                                       (lds_void *)(at + kTileHalves * 2 + u * kFilterThreads * 16), 16, 0, 0);
+    }
+    i_slot = i_slot == RING - 1 ? 0 : i_slot + 1;
+    if (++i_k == A.nk) {
+      i_k = 0;
+      if (++i_seg == A.nseg) {
+        i_seg = 0;
+        ++i_seq;
+      }
+    }
+  };
+
+  __syncthreads();   // lists ready
+  const int row = lane & 31;
+  const int ql[2] = {wq + row, wq + 32 + row};
+  float thr[2] = {sThr[ql[0]], sThr[ql[1]]};
+  const int owner = 2 * (wave >> 2) + (lane >> 5);
+  const int32_t self[2] = {sSelf[ql[0]], sSelf[ql[1]]};   // -1: none
+  int mine[2] = {0, 0};   // entries in this lane's areas
+  int32_t thr_id[2] = {INT32_MAX, INT32_MAX};
+  // byte offsets of this lane's operand chunks in a stage; those of the
+  // second 16 features are 32 bytes off (bit 1 of the chunk)
+  const int at_c = tile_slot(wc + row, lane >> 5) * 16;
+  const int at_q = kTileHalves * 2 + tile_slot(wq + row, lane >> 5) * 16;
+  floatx16 acc[NI][2];
+  // A lane's operand fragments of 16 features are read half a stage ahead of
+  // the MFMAs that use them, so that LDS reads and MFMAs overlap.  Stage
+  // st + 1 is entered in the middle of stage st: when this wave's loads of it
+  // have landed (all but those of the stage after) and its reads of stage st
+  // are done.  After the barrier that holds for every wave, and the slot of
+  // stage st takes the next loads.
+  int64_t issued = 0, st = 0;
+  int c_start = 0;
+  uint32_t at = 0;   // byte offset of the current slot
+  constexpr uint32_t kSlot = 2 * kTileHalves * 2;
+  const unsigned char *ring8 = reinterpret_cast<const unsigned char *>(ring);
+  halfx8 a0[NI], b0[2], a1[NI], b1[2];
+  auto read0 = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i)   // 32 rows further: 32 * 4 slots of 16 bytes
+      a0[i] = *reinterpret_cast<const halfx8 *>(ring8 + at + at_c + 2048 * i);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) b0[j] = *reinterpret_cast<const halfx8 *>(ring8 + at + at_q + 2048 * j);
+  };
+  auto read1 = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i) a1[i] = *reinterpret_cast<const halfx8 *>(ring8 + at + (at_c ^ 32) + 2048 * i);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) b1[j] = *reinterpret_cast<const halfx8 *>(ring8 + at + (at_q ^ 32) + 2048 * j);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto mfma = [&](const halfx8 &a, const halfx8 &b, const floatx16 &c) __attribute__((always_inline)) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
+  };
+  // The first MFMA of a half goes before the reads of the next: it is what
+  // waits for its operands, and a wait after the reads would be for them too.
+  auto finish_stage = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_sched_barrier(0);
+    if (RING == 3 && issued - st >= 3) {
+      if (kFilterWaves == 8) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+      else asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
+    } else {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+    lds_barrier();
+    at = at == (RING - 1) * kSlot ? 0 : at + kSlot;
+    acc[0][0] = mfma(a1[0], b1[0], acc[0][0]);
+    __builtin_amdgcn_sched_barrier(0);
+    read0();   // (past the last stage: read, not used)
+    __builtin_amdgcn_sched_barrier(0);
+    acc[0][1] = mfma(a1[0], b1[1], acc[0][1]);
+    if (issued < nstages) {
+      issue();
+      ++issued;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 1; i < NI; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[i][j] = mfma(a1[i], b1[j], acc[i][j]);
+    __builtin_amdgcn_sched_barrier(0);
+    ++st;
+  };
+  for (; issued < RING && issued < nstages; ++issued) issue();
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  lds_barrier();
+  read0();
+  for (int seq = 0; seq < ntiles; ++seq) {
+    {
+      const float *sv = sStart + c_start * FT + wc + 4 * (lane >> 5);
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        floatx16 v;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const floatx4 w = *reinterpret_cast<const floatx4 *>(sv + 32 * i + 8 * g);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) v[4 * g + r] = w[r];
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = mfma(a0[i], b0[j], v);
+      }
+      c_start = c_start == 2 ? 0 : c_start + 1;
+    }
+    read1();
+    finish_stage();
+#pragma unroll 1
+    for (int ks = 1; ks < per_tile; ++ks) {
+      acc[0][0] = mfma(a0[0], b0[0], acc[0][0]);
+      __builtin_amdgcn_sched_barrier(0);
+      read1();
+      acc[0][1] = mfma(a0[0], b0[1], acc[0][1]);
+#pragma unroll
+      for (int i = 1; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = mfma(a0[i], b0[j], acc[i][j]);
+      finish_stage();
+    }
+    if (seq < lead) {
+      // a lead tile (a query's own row is not a candidate, so its tile is
+      // left out)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const bool own = self[j] >= 0 && self[j] / FT == t0 + seq;
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+          for (int u = 0; u < SUB; ++u) {
+            float m = acc[i][j][u * (16 / SUB)];
+#pragma unroll
+            for (int r = 1; r < 16 / SUB; ++r) m = fmaxf(m, acc[i][j][u * (16 / SUB) + r]);
+            if (!own) lds_max(&gm[(owner * (NI * SUB) + i * SUB + u) * GP + ql[j]], m);
+          }
+      }
+      if (seq == lead - 1) {
+        // all candidates of their own: at least KP candidates reach the
+        // KP-th largest of a query's 32 maxima
+        lds_barrier();
+        for (int p = 0; p < FT / kFilterWaves; p += 2) {
+          const int q = wave * (FT / kFilterWaves) + p + (lane >> 5);
+          const float m = gm[row * GP + q];
+          int rank = 0;
+#pragma unroll 8
+          for (int e = 0; e < 32; ++e) {
+            const float o = gm[e * GP + q];
+            rank += o > m || (o == m && e < row) ? 1 : 0;
+          }
+          if (rank == KP - 1 && q0 + q < A.nq) lds_put(&sThr[q], m);
+        }
+        lds_barrier();
+        for (int e = tid; e < GP * 16; e += kFilterThreads) lds_put(&sList[e], (uint64_t)0);
+        lds_barrier();
+        thr[0] = sThr[ql[0]];
+        thr[1] = sThr[ql[1]];
+      }
+      continue;
+    }
+    // The values of a tile: D[i][j] of a 32 x 32 block sits in lane
+    // j + 32 ((i / 4) % 2), register 4 (i / 8) + i % 4.  Values that beat the
+    // threshold go to this lane's area of the query's list.  When an area is
+    // full the tile is offered again once the lists have been cut; a lane's
+    // ids ascend, so it then goes on after the last id that got in, and every
+    // offer of a lane with values left gets at least one in: its area was cut
+    // empty in between (a full area is one to be cut).
+    int c0 = (t0 + seq - lead) * FT + wc + 4 * (lane >> 5);
+    int32_t last[2] = {-1, -1};   // ids up to here have been dealt with
+    for (int tries = 0; tries <= 16 * NI; ++tries) {   // a lane has 16 NI values per query
+      asm volatile("" : "+v"(c0));   // keeps what derives from it out of the registers
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        uint64_t *area = &sList[ql[j] * C + KP + owner * AREA];
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+          float q[4];   // maxima of the registers by fours
+#pragma unroll
+          for (int g = 0; g < 4; ++g)
+            q[g] = fmaxf(fmaxf(fmaxf(acc[i][j][4 * g], acc[i][j][4 * g + 1]), acc[i][j][4 * g + 2]),
+                         acc[i][j][4 * g + 3]);
+          if (!__any(fmaxf(fmaxf(fmaxf(q[0], q[1]), q[2]), q[3]) >= thr[j])) continue;
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            if (!__any(q[g] >= thr[j])) continue;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const float v = acc[i][j][4 * g + r];
+              if (!__any(v >= thr[j])) continue;
+              const int32_t id = c0 + 32 * i + 8 * g + r;
+              if ((v > thr[j]) | ((v == thr[j]) & (id < thr_id[j])) && id != self[j] && id > last[j]) {
+                if (mine[j] < AREA) {
+                  lds_put2(area + mine[j], (uint32_t)id, __float_as_uint(v));
+                  last[j] = id;
+                }
+                ++mine[j];
+              }
+            }
+          }
+        }
+        lds_put(&sCnt[ql[j] * kOwners + owner], (uint32_t)min(mine[j], AREA));
+      }
+      const int most = max(mine[0], mine[1]);
+      if (most >= kTrigger) lds_put(&sFlag[0], seq);
+      if (most > AREA) lds_put(&sFlag[1], seq);
+      lds_barrier();
+      // Between the barriers below no wave sets a flag, so every wave sees
+      // the same
+      if (sFlag[0] != seq) break;
+      const bool again = sFlag[1] == seq;
+      // a round cuts every list with more than a few new entries, so that the
+      // next round is far off
+      constexpr int kLists = FT / kFilterWaves;   // of this wave
+      int added = 0;
+      if (lane < kLists)
+#pragma unroll
+        for (int o = 0; o < kOwners; ++o) added += sCnt[(wave * kLists + lane) * kOwners + o];
+      cut_lists<KP, C>((uint32_t)__ballot(added > 2), wave * kLists, sList, sCnt, sThr, sThrId, lane);
+      lds_barrier();   // flags read, thresholds written
+      if (tid < 2) lds_put(&sFlag[tid], -1);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        thr[j] = sThr[ql[j]];
+        thr_id[j] = sThrId[ql[j]];
+        mine[j] = sCnt[ql[j] * kOwners + owner];
+      }
+      lds_barrier();   // flags reset
+      if (!again) break;
+    }
+  }
+  __syncthreads();
+  static_assert(FT / kFilterWaves == 32, "a wave's lists in one mask");
+  cut_lists<KP, C>(~0u, wave * 32, sList, sCnt, sThr, sThrId, lane);
+  __syncthreads();
+  for (int e = tid; e < FT * KP; e += kFilterThreads) {
+    const int q = e / KP, p = e % KP;
+    if (q0 + q < A.nq) A.part[((qrow * FT + q) * A.splits + split) * KP + p] = sList[q * C + p];
+  }
+}
+
+// ---- survivors to answers -----------------------------------------------------
+
+struct FinishArgs {
+  const float *X, *Q;
+  int N, nk, k, splits;
+  int64_t nq;                    // queries of the call (compact ids)
+  int64_t qb0, qb_step, n_launch;   // launch query t is query (qb0 + t / FT qb_step) FT + t % FT
+  const int32_t *map;            // original row of query q (NULL: q)
+  const uint64_t *part;
+  int32_t *out_idx;
+  float *out_dist;
+  // certificate (fails == NULL: none)
+  const float *qnorm;            // [nq]
+  const KnnStats *xs, *qs;       // largest norm and residual of candidates and queries
+  float scale;
+  int nseg;
+  int32_t *fails;                // [0] count, then query ids
+  int32_t *pilot;                // [3]: answers that lists of 8, 16, 32 would not certify (NULL: no pilot)
+};
+
+// Bound on the error of a (scaled units) of a query of squared norm n2 (scaled)
+// against any candidate, in FP64 and rounded up by a factor well above its error
+__device__ __forceinline__ double value_error(const FinishArgs &A, double n2, double nerr, double &xm) {
+  const double sc = A.scale, up = 1.0 + 1e-6, u23 = 1.1920928955078125e-7;
+  const double nq = sqrt(n2 * (1 + nerr)) * up;
+  xm = sqrt((double)__uint_as_float(A.xs->norm2) * (1 + nerr)) * sc * up;
+  const double rx = sqrt((double)__uint_as_float(A.xs->res2) * (1 + nerr)) * up;
+  const double rq = sqrt((double)__uint_as_float(A.qs->res2) * (1 + nerr)) * up;
+  // what the segments leave out of q.c: with hi + lo, the rounding of lo
+  // (2^-11 of the residual, or 2^-25 per coordinate where lo is subnormal)
+  // and the product lo.lo
+  const double sub = 3e-8 * sqrt((double)A.N);
+  const double rest = A.nseg == 1 ? nq * rx + rq * (xm + rx)
+                                  : (nq + rq) * (rx / 2048 + sub) + (xm + rx) * (rq / 2048 + sub) + rx * rq;
+  // roundings of the accumulation: one segment takes the worst case, all of
+  // them one way; with three that would be larger than all the rest, and
+  // four times their root mean square is taken instead
+  const double n = (double)A.nseg * A.nk * FK, steps = A.nseg == 1 ? n + 16 : 4 * sqrt(n) + 16;
+  return up * rest + steps * u23 * (0.5 * xm * xm + (nq + rq) * (xm + rx))                         // accumulation
+         + 0.5 * nerr * xm * xm;                                                                  // the start value
+}
+
+// KP lanes per query: merge the ranges' lists, exact FP32 distances of the
+// survivors that can be among the k nearest, rank by (distance, id), certify.
+template <int KP>
+__global__ void __launch_bounds__(256) knn_finish_kernel(FinishArgs A) {
+  __shared__ uint64_t sm[256];
+  const int lane = threadIdx.x & 63, p = threadIdx.x & (KP - 1);
+  const int g0 = lane & ~(KP - 1);   // first lane of the group
+  uint64_t *grp = sm + (threadIdx.x & ~(KP - 1));
+  const int64_t t = ((int64_t)blockIdx.x * 256 + threadIdx.x) / KP;
+  const int64_t q = t < A.n_launch ? (A.qb0 + t / FT * A.qb_step) * FT + t % FT : A.nq;
+  const bool on = q < A.nq;
+  const uint64_t *src = A.part + t * A.splits * KP;
+  uint64_t mine = on ? src[p] : 0;
+  for (int s = 1; s < A.splits; ++s) {
+    const uint64_t in = on ? src[s * KP + p] : 0;
+    int rm = 0, ri = 0;
+#pragma unroll 4
+    for (int j = 0; j < KP; ++j) {
+      const uint64_t m = __shfl(mine, g0 + j, 64), n = __shfl(in, g0 + j, 64);
+      rm += (m > mine ? 1 : 0) + (n > mine ? 1 : 0);
+      ri += (n > in ? 1 : 0) + (m > in ? 1 : 0);
+    }
+    grp[p] = 0;
+    if (mine && rm < KP) grp[rm] = mine;
+    if (in && ri < KP) grp[ri] = in;
+    mine = grp[p];
+  }
+  const bool have = mine != 0;
+  const int64_t orig = on ? (A.map ? (int64_t)A.map[q] : q) : 0;
+  const double sc2 = (double)A.scale * A.scale, u23 = 1.1920928955078125e-7;
+  const double nerr = (A.N / 16 + 16) * u23;   // relative error of an FP32 squared norm (16 lanes, then a tree)
+  const double n2 = on ? (double)A.qnorm[orig] * sc2 : 0.0;
+  double xm = 0.0, err = 0.0;
+  int rank = 0, found = 0;
+  uint64_t last = ~0ull, kth = 0;
+#pragma unroll 4
+  for (int j = 0; j < KP; ++j) {
+    const uint64_t m = __shfl(mine, g0 + j, 64);
+    rank += m > mine ? 1 : 0;
+    found += m != 0 ? 1 : 0;
+    last = m < last ? m : last;
+  }
+  uint64_t nth[3] = {0, 0, 0};   // the 8th, 16th and 32nd best
+  bool near = have;   // may be among the k nearest
+  if (A.fails) {
+    err = value_error(A, n2, nerr, xm);
+    // a value more than two errors below the k-th best cannot be (the slack
+    // covers the rounding of the distances themselves)
+    for (int j = 0; j < KP; ++j) {
+      const uint64_t m = __shfl(mine, g0 + j, 64);
+      const int rj = __shfl(rank, g0 + j, 64);
+      kth = rj == A.k - 1 && m ? m : kth;
+#pragma unroll
+      for (int l = 0; l < 3; ++l) nth[l] = rj == (8 << l) - 1 ? m : nth[l];
+    }
+    const double slack = (A.N + 16) * u23 * (n2 + xm * xm);
+    near = have && (kth == 0 || (double)key_value(mine) >= (double)key_value(kth) - 2.0 * err - slack);
+  }
+  float d = FLT_MAX;
+  if (near)
+    d = exact_distance(A.Q + orig * A.N, A.X + (int64_t)key_id(mine) * A.N, A.N, rows_are_vec4(A.X, A.Q, A.N));
+  const int32_t id = near ? key_id(mine) : INT32_MAX;
+  rank = 0;
+#pragma unroll 4
+  for (int j = 0; j < KP; ++j) {
+    const float dj = __shfl(d, g0 + j, 64);
+    const int32_t ij = __shfl(id, g0 + j, 64);
+    rank += (dj < d || (dj == d && (ij < id || (ij == id && j < p)))) ? 1 : 0;
+  }
+  if (on && rank < A.k) {
+    A.out_idx[orig * A.k + rank] = near ? id : -1;
+    if (A.out_dist) A.out_dist[orig * A.k + rank] = d;
+  }
+  // The least squared distance of a candidate that is not among the first L of
+  // the list, between the centred rows and (their rounding: 2^-24 of each
+  // row) between the given ones, must lie above the k-th distance.
+  if (A.fails && on && rank == A.k - 1) {
+    const double top = (double)d * sc2 * (1 + (A.N + 16) * u23);
+    auto certified = [&](uint64_t last) {
+      const double least = n2 * (1 - nerr) - 2.0 * ((double)key_value(last) + err);
+      const double moved = sqrt(least > 0 ? least : 0.0) - 0.5 * u23 * (sqrt(n2 * (1 + nerr)) + xm);
+      return top < (moved > 0 ? moved * moved : 0.0) * (1 - 1e-12);
+    };
+    if (A.pilot) {
+      for (int l = 0; l < 3; ++l) {
+        const int len = 8 << l;
+        if (len <= KP && found >= len && (len < A.k || !certified(nth[l]))) atomicAdd(&A.pilot[l], 1);
+      }
+    } else if (found == KP && !certified(last)) {
+      A.fails[1 + atomicAdd(&A.fails[0], 1)] = (int32_t)orig;
+    }
+  }
+}
+
+// ---- every candidate, for the queries that no certificate covers --------------
+
+// A block takes kBruteQ queries over one range of the candidates: thread t
+// computes the FP32 distances of candidate c0 + t (a tile of 256 at a time);
+// the four waves then offer the tile's keys (distance above, id below) to two
+// queries each, whose best 64 a wave holds sorted over its lanes.  Bound by
+// the vector ALU (2 instructions per query, candidate and feature); rare.
+constexpr int kBruteQ = 8;
+
+__device__ __forceinline__ void offer_sorted(uint64_t &best, uint64_t key, int lane, int k) {
+  uint64_t mask = __ballot(key < __shfl(best, k - 1, 64));
+  while (mask) {
+    const uint64_t in = __shfl(key, __builtin_ctzll(mask), 64);
+    mask &= mask - 1;
+    const int pos = __popcll(__ballot(best < in));
+    const uint64_t up = __shfl_up(best, 1, 64);
+    best = lane < pos ? best : (lane == pos ? in : up);
+  }
+}
+
+__global__ void __launch_bounds__(256) knn_brute_kernel(const float *__restrict__ X, int64_t M, int N,
+                                                        const float *__restrict__ Q, int64_t nq,
+                                                        const int32_t *__restrict__ rows, int self_mode,
+                                                        const int32_t *__restrict__ self, int k, int splits,
+                                                        uint64_t *__restrict__ part) {
+  __shared__ uint64_t keys[kBruteQ][256];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t f0 = (int64_t)blockIdx.x * kBruteQ;
+  const int64_t per = ((M + splits - 1) / splits + 255) / 256 * 256;
+  const int64_t b = blockIdx.y * per, e = b + per < M ? b + per : M;
+  const bool vec4 = rows_are_vec4(X, Q, N);
+  uint64_t best[2] = {~0ull, ~0ull};
+  for (int64_t c0 = b; c0 < e; c0 += 256) {
+    const int64_t c = c0 + tid;
+    for (int f = 0; f < kBruteQ; ++f) {
+      uint64_t key = ~0ull;
+      if (c < e && f0 + f < nq) {
+        const int64_t q = rows[f0 + f];
+        const int64_t own = self_mode == 1 ? q : (self_mode == 2 ? (int64_t)self[q] : -1);
+        if (c != own)
+          key = (uint64_t)__float_as_uint(exact_distance(Q + q * N, X + c * N, N, vec4)) << 32 | (uint32_t)c;
+      }
+      keys[f][tid] = key;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      for (int g = 0; g < 4; ++g) offer_sorted(best[h], keys[2 * wave + h][64 * g + lane], lane, k);
+    __syncthreads();
+  }
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int64_t f = f0 + 2 * wave + h;
+    if (f < nq && lane < k) part[(f * splits + blockIdx.y) * k + lane] = best[h];
+  }
+}
+
+// one wavefront per query: the k best of its ranges' lists
+__global__ void __launch_bounds__(256) knn_brute_merge_kernel(const uint64_t *__restrict__ part, int64_t nq,
+                                                              const int32_t *__restrict__ rows, int k, int splits,
+                                                              int32_t *__restrict__ out_idx,
+                                                              float *__restrict__ out_dist) {
+  const int lane = threadIdx.x & 63;
+  const int64_t f = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (f >= nq) return;
+  uint64_t best = ~0ull;
+  const uint64_t *P = part + f * splits * k;
+  for (int base = 0; base < splits * k; base += 64)
+    offer_sorted(best, base + lane < splits * k ? P[base + lane] : ~0ull, lane, k);
+  if (lane >= k) return;
+  const int64_t q = rows[f];
+  out_idx[q * k + lane] = best == ~0ull ? -1 : (int32_t)(uint32_t)best;
+  if (out_dist) out_dist[q * k + lane] = best == ~0ull ? FLT_MAX : __uint_as_float((uint32_t)(best >> 32));
+}
+
+template <int KP>
+hipError_t launch_filter_kp(const FilterArgs &f, const FinishArgs &g, hipStream_t s) {
+  knn_filter_kernel<KP><<<(unsigned)(f.nqb * f.splits), kFilterThreads, 0, s>>>(f);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  knn_finish_kernel<KP><<<grid_for(g.n_launch * KP, 256), 256, 0, s>>>(g);
+  return hipGetLastError();
+}
+
+// candidate ranges per query tile: the number that gives the shortest
+// schedule on 256 CUs (one block each).  A tile costs about 0.9 us per stage
+// and 0.7 us for its values; a range costs about 40 us for its hits and their
+// lists, whatever its length, and each list it leaves 0.1 ns per entry to merge.
+int choose_splits(int64_t nqb, int64_t tiles, int stages, int kp) {
+  int best = 1;
+  double best_t = 1e300;
+  for (int s = 1; s <= 64 && s <= tiles; ++s) {
+    const int64_t rounds = (nqb * s + kCus - 1) / kCus, per = (tiles + s - 1) / s;
+    const double t = (double)rounds * ((double)per * (0.9 * stages + 0.7) + 40.0) + 1e-4 * (double)nqb * FT * s * kp;
+    if (t < best_t * 0.995) {
+      best_t = t;
+      best = s;
+    }
+  }
+  return best;
+}
+
+// tiles of a range that set its starting thresholds: about a thirtieth of it,
+// but all of a short one (its hits are then little more than the list)
+int lead_tiles(int64_t tiles) {
+  return (int)(tiles <= 4 ? tiles : (tiles < 64 ? 3 + tiles / 16 : (tiles < 1024 ? tiles / 32 + 5 : 37)));
+}
+
+hipError_t run_filter(const FilterArgs &f, const FinishArgs &g, int kp, hipStream_t s) {
+  switch (kp) {
+    case 8: return launch_filter_kp<8>(f, g, s);
+    case 16: return launch_filter_kp<16>(f, g, s);
+    default: return launch_filter_kp<32>(f, g, s);
+  }
+}
+
+// the shortest list with room for candidates that a misranks
+int list_length(int k) { return k + 4 <= 8 ? 8 : (k + 4 <= 16 ? 16 : 32); }
+
+// query tiles of one launch (a multiple of the CUs; bounds the lists' memory)
+constexpr int64_t kBatchTiles = 16 * kCus;
+
+int64_t knn_image_halves(int64_t M, int N) { return (M + FT - 1) / FT * FT * (int64_t)((N + FK - 1) / FK * FK); }
+
+hipError_t launch_knn_split(const float *X, int64_t M, int N, const int32_t *map, const float *mean, float scale,
+                            _Float16 *hi, _Float16 *lo, float *norms, float *start, KnnStats *stats,
+                            hipStream_t s) {
+  const bool vec = N % 4 == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0;
+  const int64_t groups = (M + FT - 1) / FT * (FT / 16);
+  knn_split_kernel<<<(unsigned)(groups < 4096 ? groups : 4096), 256, 0, s>>>(X, M, N, (N + FK - 1) / FK, map, mean,
+                                                                             scale, hi, lo, norms, start, stats, vec);
+  return hipGetLastError();
+}
+
+// Segments and list length: the pilot runs kPilotTiles query tiles spread over
+// the call with one segment and counts the answers that lists of 8, 16 and
+// (when k asks for those anyway) 32 would not certify.  A failed answer costs
+// three times its share of the sweep, a longer list more hits (at 400,000 x
+// 100 lists of 8, 16 and 32 sweep in 62, 74 and about 90 ms, against 45 ms
+// without any hit): 8 while at most one answer in 16 fails, then 16 while at
+// most one in 6 does, then 32.  When half of them fail with 16, or a quarter
+// with 32, repeating them would cost more than the two segments saved, and the
+// call uses three from the start.  Calls of fewer than 4 kPilotTiles query
+// tiles go without: a pilot would be a large part of them.  With fewer than
+// kFewTiles candidate tiles (a coarse quantizer's centroids) the lists cost
+// more than the products, so short lists and three segments are best
+// (200,000 queries against 512 centroids of width 100).
+constexpr int64_t kPilotTiles = 8;
+constexpr int64_t kFewTiles = 16;
+
+}  // namespace
+
+int KnnSearch::open(int64_t M_, int N_, const float *Q_, int64_t nq_, bool same_, int k_, float scale_, hipStream_t s_) {
+  M = M_;
+  N = N_;
+  Q = Q_;
+  nq = nq_;
+  same = same_;
+  k = k_;
+  scale = scale_;
+  s = s_;
+  few = (M + FT - 1) / FT < kFewTiles;
+  const int64_t tiles = (M + FT - 1) / FT, nx = knn_image_halves(M, N), nqi = knn_image_halves(nq, N);
+  Carve V;
+  V.add(&ch, nx);
+  V.add(&norms, M);
+  V.add(&start, tiles * FT);
+  V.add(&xstats, 1);
+  V.add(&qstats, 1);
+  V.add(&fails, nq + 1);
+  V.add(&pilot, 3);
+  V.add(&mean, N);
+  V.add(&mean_part, (int64_t)kMeanParts * N);
+  if (few) {
+    V.add(&cl, nx);
+    V.add(&rest, nq + 1);
+  }
+  if (!same) {
+    V.add(&qh, nqi);
+    V.add(&qnorm, nq);
+    if (few) V.add(&ql, nqi);
+  }
+  const int rc = V.get(S, "operands of the search");
+  if (rc) return rc;
+  if (same) {
+    qh = ch;
+    ql = cl;
+    qnorm = norms;
+    qstats = xstats;
+  }
+  return IVHD_OK;
+}
+
+int KnnSearch::run(const float *X, int self_mode, const int32_t *self, int32_t *idx, float *dist) {
+  const int nk = (N + FK - 1) / FK;
+  const int64_t tiles = (M + FT - 1) / FT, nqb = (nq + FT - 1) / FT;
+  int kp = list_length(k), rc;
+  bool three = few;   // few candidates: three segments from the start, both halves made at once
+  float *centre = few ? nullptr : mean;
+  if (!few) {
+    knn_mean_parts_kernel<<<kMeanParts, 256, 0, s>>>(X, M, N, mean_part);
+    knn_mean_kernel<<<grid_for(N, 256), 256, 0, s>>>(mean_part, M, N, mean);
+    HIPCHK(hipGetLastError());
+  }
+  HIPCHK(launch_fill_i32((int32_t *)xstats, sizeof(KnnStats) / 4, 0, s));
+  HIPCHK(launch_knn_split(X, M, N, nullptr, centre, scale, ch, cl, norms, start, xstats, s));
+  if (!same && !queries_ready) {
+    HIPCHK(launch_fill_i32((int32_t *)qstats, sizeof(KnnStats) / 4, 0, s));
+    HIPCHK(launch_knn_split(Q, nq, N, nullptr, centre, scale, qh, ql, qnorm, nullptr, qstats, s));
+    queries_ready = few;   // their images do not depend on the candidates then
+  }
+
+  FilterArgs f{};
+  f.Qh = qh;
+  f.Ch = ch;
+  f.start = start;
+  f.nk = nk;
+  f.nseg = 1;
+  f.nq = nq;
+  f.M = M;
+  f.tiles = tiles;
+  f.self_mode = self_mode;
+  f.self = self;
+  FinishArgs g{};
+  g.X = X;
+  g.Q = Q;
+  g.N = N;
+  g.nk = nk;
+  g.k = k;
+  g.nq = nq;
+  g.out_idx = idx;
+  g.out_dist = dist;
+  g.nseg = 1;
+  g.qnorm = qnorm;
+  g.xs = xstats;
+  g.qs = qstats;
+  g.scale = scale;
+
+  auto sweep = [&](int64_t qb0, int64_t step, int64_t n) -> int {
+    f.qb0 = g.qb0 = qb0;
+    f.qb_step = g.qb_step = step;
+    f.nqb = n;
+    f.splits = g.splits = choose_splits(n, tiles, nk * f.nseg, kp);
+    f.tiles_per_split = (tiles + f.splits - 1) / f.splits;
+    f.lead = lead_tiles(f.tiles_per_split);
+    g.n_launch = n * FT;
+    const int64_t need = n * FT * f.splits * kp;
+    if (need > part_cap) {   // (a larger launch is queued behind the smaller: both lists stay)
+      const int r = S.get(&part, need, "candidate lists");
+      if (r) return r;
+      part_cap = need;
+    }
+    f.part = part;
+    g.part = part;
+    HIPCHK(run_filter(f, g, kp, s));
+    return IVHD_OK;
+  };
+  // all query tiles: whole rounds of the CUs take the candidates in one range,
+  // which costs the fewest hits; the rest is split to fill the CUs once more
+  // (few candidates: one launch, a second would last as long as a round)
+  auto sweep_all = [&](int64_t n) -> int {
+    const int64_t whole = few ? n : n / kCus * kCus;
+    for (int64_t b = 0; b < whole; b += kBatchTiles) {
+      const int r = sweep(b, 1, whole - b < kBatchTiles ? whole - b : kBatchTiles);
+      if (r) return r;
+    }
+    return n > whole ? sweep(whole, 1, n - whole) : IVHD_OK;
+  };
+  int32_t failed = 0;
+  auto read_failed = [&](const int32_t *list) -> int {
+    HIPCHK(hipMemcpyAsync(&failed, list, sizeof failed, hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+    return IVHD_OK;
+  };
+  g.fails = fails;
+  if (!three && nqb >= 4 * kPilotTiles) {
+    int32_t bad[3];
+    HIPCHK(launch_fill_i32(pilot, 3, 0, s));
+    g.pilot = pilot;
+    const int want = kp;
+    kp = kp < 16 ? 16 : kp;
+    if ((rc = sweep(0, nqb / kPilotTiles, kPilotTiles))) return rc;
+    g.pilot = nullptr;
+    HIPCHK(hipMemcpyAsync(bad, pilot, sizeof bad, hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+    const int32_t all = (int32_t)(kPilotTiles * FT);
+    if (kp == 32) {
+      three = bad[2] > all / 4;
+    } else {
+      three = bad[1] > all / 2;
+      if (want == 8 && bad[0] <= all / 16) kp = 8;
+      else if (bad[1] > all / 6) kp = 32;
+    }
+  } else if (!three && kp == 8) {
+    kp = 16;
+  }
+  if (!three) {
+    HIPCHK(launch_fill_i32(fails, 1, 0, s));
+    if ((rc = sweep_all(nqb)) || (rc = read_failed(fails))) return rc;
+    if (failed == 0) return IVHD_OK;
+  }
+  // three segments: everything, or the queries that were not certified
+  const int64_t n3 = three ? nq : failed;
+  const int32_t *map = three ? nullptr : fails + 1;
+  if (!few) {
+    const int64_t nx = knn_image_halves(M, N), ni = knn_image_halves(n3, N);
+    if (!rest && (rc = S.get(&rest, nq + 1, "uncertified queries (three segments)"))) return rc;
+    if ((rc = S.get(&cl, nx, "candidate operands (low)"))) return rc;
+    HIPCHK(launch_knn_split(X, M, N, nullptr, centre, scale, nullptr, cl, nullptr, nullptr, nullptr, s));
+    if (three && same) {
+      ql = cl;
+    } else {
+      if ((rc = S.get(&ql, ni, "query operands (low)"))) return rc;
+      if (!three && (rc = S.get(&qh, ni, "query operands"))) return rc;
+      HIPCHK(launch_knn_split(Q, n3, N, map, centre, scale, three ? nullptr : qh, ql, nullptr, nullptr, nullptr, s));
+    }
+  }
+  kp = list_length(k);
+  f.Qh = qh;
+  f.Ql = ql;
+  f.Cl = cl;
+  f.nseg = g.nseg = 3;
+  f.nq = g.nq = n3;
+  f.map = g.map = map;
+  HIPCHK(launch_fill_i32(rest, 1, 0, s));
+  g.fails = rest;
+  if ((rc = sweep_all((n3 + FT - 1) / FT)) || (rc = read_failed(rest))) return rc;
+  if (failed == 0) return IVHD_OK;
+  const int64_t groups = (failed + kBruteQ - 1) / kBruteQ;
+  int64_t splits = 4 * kCus / groups;
+  splits = splits < 1 ? 1 : (splits > 64 ? 64 : splits);
+  if (splits > tiles) splits = tiles;
+  uint64_t *bp;
+  if ((rc = S.get(&bp, failed * splits * k, "candidate lists (all candidates)"))) return rc;
+  knn_brute_kernel<<<dim3((unsigned)groups, (unsigned)splits), 256, 0, s>>>(X, M, N, Q, failed, rest + 1, self_mode, self,
+                                                                            k, (int)splits, bp);
+  knn_brute_merge_kernel<<<grid_for(failed, 4), 256, 0, s>>>(bp, failed, rest + 1, k, (int)splits, idx, dist);
+  HIPCHK(hipGetLastError());
+  HIPCHK(hipStreamSynchronize(s));
+  return IVHD_OK;
+}
+
+}  // namespace ivhd

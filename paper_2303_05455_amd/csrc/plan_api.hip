@@ -298,6 +298,23 @@ int ivhd_grad_edges(const float *d_y, int64_t M, const int32_t *d_nn_idx, int32_
   return rc ? rc : rc2;
 }
 
+// the largest |x| of one or two arrays (IVHD_EINVAL when it is not finite); synchronises s
+static int largest_magnitude(const float *x, int64_t nx, const float *y, int64_t ny, float *out, hipStream_t s) {
+  Scratch S;
+  uint32_t *amax = nullptr;
+  const int rc = S.get(&amax, 1, "largest magnitude");
+  if (rc) return rc;
+  uint32_t bits = 0;
+  HIPCHK(launch_fill_i32((int32_t *)amax, 1, 0, s));
+  HIPCHK(launch_absmax(x, nx, amax, s));
+  if (y) HIPCHK(launch_absmax(y, ny, amax, s));
+  HIPCHK(hipMemcpyAsync(&bits, amax, sizeof bits, hipMemcpyDeviceToHost, s));
+  HIPCHK(hipStreamSynchronize(s));
+  std::memcpy(out, &bits, sizeof bits);
+  if (!std::isfinite(*out)) return fail(IVHD_EINVAL, "the points hold a non-finite coordinate");
+  return IVHD_OK;
+}
+
 static int knn_common(const float *d_x, int64_t M, int32_t N, const float *d_q, int64_t Q,
                       int self_mode, const int32_t *d_self, int32_t k, int32_t *d_idx,
                       float *d_dist, void *stream) {
@@ -310,51 +327,12 @@ static int knn_common(const float *d_x, int64_t M, int32_t N, const float *d_q, 
   if (Q == 0) return IVHD_OK;
   hipStream_t s = (hipStream_t)stream;
   const bool same = d_q == d_x && Q == M;
-  const int Np = knn_padded_width(N);
-  float *norms = nullptr;
-  uint32_t *amax = nullptr;
-  _Float16 *xs = nullptr, *qs = nullptr;   // [2][rows][Np]: hi then lo
-  int rc = dev_alloc(&norms, (size_t)M, "row norms");
-  if (!rc) rc = dev_alloc(&amax, 1, "largest magnitude");
-  if (!rc) rc = dev_alloc(&xs, (size_t)2 * M * Np, "split rows of X");
-  if (!rc && !same) rc = dev_alloc(&qs, (size_t)2 * Q * Np, "split rows of the queries");
-  auto cleanup = [&]() {
-    void *bufs[] = {norms, amax, xs, qs};
-    for (void *b : bufs)
-      if (b) (void)hipFree(b);
-  };
-  if (rc) {
-    cleanup();
-    return rc;
-  }
-  uint32_t bits = 0;
-  hipError_t e = hipMemsetAsync(amax, 0, sizeof *amax, s);
-  if (e == hipSuccess) e = launch_absmax(d_x, M * (int64_t)N, amax, s);
-  if (e == hipSuccess && !same) e = launch_absmax(d_q, Q * (int64_t)N, amax, s);
-  if (e == hipSuccess) e = hipMemcpyAsync(&bits, amax, sizeof bits, hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
-  if (e != hipSuccess) {
-    cleanup();
-    return hip_fail(e, "knn input scan");
-  }
-  float amx;
-  std::memcpy(&amx, &bits, sizeof amx);
-  if (!std::isfinite(amx)) {
-    cleanup();
-    return fail(IVHD_EINVAL, "the points hold a non-finite coordinate");
-  }
-  const float scale = knn_split_scale(amx);
-  _Float16 *qh = same ? xs : qs, *ql = same ? xs + M * Np : qs + Q * Np;
-  e = launch_row_norms(d_x, M, N, norms, s);
-  if (e == hipSuccess) e = launch_split(d_x, M, N, Np, scale, xs, xs + M * Np, s);
-  if (e == hipSuccess && !same) e = launch_split(d_q, Q, N, Np, scale, qs, qs + Q * Np, s);
-  if (e == hipSuccess)
-    e = launch_knn(d_x, M, N, d_q, Q, xs, xs + M * Np, qh, ql, Np, scale, self_mode, d_self, norms, k, d_idx, d_dist,
-                   s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
-  cleanup();
-  if (e != hipSuccess) return hip_fail(e, "knn");
-  return IVHD_OK;
+  float amx = 0.f;
+  int rc = largest_magnitude(d_x, M * (int64_t)N, same ? nullptr : d_q, Q * (int64_t)N, &amx, s);
+  if (rc) return rc;
+  KnnSearch K;
+  if ((rc = K.open(M, N, d_q, Q, same, k, knn_split_scale(amx), s))) return rc;
+  return K.run(d_x, self_mode, d_self, d_idx, d_dist);
 }
 
 int ivhd_knn_build(const float *d_x, int64_t M, int32_t N, int32_t k, int32_t *d_idx, void *stream) {
@@ -370,21 +348,6 @@ int ivhd_knn_query(const float *d_x, int64_t M, int32_t N, const float *d_q, int
 
 namespace ivhd {
 namespace {
-
-// device buffers released together
-struct Scratch {
-  std::vector<void *> bufs;
-  ~Scratch() {
-    for (void *b : bufs)
-      if (b) (void)hipFree(b);
-  }
-  template <typename T>
-  int get(T **p, size_t n, const char *what) {
-    int rc = dev_alloc(p, n, what);
-    if (!rc) bufs.push_back(*p);
-    return rc;
-  }
-};
 
 // per-target lists of a rows x k index array (targets in [0, ntargets)):
 // ptr [ntargets+1], src [rows*k]
@@ -429,9 +392,15 @@ int ivhd_ivf_train(const float *d_x, int64_t M, int32_t N, int32_t nlist, int32_
   int32_t *flags;
   int rc = S.get(&flags, FLAG_SLOTS, "device flags");
   if (rc) return rc;
+  float amx = 0.f;
+  if ((rc = largest_magnitude(d_x, M * (int64_t)N, nullptr, 0, &amx, s))) return rc;
   HIPCHK(launch_init_centroids(d_x, M, N, nlist, d_centroids, s));
+  // the points are prepared once for all assignments; a mean is no larger
+  // than its points, so one scale holds throughout
+  KnnSearch K;
+  if ((rc = K.open(nlist, N, d_x, M, false, 1, knn_split_scale(amx), s))) return rc;
   for (int it = 0; it <= n_iter; ++it) {
-    if ((rc = ivhd_knn_query(d_centroids, nlist, N, d_x, M, nullptr, 1, d_assign, nullptr, stream))) return rc;
+    if ((rc = K.run(d_centroids, 0, nullptr, d_assign, nullptr))) return rc;
     if (it == n_iter) break;
     Scratch L;
     int32_t *lptr, *pos_id;
@@ -439,7 +408,8 @@ int ivhd_ivf_train(const float *d_x, int64_t M, int32_t N, int32_t nlist, int32_
     HIPCHK(launch_centroid_mean(d_x, N, lptr, pos_id, nlist, d_centroids, s));
     HIPCHK(hipStreamSynchronize(s));   // before L frees the lists
   }
-  return IVHD_OK;
+  // (a sum of huge coordinates can overflow)
+  return largest_magnitude(d_centroids, (int64_t)nlist * N, nullptr, 0, &amx, s);
 }
 
 int ivhd_ivf_search(const float *d_x, int64_t M, int32_t N, const float *d_centroids, int32_t nlist,
