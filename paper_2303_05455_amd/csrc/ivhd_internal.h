@@ -5,8 +5,6 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include <vector>
-
 #include "ivhd.h"
 
 namespace ivhd {
@@ -51,46 +49,6 @@ int dev_alloc(T **p, size_t count, const char *what) {
   }
   return IVHD_OK;
 }
-
-// device buffers released together
-struct Scratch {
-  std::vector<void *> bufs;
-  Scratch() = default;
-  Scratch(const Scratch &) = delete;
-  Scratch &operator=(const Scratch &) = delete;
-  ~Scratch() {
-    for (void *b : bufs)
-      if (b) (void)hipFree(b);
-  }
-  template <typename T>
-  int get(T **p, size_t n, const char *what) {
-    int rc = dev_alloc(p, n, what);
-    if (!rc) bufs.push_back(*p);
-    return rc;
-  }
-};
-
-// several buffers out of one allocation (each on a 256-byte boundary)
-struct Carve {
-  struct Part {
-    void **p;
-    size_t at;
-  };
-  std::vector<Part> parts;
-  size_t bytes = 0;
-  template <typename T>
-  void add(T **p, size_t n) {
-    parts.push_back({reinterpret_cast<void **>(p), bytes});
-    bytes += (n * sizeof(T) + 255) / 256 * 256;
-  }
-  int get(Scratch &S, const char *what) {
-    unsigned char *base;
-    const int rc = S.get(&base, bytes, what);
-    if (!rc)
-      for (const Part &q : parts) *q.p = base + q.at;
-    return rc;
-  }
-};
 
 inline unsigned grid_for(int64_t n, int block = kBlock) {
   int64_t g = (n + block - 1) / block;
@@ -309,38 +267,12 @@ float knn_split_scale(float absmax);    // power of two keeping scaled values be
 // hi / lo FP16 rows of scale * X, [M][Np], zero padded
 hipError_t launch_split(const float *X, int64_t M, int N, int Np, float scale, _Float16 *hi, _Float16 *lo,
                         hipStream_t s);
-
-// ---- knn_filter.hip ----
-// largest squared norm and squared rounding residual of a set of rows, as
-// float bits (non-negative floats compare as integers); zero before use
-struct KnnStats {
-  uint32_t norm2, res2;
-};
-// One search: k nearest of M candidate rows to each of nq rows of Q (same: the
-// candidates are Q).  Its buffers live as long as it does.
-struct KnnSearch {
-  // allocates; scale from knn_split_scale over every coordinate
-  int open(int64_t M, int N, const float *Q, int64_t nq, bool same, int k, float scale, hipStream_t s);
-  // the answers for the candidates X [M][N]; self_mode: 0 = none, 1 = query q
-  // excludes candidate q, 2 = query q excludes self[q].  Synchronises the
-  // stream.  Against few candidates (few) it may be called again with others:
-  // the queries, which must not have changed, are prepared once.
-  int run(const float *X, int self_mode, const int32_t *self, int32_t *idx, float *dist);
-
-  Scratch S;
-  int64_t M = 0, nq = 0;
-  int N = 0, k = 0;
-  const float *Q = nullptr;
-  bool same = false, few = false, queries_ready = false;
-  float scale = 1.f;
-  hipStream_t s = nullptr;
-  _Float16 *ch = nullptr, *cl = nullptr, *qh = nullptr, *ql = nullptr;   // operand images, high and low
-  float *norms = nullptr, *start = nullptr, *qnorm = nullptr, *mean = nullptr, *mean_part = nullptr;
-  KnnStats *xstats = nullptr, *qstats = nullptr;
-  int32_t *fails = nullptr, *rest = nullptr, *pilot = nullptr;
-  uint64_t *part = nullptr;
-  int64_t part_cap = 0;
-};
+// self_mode: 0 = none, 1 = query q excludes candidate q, 2 = query q excludes self[q].
+// Xh/Xl, Qh/Ql: the split rows of X and Q at the same scale (Qh == Xh when Q == X).
+hipError_t launch_knn(const float *X, int64_t M, int N, const float *Q, int64_t nq, const _Float16 *Xh,
+                      const _Float16 *Xl, const _Float16 *Qh, const _Float16 *Ql, int Np, float scale,
+                      int self_mode, const int32_t *self, const float *cnorm, int k, int32_t *idx, float *dist,
+                      hipStream_t s);
 
 // inverted-file search (knn.hip): split rows gathered in list order
 hipError_t launch_gather_f32(const float *src, const int32_t *idx, int64_t n, float *dst, hipStream_t s);

@@ -54,7 +54,7 @@
 // products.
 #include <cfloat>
 
-#include "ivhd_internal.h"
+#include "knn_internal.h"
 #include "knn_rank.h"
 
 namespace ivhd {

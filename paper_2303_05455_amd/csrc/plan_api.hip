@@ -8,7 +8,7 @@
 
 #include <cstring>
 
-#include "ivhd_internal.h"
+#include "knn_internal.h"
 
 using namespace ivhd;
 
