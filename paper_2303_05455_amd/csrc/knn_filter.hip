@@ -914,11 +914,16 @@ hipError_t launch_knn_split(const float *X, int64_t M, int N, const int32_t *map
 // without any hit): 8 while at most one answer in 16 fails, then 16 while at
 // most one in 6 does, then 32.  When half of them fail with 16, or a quarter
 // with 32, repeating them would cost more than the two segments saved, and the
-// call uses three from the start.  Calls of fewer than 4 kPilotTiles query
-// tiles go without: a pilot would be a large part of them.  With fewer than
-// kFewTiles candidate tiles (a coarse quantizer's centroids) the lists cost
-// more than the products, so short lists and three segments are best
-// (200,000 queries against 512 centroids of width 100).
+// call uses three from the start.  Calls of fewer query tiles than CUs go
+// without a pilot, which takes as long as it takes a block to fill its lists
+// (1.4 ms with lists of 32) and leaves most CUs idle: 50,000 x 128, k 2 / 5 /
+// 10 / 20: 2.8 / 3.4 / 5.0 / 7.3 ms with one, 2.4 / 2.7 / 3.9 / 5.9 without.
+// Wide rows keep it from 4 kPilotTiles tiles on, as their failed answers cost
+// more than the pilot (20,000 x 500, k 10: 2.9 ms with it, 3.6 without).  With
+// fewer than kFewTiles candidate tiles (a coarse quantizer's centroids) the
+// lists cost more than the products, so short lists and three segments are
+// best (200,000 queries against 512 centroids of width 100).
+constexpr int kWidePilot = 256;
 constexpr int64_t kPilotTiles = 8;
 constexpr int64_t kFewTiles = 16;
 
@@ -1047,7 +1052,7 @@ int KnnSearch::run(const float *X, int self_mode, const int32_t *self, int32_t *
     return IVHD_OK;
   };
   g.fails = fails;
-  if (!three && nqb >= 4 * kPilotTiles) {
+  if (!three && nqb >= (N > kWidePilot ? 4 * kPilotTiles : kCus)) {
     int32_t bad[3];
     HIPCHK(launch_fill_i32(pilot, 3, 0, s));
     g.pilot = pilot;
