@@ -124,8 +124,7 @@ void free_ctx(ivhd_ctx *c) {
                   c->rn_csc.ptr, c->rn_csc.src, c->sc.cnt, c->sc.tmp, c->sc.part, c->sc.big, c->sc.rank, c->rn_idx,
                   c->epoch, c->flags, c->fbuf, c->fown, c->facc, c->rx, c->fflag, c->heavy, c->partials, c->d_E, c->ha, c->hb, c->vb,
                   c->adapt, c->ke_part, c->s2, c->adam};
-  for (void *b : bufs)
-    if (b) (void)hipFree(b);
+  dev_free_all(bufs, sizeof bufs / sizeof bufs[0], c->stream);
   if (c->cap) (void)hipStreamDestroy(c->cap);
   delete c;
 }

@@ -74,8 +74,7 @@ void free_enc(ivhd_enc *e) {
   void *bufs[] = {e->w, e->g, e->m, e->v, e->w16, e->xb, e->a1, e->a2, e->d2, e->z, e->dz, e->ws,
                   e->rows, e->lnn, e->lrn, e->rn_all, e->d_epoch, e->d_losses, e->xbT, e->a1T, e->d1T, e->d2T,
                   e->w2T};
-  for (void *b : bufs)
-    if (b) (void)hipFree(b);
+  dev_free_all(bufs, sizeof bufs / sizeof bufs[0], e->stream);
   delete e;
 }
 
@@ -392,9 +391,9 @@ int ivhd_enc_train_epoch(ivhd_enc *e, const uint16_t *d_x16, int64_t M, const in
       (void)ivhd_edges_destroy(e->plan);
       e->plan = nullptr;
     }
-    if (e->lnn) (void)hipFree(e->lnn);
-    if (e->lrn) (void)hipFree(e->lrn);
-    if (e->rows) (void)hipFree(e->rows);
+    dev_free(e->lnn, s);
+    dev_free(e->lrn, s);
+    dev_free(e->rows, s);
     e->lnn = e->lrn = e->rows = nullptr;
     if ((rc = dev_alloc(&e->lnn, R * nn, "batch nn lists"))) return rc;
     if (rn > 0 && (rc = dev_alloc(&e->lrn, R * rn, "batch rn lists"))) return rc;
@@ -406,7 +405,7 @@ int ivhd_enc_train_epoch(ivhd_enc *e, const uint16_t *d_x16, int64_t M, const in
     e->plan_rn = rn;
   }
   if (rn > 0 && e->rn_all_elems < M * rn) {
-    if (e->rn_all) (void)hipFree(e->rn_all);
+    dev_free(e->rn_all, s);
     e->rn_all = nullptr;
     e->rn_all_elems = 0;
     if ((rc = dev_alloc(&e->rn_all, M * rn, "epoch random neighbours"))) return rc;
@@ -414,7 +413,7 @@ int ivhd_enc_train_epoch(ivhd_enc *e, const uint16_t *d_x16, int64_t M, const in
   }
   const int64_t steps = (M + batch - 1) / batch;
   if (e->losses_cap < steps) {
-    if (e->d_losses) (void)hipFree(e->d_losses);
+    dev_free(e->d_losses, s);
     e->d_losses = nullptr;
     e->losses_cap = 0;
     if ((rc = dev_alloc(&e->d_losses, steps, "step losses"))) return rc;

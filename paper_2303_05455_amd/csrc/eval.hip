@@ -640,7 +640,7 @@ int check_indices(const int32_t *const *arrays, const int64_t *counts, int n, in
   int32_t h[FLAG_SLOTS] = {0};
   if (e == hipSuccess) e = hipMemcpyAsync(h, flags, sizeof h, hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
-  (void)hipFree(flags);
+  dev_free(flags, s);
   if (e != hipSuccess) return hip_fail(e, "index range check");
   if (h[FLAG_BAD_INDEX]) return fail(IVHD_EINVAL, "an index entry is outside [0, %lld)", (long long)hi);
   return IVHD_OK;
@@ -668,7 +668,7 @@ int ivhd_eval_neighbours(const float *d_z, int64_t M, int32_t N, const int32_t *
   const int64_t list = (int64_t)w.S * (k + 1), nd = eval_dims(N);
   w.band = eval_band(Q, nd * 8 + 8 + list * 12);
   const int64_t slots = (w.band + kRows - 1) / kRows * kRows;
-  Scratch S;
+  Scratch S(s);
   Carve c;
   c.add(&w.rq, (size_t)(slots * nd + kRows));   // the scan loads a dimension ahead
   c.add(&w.row_thr, (size_t)w.band);
@@ -698,7 +698,7 @@ int ivhd_eval_ranks(const float *d_z, int64_t M, int32_t N, const int32_t *d_row
   const int64_t nd = eval_dims(N);
   w.band = eval_band(Q, nd * 8 + kc * 12);
   const int64_t slots = (w.band + kRows - 1) / kRows * kRows;
-  Scratch S;
+  Scratch S(s);
   Carve c;
   c.add(&w.rq, (size_t)(slots * nd + kRows));
   c.add(&w.thr, (size_t)(slots * kc));
@@ -732,7 +732,7 @@ int ivhd_eval_scores(int64_t M, const int32_t *d_rows, int64_t Q, const int32_t 
   hipError_t e = launch_eval_scores(d_rows, Q, d_nx, kx, d_ny, ky, d_rank_y, d_labels, k, sums, s);
   if (e == hipSuccess) e = hipMemcpyAsync(h, sums, sizeof h, hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
-  (void)hipFree(sums);
+  dev_free(sums, s);
   if (e != hipSuccess) return hip_fail(e, "eval scores");
   const double kq = (double)k * (double)Q;
   h_out[0] = d_nx ? (double)h[0] / kq : NAN;

@@ -36,11 +36,19 @@ void clear_error();
     if (_e != hipSuccess) return ::ivhd::hip_fail(_e, #expr); \
   } while (0)
 
+// ---- pool.hip ----
+// device memory on the current device; release with dev_free_all / dev_free
+hipError_t pool_get(void **p, size_t bytes);
+// releases buffers of dev_alloc (NULL ones are skipped) that only work on
+// stream has used; synchronises it
+void dev_free_all(void *const *bufs, size_t n, hipStream_t stream);
+inline void dev_free(void *p, hipStream_t stream) { dev_free_all(&p, 1, stream); }
+
 template <typename T>
 int dev_alloc(T **p, size_t count, const char *what) {
   *p = nullptr;
   if (count == 0) count = 1;
-  hipError_t e = hipMalloc((void **)p, count * sizeof(T));
+  hipError_t e = pool_get((void **)p, count * sizeof(T));
   if (e != hipSuccess) {
     *p = nullptr;
     (void)hipGetLastError();
@@ -267,13 +275,6 @@ float knn_split_scale(float absmax);    // power of two keeping scaled values be
 // hi / lo FP16 rows of scale * X, [M][Np], zero padded
 hipError_t launch_split(const float *X, int64_t M, int N, int Np, float scale, _Float16 *hi, _Float16 *lo,
                         hipStream_t s);
-// self_mode: 0 = none, 1 = query q excludes candidate q, 2 = query q excludes self[q].
-// Xh/Xl, Qh/Ql: the split rows of X and Q at the same scale (Qh == Xh when Q == X).
-hipError_t launch_knn(const float *X, int64_t M, int N, const float *Q, int64_t nq, const _Float16 *Xh,
-                      const _Float16 *Xl, const _Float16 *Qh, const _Float16 *Ql, int Np, float scale,
-                      int self_mode, const int32_t *self, const float *cnorm, int k, int32_t *idx, float *dist,
-                      hipStream_t s);
-
 // inverted-file search (knn.hip): split rows gathered in list order
 hipError_t launch_gather_f32(const float *src, const int32_t *idx, int64_t n, float *dst, hipStream_t s);
 hipError_t launch_split_gather(const float *X, int64_t M, int N, int Np, float scale, const int32_t *pos_id,

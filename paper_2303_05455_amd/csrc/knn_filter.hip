@@ -938,6 +938,7 @@ int KnnSearch::open(int64_t M_, int N_, const float *Q_, int64_t nq_, bool same_
   k = k_;
   scale = scale_;
   s = s_;
+  S.stream = s_;
   few = (M + FT - 1) / FT < kFewTiles;
   const int64_t tiles = (M + FT - 1) / FT, nx = knn_image_halves(M, N), nqi = knn_image_halves(nq, N);
   Carve V;

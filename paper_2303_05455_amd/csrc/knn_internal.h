@@ -8,16 +8,14 @@
 
 namespace ivhd {
 
-// device buffers released together
+// device buffers of work on one stream, released together
 struct Scratch {
   std::vector<void *> bufs;
-  Scratch() = default;
+  hipStream_t stream;
+  explicit Scratch(hipStream_t s = nullptr) : stream(s) {}
   Scratch(const Scratch &) = delete;
   Scratch &operator=(const Scratch &) = delete;
-  ~Scratch() {
-    for (void *b : bufs)
-      if (b) (void)hipFree(b);
-  }
+  ~Scratch() { dev_free_all(bufs.data(), bufs.size(), stream); }
   template <typename T>
   int get(T **p, size_t n, const char *what) {
     int rc = dev_alloc(p, n, what);

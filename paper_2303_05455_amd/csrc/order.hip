@@ -65,8 +65,7 @@ int sort_vertex_order(const int32_t *root, const int32_t *indeg, const int32_t *
   int rc = IVHD_OK;
   auto cleanup = [&]() {
     void *bufs[] = {k1, k1_out, k2, k2_out, ids, ids1, temp};
-    for (void *b : bufs)
-      if (b) (void)hipFree(b);
+    dev_free_all(bufs, sizeof bufs / sizeof bufs[0], s);
   };
   hipError_t e = hipcub::DeviceRadixSort::SortPairs(nullptr, t1, k1, k1_out, ids, ids1, (int)M, 0, 32, s);
   if (e == hipSuccess)

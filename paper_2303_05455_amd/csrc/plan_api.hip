@@ -81,8 +81,7 @@ void free_edges(ivhd_edges *e) {
   void *bufs[] = {e->nn_csc.ptr, e->nn_csc.src, e->rn_csc.ptr, e->rn_csc.src, e->sc.cnt, e->sc.tmp,
                   e->sc.part, e->sc.big, e->heavy, e->flags, e->partials, e->perm, e->inv,
                   e->nn_own, e->rn_own, e->yp, e->gparts};
-  for (void *b : bufs)
-    if (b) (void)hipFree(b);
+  dev_free_all(bufs, sizeof bufs / sizeof bufs[0], e->stream);
   delete e;
 }
 
@@ -292,7 +291,7 @@ int ivhd_grad_edges(const float *d_y, int64_t M, const int32_t *d_nn_idx, int32_
       if (err == hipSuccess) err = hipStreamSynchronize(e->stream);
       if (err != hipSuccess) rc = hip_fail(err, "stress copy");
     }
-    if (d_E) (void)hipFree(d_E);
+    dev_free(d_E, (hipStream_t)stream);
   }
   int rc2 = ivhd_edges_destroy(e);
   return rc ? rc : rc2;
@@ -300,7 +299,7 @@ int ivhd_grad_edges(const float *d_y, int64_t M, const int32_t *d_nn_idx, int32_
 
 // the largest |x| of one or two arrays (IVHD_EINVAL when it is not finite); synchronises s
 static int largest_magnitude(const float *x, int64_t nx, const float *y, int64_t ny, float *out, hipStream_t s) {
-  Scratch S;
+  Scratch S(s);
   uint32_t *amax = nullptr;
   const int rc = S.get(&amax, 1, "largest magnitude");
   if (rc) return rc;
@@ -388,7 +387,7 @@ int ivhd_ivf_train(const float *d_x, int64_t M, int32_t N, int32_t nlist, int32_
   if (nlist < 2 || nlist > M) return fail(IVHD_EINVAL, "nlist = %d outside [2, M]", nlist);
   if (n_iter < 0) return fail(IVHD_EINVAL, "n_iter = %d < 0", n_iter);
   hipStream_t s = (hipStream_t)stream;
-  Scratch S;
+  Scratch S((hipStream_t)stream);
   int32_t *flags;
   int rc = S.get(&flags, FLAG_SLOTS, "device flags");
   if (rc) return rc;
@@ -428,7 +427,7 @@ int ivhd_ivf_search(const float *d_x, int64_t M, int32_t N, const float *d_centr
   if (Q * (int64_t)nprobe > (int64_t)INT32_MAX) return fail(IVHD_EINVAL, "Q * nprobe exceeds 2^31-1");
   if (Q == 0) return IVHD_OK;
   hipStream_t s = (hipStream_t)stream;
-  Scratch S;
+  Scratch S((hipStream_t)stream);
   int32_t *flags;
   int rc = S.get(&flags, FLAG_SLOTS, "device flags");
   if (rc) return rc;
@@ -510,7 +509,7 @@ int ivhd_rnn_mask(const int32_t *d_nn_idx, int64_t M, int32_t nn, const int32_t 
   if (e == hipSuccess) e = launch_validate_idx(d_nn_idx, M, nn, -1, flags, s);
   if (e == hipSuccess) e = hipMemcpyAsync(hflags, flags, sizeof hflags, hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
-  (void)hipFree(flags);
+  dev_free(flags, s);
   if (e != hipSuccess) return hip_fail(e, "validating nn_idx");
   if (hflags[FLAG_BAD_INDEX]) return fail(IVHD_EINVAL, "nn_idx holds an entry outside [-1, M) or a self edge");
   HIPCHK(launch_rnn_mask(d_nn_idx, M, nn, d_helper, kh, d_out, s));
