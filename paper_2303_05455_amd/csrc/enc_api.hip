@@ -51,6 +51,7 @@ struct ivhd_enc {
   int32_t *rn_all = nullptr;
   int64_t rn_all_elems = 0;
   int64_t *d_epoch = nullptr;
+  uint16_t *pack = nullptr;   // the fused forward's weights in its lanes' order
   double *d_losses = nullptr;
   int64_t losses_cap = 0;
 };
@@ -73,7 +74,7 @@ void free_enc(ivhd_enc *e) {
   if (e->plan) (void)ivhd_edges_destroy(e->plan);
   void *bufs[] = {e->w, e->g, e->m, e->v, e->w16, e->xb, e->a1, e->a2, e->d2, e->z, e->dz, e->ws,
                   e->rows, e->lnn, e->lrn, e->rn_all, e->d_epoch, e->d_losses, e->xbT, e->a1T, e->d1T, e->d2T,
-                  e->w2T};
+                  e->w2T, e->pack};
   dev_free_all(bufs, sizeof bufs / sizeof bufs[0], e->stream);
   delete e;
 }
@@ -97,9 +98,27 @@ GemmArgs gemm(const uint16_t *A, const uint16_t *B, int64_t M, int64_t N, int64_
   return g;
 }
 
-// forward of R rows (R <= r_cap) from BF16 input X (row pitch n_in) into z
-int forward_rows(ivhd_enc *e, const uint16_t *X, int64_t R, float *z) {
+// forward of R rows from BF16 input X (row pitch n_in) into z, the hidden
+// activations into a1 and a2 if they are wanted (R <= r_cap then)
+int forward_rows(ivhd_enc *e, const uint16_t *X, int64_t R, float *z, bool keep) {
   hipStream_t s = e->stream;
+  if (mlp_ok(X, e->w16 + e->oW1, e->n_in, e->h1, e->h2)) {
+    MlpArgs m{};
+    m.X = X;
+    m.b1 = e->w + e->ob1;
+    m.b2 = e->w + e->ob2;
+    m.b3 = e->w + e->ob3;
+    m.W3 = e->w16 + e->oW3;
+    m.A1 = keep ? e->a1 : nullptr;
+    m.A2 = keep ? e->a2 : nullptr;
+    m.Z = z;
+    m.R = R;
+    m.n_in = e->n_in;
+    m.h1 = e->h1;
+    m.h2 = e->h2;
+    HIPCHK(launch_mlp_forward(m, e->w16 + e->oW1, e->w16 + e->oW2, e->pack, s));
+    return IVHD_OK;
+  }
   GemmArgs g1 = gemm(X, e->w16 + e->oW1, R, e->h1, e->n_in, e->n_in, e->n_in, e->a1, e->h1);
   g1.bias = e->w + e->ob1;
   HIPCHK(launch_gemm_bf16(g1, 0, 1, GEMM_EPI_BIAS_RELU_BF16, 1, s));
@@ -138,10 +157,11 @@ int feature_major(const uint16_t *in, int64_t R, int64_t C, int64_t ldo, uint16_
   return IVHD_OK;
 }
 
-// batch input rows into e->xb: rows[r] of src when rows is given, else the R
-// rows of src; with the 16-byte path the feature-major copy e->xbT is
-// written in the same pass (*xbT_ready)
-int stage_batch(ivhd_enc *e, const uint16_t *src, const int32_t *rows, int64_t R, bool *xbT_ready) {
+// batch input rows: rows[r] of src into e->xb when rows is given, else the R
+// rows of src as they are (*X); with the 16-byte path the feature-major copy
+// e->xbT is written in the same pass (*xbT_ready)
+int stage_batch(ivhd_enc *e, const uint16_t *src, const int32_t *rows, int64_t R, const uint16_t **X,
+                bool *xbT_ready) {
   hipStream_t s = e->stream;
   TileTArgs t;
   t.in = src;
@@ -149,27 +169,26 @@ int stage_batch(ivhd_enc *e, const uint16_t *src, const int32_t *rows, int64_t R
   t.R = R;
   t.C = e->n_in;
   t.ldo = (R + 7) / 8 * 8;
-  t.out = e->xb;
+  t.out = rows ? e->xb : nullptr;
   t.outT = e->xbT;
+  *X = rows ? e->xb : src;
   *xbT_ready = tile_t_ok(t);
   if (*xbT_ready) {
     HIPCHK(launch_tile_t(rows ? TT_GATHER : TT_COPY, t, s));
   } else if (rows) {
     HIPCHK(launch_gather_rows(src, e->n_in, rows, R, e->xb, s));
-  } else {
-    HIPCHK(hipMemcpyAsync(e->xb, src, (size_t)R * e->n_in * sizeof(uint16_t), hipMemcpyDeviceToDevice, s));
   }
   return IVHD_OK;
 }
 
-// one step on the batch already in e->xb (R rows) with local edge plan `plan`
-int train_step_rows(ivhd_enc *e, int64_t R, bool xbT_ready, ivhd_edges *plan, float c, float eps, float lr,
+// one step on the batch X (R rows) with local edge plan `plan`
+int train_step_rows(ivhd_enc *e, const uint16_t *X, int64_t R, bool xbT_ready, ivhd_edges *plan, float c, float eps, float lr,
                     float scale, double *d_loss) {
   hipStream_t s = e->stream;
   const int64_t Rp = (R + 7) / 8 * 8;
-  int rc = forward_rows(e, e->xb, R, e->z);
+  int rc = forward_rows(e, X, R, e->z, true);
   if (rc) return rc;
-  if (!xbT_ready && (rc = feature_major(e->xb, R, e->n_in, Rp, e->xbT, s))) return rc;
+  if (!xbT_ready && (rc = feature_major(X, R, e->n_in, Rp, e->xbT, s))) return rc;
   if ((rc = feature_major(e->a1, R, e->h1, Rp, e->a1T, s))) return rc;
   if ((rc = feature_major(e->w16 + e->oW2, e->h2, e->h1, e->h2, e->w2T, s))) return rc;
   if (d_loss) {   // the batch stress and its gradient from one pass
@@ -301,6 +320,7 @@ int ivhd_enc_create(ivhd_enc **out, int32_t n_in, int32_t h1, int32_t h2, uint64
   ENC_CHK(dev_alloc(&e->dz, max_rows * 2, "embedding gradient"));
   ENC_CHK(dev_alloc(&e->ws, e->ws_elems, "encoder workspace"));
   ENC_CHK(dev_alloc(&e->d_epoch, 1, "epoch counter"));
+  if (mlp_ok(nullptr, nullptr, n_in, h1, h2)) ENC_CHK(dev_alloc(&e->pack, mlp_pack_elems(n_in, h1), "packed weights"));
   hipStream_t s = e->stream;
   ENC_HIP(launch_fill_i32((int32_t *)e->w, np, 0, s));
   ENC_HIP(launch_fill_i32((int32_t *)e->m, np, 0, s));
@@ -351,9 +371,11 @@ int ivhd_enc_embed(ivhd_enc *e, const uint16_t *d_x16, int64_t rows, float *d_z)
   if (!enc_live(e)) return fail(IVHD_ESTATE, "invalid encoder");
   if (rows < 0) return fail(IVHD_EINVAL, "rows = %lld < 0", (long long)rows);
   if (rows > 0 && (!d_x16 || !d_z)) return fail(IVHD_EINVAL, "d_x16 and d_z must not be NULL");
-  for (int64_t r0 = 0; r0 < rows; r0 += e->r_cap) {
-    const int64_t R = rows - r0 < e->r_cap ? rows - r0 : e->r_cap;
-    int rc = forward_rows(e, d_x16 + r0 * e->n_in, R, d_z + 2 * r0);
+  // the fused pass needs no room for activations: all rows at once
+  const int64_t step = mlp_ok(d_x16, e->w16 + e->oW1, e->n_in, e->h1, e->h2) ? (int64_t)1 << 30 : e->r_cap;
+  for (int64_t r0 = 0; r0 < rows; r0 += step) {
+    const int64_t R = rows - r0 < step ? rows - r0 : step;
+    int rc = forward_rows(e, d_x16 + r0 * e->n_in, R, d_z + 2 * r0, false);
     if (rc) return rc;
   }
   return IVHD_OK;
@@ -366,9 +388,10 @@ int ivhd_enc_train_step(ivhd_enc *e, const uint16_t *d_xb16, int64_t R, ivhd_edg
   if (!d_xb16 || !plan) return fail(IVHD_EINVAL, "d_xb16 and plan must not be NULL");
   if (!(lr > 0.f) || !std::isfinite(lr)) return fail(IVHD_EINVAL, "lr = %g must be > 0", (double)lr);
   bool ready = false;
-  int rc = stage_batch(e, d_xb16, nullptr, R, &ready);
+  const uint16_t *X = nullptr;
+  int rc = stage_batch(e, d_xb16, nullptr, R, &X, &ready);
   if (rc) return rc;
-  return train_step_rows(e, R, ready, plan, c, eps, lr, loss_scale, d_loss);
+  return train_step_rows(e, X, R, ready, plan, c, eps, lr, loss_scale, d_loss);
 }
 
 int ivhd_enc_train_epoch(ivhd_enc *e, const uint16_t *d_x16, int64_t M, const int32_t *d_nn_idx, int32_t nn,
@@ -434,8 +457,9 @@ int ivhd_enc_train_epoch(ivhd_enc *e, const uint16_t *d_x16, int64_t M, const in
   for (int64_t st = 0; st < steps; ++st) {
     HIPCHK(launch_batch_rows(d_nn_idx, nn, e->rn_all, rn, M, batch, a, c0, st * batch, e->rows, s));
     bool ready = false;
-    if ((rc = stage_batch(e, d_x16, e->rows, R, &ready))) return rc;
-    if ((rc = train_step_rows(e, R, ready, e->plan, c, eps, lr, scale, e->d_losses + st))) return rc;
+    const uint16_t *X = nullptr;
+    if ((rc = stage_batch(e, d_x16, e->rows, R, &X, &ready))) return rc;
+    if ((rc = train_step_rows(e, X, R, ready, e->plan, c, eps, lr, scale, e->d_losses + st))) return rc;
   }
   if (h_loss) {
     double *tmp = new (std::nothrow) double[steps];

@@ -64,6 +64,27 @@ hipError_t launch_adam(float *w, const float *g, float *m, float *v, uint16_t *w
 hipError_t launch_glorot(float *w, int64_t n, int fan_in, int fan_out, uint64_t seed, uint64_t offset,
                          hipStream_t s);
 
+// ---- enc_mlp.hip ----
+// the whole forward pass of R rows X [R][n_in] into Z [R][2]; A1 and A2, the
+// hidden activations, are stored when A1 is given (both then)
+struct MlpArgs {
+  const uint16_t *X;
+  const uint16_t *W1p, *W2p;   // packed weights (set by launch_mlp_forward)
+  const float *b1, *b2, *b3;
+  const uint16_t *W3;          // [2][h2]
+  uint16_t *A1, *A2;
+  float *Z;
+  int64_t R;
+  int n_in, h1, h2;
+};
+// rows of whole 16-byte chunks (X and the weights) and hidden widths that leave
+// none of the eight wavefronts of 64 columns idle; W2 lies h1 rows and the
+// biases behind W1
+bool mlp_ok(const uint16_t *X, const uint16_t *W1, int n_in, int h1, int h2);
+int64_t mlp_pack_elems(int n_in, int h1);
+// pack: [mlp_pack_elems] scratch, 16-byte aligned
+hipError_t launch_mlp_forward(MlpArgs a, const uint16_t *W1, const uint16_t *W2, uint16_t *pack, hipStream_t s);
+
 hipError_t launch_batch_rows(const int32_t *nn_idx, int nn, const int32_t *rn_idx, int rn, int64_t M, int64_t B,
                              uint64_t a, uint64_t c0, int64_t off, int32_t *rows, hipStream_t s);
 hipError_t launch_batch_plan(int64_t B, int nn, int rn, int32_t *lnn, int32_t *lrn, hipStream_t s);
