@@ -9,12 +9,12 @@
 // single 16-byte LDS read.  The instruction is v_mfma_f32_16x16x32_bf16:
 // lane l supplies A[l%16][8(l/16)..+8) and B[8(l/16)..+8)[l%16], and
 // receives D[4(l/16)+r][l%16], r = 0..3.
-// Two kernels: gemm_nt_kernel when both operands are K-contiguous (ta = 0,
-// tb = 1) with 16-byte rows (every GEMM of the training step is arranged
-// so): 256 x 128 tiles of 8 waves, K steps of 32 through a ring of LDS
-// stages filled by direct-to-LDS loads; gemm_kernel for every other
-// layout: 128 x 128 tiles of 4 waves, K steps of 32 staged through
-// registers.
+// Three kernels: gemm_nt_kernel when both operands are K-contiguous (ta = 0,
+// tb = 1) with 16-byte rows, gemm_tn_kernel when both are K-major (ta = 1,
+// tb = 0) with 16-byte rows: the training step's input and weight gradients,
+// 256 x 128 tiles of 8 waves, K steps of 32 through a ring of LDS stages filled
+// by direct-to-LDS loads; gemm_kernel for every other layout: 128 x 128 tiles
+// of 4 waves, K steps of 32 staged through registers.
 // Epilogues: FP32 store (split-K partials: the K split selects the K range
 // and the output slab), bias + ReLU -> BF16, or (dgrad) multiply by the
 // ReLU derivative read from the forward activation -> BF16.
@@ -31,18 +31,20 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 constexpr int TM = 128, TN = 128, TK = 32;
 constexpr int KP = TK + 8;   // LDS row pitch in bf16 (80 bytes: 16-byte aligned rows)
 constexpr int kGemmThreads = 256;
+constexpr int kColsumLanes = 8, kColsumThreads = 32 * kColsumLanes;   // row lanes of the column sums
 
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
-__device__ __forceinline__ uint16_t f2bf(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7f800000u) == 0x7f800000u && (u & 0x007fffffu)) return (uint16_t)((u >> 16) | 0x40);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
+// to nearest even, a NaN quietened: the conversion instruction's results, which
+// the eight integer operations of doing it by hand have for every float
+__device__ __forceinline__ uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 
 struct alignas(16) U16x8 {
   uint16_t v[8];
+};
+
+struct alignas(8) U16x4 {
+  uint16_t v[4];
 };
 
 // one operand tile (rows r0..r0+127 of op, k0..k0+31) in two halves, so the
@@ -223,92 +225,12 @@ typedef __attribute__((address_space(3))) void lds_void;
 
 __device__ __forceinline__ int ring_slot(int row, int chunk) { return row * 4 + (chunk ^ ((row >> 1) & 3)); }
 
+// Epilogue of both 256 x 128 kernels; the ring S is free.
 template <int EPI>
-__global__ void __launch_bounds__(kNtThreads, 2) gemm_nt_kernel(GemmArgs g, int64_t tiles_m, int64_t tiles_n) {
-  __shared__ __attribute__((aligned(16))) uint16_t S[kRing * kStage];
+__device__ __forceinline__ void ring_epilogue(const GemmArgs &g, const floatx4 (&acc)[4][4], uint16_t *S, int64_t m0,
+                                              int64_t n0, int64_t z) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int64_t nb = (int64_t)gridDim.x, lin = blockIdx.x;
-  const int64_t q = nb / kXcds, rem = nb % kXcds, x = lin % kXcds, i = lin / kXcds;
-  const int64_t tile = x < rem ? x * (q + 1) + i : rem * (q + 1) + (x - rem) * q + i;
-  const int64_t per_z = tiles_m * tiles_n, z = tile / per_z, t = tile % per_z;
-  const bool m_outer = tiles_m >= tiles_n;
-  const int64_t m0 = (m_outer ? t / tiles_n : t % tiles_m) * BM;
-  const int64_t n0 = (m_outer ? t % tiles_n : t / tiles_m) * BN;
-  const int64_t kbeg = z * g.kchunk;
-  const int64_t kend = kbeg + g.kchunk < g.K ? kbeg + g.kchunk : g.K;
-  const int nsteps = (int)((kend - kbeg + BK - 1) / BK);
   const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
-
-  // this thread's chunks of every stage: slot (wave * kStageLoads + c) * 64 + lane
-  int row_of[kStageLoads], chunk_of[kStageLoads];
-#pragma unroll
-  for (int c = 0; c < kStageLoads; ++c) {
-    const int slot = (wave * kStageLoads + c) * 64 + lane, r = slot >> 2;
-    row_of[c] = r;
-    chunk_of[c] = (slot & 3) ^ ((r >> 1) & 3);
-  }
-  auto issue = [&](int st) {
-    const int64_t k0 = kbeg + (int64_t)st * BK;
-    uint16_t *base = S + (st % kRing) * kStage;
-#pragma unroll
-    for (int c = 0; c < kStageLoads; ++c) {
-      const int64_t k = k0 + chunk_of[c] * 8;
-      const int r = row_of[c];
-      const uint16_t *p;
-      if (r < BM) {
-        const int64_t ra = m0 + r;
-        p = ra < g.M && k < kend ? g.A + ra * g.lda + k : g.A;
-      } else {
-        const int64_t rb = n0 + (r - BM);
-        p = rb < g.N && k < kend ? g.B + rb * g.ldb + k : g.B;
-      }
-      __builtin_amdgcn_global_load_lds((const void *)p, (lds_void *)(base + (wave * kStageLoads + c) * 64 * 8), 16,
-                                       0, 0);
-    }
-  };
-
-  floatx4 acc[4][4];
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
-
-  static_assert(kRing == 3 && kStageLoads == 3, "the vmcnt waits below count three loads per stage");
-  int issued = 0;
-  for (; issued < kRing - 1 && issued < nsteps; ++issued) issue(issued);
-  for (int st = 0; st < nsteps; ++st) {
-    // this step's loads are done once at most the later stages' remain
-    if (issued - st - 1 >= 1) asm volatile("s_waitcnt vmcnt(3)" ::: "memory");
-    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    uint16_t *base = S + (st % kRing) * kStage;
-    if (kbeg + (int64_t)(st + 1) * BK > kend) {   // K tail: zero this thread's chunks past the end
-#pragma unroll
-      for (int c = 0; c < kStageLoads; ++c)
-        if (kbeg + (int64_t)st * BK + chunk_of[c] * 8 >= kend)
-          *reinterpret_cast<u32x4 *>(base + (wave * kStageLoads + c) * 64 * 8 + lane * 8) = u32x4{0u, 0u, 0u, 0u};
-    }
-    // LDS writes done, then the barrier: the stage is complete for every
-    // wave, and every wave has finished reading the stage loaded next
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    if (issued < nsteps) issue(issued++);
-    const uint16_t *As = base, *Bs = base + BM * BK;
-    const int kc = lane >> 4;
-    bf16x8 a[4], b[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      a[u] = *reinterpret_cast<const bf16x8 *>(As + ring_slot(wm + 16 * u + (lane & 15), kc) * 8);
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      b[u] = *reinterpret_cast<const bf16x8 *>(Bs + ring_slot(wn + 16 * u + (lane & 15), kc) * 8);
-#pragma unroll
-    for (int ii = 0; ii < 4; ++ii)
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj)
-        acc[ii][jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ii], b[jj], acc[ii][jj], 0, 0, 0);
-  }
-  __syncthreads();   // all loads landed and all operand reads done: the ring is free
-
   // Epilogue.  Wave (wm, wn) holds rows wm..wm+63 and columns wn..wn+63 as
   // 4 x 4 MFMA results; lane l has column l % 16 and rows 4 (l / 16)..+4 of
   // each.  The tile goes through LDS so that every thread finishes whole row
@@ -400,14 +322,250 @@ __global__ void __launch_bounds__(kNtThreads, 2) gemm_nt_kernel(GemmArgs g, int6
   }
 }
 
+template <int EPI>
+__global__ void __launch_bounds__(kNtThreads, 2) gemm_nt_kernel(GemmArgs g, int64_t tiles_m, int64_t tiles_n) {
+  __shared__ __attribute__((aligned(16))) uint16_t S[kRing * kStage];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t nb = (int64_t)gridDim.x, lin = blockIdx.x;
+  const int64_t q = nb / kXcds, rem = nb % kXcds, x = lin % kXcds, i = lin / kXcds;
+  const int64_t tile = x < rem ? x * (q + 1) + i : rem * (q + 1) + (x - rem) * q + i;
+  const int64_t per_z = tiles_m * tiles_n, z = tile / per_z, t = tile % per_z;
+  const bool m_outer = tiles_m >= tiles_n;
+  const int64_t m0 = (m_outer ? t / tiles_n : t % tiles_m) * BM;
+  const int64_t n0 = (m_outer ? t % tiles_n : t / tiles_m) * BN;
+  const int64_t kbeg = z * g.kchunk;
+  const int64_t kend = kbeg + g.kchunk < g.K ? kbeg + g.kchunk : g.K;
+  const int nsteps = (int)((kend - kbeg + BK - 1) / BK);
+  const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
+
+  // this thread's chunks of every stage: slot (wave * kStageLoads + c) * 64 + lane
+  int row_of[kStageLoads], chunk_of[kStageLoads];
+#pragma unroll
+  for (int c = 0; c < kStageLoads; ++c) {
+    const int slot = (wave * kStageLoads + c) * 64 + lane, r = slot >> 2;
+    row_of[c] = r;
+    chunk_of[c] = (slot & 3) ^ ((r >> 1) & 3);
+  }
+  auto issue = [&](int st) {
+    const int64_t k0 = kbeg + (int64_t)st * BK;
+    uint16_t *base = S + (st % kRing) * kStage;
+#pragma unroll
+    for (int c = 0; c < kStageLoads; ++c) {
+      const int64_t k = k0 + chunk_of[c] * 8;
+      const int r = row_of[c];
+      const uint16_t *p;
+      if (r < BM) {
+        const int64_t ra = m0 + r;
+        p = ra < g.M && k < kend ? g.A + ra * g.lda + k : g.A;
+      } else {
+        const int64_t rb = n0 + (r - BM);
+        p = rb < g.N && k < kend ? g.B + rb * g.ldb + k : g.B;
+      }
+      __builtin_amdgcn_global_load_lds((const void *)p, (lds_void *)(base + (wave * kStageLoads + c) * 64 * 8), 16,
+                                       0, 0);
+    }
+  };
+
+  floatx4 acc[4][4];
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int b = 0; b < 4; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+  static_assert(kRing == 3 && kStageLoads == 3, "the vmcnt waits below count three loads per stage");
+  int issued = 0;
+  for (; issued < kRing - 1 && issued < nsteps; ++issued) issue(issued);
+  for (int st = 0; st < nsteps; ++st) {
+    // this step's loads are done once at most the later stages' remain
+    if (issued - st - 1 >= 1) asm volatile("s_waitcnt vmcnt(3)" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    uint16_t *base = S + (st % kRing) * kStage;
+    if (kbeg + (int64_t)(st + 1) * BK > kend) {   // K tail: zero this thread's chunks past the end
+#pragma unroll
+      for (int c = 0; c < kStageLoads; ++c)
+        if (kbeg + (int64_t)st * BK + chunk_of[c] * 8 >= kend)
+          *reinterpret_cast<u32x4 *>(base + (wave * kStageLoads + c) * 64 * 8 + lane * 8) = u32x4{0u, 0u, 0u, 0u};
+    }
+    // LDS writes done, then the barrier: the stage is complete for every
+    // wave, and every wave has finished reading the stage loaded next
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    if (issued < nsteps) issue(issued++);
+    const uint16_t *As = base, *Bs = base + BM * BK;
+    const int kc = lane >> 4;
+    bf16x8 a[4], b[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      a[u] = *reinterpret_cast<const bf16x8 *>(As + ring_slot(wm + 16 * u + (lane & 15), kc) * 8);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      b[u] = *reinterpret_cast<const bf16x8 *>(Bs + ring_slot(wn + 16 * u + (lane & 15), kc) * 8);
+#pragma unroll
+    for (int ii = 0; ii < 4; ++ii)
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj)
+        acc[ii][jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ii], b[jj], acc[ii][jj], 0, 0, 0);
+  }
+  __syncthreads();   // all loads landed and all operand reads done: the ring is free
+  ring_epilogue<EPI>(g, acc, S, m0, n0, z);
+}
+
+// ---- both operands K-major (opA = A[k][m], opB = B[k][n]) ----------------
+// The weight gradients: sums over the rows of a batch of products of two
+// row-major matrices.  Tiles, ring and epilogue are gemm_nt_kernel's; a stage
+// holds 32 rows of k, 512 bytes of A and 256 of B each, and the operands, 8
+// consecutive k of one column, come from two transposing LDS reads
+// (ds_read_b64_tr_b16: of 16 lanes, lane 4 i + j reads columns 4 j..+4 of row i,
+// and lane m receives column m of the four rows).  Chunk c of row r sits in
+// place c ^ 2 (r & 3) of its row, so that the four rows of a read fall on
+// distinct banks.  No operand is transposed in memory first, which took 31 to
+// 35 us for each of four 57,344-row matrices; the products take as long as on
+// transposed ones (65 us for 512 x 512 and 512 x 784 over 57,344 rows, the
+// mean) and add the same terms in the same order.  Needs 16-byte aligned operands with
+// lda, ldb, M and N multiples of 8 (N: or rows of B that hold whole chunks up to
+// it), and lda and ldb below 2^26 (a stage within 4 GB).
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+// byte offset in its tile (of `pitch` columns) of what the lane reads for the operand of columns col0..+16
+__device__ __forceinline__ uint32_t tr_offset(int pitch, int col0, int lane) {
+  const int q = lane & 3, i = (lane >> 2) & 3, row = 8 * (lane >> 4) + i;   // rows row and row + 4: the same i
+  return 2u * (uint32_t)(row * pitch + ((((col0 >> 3) + (q >> 1)) ^ (i << 1)) << 3) + 4 * (q & 1));
+}
+
+// four operands' halves, in LDS behind the loads of later stages: as the
+// compiler would wait for all of those before an LDS read, the reads are
+// written out, with their own wait
+template <int PITCH>
+__device__ __forceinline__ void tr_operands(const uint32_t (&at)[4], bf16x8 (&v)[4]) {
+  u32x2 lo[4], hi[4];
+  asm volatile(
+      "ds_read_b64_tr_b16 %0, %8\n\t"
+      "ds_read_b64_tr_b16 %1, %8 offset:%12\n\t"
+      "ds_read_b64_tr_b16 %2, %9\n\t"
+      "ds_read_b64_tr_b16 %3, %9 offset:%12\n\t"
+      "ds_read_b64_tr_b16 %4, %10\n\t"
+      "ds_read_b64_tr_b16 %5, %10 offset:%12\n\t"
+      "ds_read_b64_tr_b16 %6, %11\n\t"
+      "ds_read_b64_tr_b16 %7, %11 offset:%12\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(lo[0]), "=&v"(hi[0]), "=&v"(lo[1]), "=&v"(hi[1]), "=&v"(lo[2]), "=&v"(hi[2]), "=&v"(lo[3]), "=&v"(hi[3])
+      : "v"(at[0]), "v"(at[1]), "v"(at[2]), "v"(at[3]), "n"(8 * PITCH)
+      : "memory");
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+    v[u] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo[u], hi[u], 0, 1, 2, 3));
+}
+
+template <int EPI>
+__global__ void __launch_bounds__(kNtThreads, 4) gemm_tn_kernel(GemmArgs g, int64_t tiles_m, int64_t tiles_n) {
+  __shared__ __attribute__((aligned(16))) uint16_t S[kRing * kStage];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t nb = (int64_t)gridDim.x, lin = blockIdx.x;
+  const int64_t q = nb / kXcds, rem = nb % kXcds, x = lin % kXcds, i = lin / kXcds;
+  const int64_t tile = x < rem ? x * (q + 1) + i : rem * (q + 1) + (x - rem) * q + i;
+  const int64_t per_z = tiles_m * tiles_n, z = tile / per_z, t = tile % per_z;
+  const bool m_outer = tiles_m >= tiles_n;
+  const int64_t m0 = (m_outer ? t / tiles_n : t % tiles_m) * BM;
+  const int64_t n0 = (m_outer ? t % tiles_n : t / tiles_m) * BN;
+  const int64_t kbeg = z * g.kchunk;
+  const int64_t kend = kbeg + g.kchunk < g.K ? kbeg + g.kchunk : g.K;
+  const int nsteps = (int)((kend - kbeg + BK - 1) / BK);
+  const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
+
+  // this thread's chunks of every stage: row of k, and bytes from the stage's
+  // first row of the operand
+  int row_of[kStageLoads];
+  uint32_t off[kStageLoads];
+#pragma unroll
+  for (int c = 0; c < kStageLoads; ++c) {
+    const int slot = (wave * kStageLoads + c) * 64 + lane;
+    const bool isA = slot < BK * BM / 8;
+    const int rs = isA ? slot : slot - BK * BM / 8, per = isA ? BM / 8 : BN / 8;
+    const int r = rs / per, ch = (rs % per) ^ ((r & 3) << 1);
+    const int64_t col = (isA ? m0 : n0) + 8 * ch;
+    row_of[c] = r;
+    // a chunk past the last column reads the first one: its outputs are not stored
+    off[c] = (uint32_t)((r * (isA ? g.lda : g.ldb) + (col < (isA ? g.M : g.N) ? col : 0)) * 2);
+  }
+  auto issue = [&](int st) {
+    uint16_t *base = S + (st % kRing) * kStage;
+    const int64_t k0 = kbeg + (int64_t)st * BK;
+    const int left = kend - k0 < BK ? (int)(kend - k0) : BK;   // rows past the end read row k0 and are zeroed later
+#pragma unroll
+    for (int c = 0; c < kStageLoads; ++c) {
+      const bool isA = __builtin_amdgcn_readfirstlane((wave * kStageLoads + c) * 64) < BK * BM / 8;
+      const unsigned char *from = reinterpret_cast<const unsigned char *>(isA ? g.A + k0 * g.lda : g.B + k0 * g.ldb);
+      __builtin_amdgcn_global_load_lds((const void *)(from + (row_of[c] < left ? off[c] : 0u)),
+                                       (lds_void *)(base + (wave * kStageLoads + c) * 64 * 8), 16, 0, 0);
+    }
+  };
+
+  uint32_t at_a[4], at_b[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    at_a[u] = tr_offset(BM, wm + 16 * u, lane);
+    at_b[u] = tr_offset(BN, wn + 16 * u, lane);
+  }
+  floatx4 acc[4][4];
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int b = 0; b < 4; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+  int issued = 0;
+  for (; issued < kRing - 1 && issued < nsteps; ++issued) issue(issued);
+  for (int st = 0; st < nsteps; ++st) {
+    if (issued - st - 1 >= 1) asm volatile("s_waitcnt vmcnt(3)" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    uint16_t *base = S + (st % kRing) * kStage;
+    if (kbeg + (int64_t)(st + 1) * BK > kend) {   // K tail: zero this thread's rows past the end
+#pragma unroll
+      for (int c = 0; c < kStageLoads; ++c)
+        if (kbeg + (int64_t)st * BK + row_of[c] >= kend)
+          *reinterpret_cast<u32x4 *>(base + (wave * kStageLoads + c) * 64 * 8 + lane * 8) = u32x4{0u, 0u, 0u, 0u};
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    if (issued < nsteps) issue(issued++);
+    uint32_t stage = (uint32_t)(uintptr_t)(lds_void *)base;
+    asm volatile("" : "+s"(stage));   // added here each step: the sums of all stages overflow the registers
+    uint32_t pa[4], pb[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      pa[u] = stage + at_a[u];
+      pb[u] = stage + BK * BM * 2 + at_b[u];
+    }
+    bf16x8 a[4], b[4];
+    tr_operands<BM>(pa, a);
+    tr_operands<BN>(pb, b);
+#pragma unroll
+    for (int ii = 0; ii < 4; ++ii)
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj)
+        acc[ii][jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ii], b[jj], acc[ii][jj], 0, 0, 0);
+  }
+  __syncthreads();   // all loads landed and all operand reads done: the ring is free
+  ring_epilogue<EPI>(g, acc, S, m0, n0, z);
+}
+
 // sum of `splits` FP32 slabs [M][ldc] in slab order -> out (FP32, ld = ldo)
 __global__ void splitk_reduce_kernel(const float *__restrict__ part, int splits, int64_t M, int64_t N,
                                      int64_t ldp, float *__restrict__ out, int64_t ldo) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= M * N) return;
   const int64_t m = e / N, n = e % N;
+  const float *p = part + m * ldp + n;
+  const int64_t slab = M * ldp;
   float s = 0.f;
-  for (int z = 0; z < splits; ++z) s += part[(int64_t)z * M * ldp + m * ldp + n];
+  int z = 0;
+  for (; z + 8 <= splits; z += 8) {   // eight slabs in flight, added in order
+    float x[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) x[u] = p[(z + u) * slab];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s += x[u];
+  }
+  for (; z < splits; ++z) s += p[z * slab];
   out[m * ldo + n] = s;
 }
 
@@ -448,22 +606,25 @@ __global__ void f32_to_bf16_kernel(const float *__restrict__ x, int64_t n, uint1
   if (e < n) y[e] = f2bf(x[e]);
 }
 
-// out[r][:] = X[rows[r]][:] (BF16 rows of width N); 16-byte chunks when the
-// rows are 16-byte multiples (N % 8 == 0, aligned bases), else elements
+// out[r][0..ldo) = X[rows[r]][0..N) and zeros (rows NULL: X[r]), by 16-byte
+// chunks of out; X's rows start at any element
+typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(2)));
+
 __global__ void gather_rows_kernel(const uint16_t *__restrict__ X, int64_t N, const int32_t *__restrict__ rows,
-                                   int64_t R, uint16_t *__restrict__ out, bool vec) {
+                                   int64_t R, uint16_t *__restrict__ out, int64_t ldo) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (vec) {
-    const int64_t cpr = N / 8;   // chunks per row
-    if (e >= R * cpr) return;
-    const int64_t r = e / cpr, c = e % cpr;
-    *reinterpret_cast<U16x8 *>(out + r * N + 8 * c) =
-        *reinterpret_cast<const U16x8 *>(X + (int64_t)rows[r] * N + 8 * c);
-    return;
-  }
-  if (e >= R * N) return;
-  const int64_t r = e / N, k = e % N;
-  out[e] = X[(int64_t)rows[r] * N + k];
+  const int64_t cpr = ldo / 8;   // chunks per row
+  if (e >= R * cpr) return;
+  const int64_t r = e / cpr, k = (e - r * cpr) * 8;
+  const uint16_t *x = X + (rows ? (int64_t)rows[r] : r) * N + k;
+  u32x4 v = u32x4{0u, 0u, 0u, 0u};
+  if (k + 8 <= N)
+    v = *reinterpret_cast<const u32x4u *>(x);
+  else
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (k + j < N) v[j >> 1] |= (uint32_t)x[j] << (16 * (j & 1));
+  *reinterpret_cast<u32x4 *>(out + r * ldo + k) = v;
 }
 
 // Z[r][o] = b3[o] + sum_k H[r][k] W3[o][k], o < 2 (one wavefront per row;
@@ -506,103 +667,148 @@ __global__ void __launch_bounds__(256) head_forward_kernel(const uint16_t *__res
   }
 }
 
-// dH[r][k] = (dZ[r][0] W3[0][k] + dZ[r][1] W3[1][k]) * [H[r][k] > 0]  -> BF16
-__global__ void head_dgrad_kernel(const float *__restrict__ dZ, const uint16_t *__restrict__ W3,
-                                  const uint16_t *__restrict__ H, int64_t R, int K, uint16_t *__restrict__ dH) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= R * K) return;
-  const int64_t r = e / K;
-  const int k = (int)(e % K);
-  const float g = dZ[2 * r] * bf2f(W3[k]) + dZ[2 * r + 1] * bf2f(W3[K + k]);
-  dH[e] = f2bf(bf2f(H[e]) > 0.f ? g : 0.f);
+// Column sums of a BF16 matrix X [R][J], J even (the bias gradients), as the
+// sums of kBiasLanes lanes: lane t takes rows 8 t..8 t + 7 of every 8 kBiasLanes,
+// in order, and a tree adds the lanes.  bias_lanes_kernel: a wavefront per lane
+// and 128 columns, 32 rows in flight: part[t][J].
+constexpr int kBiasLanes = 256;
+constexpr int kBiasAhead = 4;   // groups of 8 rows in flight (the loads one by one: 70 us for 57,344 x 512, so 12)
+
+__global__ void __launch_bounds__(256) bias_lanes_kernel(const uint16_t *__restrict__ X, int64_t R, int64_t J,
+                                                        float *__restrict__ part) {
+  const int t = (int)blockIdx.y * 4 + (threadIdx.x >> 6);
+  const int64_t j = ((int64_t)blockIdx.x * 64 + (threadIdx.x & 63)) * 2;
+  if (j >= J) return;
+  float s0 = 0.f, s1 = 0.f;
+  int64_t r0 = 8 * t;
+  for (; r0 + 8 * kBiasLanes * (kBiasAhead - 1) + 8 <= R; r0 += 8 * kBiasLanes * kBiasAhead) {
+    const uint16_t *p = X + r0 * J + j;
+    uint32_t x[kBiasAhead * 8];
+#pragma unroll
+    for (int g = 0; g < kBiasAhead; ++g)
+#pragma unroll
+      for (int u = 0; u < 8; ++u) x[g * 8 + u] = *reinterpret_cast<const uint32_t *>(p + (g * 8 * kBiasLanes + u) * J);
+    __builtin_amdgcn_sched_barrier(0);   // all on their way before the first is added
+#pragma unroll
+    for (int u = 0; u < kBiasAhead * 8; ++u) {
+      s0 += __uint_as_float(x[u] << 16);
+      s1 += __uint_as_float(x[u] & 0xffff0000u);
+    }
+  }
+  for (; r0 < R; r0 += 8 * kBiasLanes)
+    for (int u = 0; u < 8 && r0 + u < R; ++u) {
+      const uint32_t x = *reinterpret_cast<const uint32_t *>(X + (r0 + u) * J + j);
+      s0 += __uint_as_float(x << 16);
+      s1 += __uint_as_float(x & 0xffff0000u);
+    }
+  part[t * J + j] = s0;
+  part[t * J + j + 1] = s1;
 }
 
-// A 64-row x 64-column tile of a BF16 [R][C] matrix is formed, optionally
-// written row-major to `out`, and written feature-major to outT [C][ldo]
-// (entries r >= R zero) through LDS, all with 16-byte accesses:
-//   TT_COPY       the tile of `in`
-//   TT_GATHER     rows `rows[r]` of `in` (a batch gathered from the data)
-//   TT_HEAD_DGRAD the head's input gradient from the activations `in` = H:
-//                 (dZ[r][0] W3[0][k] + dZ[r][1] W3[1][k]) * [H[r][k] > 0]
-// Needs C and ldo multiples of 8 and 16-byte aligned in, out, outT.
-__global__ void __launch_bounds__(256) tile_t_kernel(int mode, TileTArgs a) {
-  __shared__ uint32_t t[64][33];   // 64 rows of 64 BF16 (+ one word of padding)
-  const int64_t r0 = (int64_t)blockIdx.x * 64, c0 = (int64_t)blockIdx.y * 64;
+// out[j] = the tree sum of part[0..kBiasLanes)[j]: lane t adds lane t + w, w = 128, 64, ...
+__global__ void __launch_bounds__(kBiasLanes) bias_tree_kernel(const float *__restrict__ part, int64_t J,
+                                                              float *__restrict__ out) {
+  __shared__ float red[kBiasLanes][8];
+  const int t = threadIdx.x;
+  const int64_t j0 = (int64_t)blockIdx.x * 8;
 #pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    const int id = threadIdx.x + 256 * c, rl = id >> 3, cc = (id & 7) * 8;
-    const int64_t r = r0 + rl, col = c0 + cc;
-    U16x8 v = {};
-    if (r < a.R && col < a.C) {
-      const int64_t src = (mode == TT_GATHER ? (int64_t)a.rows[r] : r) * a.C + col;
-      v = *reinterpret_cast<const U16x8 *>(a.in + src);
-      if (mode == TT_HEAD_DGRAD) {
-        const float g0 = a.dz[2 * r], g1 = a.dz[2 * r + 1];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const float g = g0 * bf2f(a.w3[col + j]) + g1 * bf2f(a.w3[a.C + col + j]);
-          v.v[j] = f2bf(bf2f(v.v[j]) > 0.f ? g : 0.f);
-        }
-      }
-      if (a.out) *reinterpret_cast<U16x8 *>(a.out + r * a.C + col) = v;
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) t[rl][cc / 2 + j] = (uint32_t)v.v[2 * j] | ((uint32_t)v.v[2 * j + 1] << 16);
-  }
+  for (int e = 0; e < 8; ++e) red[t][e] = j0 + e < J ? part[t * J + j0 + e] : 0.f;
   __syncthreads();
+  for (int w = kBiasLanes / 2; w > 0; w >>= 1) {
+    if (t < w)
 #pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    const int id = threadIdx.x + 256 * c, kl = id >> 3, rc = (id & 7) * 8;
-    const int64_t k = c0 + kl, rr = r0 + rc;
-    if (k < a.C && rr < a.ldo) {
-      U16x8 o;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) o.v[j] = (uint16_t)(t[rc + j][kl >> 1] >> ((kl & 1) * 16));
-      *reinterpret_cast<U16x8 *>(a.outT + k * a.ldo + rr) = o;
-    }
-  }
-}
-
-// out[j] = sum over the L entries of row j of a BF16 [J][L] matrix: each
-// thread sums its 8-element chunks (stride = block size) in order, then a
-// fixed tree over the block; deterministic
-__global__ void __launch_bounds__(kBlock) rowsum_bf16_kernel(const uint16_t *__restrict__ X, int64_t L,
-                                                            float *__restrict__ out) {
-  __shared__ float red[kBlock];
-  const uint16_t *row = X + (int64_t)blockIdx.x * L;
-  float acc = 0.f;
-  const bool vec = L % 8 == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0;
-  if (vec) {
-    for (int64_t c = threadIdx.x; c < L / 8; c += kBlock) {
-      const U16x8 v = *reinterpret_cast<const U16x8 *>(row + 8 * c);
-#pragma unroll
-      for (int j = 0; j < 8; ++j) acc += bf2f(v.v[j]);
-    }
-  } else {
-    for (int64_t c = threadIdx.x; c < L; c += kBlock) acc += bf2f(row[c]);
-  }
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int w = kBlock / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+      for (int e = 0; e < 8; ++e) red[t][e] += red[t + w][e];
     __syncthreads();
   }
-  if (threadIdx.x == 0) out[blockIdx.x] = red[0];
+  if (t < 8 && j0 + t < J) out[j0 + t] = red[0][t];
+}
+
+// Backward of the head on kColsumRows rows and 128 columns: the input gradient
+//   dH[r][k] = (dZ[r][0] W3[0][k] + dZ[r][1] W3[1][k]) * [H[r][k] > 0]  -> BF16
+// and, while H is at hand, the chunk's column sums of dZ[.][0] x H and
+// dZ[.][1] x H (dW3) into part[chunk][2 K].  The sums' order is colsum_kernel's.
+// Needs K % 4 == 0 and 8-byte aligned H and dH.  Bound by memory: H read and dH
+// written once, 57,344 x 512 in 30 us, where two passes over H took 48.
+__global__ void __launch_bounds__(kColsumThreads) head_backward_kernel(const float *__restrict__ dZ,
+                                                           const uint16_t *__restrict__ W3,
+                                                           const uint16_t *__restrict__ H, int64_t R, int K,
+                                                           uint16_t *__restrict__ dH, float *__restrict__ part) {
+  constexpr int V = 4;
+  __shared__ float red[kColsumLanes][32 * V + 1];
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  const int k0 = (int)(blockIdx.x * 32 + tx) * V;
+  const int64_t r0 = (int64_t)blockIdx.y * kColsumRows;
+  const int64_t r1 = r0 + kColsumRows < R ? r0 + kColsumRows : R;
+  float sum[2][V], w0[V], w1[V];
+#pragma unroll
+  for (int e = 0; e < V; ++e) {
+    sum[0][e] = sum[1][e] = 0.f;
+    w0[e] = k0 < K ? bf2f(W3[k0 + e]) : 0.f;
+    w1[e] = k0 < K ? bf2f(W3[K + k0 + e]) : 0.f;
+  }
+  auto load = [&](int64_t r) { return *reinterpret_cast<const U16x4 *>(H + r * K + k0); };
+  auto take = [&](int64_t r, U16x4 h, float g0, float g1) {
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+#pragma clang fp contract(off)
+      // the roundings are written out: the compiler's own fusions vary with the code around them
+      const float x = bf2f(h.v[e]);
+      const float g = fmaf(g0, w0[e], g1 * w1[e]);
+      h.v[e] = f2bf(x > 0.f ? g : 0.f);
+      sum[0][e] = sum[0][e] + g0 * x;
+      sum[1][e] = sum[1][e] + g1 * x;
+    }
+    *reinterpret_cast<U16x4 *>(dH + r * K + k0) = h;
+  };
+  if (k0 < K) {
+    constexpr int kAhead = 8;
+    int64_t r = r0 + ty;
+    for (; r + (kAhead - 1) * kColsumLanes < r1; r += kAhead * kColsumLanes) {
+      U16x4 h[kAhead];
+      float g0[kAhead], g1[kAhead];
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        h[u] = load(r + u * kColsumLanes);
+        g0[u] = dZ[2 * (r + u * kColsumLanes)];
+        g1[u] = dZ[2 * (r + u * kColsumLanes) + 1];
+      }
+      __builtin_amdgcn_sched_barrier(0);   // all on their way before the first is used
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) take(r + u * kColsumLanes, h[u], g0[u], g1[u]);
+    }
+    for (; r < r1; r += kColsumLanes) take(r, load(r), dZ[2 * r], dZ[2 * r + 1]);
+  }
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < V; ++e) red[ty][tx * V + e] = sum[q][e];
+    __syncthreads();
+    for (int c = threadIdx.x; c < 32 * V; c += kColsumThreads) {
+      const int k = (int)blockIdx.x * 32 * V + c;
+      if (k >= K) continue;
+      float t = red[0][c];
+#pragma unroll
+      for (int y = 1; y < kColsumLanes; ++y) t += red[y][c];
+      part[(int64_t)blockIdx.y * 2 * K + (int64_t)q * K + k] = t;
+    }
+  }
 }
 
 // column sums over row chunks: part[c][j] = sum_{r in chunk c} f(r, j) for
 //   mode 0: BF16 matrix X[R][J]
 //   mode 1: dZ (FP32 [R][2]) x H (BF16 [R][K]): j = o*K + k -> dZ[r][o] H[r][k]  (dW3)
 //   mode 2: FP32 matrix [R][J]            (bias gradient of the head, later levels)
-// A block of 8 x 32 threads covers 32 V-column groups of one chunk of
-// kColsumRows rows: row lane ty sums rows ty, ty + 8, ... in order, then
-// the eight lane sums are added in order ty = 0..7 (deterministic).  V = 8
-// needs J (and K) multiples of 8 and a 16-byte aligned source.
+// A block of kColsumLanes x 32 threads covers 32 V-column groups of one chunk
+// of kColsumRows rows: row lane ty sums rows ty, ty + kColsumLanes, ... in
+// order, then the lane sums are added in order of ty (deterministic).  V = 4
+// needs J (and K) multiples of 4 and a 16-byte aligned source; eight rows in
+// flight, as with four and V = 8 57,344 x 512 took 24 us.
 template <int V>
-__global__ void __launch_bounds__(256) colsum_kernel(int mode, const void *__restrict__ Xp,
+__global__ void __launch_bounds__(kColsumThreads) colsum_kernel(int mode, const void *__restrict__ Xp,
                                                     const float *__restrict__ dZ, int64_t R, int64_t J, int64_t K,
                                                     float *__restrict__ part) {
-  __shared__ float red[8][32 * V + 1];
+  __shared__ float red[kColsumLanes][32 * V + 1];
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
   const int64_t j0 = ((int64_t)blockIdx.x * 32 + tx) * V;
   const int64_t r0 = (int64_t)blockIdx.y * kColsumRows;
@@ -612,26 +818,23 @@ __global__ void __launch_bounds__(256) colsum_kernel(int mode, const void *__res
   for (int e = 0; e < V; ++e) acc[e] = 0.f;
   if (j0 < J) {
     const int64_t half = mode == 1 ? j0 / K : 0, col = mode == 1 ? j0 % K : j0, ld = mode == 1 ? K : J;
-#pragma unroll 4
-    for (int64_t r = r0 + ty; r < r1; r += 8) {
+#pragma unroll 8
+    for (int64_t r = r0 + ty; r < r1; r += kColsumLanes) {
       float x[V];
       if (mode == 2) {
         const float *X = static_cast<const float *>(Xp) + r * J + j0;
-        if (V == 8) {
-          const floatx4 lo = *reinterpret_cast<const floatx4 *>(X), hi = *reinterpret_cast<const floatx4 *>(X + 4);
+        if (V == 4) {
+          const floatx4 v = *reinterpret_cast<const floatx4 *>(X);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            x[e] = lo[e];
-            x[e + 4] = hi[e];
-          }
+          for (int e = 0; e < V; ++e) x[e] = v[e];
         } else {
           x[0] = X[0];
         }
       } else {
         const uint16_t *X = static_cast<const uint16_t *>(Xp) + r * ld + col;
         const float w = mode == 1 ? dZ[2 * r + half] : 1.f;
-        if (V == 8) {
-          const U16x8 v = *reinterpret_cast<const U16x8 *>(X);
+        if (V == 4) {
+          const U16x4 v = *reinterpret_cast<const U16x4 *>(X);
 #pragma unroll
           for (int e = 0; e < V; ++e) x[e] = mode == 1 ? w * bf2f(v.v[e]) : bf2f(v.v[e]);
         } else {
@@ -650,7 +853,7 @@ __global__ void __launch_bounds__(256) colsum_kernel(int mode, const void *__res
     for (int e = 0; e < V; ++e) {
       float t = red[0][tx * V + e];
 #pragma unroll
-      for (int q = 1; q < 8; ++q) t += red[q][tx * V + e];
+      for (int q = 1; q < kColsumLanes; ++q) t += red[q][tx * V + e];
       part[(int64_t)blockIdx.y * J + j0 + e] = t;
     }
   }
@@ -702,9 +905,22 @@ hipError_t launch_gemm_bf16(const GemmArgs &g0, int ta, int tb, int epi, int spl
   if (g.kchunk < NTK) g.kchunk = NTK;
   splits = (int)((g.K + g.kchunk - 1) / g.kchunk);
   if (splits < 1) splits = 1;
-  if (!ta && tb && g.vec_a && g.vec_b && g.K % 8 == 0) {
+  const bool nt = !ta && tb && g.vec_a && g.vec_b && g.K % 8 == 0;
+  const bool tn_ok = ta && !tb && g.vec_a && g.vec_b && g.M % 8 == 0 && (g.N % 8 == 0 || g.whole_b) &&
+                     g.lda < (int64_t)1 << 26 && g.ldb < (int64_t)1 << 26;
+  if (nt || tn_ok) {
     const int64_t tm = (g.M + BM - 1) / BM, tn = (g.N + BN - 1) / BN, nb = tm * tn * splits;
     if (nb > INT32_MAX) return hipErrorInvalidValue;
+    if (tn_ok) {
+      switch (epi) {
+        case GEMM_EPI_F32: gemm_tn_kernel<GEMM_EPI_F32><<<(unsigned)nb, kNtThreads, 0, s>>>(g, tm, tn); break;
+        case GEMM_EPI_BIAS_RELU_BF16:
+          gemm_tn_kernel<GEMM_EPI_BIAS_RELU_BF16><<<(unsigned)nb, kNtThreads, 0, s>>>(g, tm, tn);
+          break;
+        default: gemm_tn_kernel<GEMM_EPI_RELU_MASK_BF16><<<(unsigned)nb, kNtThreads, 0, s>>>(g, tm, tn); break;
+      }
+      return hipGetLastError();
+    }
     switch (epi) {
       case GEMM_EPI_F32: gemm_nt_kernel<GEMM_EPI_F32><<<(unsigned)nb, kNtThreads, 0, s>>>(g, tm, tn); break;
       case GEMM_EPI_BIAS_RELU_BF16:
@@ -744,35 +960,15 @@ hipError_t launch_transpose_bf16(const uint16_t *in, int64_t R, int64_t C, uint1
   return hipGetLastError();
 }
 
-bool tile_t_ok(const TileTArgs &a) {
-  auto al = [](const void *p) { return p == nullptr || (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
-  return a.C % 8 == 0 && a.ldo % 8 == 0 && a.ldo >= a.R && al(a.in) && al(a.out) && al(a.outT) && a.outT;
-}
-
-hipError_t launch_tile_t(int mode, const TileTArgs &a, hipStream_t s) {
-  if (!tile_t_ok(a)) return hipErrorInvalidValue;
-  if (a.ldo == 0 || a.C == 0) return hipSuccess;
-  if ((a.C + 63) / 64 > 65535 || (a.ldo + 63) / 64 > INT32_MAX) return hipErrorInvalidValue;
-  tile_t_kernel<<<dim3((unsigned)((a.ldo + 63) / 64), (unsigned)((a.C + 63) / 64)), 256, 0, s>>>(mode, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_rowsum_bf16(const uint16_t *X, int64_t J, int64_t L, float *out, hipStream_t s) {
-  if (J == 0) return hipSuccess;
-  if (J > INT32_MAX) return hipErrorInvalidValue;
-  rowsum_bf16_kernel<<<(unsigned)J, kBlock, 0, s>>>(X, L, out);
-  return hipGetLastError();
-}
-
 hipError_t launch_f32_to_bf16(const float *x, int64_t n, uint16_t *y, hipStream_t s) {
   f32_to_bf16_kernel<<<grid_for(n), kBlock, 0, s>>>(x, n, y);
   return hipGetLastError();
 }
 
 hipError_t launch_gather_rows(const uint16_t *X, int64_t N, const int32_t *rows, int64_t R, uint16_t *out,
-                              hipStream_t s) {
-  const bool vec = N % 8 == 0 && ((uintptr_t)X % 16 == 0) && ((uintptr_t)out % 16 == 0);
-  gather_rows_kernel<<<grid_for(vec ? R * (N / 8) : R * N), kBlock, 0, s>>>(X, N, rows, R, out, vec);
+                              int64_t ldo, hipStream_t s) {
+  if (ldo % 8 || (reinterpret_cast<uintptr_t>(out) & 15)) return hipErrorInvalidValue;
+  gather_rows_kernel<<<grid_for(R * (ldo / 8)), kBlock, 0, s>>>(X, N, rows, R, out, ldo);
   return hipGetLastError();
 }
 
@@ -781,12 +977,6 @@ hipError_t launch_head_forward(const uint16_t *H, int64_t R, int K, const uint16
   const bool vec = K % 8 == 0 && (reinterpret_cast<uintptr_t>(H) & 15) == 0 &&
                    (reinterpret_cast<uintptr_t>(W3) & 15) == 0;
   head_forward_kernel<<<grid_for(R, 4), 256, 0, s>>>(H, R, K, W3, b3, Z, vec);
-  return hipGetLastError();
-}
-
-hipError_t launch_head_dgrad(const float *dZ, const uint16_t *W3, const uint16_t *H, int64_t R, int K,
-                             uint16_t *dH, hipStream_t s) {
-  head_dgrad_kernel<<<grid_for(R * K), kBlock, 0, s>>>(dZ, W3, H, R, K, dH);
   return hipGetLastError();
 }
 
@@ -809,18 +999,40 @@ hipError_t launch_colsum(int mode, const void *X, const float *dZ, int64_t R, in
     const int m = level == 0 ? mode : 2;
     const int64_t chunks = (rows + kColsumRows - 1) / kColsumRows;
     float *dst = chunks == 1 ? out : buf[level & 1];
-    const bool vec8 = J % 8 == 0 && (m != 1 || K % 8 == 0) && (reinterpret_cast<uintptr_t>(src) & 15) == 0;
-    if (vec8)
-      colsum_kernel<8><<<dim3((unsigned)((J / 8 + 31) / 32), (unsigned)chunks), 256, 0, s>>>(m, src, dZ, rows, J,
+    const bool vec4 = J % 4 == 0 && (m != 1 || K % 4 == 0) && (reinterpret_cast<uintptr_t>(src) & 15) == 0;
+    if (vec4)
+      colsum_kernel<4><<<dim3((unsigned)((J / 4 + 31) / 32), (unsigned)chunks), kColsumThreads, 0, s>>>(m, src, dZ, rows, J,
                                                                                            K, dst);
     else
-      colsum_kernel<1><<<dim3((unsigned)((J + 31) / 32), (unsigned)chunks), 256, 0, s>>>(m, src, dZ, rows, J, K,
+      colsum_kernel<1><<<dim3((unsigned)((J + 31) / 32), (unsigned)chunks), kColsumThreads, 0, s>>>(m, src, dZ, rows, J, K,
                                                                                        dst);
     if (chunks == 1) break;
     src = dst;
     rows = chunks;
   }
   return hipGetLastError();
+}
+
+int64_t bias_workspace(int64_t J) { return kBiasLanes * J; }
+
+hipError_t launch_bias_sum(const uint16_t *X, int64_t R, int64_t J, float *ws, float *out, hipStream_t s) {
+  if (R < 1 || J < 2 || J % 2 || (reinterpret_cast<uintptr_t>(X) & 3)) return hipErrorInvalidValue;
+  bias_lanes_kernel<<<dim3((unsigned)((J + 127) / 128), kBiasLanes / 4), 256, 0, s>>>(X, R, J, ws);
+  bias_tree_kernel<<<(unsigned)((J + 7) / 8), kBiasLanes, 0, s>>>(ws, J, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_head_backward(const float *dZ, const uint16_t *W3, const uint16_t *H, int64_t R, int K,
+                                uint16_t *dH, float *ws, float *out, hipStream_t s) {
+  if (R < 1 || (R + kColsumRows - 1) / kColsumRows > 65535) return hipErrorInvalidValue;
+  const int64_t chunks = (R + kColsumRows - 1) / kColsumRows, J = 2 * (int64_t)K;
+  float *part = chunks == 1 ? out : ws;
+  if (K % 4 || ((reinterpret_cast<uintptr_t>(H) | reinterpret_cast<uintptr_t>(dH)) & 7)) return hipErrorInvalidValue;
+  head_backward_kernel<<<dim3((unsigned)((K / 4 + 31) / 32), (unsigned)chunks), kColsumThreads, 0, s>>>(dZ, W3, H, R, K,
+                                                                                                      dH, part);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || chunks == 1) return e;
+  return launch_colsum(2, part, nullptr, chunks, J, J, ws + chunks * J, out, s);
 }
 
 hipError_t launch_adam(float *w, const float *g, float *m, float *v, uint16_t *w16, int64_t n, float lr, float b1,

@@ -26,6 +26,7 @@
 
 struct ivhd_enc {
   int32_t n_in = 0, h1 = 0, h2 = 0;
+  int64_t x_pitch = 0;   // of the batch input: n_in rounded up to 8
   hipStream_t stream = nullptr;
   int64_t n_params = 0;
   int64_t oW1 = 0, ob1 = 0, oW2 = 0, ob2 = 0, oW3 = 0, ob3 = 0;
@@ -34,14 +35,11 @@ struct ivhd_enc {
   int64_t t = 0;
   int64_t r_cap = 0;
   uint16_t *xb = nullptr, *a1 = nullptr, *a2 = nullptr, *d2 = nullptr;
-  // feature-major copies [features][Rp] (Rp = rows rounded up to 8, the
-  // padding zero) and W2 as [h1][h2], so that every backward GEMM reads both
-  // operands with K contiguous; the layer-1 gradient exists only this way
-  uint16_t *xbT = nullptr, *a1T = nullptr, *d1T = nullptr, *d2T = nullptr, *w2T = nullptr;
+  uint16_t *d1 = nullptr;
+  uint16_t *w2T = nullptr;   // W2 as [h1][h2]: K contiguous in the layer-2 input gradient
   float *z = nullptr, *dz = nullptr;
   float *ws = nullptr;
   int64_t ws_elems = 0;
-  int splits = 32;   // K splits of the weight-gradient GEMMs: 8-14 output tiles each, so 256-448 blocks
   // epoch training state
   int32_t *rows = nullptr;
   int32_t *lnn = nullptr, *lrn = nullptr;
@@ -73,8 +71,8 @@ void free_enc(ivhd_enc *e) {
   if (!e) return;
   if (e->plan) (void)ivhd_edges_destroy(e->plan);
   void *bufs[] = {e->w, e->g, e->m, e->v, e->w16, e->xb, e->a1, e->a2, e->d2, e->z, e->dz, e->ws,
-                  e->rows, e->lnn, e->lrn, e->rn_all, e->d_epoch, e->d_losses, e->xbT, e->a1T, e->d1T, e->d2T,
-                  e->w2T, e->pack};
+                  e->rows, e->lnn, e->lrn, e->rn_all, e->d_epoch, e->d_losses, e->d1, e->w2T,
+                  e->pack};
   dev_free_all(bufs, sizeof bufs / sizeof bufs[0], e->stream);
   delete e;
 }
@@ -98,13 +96,14 @@ GemmArgs gemm(const uint16_t *A, const uint16_t *B, int64_t M, int64_t N, int64_
   return g;
 }
 
-// forward of R rows from BF16 input X (row pitch n_in) into z, the hidden
+// forward of R rows from BF16 input X (row pitch ldx) into z, the hidden
 // activations into a1 and a2 if they are wanted (R <= r_cap then)
-int forward_rows(ivhd_enc *e, const uint16_t *X, int64_t R, float *z, bool keep) {
+int forward_rows(ivhd_enc *e, const uint16_t *X, int64_t ldx, int64_t R, float *z, bool keep) {
   hipStream_t s = e->stream;
-  if (mlp_ok(X, e->w16 + e->oW1, e->n_in, e->h1, e->h2)) {
+  if (mlp_ok(e->n_in, e->h1, e->h2)) {
     MlpArgs m{};
     m.X = X;
+    m.ldx = (int)ldx;
     m.b1 = e->w + e->ob1;
     m.b2 = e->w + e->ob2;
     m.b3 = e->w + e->ob3;
@@ -119,7 +118,7 @@ int forward_rows(ivhd_enc *e, const uint16_t *X, int64_t R, float *z, bool keep)
     HIPCHK(launch_mlp_forward(m, e->w16 + e->oW1, e->w16 + e->oW2, e->pack, s));
     return IVHD_OK;
   }
-  GemmArgs g1 = gemm(X, e->w16 + e->oW1, R, e->h1, e->n_in, e->n_in, e->n_in, e->a1, e->h1);
+  GemmArgs g1 = gemm(X, e->w16 + e->oW1, R, e->h1, e->n_in, ldx, e->n_in, e->a1, e->h1);
   g1.bias = e->w + e->ob1;
   HIPCHK(launch_gemm_bf16(g1, 0, 1, GEMM_EPI_BIAS_RELU_BF16, 1, s));
   GemmArgs g2 = gemm(e->a1, e->w16 + e->oW2, R, e->h2, e->h1, e->h1, e->h1, e->a2, e->h2);
@@ -129,103 +128,60 @@ int forward_rows(ivhd_enc *e, const uint16_t *X, int64_t R, float *z, bool keep)
   return IVHD_OK;
 }
 
-// weight gradient dW[M][N] = A^T B over R rows, split over K = R, into g;
-// AT [M][R] and BT [N][R] are the transposed operands (K contiguous)
-int wgrad(ivhd_enc *e, const uint16_t *AT, int64_t M, const uint16_t *BT, int64_t N, int64_t R, float *out) {
+// K splits of the weight gradients: 8-14 output tiles each, so 256-448 blocks
+constexpr int kWgradSplits = 32;
+
+// weight gradient dW[M][N] = A^T B over R rows (A [R][M], B [R][ldb] with ldb at
+// least N rounded up to 8), split over K = R, into out
+int wgrad(ivhd_enc *e, const uint16_t *A, int64_t M, const uint16_t *B, int64_t N, int64_t ldb, int64_t R,
+          float *out) {
   hipStream_t s = e->stream;
-  const int splits = gemm_splits_used(R, e->splits);
-  GemmArgs gg = gemm(AT, BT, M, N, R, R, R, e->ws, N);
-  HIPCHK(launch_gemm_bf16(gg, 0, 1, GEMM_EPI_F32, e->splits, s));
+  const int splits = gemm_splits_used(R, kWgradSplits);
+  GemmArgs gg = gemm(A, B, M, N, R, M, ldb, e->ws, N);
+  gg.whole_b = true;
+  HIPCHK(launch_gemm_bf16(gg, 1, 0, GEMM_EPI_F32, kWgradSplits, s));
   HIPCHK(launch_splitk_reduce(e->ws, splits, M, N, N, out, N, s));
   return IVHD_OK;
 }
 
-// feature-major copy outT [C][Rp] of in [R][C] (16-byte tile path when it
-// applies, else the element transposer)
-int feature_major(const uint16_t *in, int64_t R, int64_t C, int64_t ldo, uint16_t *outT, hipStream_t s) {
-  TileTArgs t;
-  t.in = in;
-  t.R = R;
-  t.C = C;
-  t.ldo = ldo;
-  t.outT = outT;
-  if (tile_t_ok(t)) {
-    HIPCHK(launch_tile_t(TT_COPY, t, s));
-  } else {
-    HIPCHK(launch_transpose_bf16(in, R, C, outT, ldo, s));
+// batch input rows at *X with pitch x_pitch: the R rows of src as they are when
+// they are whole 16-byte chunks and rows is NULL, else copied (rows[r] of src)
+// into e->xb, padded with zeros
+int stage_batch(ivhd_enc *e, const uint16_t *src, const int32_t *rows, int64_t R, const uint16_t **X) {
+  if (!rows && e->n_in == e->x_pitch && aligned16(src)) {
+    *X = src;
+    return IVHD_OK;
   }
-  return IVHD_OK;
-}
-
-// batch input rows: rows[r] of src into e->xb when rows is given, else the R
-// rows of src as they are (*X); with the 16-byte path the feature-major copy
-// e->xbT is written in the same pass (*xbT_ready)
-int stage_batch(ivhd_enc *e, const uint16_t *src, const int32_t *rows, int64_t R, const uint16_t **X,
-                bool *xbT_ready) {
-  hipStream_t s = e->stream;
-  TileTArgs t;
-  t.in = src;
-  t.rows = rows;
-  t.R = R;
-  t.C = e->n_in;
-  t.ldo = (R + 7) / 8 * 8;
-  t.out = rows ? e->xb : nullptr;
-  t.outT = e->xbT;
-  *X = rows ? e->xb : src;
-  *xbT_ready = tile_t_ok(t);
-  if (*xbT_ready) {
-    HIPCHK(launch_tile_t(rows ? TT_GATHER : TT_COPY, t, s));
-  } else if (rows) {
-    HIPCHK(launch_gather_rows(src, e->n_in, rows, R, e->xb, s));
-  }
+  *X = e->xb;
+  HIPCHK(launch_gather_rows(src, e->n_in, rows, R, e->xb, e->x_pitch, e->stream));
   return IVHD_OK;
 }
 
 // one step on the batch X (R rows) with local edge plan `plan`
-int train_step_rows(ivhd_enc *e, const uint16_t *X, int64_t R, bool xbT_ready, ivhd_edges *plan, float c, float eps, float lr,
+int train_step_rows(ivhd_enc *e, const uint16_t *X, int64_t R, ivhd_edges *plan, float c, float eps, float lr,
                     float scale, double *d_loss) {
   hipStream_t s = e->stream;
-  const int64_t Rp = (R + 7) / 8 * 8;
-  int rc = forward_rows(e, X, R, e->z, true);
+  int rc = forward_rows(e, X, e->x_pitch, R, e->z, true);
   if (rc) return rc;
-  if (!xbT_ready && (rc = feature_major(X, R, e->n_in, Rp, e->xbT, s))) return rc;
-  if ((rc = feature_major(e->a1, R, e->h1, Rp, e->a1T, s))) return rc;
-  if ((rc = feature_major(e->w16 + e->oW2, e->h2, e->h1, e->h2, e->w2T, s))) return rc;
+  HIPCHK(launch_transpose_bf16(e->w16 + e->oW2, e->h2, e->h1, e->w2T, e->h2, s));
   if (d_loss) {   // the batch stress and its gradient from one pass
     if ((rc = ivhd_edges_stress_grad(plan, e->z, c, eps, nullptr, d_loss, e->dz))) return rc;
   } else if ((rc = ivhd_edges_grad(plan, e->z, c, eps, nullptr, e->dz))) {
     return rc;
   }
-  // head: d2 = input gradient of the head, row-major and feature-major
-  TileTArgs hd;
-  hd.in = e->a2;
-  hd.dz = e->dz;
-  hd.w3 = e->w16 + e->oW3;
-  hd.R = R;
-  hd.C = e->h2;
-  hd.ldo = Rp;
-  hd.out = e->d2;
-  hd.outT = e->d2T;
-  if (tile_t_ok(hd)) {
-    HIPCHK(launch_tile_t(TT_HEAD_DGRAD, hd, s));
-  } else {
-    HIPCHK(launch_head_dgrad(e->dz, e->w16 + e->oW3, e->a2, R, e->h2, e->d2, s));
-    HIPCHK(launch_transpose_bf16(e->d2, R, e->h2, e->d2T, Rp, s));
-  }
-  HIPCHK(launch_colsum(1, e->a2, e->dz, R, 2 * (int64_t)e->h2, e->h2, e->ws, e->g + e->oW3, s));
+  // head: its input gradient d2, and the sums over the rows of dz x a2 (dW3)
+  HIPCHK(launch_head_backward(e->dz, e->w16 + e->oW3, e->a2, R, e->h2, e->d2, e->ws, e->g + e->oW3, s));
   HIPCHK(launch_colsum(2, e->dz, nullptr, R, 2, 2, e->ws, e->g + e->ob3, s));
-  HIPCHK(launch_rowsum_bf16(e->d2T, e->h2, Rp, e->g + e->ob2, s));
-  // layer 2, feature-major: d1^T = (W2^T d2^T) * relu'(a1^T); columns r >= R
-  // come out zero because the mask a1^T is zero there (rows of d2 past R are
-  // never multiplied into a stored value otherwise)
-  GemmArgs gd = gemm(e->w2T, e->d2, e->h1, Rp, e->h2, e->h2, e->h2, e->d1T, Rp);
-  gd.mask = e->a1T;
-  gd.ldm = Rp;
+  HIPCHK(launch_bias_sum(e->d2, R, e->h2, e->ws, e->g + e->ob2, s));
+  // layer 2: d1 = (d2 W2) * relu'(a1)
+  GemmArgs gd = gemm(e->d2, e->w2T, R, e->h1, e->h2, e->h2, e->h2, e->d1, e->h1);
+  gd.mask = e->a1;
+  gd.ldm = e->h1;
   HIPCHK(launch_gemm_bf16(gd, 0, 1, GEMM_EPI_RELU_MASK_BF16, 1, s));
-  if ((rc = wgrad(e, e->d2T, e->h2, e->a1T, e->h1, Rp, e->g + e->oW2))) return rc;
+  if ((rc = wgrad(e, e->d2, e->h2, e->a1, e->h1, e->h1, R, e->g + e->oW2))) return rc;
   // layer 1
-  HIPCHK(launch_rowsum_bf16(e->d1T, e->h1, Rp, e->g + e->ob1, s));
-  if ((rc = wgrad(e, e->d1T, e->h1, e->xbT, e->n_in, Rp, e->g + e->oW1))) return rc;
+  HIPCHK(launch_bias_sum(e->d1, R, e->h1, e->ws, e->g + e->ob1, s));
+  if ((rc = wgrad(e, e->d1, e->h1, X, e->n_in, e->x_pitch, R, e->g + e->oW1))) return rc;
   // Adam
   e->t += 1;
   HIPCHK(launch_adam(e->w, e->g, e->m, e->v, e->w16, e->n_params, lr, 0.9f, 0.999f, 1e-8f, e->t, scale, s));
@@ -265,6 +221,7 @@ int ivhd_enc_create(ivhd_enc **out, int32_t n_in, int32_t h1, int32_t h2, uint64
   ivhd_enc *e = new (std::nothrow) ivhd_enc();
   if (!e) return fail(IVHD_ENOMEM, "host allocation of the encoder failed");
   e->n_in = n_in;
+  e->x_pitch = (n_in + 7) / 8 * 8;
   e->h1 = h1;
   e->h2 = h2;
   e->stream = (hipStream_t)stream;
@@ -276,9 +233,9 @@ int ivhd_enc_create(ivhd_enc **out, int32_t n_in, int32_t h1, int32_t h2, uint64
   e->ob3 = e->oW3 + 2 * (int64_t)h2;
   e->n_params = e->ob3 + 2;
   e->r_cap = max_rows;
-  const int64_t wmax = (int64_t)h1 * n_in > (int64_t)h2 * h1 ? (int64_t)h1 * n_in : (int64_t)h2 * h1;
-  e->ws_elems = wmax * e->splits;
-  const int64_t jmax = std::max<int64_t>(2 * (int64_t)h2, std::max(h1, h2));
+  e->ws_elems = kWgradSplits * std::max((int64_t)h1 * n_in, (int64_t)h2 * h1);
+  e->ws_elems = std::max(e->ws_elems, bias_workspace(std::max(h1, h2)));
+  const int64_t jmax = 2 * (int64_t)h2;
   const int64_t colsum_ws = colsum_workspace(max_rows, jmax);
   if (colsum_ws > e->ws_elems) e->ws_elems = colsum_ws;
   int rc;
@@ -305,22 +262,17 @@ int ivhd_enc_create(ivhd_enc **out, int32_t n_in, int32_t h1, int32_t h2, uint64
   ENC_CHK(dev_alloc(&e->m, np, "Adam first moments"));
   ENC_CHK(dev_alloc(&e->v, np, "Adam second moments"));
   ENC_CHK(dev_alloc(&e->w16, np, "BF16 weights"));
-  ENC_CHK(dev_alloc(&e->xb, max_rows * n_in, "batch input"));
+  ENC_CHK(dev_alloc(&e->xb, max_rows * e->x_pitch, "batch input"));
   ENC_CHK(dev_alloc(&e->a1, max_rows * h1, "layer-1 activations"));
   ENC_CHK(dev_alloc(&e->a2, max_rows * h2, "layer-2 activations"));
-  const int64_t rows_p = (max_rows + 7) / 8 * 8;
-  // read as a GEMM operand of Rp rows
-  ENC_CHK(dev_alloc(&e->d2, rows_p * h2, "layer-2 gradients"));
-  ENC_CHK(dev_alloc(&e->xbT, rows_p * n_in, "feature-major batch input"));
-  ENC_CHK(dev_alloc(&e->a1T, rows_p * h1, "feature-major layer-1 activations"));
-  ENC_CHK(dev_alloc(&e->d1T, rows_p * h1, "feature-major layer-1 gradients"));
-  ENC_CHK(dev_alloc(&e->d2T, rows_p * h2, "feature-major layer-2 gradients"));
+  ENC_CHK(dev_alloc(&e->d2, max_rows * h2, "layer-2 gradients"));
+  ENC_CHK(dev_alloc(&e->d1, max_rows * h1, "layer-1 gradients"));
   ENC_CHK(dev_alloc(&e->w2T, (int64_t)h1 * h2, "transposed W2"));
   ENC_CHK(dev_alloc(&e->z, max_rows * 2, "embedding"));
   ENC_CHK(dev_alloc(&e->dz, max_rows * 2, "embedding gradient"));
   ENC_CHK(dev_alloc(&e->ws, e->ws_elems, "encoder workspace"));
   ENC_CHK(dev_alloc(&e->d_epoch, 1, "epoch counter"));
-  if (mlp_ok(nullptr, nullptr, n_in, h1, h2)) ENC_CHK(dev_alloc(&e->pack, mlp_pack_elems(n_in, h1), "packed weights"));
+  if (mlp_ok(n_in, h1, h2)) ENC_CHK(dev_alloc(&e->pack, mlp_pack_elems(n_in, h1), "packed weights"));
   hipStream_t s = e->stream;
   ENC_HIP(launch_fill_i32((int32_t *)e->w, np, 0, s));
   ENC_HIP(launch_fill_i32((int32_t *)e->m, np, 0, s));
@@ -372,10 +324,10 @@ int ivhd_enc_embed(ivhd_enc *e, const uint16_t *d_x16, int64_t rows, float *d_z)
   if (rows < 0) return fail(IVHD_EINVAL, "rows = %lld < 0", (long long)rows);
   if (rows > 0 && (!d_x16 || !d_z)) return fail(IVHD_EINVAL, "d_x16 and d_z must not be NULL");
   // the fused pass needs no room for activations: all rows at once
-  const int64_t step = mlp_ok(d_x16, e->w16 + e->oW1, e->n_in, e->h1, e->h2) ? (int64_t)1 << 30 : e->r_cap;
+  const int64_t step = mlp_ok(e->n_in, e->h1, e->h2) ? (int64_t)1 << 30 : e->r_cap;
   for (int64_t r0 = 0; r0 < rows; r0 += step) {
     const int64_t R = rows - r0 < step ? rows - r0 : step;
-    int rc = forward_rows(e, d_x16 + r0 * e->n_in, R, d_z + 2 * r0, false);
+    int rc = forward_rows(e, d_x16 + r0 * e->n_in, e->n_in, R, d_z + 2 * r0, false);
     if (rc) return rc;
   }
   return IVHD_OK;
@@ -387,11 +339,10 @@ int ivhd_enc_train_step(ivhd_enc *e, const uint16_t *d_xb16, int64_t R, ivhd_edg
   if (R < 1 || R > e->r_cap) return fail(IVHD_EINVAL, "R = %lld outside [1, max_rows]", (long long)R);
   if (!d_xb16 || !plan) return fail(IVHD_EINVAL, "d_xb16 and plan must not be NULL");
   if (!(lr > 0.f) || !std::isfinite(lr)) return fail(IVHD_EINVAL, "lr = %g must be > 0", (double)lr);
-  bool ready = false;
   const uint16_t *X = nullptr;
-  int rc = stage_batch(e, d_xb16, nullptr, R, &X, &ready);
+  int rc = stage_batch(e, d_xb16, nullptr, R, &X);
   if (rc) return rc;
-  return train_step_rows(e, X, R, ready, plan, c, eps, lr, loss_scale, d_loss);
+  return train_step_rows(e, X, R, plan, c, eps, lr, loss_scale, d_loss);
 }
 
 int ivhd_enc_train_epoch(ivhd_enc *e, const uint16_t *d_x16, int64_t M, const int32_t *d_nn_idx, int32_t nn,
@@ -456,10 +407,9 @@ int ivhd_enc_train_epoch(ivhd_enc *e, const uint16_t *d_x16, int64_t M, const in
   const float scale = 1.f / (float)batch;
   for (int64_t st = 0; st < steps; ++st) {
     HIPCHK(launch_batch_rows(d_nn_idx, nn, e->rn_all, rn, M, batch, a, c0, st * batch, e->rows, s));
-    bool ready = false;
     const uint16_t *X = nullptr;
-    if ((rc = stage_batch(e, d_x16, e->rows, R, &X, &ready))) return rc;
-    if ((rc = train_step_rows(e, X, R, ready, e->plan, c, eps, lr, scale, e->d_losses + st))) return rc;
+    if ((rc = stage_batch(e, d_x16, e->rows, R, &X))) return rc;
+    if ((rc = train_step_rows(e, X, R, e->plan, c, eps, lr, scale, e->d_losses + st))) return rc;
   }
   if (h_loss) {
     double *tmp = new (std::nothrow) double[steps];

@@ -37,6 +37,7 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(2)));   // 16 bytes at any element
 
 constexpr int kWide = 512;            // columns of a block: eight wavefronts of 64
 constexpr int kMlpThreads = 512;
@@ -45,12 +46,9 @@ constexpr int kSteps = kStageK / 32;
 
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
-__device__ __forceinline__ uint16_t f2bf(float f) {   // to nearest even
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7f800000u) == 0x7f800000u && (u & 0x007fffffu)) return (uint16_t)((u >> 16) | 0x40);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
+// to nearest even, a NaN quietened: the conversion instruction's results, which
+// the eight integer operations of doing it by hand have for every float
+__device__ __forceinline__ uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 
 // P[tile][step][lane][8] = W[16 tile + lane % 16][32 step + 8 (lane / 16) + 0..7],
 // zero outside W [n][k]; kWide / 16 tiles
@@ -66,7 +64,15 @@ __global__ void pack_kernel(PackArgs first, PackArgs second) {   // blockIdx.y: 
   const int lane = (int)(t & 63), step = (int)((t >> 6) % a.steps), tile = (int)((t >> 6) / a.steps);
   const int row = 16 * tile + (lane & 15), k0 = 32 * step + 8 * (lane >> 4);
   u32x4 v = u32x4{0u, 0u, 0u, 0u};
-  if (row < a.n && k0 + 8 <= a.k) v = *reinterpret_cast<const u32x4 *>(a.W + (int64_t)row * a.k + k0);
+  if (row < a.n) {
+    const uint16_t *w = a.W + (int64_t)row * a.k + k0;
+    if (k0 + 8 <= a.k)
+      v = *reinterpret_cast<const u32x4u *>(w);
+    else
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if (k0 + e < a.k) v[e >> 1] |= (uint32_t)w[e] << (16 * (e & 1));
+  }
   *reinterpret_cast<u32x4 *>(a.P + t * 8) = v;
 }
 
@@ -102,21 +108,35 @@ __global__ void __launch_bounds__(kMlpThreads, 2) mlp_forward_kernel(MlpArgs a) 
   };
 
   u32x4 x[T::kFetch];
-  const unsigned char *Xb = reinterpret_cast<const unsigned char *>(a.X + r0 * a.n_in);
+  const unsigned char *Xb = reinterpret_cast<const unsigned char *>(a.X + r0 * a.ldx);
   const uint32_t last = (uint32_t)(a.R - 1 - r0 < T::kRows - 1 ? a.R - 1 - r0 : T::kRows - 1);
   uint32_t at[T::kFetch];   // byte of the thread's chunk of stage 0 (its rows are within 128 x 128 KB)
 #pragma unroll
   for (int i = 0; i < T::kFetch; ++i) {
     const uint32_t m = (uint32_t)(tid + kMlpThreads * i) >> 4;
-    at[i] = ((m < last ? m : last) * (uint32_t)a.n_in + (tid & 15) * 8u) * 2u;
+    at[i] = ((m < last ? m : last) * (uint32_t)a.ldx + (tid & 15) * 8u) * 2u;
   }
   auto fetch = [&](int st) {
-    const uint32_t k = st * kStageK * 2u;
-    const bool in = st * kStageK + (tid & 15) * 8 < a.n_in;
+    const int k = st * kStageK + (tid & 15) * 8;
+    const bool in = k < a.n_in;
+    // a row's last chunk that is not whole (only where the pitch is not a
+    // multiple of 8): its elements are the last of the eight at the row's end
+    const int past = k + 8 - a.ldx;
+    const uint32_t step = (uint32_t)(st * kStageK - (in && past > 0 ? past : 0)) * 2u;
 #pragma unroll
     for (int i = 0; i < T::kFetch; ++i) {
-      x[i] = *reinterpret_cast<const u32x4 *>(Xb + (in ? at[i] + k : 0u));
+      x[i] = *reinterpret_cast<const u32x4u *>(Xb + (in ? at[i] + step : 0u));
       if (!in) x[i] = u32x4{0u, 0u, 0u, 0u};
+    }
+    if (in && past > 0) {
+#pragma unroll
+      for (int i = 0; i < T::kFetch; ++i) {
+        uint64_t lo = (uint64_t)x[i][1] << 32 | x[i][0], hi = (uint64_t)x[i][3] << 32 | x[i][2];
+        const int sh = 16 * past;   // 16 to 112
+        lo = sh >= 64 ? hi >> (sh - 64) : lo >> sh | hi << (64 - sh);
+        hi = sh >= 64 ? 0 : hi >> sh;
+        x[i] = u32x4{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
+      }
     }
   };
   auto put = [&](int st) {
@@ -250,9 +270,8 @@ hipError_t launch_rt(const MlpArgs &a, hipStream_t s) {
 
 }  // namespace
 
-bool mlp_ok(const uint16_t *X, const uint16_t *W1, int n_in, int h1, int h2) {
-  return n_in % 8 == 0 && (reinterpret_cast<uintptr_t>(W1) & 15) == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0 && h1 % 8 == 0 && h2 % 8 == 0 && h1 <= kWide &&
-         h2 <= kWide && h1 > kWide - 64 && h2 > kWide - 64;
+bool mlp_ok(int n_in, int h1, int h2) {
+  return n_in >= 8 && h1 % 8 == 0 && h2 % 8 == 0 && h1 <= kWide && h2 <= kWide && h1 > kWide - 64 && h2 > kWide - 64;
 }
 
 int64_t mlp_pack_elems(int n_in, int h1) { return ((n_in + 31) / 32 + (h1 + 31) / 32) * (int64_t)(kWide * 32); }

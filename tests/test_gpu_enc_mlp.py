@@ -30,7 +30,9 @@ def _value(bits):
 # and widest layers
 @pytest.mark.parametrize("rows,n_in,h1,h2", [
     (1, 8, 512, 512), (33, 32, 456, 512), (8192, 128, 512, 456), (8193, 136, 480, 512), (20000, 40, 512, 504),
-    (27001, 784, 512, 512), (30000, 264, 504, 464), (127, 1024, 512, 512)])
+    (27001, 784, 512, 512), (30000, 264, 504, 464), (127, 1024, 512, 512),
+    # rows of any width and alignment: the last chunk of a row not whole
+    (300, 9, 512, 512), (17, 100, 512, 512), (1, 131, 512, 512), (113, 255, 512, 512), (9000, 390, 512, 512)])
 def test_fused_forward_matches_its_layers(pkg, rows, n_in, h1, h2):
     api, parametric = pkg
     rng = np.random.default_rng(rows + n_in)
@@ -53,3 +55,26 @@ def test_fused_forward_matches_its_layers(pkg, rows, n_in, h1, h2):
     bound = n / (1 - n) * (np.abs(h) @ np.abs(w).T) + 2.0 ** -23 * np.abs(ref)
     assert np.all(np.abs(z - ref) <= bound + 1e-30)
     enc.close()
+
+
+# K-major operands with 16-byte rows: one row of k and tails of its steps of 32,
+# ragged tiles of 256 x 128, every epilogue, split-K
+@pytest.mark.parametrize("M,N,K,epi,splits", [
+    (8, 8, 1, 0, 1), (256, 128, 33, 1, 1), (264, 136, 95, 2, 1), (16, 512, 64, 1, 1), (520, 640, 4097, 0, 7),
+    (512, 784, 5001, 0, 32)])
+def test_k_major_product_equals_the_one_of_transposed_copies(pkg, M, N, K, epi, splits):
+    """The same terms in the same order on the K-contiguous path (its K padded
+    with zeros to a multiple of 8, which adds nothing): equal bits."""
+    api, _ = pkg
+    rng = np.random.default_rng(M + N + K)
+    a, b = (torch.from_numpy(mlp.bf16_bits(rng.normal(size=(K, w)).astype(np.float32)).copy()).cuda() for w in (M, N))
+    bias = torch.as_tensor(rng.normal(size=N).astype(np.float32)).cuda() if epi == 1 else None
+    mask = torch.from_numpy(mlp.bf16_bits(rng.normal(size=(M, N)).astype(np.float32)).copy()).cuda() if epi == 2 else None
+    kw = dict(epilogue=epi, bias=bias, mask=mask, ldm=N if epi == 2 else 0, splits=splits)
+    got = api.ivhd_gemm_bf16(a, b, M, N, K, lda=M, ldb=N, trans_a=True, **kw)
+    Kp = (K + 7) // 8 * 8
+    at, bt = (torch.zeros((w, Kp), dtype=torch.int16, device="cuda") for w in (M, N))
+    at[:, :K] = a.T
+    bt[:, :K] = b.T
+    ref = api.ivhd_gemm_bf16(at, bt, M, N, Kp, lda=Kp, ldb=Kp, trans_b=True, **kw)
+    assert torch.equal(got, ref)
