@@ -328,8 +328,7 @@ int load_state(ivhd_ctx *c, const float2 *y, const float2 *v) {
 
 // internal state -> caller's buffers
 int store_state(ivhd_ctx *c) {
-  HIPCHK(launch_gather_f2(c->cur(), c->inv, c->p.M, c->y_user, c->stream));
-  HIPCHK(launch_gather_f2(c->vcur(), c->inv, c->p.M, c->v_user, c->stream));
+  HIPCHK(launch_gather_pair(c->cur(), c->vcur(), c->inv, c->p.M, c->y_user, c->v_user, c->stream));
   return IVHD_OK;
 }
 

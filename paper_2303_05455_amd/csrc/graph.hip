@@ -153,6 +153,19 @@ __global__ void gather_f2_kernel(const float2 *__restrict__ src, const int32_t *
   if (p < M) dst[p] = src[idx ? (int64_t)idx[p] : p];
 }
 
+// the same for two arrays at once: a context's positions and velocities, in one
+// launch as a launch is what a small one costs (10 iterations of 2,000 vertices
+// and the copy out: 46 us with two launches, 43 with one)
+__global__ void gather_pair_kernel(const float2 *src0, const float2 *src1, const int32_t *__restrict__ idx, int64_t M,
+                                   float2 *dst0, float2 *dst1) {
+  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (p >= M) return;
+  const int64_t i = idx ? (int64_t)idx[p] : p;
+  const float2 a = src0[i], b = src1[i];
+  dst0[p] = a;
+  dst1[p] = b;
+}
+
 // flags[FLAG_BAD_INDEX] = 1 if an entry is outside [0, hi)
 __global__ void range_check_kernel(const int32_t *__restrict__ idx, int64_t n, int32_t hi, int32_t *flags) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -406,6 +419,12 @@ hipError_t launch_probe_atomic(uint64_t *acc, const int32_t *idx, int64_t n, hip
 
 hipError_t launch_gather_f2(const float2 *src, const int32_t *idx, int64_t M, float2 *dst, hipStream_t s) {
   gather_f2_kernel<<<grid_for(M), kBlock, 0, s>>>(src, idx, M, dst);
+  return hipGetLastError();
+}
+
+hipError_t launch_gather_pair(const float2 *src0, const float2 *src1, const int32_t *idx, int64_t M, float2 *dst0,
+                              float2 *dst1, hipStream_t s) {
+  gather_pair_kernel<<<grid_for(M), kBlock, 0, s>>>(src0, src1, idx, M, dst0, dst1);
   return hipGetLastError();
 }
 
