@@ -195,6 +195,46 @@ __global__ void count_kernel(const int32_t *__restrict__ idx, int64_t M, int k, 
   if (j >= 0) atomicAdd(&cnt[j], 1);
 }
 
+// The two passes of a transposition onto few targets (an inverted file's
+// lists), a block to kFewChunk entries: atomics on a few hundred counters wait
+// for each other (200,000 and 1,600,000 entries onto 512 targets: 140 us a pass,
+// the mean), so a block counts in LDS and adds each counter once; the scatter
+// takes its places from the same counts.  24 us.
+constexpr int kFewTargets = 4096;   // counters in LDS: 16 KB
+constexpr int kFewChunk = 4096;
+
+__global__ void __launch_bounds__(kBlock) count_few_kernel(const int32_t *__restrict__ idx, int64_t n, int ntargets,
+                                                           int32_t *cnt) {
+  __shared__ int32_t here[kFewTargets];
+  for (int t = threadIdx.x; t < ntargets; t += kBlock) here[t] = 0;
+  __syncthreads();
+  const int64_t e0 = (int64_t)blockIdx.x * kFewChunk;
+  const int64_t e1 = e0 + kFewChunk < n ? e0 + kFewChunk : n;
+  for (int64_t e = e0 + threadIdx.x; e < e1; e += kBlock)
+    if (idx[e] >= 0) atomicAdd(&here[idx[e]], 1);
+  __syncthreads();
+  for (int t = threadIdx.x; t < ntargets; t += kBlock)
+    if (here[t]) atomicAdd(&cnt[t], here[t]);
+}
+
+__global__ void __launch_bounds__(kBlock) scatter_few_kernel(const int32_t *__restrict__ idx, int64_t n, int k,
+                                                             int ntargets, int32_t *cursor,
+                                                             int32_t *__restrict__ tmp) {
+  __shared__ int32_t here[kFewTargets];
+  for (int t = threadIdx.x; t < ntargets; t += kBlock) here[t] = 0;
+  __syncthreads();
+  const int64_t e0 = (int64_t)blockIdx.x * kFewChunk;
+  const int64_t e1 = e0 + kFewChunk < n ? e0 + kFewChunk : n;
+  for (int64_t e = e0 + threadIdx.x; e < e1; e += kBlock)
+    if (idx[e] >= 0) atomicAdd(&here[idx[e]], 1);
+  __syncthreads();
+  for (int t = threadIdx.x; t < ntargets; t += kBlock)
+    if (here[t]) here[t] = atomicAdd(&cursor[t], here[t]);
+  __syncthreads();
+  for (int64_t e = e0 + threadIdx.x; e < e1; e += kBlock)
+    if (idx[e] >= 0) tmp[atomicAdd(&here[idx[e]], 1)] = (int32_t)(e / k);
+}
+
 // exclusive scan of one value per thread over the block; returns the prefix
 // and the block total.  256 threads = 4 waves of 64.
 __device__ __forceinline__ int32_t block_exclusive_scan(int32_t val, int32_t *lds, int32_t &total) {
@@ -459,10 +499,15 @@ hipError_t launch_transpose(const int32_t *idx, int64_t rows, int k, int64_t nta
                             hipStream_t s) {
   fill_i32_kernel<<<grid_for(ntargets + 1), kBlock, 0, s>>>(cnt, ntargets + 1, 0);
   fill_i32_kernel<<<1, kBlock, 0, s>>>(flags + FLAG_BIG_COUNT, 1, 0);
-  count_kernel<<<grid_for(rows * k), kBlock, 0, s>>>(idx, rows, k, cnt);
+  const int64_t n = rows * k;
+  // enough entries to a counter that they collide, and to a block that its counts pay
+  const bool few = ntargets <= kFewTargets && n >= 16 * ntargets && n >= kFewChunk;
+  if (few) count_few_kernel<<<grid_for(n, kFewChunk), kBlock, 0, s>>>(idx, n, (int)ntargets, cnt);
+  else count_kernel<<<grid_for(n), kBlock, 0, s>>>(idx, rows, k, cnt);
   hipError_t e = launch_scan(cnt, ntargets, part, ptr, s);
   if (e != hipSuccess) return e;
-  scatter_kernel<<<grid_for(rows * k), kBlock, 0, s>>>(idx, rows, k, cnt, tmp);
+  if (few) scatter_few_kernel<<<grid_for(n, kFewChunk), kBlock, 0, s>>>(idx, n, k, (int)ntargets, cnt, tmp);
+  else scatter_kernel<<<grid_for(n), kBlock, 0, s>>>(idx, rows, k, cnt, tmp);
   sort_small_kernel<<<grid_for(ntargets), kBlock, 0, s>>>(ptr, tmp, ntargets, big, flags, src_out);
   sort_big_kernel<<<kBigSortBlocks, kBlock, 0, s>>>(ptr, tmp, big, flags, src_out);
   return hipGetLastError();

@@ -407,7 +407,18 @@ __global__ void centroid_mean_kernel(const float *__restrict__ X, int N, const i
   const float inv = 1.f / (float)(e - b);
   for (int d = threadIdx.x; d < N; d += blockDim.x) {
     float s = 0.f;
-    for (int32_t p = b; p < e; ++p) s += X[(int64_t)pos_id[p] * N + d];
+    int32_t p = b;
+    // sixteen points in flight, added in order (one by one: 428 us for 200,000
+    // points of 100 dimensions in 512 lists)
+    for (; p + 16 <= e; p += 16) {
+      float x[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) x[u] = X[(int64_t)pos_id[p + u] * N + d];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u = 0; u < 16; ++u) s += x[u];
+    }
+    for (; p < e; ++p) s += X[(int64_t)pos_id[p] * N + d];
     C[(int64_t)c * N + d] = s * inv;
   }
 }

@@ -401,7 +401,7 @@ int ivhd_ivf_train(const float *d_x, int64_t M, int32_t N, int32_t nlist, int32_
   for (int it = 0; it <= n_iter; ++it) {
     if ((rc = K.run(d_centroids, 0, nullptr, d_assign, nullptr))) return rc;
     if (it == n_iter) break;
-    Scratch L;
+    Scratch L(s);
     int32_t *lptr, *pos_id;
     if ((rc = transpose_lists(L, d_assign, M, 1, nlist, &lptr, &pos_id, flags, s))) return rc;
     HIPCHK(launch_centroid_mean(d_x, N, lptr, pos_id, nlist, d_centroids, s));
