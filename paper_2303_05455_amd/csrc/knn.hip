@@ -311,12 +311,24 @@ ivf_list_kernel(const float *__restrict__ X, int N, const float *__restrict__ Q,
     }
     __syncthreads();
     if (have_q) {
-      for (int m = 0; m < CBW / 2; ++m) {
-        const int col = 2 * m + half;
-        if (c0 + col >= pend) continue;
-        const int32_t id = pos_id[c0 + col];
-        if (id == my_self) continue;
-        list_insert<KP>(ks, ki, sS[my_row * SPW + col], id);
+      // Sixteen scores at a time, those at or below the row's threshold first
+      // marked and then inserted: an insertion costs some 55 instructions of
+      // all lanes that have one, and of a list's few hundred points most pass
+      // no threshold once the list is full (200,000 queries, 8 of 512 lists of
+      // 390 points, k = 5: 5.8 ms inserting one by one, 4.4 so).
+      for (int m0 = 0; m0 < CBW / 2; m0 += 16) {
+        uint32_t hits = 0;
+#pragma unroll
+        for (int m = 0; m < 16; ++m) {
+          const int col = 2 * (m0 + m) + half;
+          hits |= sS[my_row * SPW + col] <= ks[KP - 1] && c0 + col < pend ? 1u << m : 0u;
+        }
+        while (hits) {
+          const int col = 2 * (m0 + __builtin_ctz(hits)) + half;
+          hits &= hits - 1;
+          const int32_t id = pos_id[c0 + col];
+          if (id != my_self) list_insert<KP>(ks, ki, sS[my_row * SPW + col], id);
+        }
       }
     }
   }
