@@ -225,16 +225,19 @@ __device__ __forceinline__ float2 light_force(const StepArgs &A, int64_t i, floa
 // graph): the vertex's edge list (out-nn | out-rn | in-nn | in-rn) is split
 // over the group's lanes round-robin, then reduced with a fixed butterfly
 // over the group; every lane of the group returns the total.  r is the
-// lane's rank in the group, [ns, ne) the vertex's nn in-edge segment.  With
+// lane's rank in the group, [ns, ne) the vertex's nn in-edge segment and
+// [rs, re) its rn one (empty where those are not gathered).  With
 // ST each lane adds the stress terms of its out-edges to its own es.
 template <bool L1, bool ARN, bool ST, int G>
 __device__ __forceinline__ float2 spread_force(const StepArgs &A, int64_t i, float2 yi, int r, int32_t ns,
-                                               int32_t ne, double &es) {
+                                               int32_t ne, int32_t rs, int32_t re, double &es) {
   static_assert(G >= 2 && G <= 64 && (G & (G - 1)) == 0, "a group is a power of two within a wavefront");
   const float2 *__restrict__ y = A.h;
-  const int32_t rs = !ARN && A.rn > 0 ? A.rn_ptr[i] : 0, re = !ARN && A.rn > 0 ? A.rn_ptr[i + 1] : 0;
   const int32_t n_out = A.nn + A.rn, n_in_nn = ne - ns;
   const int32_t total = n_out + n_in_nn + (re - rs);
+  // the four lists, each so that edge e is its entry e
+  const int32_t *__restrict__ out_nn = A.nn_idx + i * A.nn, *__restrict__ out_rn = A.rn_idx + (i * A.rn - A.nn);
+  const int32_t *__restrict__ nn_in = A.nn_src + (ns - n_out), *__restrict__ rn_in = A.rn_src + (rs - n_out - n_in_nn);
   float fx = 0.f, fy = 0.f;
   // four of a lane's edges at a time: their index and position loads are
   // issued together, the terms are still added in ascending edge order
@@ -244,29 +247,27 @@ __device__ __forceinline__ float2 spread_force(const StepArgs &A, int64_t i, flo
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int32_t e = e0 + u * G;
-      int32_t o = -1;
-      int k = 0;
-      if (e < total) {
-        if (e < A.nn) {
-          o = A.nn_idx[i * A.nn + e];
-          k = 1;
-        } else if (e < n_out) {
-          o = A.rn_idx[i * A.rn + (e - A.nn)];
-          k = 2;
-        } else if (e < n_out + n_in_nn) {
-          o = A.nn_src[ns + (e - n_out)];
-          k = 1;
-        } else {
-          o = A.rn_src[rs + (e - n_out - n_in_nn)];
-          k = 2;
-        }
-      }
+      // the list is chosen by its address, so that the lanes of a wavefront,
+      // which are in all four of them, load with one instruction
+      const bool in_nn = e >= n_out && e < n_out + n_in_nn;
+      const int32_t *p = e < A.nn ? out_nn : e < n_out ? out_rn : in_nn ? nn_in : rn_in;
+      const int32_t o = e < total ? p[e] : -1;
       other[u] = o;
-      kind[u] = o >= 0 ? k : 0;
+      kind[u] = o < 0 ? 0 : (e < A.nn || in_nn) ? 1 : 2;
     }
     float2 yo[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) yo[u] = kind[u] ? y[other[u]] : yi;
+    for (int u = 0; u < 4; ++u) {   // an absent edge reads the vertex itself: no branch around a load
+      const int64_t o = kind[u] ? (int64_t)other[u] : i;
+      if constexpr (G == kSmallGraphLanes)   // (its positions are within 4 GB: a 32-bit offset)
+        yo[u] = *reinterpret_cast<const float2 *>(reinterpret_cast<const unsigned char *>(y) + (uint32_t)o * 8u);
+      else
+        yo[u] = y[o];
+    }
+    // all four on their way before the first is waited for (else each goes
+    // into the branch that uses it)
+    asm volatile("" : "+v"(yo[0].x), "+v"(yo[0].y), "+v"(yo[1].x), "+v"(yo[1].y), "+v"(yo[2].x), "+v"(yo[2].y),
+                      "+v"(yo[3].x), "+v"(yo[3].y));
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       if (!kind[u]) continue;
@@ -287,15 +288,15 @@ __device__ __forceinline__ float2 spread_force(const StepArgs &A, int64_t i, flo
 }
 
 // v' = a v + b f, y' = y + v' (Adam: its moment update instead).  hi is the
-// position the force was taken at (y itself unless OPT_NEST).  Returns the
+// position the force was taken at (y itself unless OPT_NEST), v0 the vertex's
+// velocity.  Returns the
 // vertex's |v'|^2 - |v|^2 in FP64 for OPT_ADAPT (+inf when the tentative
 // position is not finite, which forces a rejection); the non-finite flag is
 // raised only for steps that are final.
 template <int OPT>
-__device__ __forceinline__ double apply_update(const StepArgs &A, int64_t i, float2 hi, float2 f) {
+__device__ __forceinline__ double apply_update(const StepArgs &A, int64_t i, float2 hi, float2 f, float2 v0) {
   constexpr bool NEST = OPT == OPT_NEST, ADAPT = OPT == OPT_ADAPT, ADAM = OPT == OPT_ADAM;
   const float2 yi = NEST ? A.y[i] : hi;
-  const float2 v0 = A.v[i];
   float2 yn;
   float2 v;
   if (ADAM) {
@@ -363,7 +364,9 @@ __global__ void __launch_bounds__(kDetBlock) det_kernel(StepArgs A, float2 *out)
     if (h < A.n_heavy) {   // uniform over the wavefront
       const int64_t i = A.heavy[h];
       const float2 hi = A.h[i];
-      const float2 f = spread_force<L1, ARN, ST, 64>(A, i, hi, lane, A.nn_ptr[i], A.nn_ptr[i + 1], es);
+      const bool in_rn = !ARN && A.rn > 0;
+      const float2 f = spread_force<L1, ARN, ST, 64>(A, i, hi, lane, A.nn_ptr[i], A.nn_ptr[i + 1],
+                                                     in_rn ? A.rn_ptr[i] : 0, in_rn ? A.rn_ptr[i + 1] : 0, es);
       if (lane == 0) {
         if (ARN) {
           A.fown[i] = f;
@@ -371,7 +374,7 @@ __global__ void __launch_bounds__(kDetBlock) det_kernel(StepArgs A, float2 *out)
           const float g = -2.f * (A.gscale ? *A.gscale : 1.f);
           out[A.out_perm ? A.out_perm[i] : i] = make_float2(g * f.x, g * f.y);
         } else {
-          ke = apply_update<OPT>(A, i, hi, f);
+          ke = apply_update<OPT>(A, i, hi, f, A.v[i]);
         }
       }
     }
@@ -387,11 +390,26 @@ __global__ void __launch_bounds__(kDetBlock) det_kernel(StepArgs A, float2 *out)
     const int r = (int)(threadIdx.x % G);
     if (tile < A.light_tiles && i < A.M) {
       const int32_t ns = A.nn_ptr[i], ne = A.nn_ptr[i + 1];
+      // a small graph's launch is a chain of loads: what does not depend on
+      // the nn list's bounds goes out with them (70,000 vertices, nn = 5: 8.1
+      // us an iteration with five rounds of loads one behind the other and a
+      // branch for each list and each absent edge, 6.7 with three and none)
+      int32_t rs = 0, re = 0;
+      float2 early = make_float2(0.f, 0.f), v_early = early;
+      if constexpr (G > 1) {
+        early = A.h[i];
+        if (!ARN && A.rn > 0) {
+          rs = A.rn_ptr[i];
+          re = A.rn_ptr[i + 1];
+        }
+        if (!GRAD && !ARN) v_early = A.v[i];
+        asm volatile("" : "+v"(rs), "+v"(re), "+v"(early.x), "+v"(early.y), "+v"(v_early.x), "+v"(v_early.y));
+      }
       if (ne - ns <= A.heavy_deg) {   // else served by a heavy wavefront
-        const float2 hi = A.h[i];
+        const float2 hi = G > 1 ? early : A.h[i];
         float2 f;
         if constexpr (G == 1) f = light_force<L1, ARN, ST>(A, i, hi, ns, ne, es);
-        else f = spread_force<L1, ARN, ST, G>(A, i, hi, r, ns, ne, es);
+        else f = spread_force<L1, ARN, ST, G>(A, i, hi, r, ns, ne, rs, re, es);
         if (r != 0) {
           // the group's leader stores the result
         } else if (ARN) {
@@ -400,7 +418,7 @@ __global__ void __launch_bounds__(kDetBlock) det_kernel(StepArgs A, float2 *out)
           const float g = -2.f * (A.gscale ? *A.gscale : 1.f);
           out[A.out_perm ? A.out_perm[i] : i] = make_float2(g * f.x, g * f.y);
         } else {
-          ke = apply_update<OPT>(A, i, hi, f);
+          ke = apply_update<OPT>(A, i, hi, f, G > 1 ? v_early : A.v[i]);
         }
       }
     }
@@ -444,7 +462,7 @@ __global__ void __launch_bounds__(kBlock) atomic_update_kernel(StepArgs A) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= A.M) return;
   const float2 f = gather_reactions(A, i);
-  (void)apply_update<OPT>(A, i, OPT == OPT_NEST ? make_float2(0.f, 0.f) : A.y[i], f);
+  (void)apply_update<OPT>(A, i, OPT == OPT_NEST ? make_float2(0.f, 0.f) : A.y[i], f, A.v[i]);
 }
 
 __global__ void __launch_bounds__(kBlock) atomic_grad_out_kernel(StepArgs A, float2 *out) {
