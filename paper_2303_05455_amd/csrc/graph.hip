@@ -195,44 +195,83 @@ __global__ void count_kernel(const int32_t *__restrict__ idx, int64_t M, int k, 
   if (j >= 0) atomicAdd(&cnt[j], 1);
 }
 
-// The two passes of a transposition onto few targets (an inverted file's
-// lists), a block to kFewChunk entries: atomics on a few hundred counters wait
-// for each other (200,000 and 1,600,000 entries onto 512 targets: 140 us a pass,
-// the mean), so a block counts in LDS and adds each counter once; the scatter
-// takes its places from the same counts.  24 us.
-constexpr int kFewTargets = 4096;   // counters in LDS: 16 KB
-constexpr int kFewChunk = 4096;
+// A transposition onto few targets (an inverted file's lists), a block to
+// kFewChunk entries.  The general passes would wait for atomics on a few hundred
+// counters and sort every target's whole segment (200,000 and 1,600,000 entries
+// onto 512 targets: 140 + 140 + 240 us, the mean).  Here a block counts in LDS
+// and writes its counts (few_count_kernel), their running sums over the blocks
+// give each block its place in every segment (few_offsets_kernel), and each
+// block sorts its entries by (target, entry) in LDS and writes them there
+// (few_place_kernel): segments come out ascending.  60 us.
+constexpr int kFewTargets = 2048;   // so that the blocks' counts fit the scatter buffer
+constexpr int kFewChunk = 4096;     // 12 bits of a sort key, above them 11 of the target
+constexpr int kFewThreads = 1024;
 
-__global__ void __launch_bounds__(kBlock) count_few_kernel(const int32_t *__restrict__ idx, int64_t n, int ntargets,
-                                                           int32_t *cnt) {
+__global__ void __launch_bounds__(kFewThreads) few_count_kernel(const int32_t *__restrict__ idx, int64_t n,
+                                                                int ntargets, int32_t *__restrict__ counts) {
   __shared__ int32_t here[kFewTargets];
-  for (int t = threadIdx.x; t < ntargets; t += kBlock) here[t] = 0;
+  for (int t = threadIdx.x; t < ntargets; t += kFewThreads) here[t] = 0;
   __syncthreads();
   const int64_t e0 = (int64_t)blockIdx.x * kFewChunk;
   const int64_t e1 = e0 + kFewChunk < n ? e0 + kFewChunk : n;
-  for (int64_t e = e0 + threadIdx.x; e < e1; e += kBlock)
+  for (int64_t e = e0 + threadIdx.x; e < e1; e += kFewThreads)
     if (idx[e] >= 0) atomicAdd(&here[idx[e]], 1);
   __syncthreads();
-  for (int t = threadIdx.x; t < ntargets; t += kBlock)
-    if (here[t]) atomicAdd(&cnt[t], here[t]);
+  for (int t = threadIdx.x; t < ntargets; t += kFewThreads) counts[(int64_t)blockIdx.x * ntargets + t] = here[t];
 }
 
-__global__ void __launch_bounds__(kBlock) scatter_few_kernel(const int32_t *__restrict__ idx, int64_t n, int k,
-                                                             int ntargets, int32_t *cursor,
-                                                             int32_t *__restrict__ tmp) {
-  __shared__ int32_t here[kFewTargets];
-  for (int t = threadIdx.x; t < ntargets; t += kBlock) here[t] = 0;
-  __syncthreads();
+// counts[b][t] -> the sum of counts[0..b)[t]; cnt[t] = the sum over all nb blocks
+__global__ void __launch_bounds__(64) few_offsets_kernel(int32_t *__restrict__ counts, int nb, int ntargets,
+                                                         int32_t *__restrict__ cnt) {
+  const int t = (int)blockIdx.x * 64 + threadIdx.x;
+  if (t >= ntargets) return;
+  int32_t run = 0;
+  for (int b = 0; b < nb; b += 16) {   // sixteen in flight
+    int32_t v[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) v[u] = b + u < nb ? counts[(int64_t)(b + u) * ntargets + t] : 0;
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      if (b + u < nb) counts[(int64_t)(b + u) * ntargets + t] = run;
+      run += v[u];
+    }
+  }
+  cnt[t] = run;
+}
+
+__global__ void __launch_bounds__(kFewThreads) few_place_kernel(const int32_t *__restrict__ idx, int64_t n, int k,
+                                                                int ntargets, const int32_t *__restrict__ ptr,
+                                                                const int32_t *__restrict__ counts,
+                                                                int32_t *__restrict__ src_out) {
+  __shared__ uint32_t key[kFewChunk];
+  __shared__ int32_t first[kFewTargets];   // the target's first place in key
   const int64_t e0 = (int64_t)blockIdx.x * kFewChunk;
-  const int64_t e1 = e0 + kFewChunk < n ? e0 + kFewChunk : n;
-  for (int64_t e = e0 + threadIdx.x; e < e1; e += kBlock)
-    if (idx[e] >= 0) atomicAdd(&here[idx[e]], 1);
+  for (int i = threadIdx.x; i < kFewChunk; i += kFewThreads) {
+    const int32_t j = e0 + i < n ? idx[e0 + i] : -1;
+    key[i] = j >= 0 ? (uint32_t)j * kFewChunk + (uint32_t)i : ~0u;
+  }
+  for (int size = 2; size <= kFewChunk; size *= 2)
+    for (int stride = size / 2; stride > 0; stride /= 2) {
+      __syncthreads();
+      for (int h = threadIdx.x; h < kFewChunk / 2; h += kFewThreads) {
+        const int i = 2 * h - (h & (stride - 1)), j = i + stride;
+        const uint32_t x = key[i], y = key[j];
+        if ((x > y) == ((i & size) == 0)) {
+          key[i] = y;
+          key[j] = x;
+        }
+      }
+    }
   __syncthreads();
-  for (int t = threadIdx.x; t < ntargets; t += kBlock)
-    if (here[t]) here[t] = atomicAdd(&cursor[t], here[t]);
+  for (int i = threadIdx.x; i < kFewChunk; i += kFewThreads)
+    if (key[i] != ~0u && (i == 0 || key[i] / kFewChunk != key[i - 1] / kFewChunk)) first[key[i] / kFewChunk] = i;
   __syncthreads();
-  for (int64_t e = e0 + threadIdx.x; e < e1; e += kBlock)
-    if (idx[e] >= 0) tmp[atomicAdd(&here[idx[e]], 1)] = (int32_t)(e / k);
+  for (int i = threadIdx.x; i < kFewChunk; i += kFewThreads) {
+    if (key[i] == ~0u) continue;
+    const int t = (int)(key[i] / kFewChunk);
+    src_out[ptr[t] + counts[(int64_t)blockIdx.x * ntargets + t] + (i - first[t])] =
+        (int32_t)((e0 + key[i] % kFewChunk) / k);
+  }
 }
 
 // exclusive scan of one value per thread over the block; returns the prefix
@@ -500,14 +539,21 @@ hipError_t launch_transpose(const int32_t *idx, int64_t rows, int k, int64_t nta
   fill_i32_kernel<<<grid_for(ntargets + 1), kBlock, 0, s>>>(cnt, ntargets + 1, 0);
   fill_i32_kernel<<<1, kBlock, 0, s>>>(flags + FLAG_BIG_COUNT, 1, 0);
   const int64_t n = rows * k;
-  // enough entries to a counter that they collide, and to a block that its counts pay
-  const bool few = ntargets <= kFewTargets && n >= 16 * ntargets && n >= kFewChunk;
-  if (few) count_few_kernel<<<grid_for(n, kFewChunk), kBlock, 0, s>>>(idx, n, (int)ntargets, cnt);
-  else count_kernel<<<grid_for(n), kBlock, 0, s>>>(idx, rows, k, cnt);
+  // enough entries to a target that they collide, and to a block that its
+  // counts pay (they then take at most n (1 / 2 + 1 / 16) entries of tmp)
+  if (ntargets <= kFewTargets && n >= 16 * ntargets && n >= kFewChunk) {
+    const int64_t nb = (n + kFewChunk - 1) / kFewChunk;
+    few_count_kernel<<<(unsigned)nb, kFewThreads, 0, s>>>(idx, n, (int)ntargets, tmp);
+    few_offsets_kernel<<<grid_for(ntargets, 64), 64, 0, s>>>(tmp, (int)nb, (int)ntargets, cnt);
+    const hipError_t e = launch_scan(cnt, ntargets, part, ptr, s);
+    if (e != hipSuccess) return e;
+    few_place_kernel<<<(unsigned)nb, kFewThreads, 0, s>>>(idx, n, k, (int)ntargets, ptr, tmp, src_out);
+    return hipGetLastError();
+  }
+  count_kernel<<<grid_for(n), kBlock, 0, s>>>(idx, rows, k, cnt);
   hipError_t e = launch_scan(cnt, ntargets, part, ptr, s);
   if (e != hipSuccess) return e;
-  if (few) scatter_few_kernel<<<grid_for(n, kFewChunk), kBlock, 0, s>>>(idx, n, k, (int)ntargets, cnt, tmp);
-  else scatter_kernel<<<grid_for(n), kBlock, 0, s>>>(idx, rows, k, cnt, tmp);
+  scatter_kernel<<<grid_for(n), kBlock, 0, s>>>(idx, rows, k, cnt, tmp);
   sort_small_kernel<<<grid_for(ntargets), kBlock, 0, s>>>(ptr, tmp, ntargets, big, flags, src_out);
   sort_big_kernel<<<kBigSortBlocks, kBlock, 0, s>>>(ptr, tmp, big, flags, src_out);
   return hipGetLastError();

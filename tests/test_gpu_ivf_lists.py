@@ -17,8 +17,9 @@ def p():
 
 
 # 4096 entries and 16 to a target are the least of the path for few targets,
-# 4096 targets its most; chunks of 4096 entries
-@pytest.mark.parametrize("M,nlist", [(4095, 2), (4096, 2), (4096, 256), (4096, 257), (8193, 31), (65535, 4096),
+# 2048 targets its most; chunks of 4096 entries
+@pytest.mark.parametrize("M,nlist", [(4095, 2), (4096, 2), (4096, 256), (4096, 257), (8193, 31), (32767, 2048), (32768, 2048),
+                                     (40001, 2049), (65535, 4096),
                                      (65537, 4096), (70000, 4097)])
 def test_means_are_sums_in_ascending_order(p, M, nlist):
     rng = np.random.default_rng(M + nlist)
