@@ -896,13 +896,16 @@ constexpr int64_t kBatchTiles = 16 * kCus;
 
 int64_t knn_image_halves(int64_t M, int N) { return (M + FT - 1) / FT * FT * (int64_t)((N + FK - 1) / FK * FK); }
 
+// (an image without room for the rows is refused)
 hipError_t launch_knn_split(const float *X, int64_t M, int N, const int32_t *map, const float *mean, float scale,
-                            _Float16 *hi, _Float16 *lo, float *norms, float *start, KnnStats *stats,
+                            const KnnImage &hi, const KnnImage &lo, float *norms, float *start, KnnStats *stats,
                             hipStream_t s) {
+  const int64_t need = knn_image_halves(M, N);
+  if ((hi.p && need > hi.halves) || (lo.p && need > lo.halves)) return hipErrorInvalidValue;
   const bool vec = N % 4 == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0;
   const int64_t groups = (M + FT - 1) / FT * (FT / 16);
   knn_split_kernel<<<(unsigned)(groups < 4096 ? groups : 4096), 256, 0, s>>>(X, M, N, (N + FK - 1) / FK, map, mean,
-                                                                             scale, hi, lo, norms, start, stats, vec);
+                                                                             scale, hi.p, lo.p, norms, start, stats, vec);
   return hipGetLastError();
 }
 
@@ -942,7 +945,11 @@ int KnnSearch::open(int64_t M_, int N_, const float *Q_, int64_t nq_, bool same_
   few = (M + FT - 1) / FT < kFewTiles;
   const int64_t tiles = (M + FT - 1) / FT, nx = knn_image_halves(M, N), nqi = knn_image_halves(nq, N);
   Carve V;
-  V.add(&ch, nx);
+  auto image = [&](KnnImage *im, int64_t halves) {
+    V.add(&im->p, halves);
+    im->halves = halves;
+  };
+  image(&ch, nx);
   V.add(&norms, M);
   V.add(&start, tiles * FT);
   V.add(&xstats, 1);
@@ -952,13 +959,13 @@ int KnnSearch::open(int64_t M_, int N_, const float *Q_, int64_t nq_, bool same_
   V.add(&mean, N);
   V.add(&mean_part, (int64_t)kMeanParts * N);
   if (few) {
-    V.add(&cl, nx);
+    image(&cl, nx);
     V.add(&rest, nq + 1);
   }
   if (!same) {
-    V.add(&qh, nqi);
+    image(&qh, nqi);
     V.add(&qnorm, nq);
-    if (few) V.add(&ql, nqi);
+    if (few) image(&ql, nqi);
   }
   const int rc = V.get(S, "operands of the search");
   if (rc) return rc;
@@ -991,8 +998,9 @@ int KnnSearch::run(const float *X, int self_mode, const int32_t *self, int32_t *
   }
 
   FilterArgs f{};
-  f.Qh = qh;
-  f.Ch = ch;
+  KnnImage qi = qh;   // of the queries that are swept
+  f.Qh = qi.p;
+  f.Ch = ch.p;
   f.start = start;
   f.nk = nk;
   f.nseg = 1;
@@ -1024,6 +1032,8 @@ int KnnSearch::run(const float *X, int self_mode, const int32_t *self, int32_t *
     f.tiles_per_split = (tiles + f.splits - 1) / f.splits;
     f.lead = lead_tiles(f.tiles_per_split);
     g.n_launch = n * FT;
+    if ((qb0 + (n - 1) * step + 1) * nk * kTileHalves > qi.halves || tiles * nk * kTileHalves > ch.halves)
+      return fail(IVHD_ESTATE, "kNN: query tiles outside their operands");
     const int64_t need = n * FT * f.splits * kp;
     if (need > part_cap) {   // (a larger launch is queued behind the smaller: both lists stay)
       const int r = S.get(&part, need, "candidate lists");
@@ -1082,39 +1092,46 @@ int KnnSearch::run(const float *X, int self_mode, const int32_t *self, int32_t *
   // three segments: everything, or the queries that were not certified
   const int64_t n3 = three ? nq : failed;
   const int32_t *map = three ? nullptr : fails + 1;
+  Scratch R(s);   // of this run
+  KnnImage low_c = cl, low_q = ql;
+  int32_t *left = rest;
   if (!few) {
-    const int64_t nx = knn_image_halves(M, N), ni = knn_image_halves(n3, N);
-    if (!rest && (rc = S.get(&rest, nq + 1, "uncertified queries (three segments)"))) return rc;
-    if ((rc = S.get(&cl, nx, "candidate operands (low)"))) return rc;
-    HIPCHK(launch_knn_split(X, M, N, nullptr, centre, scale, nullptr, cl, nullptr, nullptr, nullptr, s));
+    auto image = [&](KnnImage *im, int64_t rows, const char *what) -> int {
+      im->halves = knn_image_halves(rows, N);
+      return R.get(&im->p, im->halves, what);
+    };
+    if ((rc = R.get(&left, nq + 1, "uncertified queries (three segments)"))) return rc;
+    if ((rc = image(&low_c, M, "candidate operands (low)"))) return rc;
+    HIPCHK(launch_knn_split(X, M, N, nullptr, centre, scale, KnnImage{}, low_c, nullptr, nullptr, nullptr, s));
     if (three && same) {
-      ql = cl;
+      low_q = low_c;
     } else {
-      if ((rc = S.get(&ql, ni, "query operands (low)"))) return rc;
-      if (!three && (rc = S.get(&qh, ni, "query operands"))) return rc;
-      HIPCHK(launch_knn_split(Q, n3, N, map, centre, scale, three ? nullptr : qh, ql, nullptr, nullptr, nullptr, s));
+      if ((rc = image(&low_q, n3, "query operands (low)"))) return rc;
+      if (!three && (rc = image(&qi, n3, "query operands"))) return rc;
+      HIPCHK(launch_knn_split(Q, n3, N, map, centre, scale, three ? KnnImage{} : qi, low_q, nullptr, nullptr, nullptr,
+                              s));
     }
   }
   kp = list_length(k);
-  f.Qh = qh;
-  f.Ql = ql;
-  f.Cl = cl;
+  f.Qh = qi.p;
+  f.Ql = low_q.p;
+  f.Cl = low_c.p;
   f.nseg = g.nseg = 3;
   f.nq = g.nq = n3;
   f.map = g.map = map;
-  HIPCHK(launch_fill_i32(rest, 1, 0, s));
-  g.fails = rest;
-  if ((rc = sweep_all((n3 + FT - 1) / FT)) || (rc = read_failed(rest))) return rc;
+  HIPCHK(launch_fill_i32(left, 1, 0, s));
+  g.fails = left;
+  if ((rc = sweep_all((n3 + FT - 1) / FT)) || (rc = read_failed(left))) return rc;
   if (failed == 0) return IVHD_OK;
   const int64_t groups = (failed + kBruteQ - 1) / kBruteQ;
   int64_t splits = 4 * kCus / groups;
   splits = splits < 1 ? 1 : (splits > 64 ? 64 : splits);
   if (splits > tiles) splits = tiles;
   uint64_t *bp;
-  if ((rc = S.get(&bp, failed * splits * k, "candidate lists (all candidates)"))) return rc;
-  knn_brute_kernel<<<dim3((unsigned)groups, (unsigned)splits), 256, 0, s>>>(X, M, N, Q, failed, rest + 1, self_mode, self,
+  if ((rc = R.get(&bp, failed * splits * k, "candidate lists (all candidates)"))) return rc;
+  knn_brute_kernel<<<dim3((unsigned)groups, (unsigned)splits), 256, 0, s>>>(X, M, N, Q, failed, left + 1, self_mode, self,
                                                                             k, (int)splits, bp);
-  knn_brute_merge_kernel<<<grid_for(failed, 4), 256, 0, s>>>(bp, failed, rest + 1, k, (int)splits, idx, dist);
+  knn_brute_merge_kernel<<<grid_for(failed, 4), 256, 0, s>>>(bp, failed, left + 1, k, (int)splits, idx, dist);
   HIPCHK(hipGetLastError());
   HIPCHK(hipStreamSynchronize(s));
   return IVHD_OK;

@@ -51,15 +51,23 @@ struct Carve {
 struct KnnStats {
   uint32_t norm2, res2;
 };
+// operand images of whole tiles of rows, and the room that was allocated
+struct KnnImage {
+  _Float16 *p = nullptr;
+  int64_t halves = 0;
+};
 // One search: k nearest of M candidate rows to each of nq rows of Q (same: the
-// candidates are Q).  Its buffers live as long as it does.
+// candidates are Q).  What open allocates lives as long as it does and is never
+// replaced; what a run needs beyond that, for the queries that it repeats, is
+// the run's own.
 struct KnnSearch {
   // allocates; scale from knn_split_scale over every coordinate
   int open(int64_t M, int N, const float *Q, int64_t nq, bool same, int k, float scale, hipStream_t s);
   // the answers for the candidates X [M][N]; self_mode: 0 = none, 1 = query q
   // excludes candidate q, 2 = query q excludes self[q].  Synchronises the
-  // stream.  Against few candidates (few) it may be called again with others:
-  // the queries, which must not have changed, are prepared once.
+  // stream.  It may be called again with other candidates, as many and at the
+  // same scale, and the same queries: against few candidates (few), where the
+  // queries' images do not depend on the candidates, those are prepared once.
   int run(const float *X, int self_mode, const int32_t *self, int32_t *idx, float *dist);
 
   Scratch S;
@@ -69,10 +77,10 @@ struct KnnSearch {
   bool same = false, few = false, queries_ready = false;
   float scale = 1.f;
   hipStream_t s = nullptr;
-  _Float16 *ch = nullptr, *cl = nullptr, *qh = nullptr, *ql = nullptr;   // operand images, high and low
+  KnnImage ch, cl, qh, ql;   // operands, high and low; the low ones only with few
   float *norms = nullptr, *start = nullptr, *qnorm = nullptr, *mean = nullptr, *mean_part = nullptr;
   KnnStats *xstats = nullptr, *qstats = nullptr;
-  int32_t *fails = nullptr, *rest = nullptr, *pilot = nullptr;
+  int32_t *fails = nullptr, *rest = nullptr, *pilot = nullptr;   // rest: only with few
   uint64_t *part = nullptr;
   int64_t part_cap = 0;
 };
