@@ -11,11 +11,14 @@
 // Lifetime: every object and call works on one stream, and dev_free_all
 // synchronises it before it takes the buffers, so no kernel or copy still uses
 // one that is handed out again (a stream that cannot be waited for, or that
-// captures: hipFree, as ever).  Not the whole device: hipDeviceSynchronize breaks
+// captures: hipFree, as ever).  The null stream is one of each device: it is the
+// buffers' device whose stream is waited for, whichever is current.  Not the
+// whole device: hipDeviceSynchronize breaks
 // the graph captures of other threads.  What waits is bounded (kMaxIdle),
 // buffers above kMaxBlock never wait, a buffer that was not asked for again
 // during kMaxAge releases is given back to the device, and when an allocation
 // fails all of them are before it is tried again.
+#include <algorithm>
 #include <mutex>
 #include <new>
 #include <unordered_map>
@@ -102,12 +105,30 @@ hipError_t get(void **p, size_t bytes) {
   return e;
 }
 
+// waits for the stream (of that device, if it is the null stream); false when it cannot be waited for
+bool wait_for(hipStream_t stream, int device, int current) {
+  if (device != current && hipSetDevice(device) != hipSuccess) return false;
+  hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+  const bool done = hipStreamIsCapturing(stream, &capturing) == hipSuccess &&
+                    capturing == hipStreamCaptureStatusNone && hipStreamSynchronize(stream) == hipSuccess;
+  return (device == current || hipSetDevice(current) == hipSuccess) && done;
+}
+
 void put(void *const *bufs, size_t n, hipStream_t stream) {
   Pool &P = pool();
   std::vector<Block> back;
-  hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-  const bool idle = hipStreamIsCapturing(stream, &capturing) == hipSuccess &&
-                    capturing == hipStreamCaptureStatusNone && hipStreamSynchronize(stream) == hipSuccess;
+  std::vector<int> devices;   // of the buffers: one, as a rule
+  {
+    std::lock_guard<std::mutex> lk(P.mu);
+    for (size_t i = 0; i < n; ++i) {
+      const auto it = bufs[i] ? P.used.find(bufs[i]) : P.used.end();
+      if (it != P.used.end() && std::find(devices.begin(), devices.end(), it->second.device) == devices.end())
+        devices.push_back(it->second.device);
+    }
+  }
+  int current = 0;
+  bool idle = hipGetDevice(&current) == hipSuccess;
+  for (const int d : devices) idle = idle && wait_for(stream, d, current);
   if (!idle) (void)hipGetLastError();
   {
     std::lock_guard<std::mutex> lk(P.mu);

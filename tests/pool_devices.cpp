@@ -1,0 +1,96 @@
+// Host check of the device buffer pool (pool.hip) against a stand-in for the
+// HIP runtime with two devices: a buffer that work still uses must not be
+// handed out.  Built and run by test_pool_devices.py.
+#include <cstdio>
+#include <cstdlib>
+#include <map>
+#include <set>
+
+#include "ivhd_internal.h"
+
+namespace {
+int g_device = 0;
+bool g_capturing = false;
+std::map<void *, int> g_of;                              // allocation -> device
+std::map<std::pair<int, hipStream_t>, std::set<void *>> g_busy;   // (device, stream): what queued work uses
+
+void check(bool ok, const char *what) {
+  if (ok) return;
+  std::printf("FAILED: %s\n", what);
+  std::exit(1);
+}
+bool busy(void *p) {
+  for (const auto &q : g_busy)
+    if (q.second.count(p)) return true;
+  return false;
+}
+hipStream_t stream_no(int k) { return reinterpret_cast<hipStream_t>(static_cast<uintptr_t>(k)); }
+}  // namespace
+
+extern "C" {
+hipError_t hipGetDevice(int *d) {
+  *d = g_device;
+  return hipSuccess;
+}
+hipError_t hipSetDevice(int d) {
+  if (d < 0 || d > 1) return hipErrorInvalidDevice;
+  g_device = d;
+  return hipSuccess;
+}
+hipError_t hipMalloc(void **p, size_t bytes) {
+  *p = std::malloc(bytes);
+  g_of[*p] = g_device;
+  return hipSuccess;
+}
+hipError_t hipFree(void *p) {   // waits for the device of the buffer
+  check(g_of.count(p) == 1, "freed what is allocated");
+  for (auto &q : g_busy)
+    if (q.first.first == g_of[p]) q.second.clear();
+  g_of.erase(p);
+  std::free(p);
+  return hipSuccess;
+}
+hipError_t hipStreamSynchronize(hipStream_t s) {
+  for (auto &q : g_busy)
+    if (q.first.second == s && (s || q.first.first == g_device)) q.second.clear();
+  return hipSuccess;
+}
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *st) {
+  *st = g_capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+  return hipSuccess;
+}
+hipError_t hipGetLastError() { return hipSuccess; }
+}
+
+int main() {
+  // the buffers' device and the one current at the release, on the null and a named stream
+  for (int of = 0; of < 2; ++of)
+    for (int at = 0; at < 2; ++at)
+      for (int st = 0; st < 2; ++st) {
+        const hipStream_t s = stream_no(16 * st);
+        (void)hipSetDevice(of);
+        void *b[3] = {};
+        check(ivhd::pool_get(&b[0], 1000) == hipSuccess && ivhd::pool_get(&b[2], 5000) == hipSuccess, "allocates");
+        check(!busy(b[0]) && !busy(b[2]), "an unused buffer is handed out");
+        g_busy[{of, s}] = {b[0], b[2]};
+        (void)hipSetDevice(at);
+        ivhd::dev_free_all(b, 3, s);
+        check(g_device == at, "the current device stays");
+        for (int dev = 0; dev < 2; ++dev) {
+          (void)hipSetDevice(dev);
+          void *p = nullptr;
+          check(ivhd::pool_get(&p, 1000) == hipSuccess && g_of[p] == dev, "a buffer of the current device");
+          check(!busy(p), "no buffer that queued work still uses");
+          ivhd::dev_free(p, s);
+        }
+      }
+  // a capturing stream: given back to the device, not kept
+  (void)hipSetDevice(0);
+  void *p = nullptr;
+  check(ivhd::pool_get(&p, 77777) == hipSuccess, "allocates");
+  g_capturing = true;
+  ivhd::dev_free(p, stream_no(16));
+  check(g_of.count(p) == 0, "freed while a capture is on");
+  std::printf("ok\n");
+  return 0;
+}
