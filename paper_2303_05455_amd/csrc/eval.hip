@@ -44,6 +44,7 @@
 
 #include "ivhd_internal.h"
 #include "knn_internal.h"
+#include "knn_rank.h"
 
 namespace ivhd {
 namespace {
@@ -186,11 +187,6 @@ __device__ __forceinline__ void tile_distances(const float *__restrict__ Z, int 
       for (int c = 0; c < kCand; ++c) z[c] = zn[c];
     }
   }
-}
-
-__device__ __forceinline__ void wave_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
 }
 
 // One wavefront keeps the smallest pairs of a buffer of n <= 64 E: at least

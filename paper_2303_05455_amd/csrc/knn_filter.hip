@@ -701,9 +701,12 @@ __global__ void __launch_bounds__(256) knn_finish_kernel(FinishArgs A) {
       ri += (n > in ? 1 : 0) + (m > in ? 1 : 0);
     }
     grp[p] = 0;
+    wave_fence();   // lanes write each other's places
     if (mine && rm < KP) grp[rm] = mine;
     if (in && ri < KP) grp[ri] = in;
+    wave_fence();
     mine = grp[p];
+    wave_fence();
   }
   const bool have = mine != 0;
   const int64_t orig = on ? (A.map ? (int64_t)A.map[q] : q) : 0;

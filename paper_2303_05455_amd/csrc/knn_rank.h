@@ -6,6 +6,12 @@
 
 namespace ivhd {
 
+// orders the LDS accesses of a wavefront's lanes on both sides of it
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 __device__ __forceinline__ bool pair_less(float a, int32_t ia, float b, int32_t ib) {
   return a < b || (a == b && ia < ib);
 }
