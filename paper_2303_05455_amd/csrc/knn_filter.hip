@@ -53,6 +53,8 @@
 // what a hit costs (about 0.2 us of its wave) is what is left above the
 // products.
 #include <cfloat>
+#include <cmath>
+#include <cstring>
 
 #include "knn_internal.h"
 #include "knn_rank.h"
@@ -101,53 +103,68 @@ __device__ __forceinline__ float key_value(uint64_t k) {
 
 // ---- operands ---------------------------------------------------------------
 
-// Column means in two fixed-order steps: partial sums over row ranges, then
-// their sum.  Centred data have smaller norms, hence smaller error bounds.
-constexpr int kMeanParts = 256;
+// Centre and spread of a set of rows, from kSampleRows of them spread over it:
+// mean[n] the median of the sample's feature n, spread the largest over the
+// features of a quantile of |x - mean| (float bits; zero before use): the third
+// quartile, or what only three of the sample exceed where that is 0.  Centred data
+// have smaller norms, hence smaller error bounds; median and quantile, since rows
+// far off (a missing-value code) would pull a mean away from all the others and
+// push those below the FP16 grid; and a value of the data as the centre, so that
+// differences from it stay on the data's own grid.
+constexpr int kSampleRows = 255;
 
-__global__ void __launch_bounds__(256) knn_mean_parts_kernel(const float *__restrict__ X, int64_t M, int N,
-                                                             float *__restrict__ part) {
-  const int64_t per = (M + kMeanParts - 1) / kMeanParts, r0 = blockIdx.x * per, r1 = r0 + per < M ? r0 + per : M;
-  __shared__ float red[4][64];
-  const int c = threadIdx.x & 63, w = threadIdx.x >> 6;
-  for (int n0 = 0; n0 < N; n0 += 64) {
-    float t = 0.f;
-    if (n0 + c < N) {
-#pragma unroll 8
-      for (int64_t r = r0 + w; r < r1; r += 4) t += X[r * N + n0 + c];
-    }
-    red[w][c] = t;
-    __syncthreads();
-    if (w == 0 && n0 + c < N)
-      part[(int64_t)blockIdx.x * N + n0 + c] = ((red[0][c] + red[1][c]) + red[2][c]) + red[3][c];
-    __syncthreads();
-  }
+__global__ void __launch_bounds__(256) knn_sample_kernel(const float *__restrict__ X, int64_t M, int N,
+                                                         float *__restrict__ mean, uint32_t *__restrict__ spread) {
+  __shared__ float v[256], quartile, most;
+  const int n = blockIdx.x, p = threadIdx.x;
+  const int rows = M < kSampleRows ? (int)M : kSampleRows;
+  auto rank_of = [&](float x) {   // place of the thread's value among the sample's, in v
+    int rank = 0;
+    for (int e = 0; e < rows; ++e) rank += v[e] < x || (v[e] == x && e < p) ? 1 : 0;
+    return rank;
+  };
+  const float x = p < rows ? X[(int64_t)p * M / rows * N + n] : 0.f;
+  v[p] = x;
+  __syncthreads();
+  if (p < rows && rank_of(x) == rows / 2) mean[n] = most = x;
+  __syncthreads();
+  const float far = fabsf(x - most);
+  __syncthreads();
+  v[p] = far;
+  __syncthreads();
+  const int rank = p < rows ? rank_of(far) : -1;
+  if (rank == rows * 3 / 4) quartile = far;
+  if (rank == (rows > 4 ? rows - 4 : rows - 1)) most = far;
+  __syncthreads();
+  const float q = quartile > 0.f ? quartile : most;
+  if (p == 0 && q > 0.f) atomicMax(spread, __float_as_uint(q));   // non-negative floats compare as integers
 }
 
-__global__ void __launch_bounds__(256) knn_mean_kernel(const float *__restrict__ part, int64_t M, int N,
-                                                       float *__restrict__ mean) {
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= N) return;
-  float t = 0.f;
-#pragma unroll 8
-  for (int p = 0; p < kMeanParts; ++p) t += part[(int64_t)p * N + c];
-  mean[c] = t / (float)M;
-}
+// Class of a row by its squared norm: a factor of two to a class
+__device__ __forceinline__ int norm_class(float norm2) { return (int)(__float_as_uint(norm2) >> 23); }
 
-// Stage images of scale * (X - mean) (mean NULL: 0; rows taken through `map` when given),
-// the rows' squared norms, start values and the largest norm and residual.
+__device__ __forceinline__ float clamp_half(float t) { return fminf(fmaxf(t, -65504.f), 65504.f); }
+
+// Stage images of scale * (X - mean) (rows taken through `map` when given), and
+// in those units the rows' squared norms and rounding residuals, start values and
+// the statistics of the set.  A coordinate beyond the FP16 range is held at its
+// end: all of it that is missing counts as the row's residual.
 // 16 lanes per row, 8 features per lane and step; a block walks rows 16 at a
-// time so that the two maxima cost a block one atomic each.
+// time so that the maxima cost a block one atomic each.
 __global__ void __launch_bounds__(256) knn_split_kernel(const float *__restrict__ X, int64_t M, int N, int nk,
                                                         const int32_t *__restrict__ map,
                                                         const float *__restrict__ mean, float scale,
                                                         _Float16 *__restrict__ hi, _Float16 *__restrict__ lo,
-                                                        float *__restrict__ norms, float *__restrict__ start,
-                                                        KnnStats *__restrict__ stats, bool vec) {
-  __shared__ float smax[2][4];
+                                                        float *__restrict__ norms, float *__restrict__ res,
+                                                        float *__restrict__ start, KnnStats *__restrict__ stats,
+                                                        bool vec) {
+  __shared__ float smax[4];
+  __shared__ uint32_t cls[kNormClasses];
   const int g = threadIdx.x & 15;
   const int64_t rows = (M + FT - 1) / FT * FT;
-  float top_s = 0.f, top_e = 0.f;
+  float top_s = 0.f;
+  if (stats) cls[threadIdx.x] = 0;
+  __syncthreads();
   for (int64_t row = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4); row < rows; row += (int64_t)gridDim.x * 16) {
     const bool real = row < M;
     const int64_t src = real ? (map ? (int64_t)map[row] : row) : 0;
@@ -158,13 +175,9 @@ __global__ void __launch_bounds__(256) knn_split_kernel(const float *__restrict_
     for (int c = g; c < nk * 4; c += 16) {
       float v[8];
       if (vec && 8 * c + 8 <= N) {
-        floatx4 m0 = {}, m1 = {};
-        if (mean) {
-          m0 = *reinterpret_cast<const floatx4 *>(mean + 8 * c);
-          m1 = *reinterpret_cast<const floatx4 *>(mean + 8 * c + 4);
-        }
-        const floatx4 u = *reinterpret_cast<const floatx4 *>(x + 8 * c) - m0;
-        const floatx4 w = *reinterpret_cast<const floatx4 *>(x + 8 * c + 4) - m1;
+        const floatx4 u = *reinterpret_cast<const floatx4 *>(x + 8 * c) - *reinterpret_cast<const floatx4 *>(mean + 8 * c);
+        const floatx4 w =
+            *reinterpret_cast<const floatx4 *>(x + 8 * c + 4) - *reinterpret_cast<const floatx4 *>(mean + 8 * c + 4);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           v[j] = real ? u[j] : 0.f;
@@ -172,17 +185,17 @@ __global__ void __launch_bounds__(256) knn_split_kernel(const float *__restrict_
         }
       } else {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = real && 8 * c + j < N ? x[8 * c + j] - (mean ? mean[8 * c + j] : 0.f) : 0.f;
+        for (int j = 0; j < 8; ++j) v[j] = real && 8 * c + j < N ? x[8 * c + j] - mean[8 * c + j] : 0.f;
       }
       halfx8 h, l;
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
-        s += v[j] * v[j];
         const float t = v[j] * scale;
-        h[j] = (_Float16)t;
-        const float d = t - (float)h[j];
-        e += d * d;
-        l[j] = (_Float16)d;
+        s += t * t;
+        h[j] = (_Float16)clamp_half(t);
+        const float d = t - (float)h[j], dc = clamp_half(d);
+        e += d == dc ? d * d : INFINITY;   // (what the low part cannot hold either)
+        l[j] = (_Float16)dc;
       }
       const int64_t at = base + (int64_t)(c >> 2) * kTileHalves + tile_slot(r, c & 3) * 8;
       if (hi) *reinterpret_cast<halfx8 *>(hi + at) = h;
@@ -195,27 +208,34 @@ __global__ void __launch_bounds__(256) knn_split_kernel(const float *__restrict_
     }
     if (g == 0) {
       if (norms && real) norms[row] = s;
-      if (start) start[row] = real ? -0.5f * s * scale * scale : kPadStart;
+      if (res && real) res[row] = e;
+      if (start) start[row] = real ? -0.5f * s : kPadStart;
+      if (stats && e > 0.f) atomicMax(&cls[norm_class(s)], __float_as_uint(e));
     }
     top_s = fmaxf(top_s, s);
-    top_e = fmaxf(top_e, e);
   }
   if (!stats) return;
 #pragma unroll
-  for (int o = 32; o >= 16; o >>= 1) {
-    top_s = fmaxf(top_s, __shfl_xor(top_s, o, 64));
-    top_e = fmaxf(top_e, __shfl_xor(top_e, o, 64));
-  }
-  if ((threadIdx.x & 63) == 0) {
-    smax[0][threadIdx.x >> 6] = top_s;
-    smax[1][threadIdx.x >> 6] = top_e;
-  }
+  for (int o = 32; o >= 16; o >>= 1) top_s = fmaxf(top_s, __shfl_xor(top_s, o, 64));
+  if ((threadIdx.x & 63) == 0) smax[threadIdx.x >> 6] = top_s;
   __syncthreads();
-  if (threadIdx.x < 2) {   // non-negative floats compare as integers
-    const float *m = smax[threadIdx.x];
-    const float t = fmaxf(fmaxf(m[0], m[1]), fmaxf(m[2], m[3]));
-    atomicMax(threadIdx.x == 0 ? &stats->norm2 : &stats->res2, __float_as_uint(t));
+  if (threadIdx.x == 0)   // non-negative floats compare as integers
+    atomicMax(&stats->norm2, __float_as_uint(fmaxf(fmaxf(smax[0], smax[1]), fmaxf(smax[2], smax[3]))));
+  if (cls[threadIdx.x]) atomicMax(&stats->res2[threadIdx.x], cls[threadIdx.x]);
+}
+
+// res2[c] <- the largest of classes 0..c
+__global__ void __launch_bounds__(kNormClasses) knn_classes_kernel(KnnStats *stats) {
+  __shared__ uint32_t m[kNormClasses];
+  const int t = threadIdx.x;
+  m[t] = stats->res2[t];
+  for (int o = 1; o < kNormClasses; o *= 2) {
+    __syncthreads();
+    const uint32_t w = t >= o ? m[t - o] : 0u;
+    __syncthreads();
+    m[t] = w > m[t] ? w : m[t];
   }
+  stats->res2[t] = m[t];
 }
 
 // ---- the filter -------------------------------------------------------------
@@ -224,7 +244,7 @@ struct FilterArgs {
   const _Float16 *Qh, *Ql, *Ch, *Cl;   // stage images; the lo ones only with nseg = 3
   const float *start;                  // [tiles * FT]
   int nk, nseg;                        // stages per segment, segments
-  int64_t nq, M;
+  int64_t nq;
   int64_t qb0, qb_step;                // query tile of item row r: qb0 + r qb_step
   int64_t nqb;                         // query tiles of this launch
   int splits;                          // candidate ranges
@@ -641,41 +661,47 @@ __global__ void __launch_bounds__(kFilterThreads, kFilterWaves / 4) knn_filter_k
 struct FinishArgs {
   const float *X, *Q;
   int N, nk, k, splits;
-  int64_t nq;                    // queries of the call (compact ids)
+  int64_t nq, M;                 // queries of the call (compact ids), candidates
   int64_t qb0, qb_step, n_launch;   // launch query t is query (qb0 + t / FT qb_step) FT + t % FT
   const int32_t *map;            // original row of query q (NULL: q)
+  int self_mode;                 // 0 none, 1 the query's own row, 2 self[]
+  const int32_t *self;
   const uint64_t *part;
   int32_t *out_idx;
   float *out_dist;
-  // certificate (fails == NULL: none)
-  const float *qnorm;            // [nq]
-  const KnnStats *xs, *qs;       // largest norm and residual of candidates and queries
+  // certificate; norms and residuals in scaled units, centred
+  const float *qnorm, *qres;     // [rows of Q] squared norm, squared residual
+  const KnnStats *xs;            // of the candidates, after knn_classes_kernel
   float scale;
   int nseg;
   int32_t *fails;                // [0] count, then query ids
   int32_t *pilot;                // [3]: answers that lists of 8, 16, 32 would not certify (NULL: no pilot)
 };
 
-// Bound on the error of a (scaled units) of a query of squared norm n2 (scaled)
-// against any candidate, in FP64 and rounded up by a factor well above its error
-__device__ __forceinline__ double value_error(const FinishArgs &A, double n2, double nerr, double &xm) {
-  const double sc = A.scale, up = 1.0 + 1e-6, u23 = 1.1920928955078125e-7;
-  const double nq = sqrt(n2 * (1 + nerr)) * up;
-  xm = sqrt((double)__uint_as_float(A.xs->norm2) * (1 + nerr)) * sc * up;
-  const double rx = sqrt((double)__uint_as_float(A.xs->res2) * (1 + nerr)) * up;
-  const double rq = sqrt((double)__uint_as_float(A.qs->res2) * (1 + nerr)) * up;
+// The rows' own figures that bound the error of a query's values, in FP64 and
+// rounded up by a factor well above its error
+struct QueryBound {
+  double nq, rq, nerr;   // norm, residual, relative error of an FP32 sum of N squares
+};
+constexpr double kUp = 1.0 + 1e-6, kU23 = 1.1920928955078125e-7;
+
+// Bound on the error of a against any candidate of norm up to x (infinite when
+// the rows' figures give none)
+__device__ __forceinline__ double value_error(const FinishArgs &A, const QueryBound &B, double x) {
+  const float limit = (float)(x * x * (1 + B.nerr) * kUp);
+  const double rx = sqrt((double)__uint_as_float(A.xs->res2[norm_class(limit) & (kNormClasses - 1)]) * (1 + B.nerr)) * kUp;
   // what the segments leave out of q.c: with hi + lo, the rounding of lo
   // (2^-11 of the residual, or 2^-25 per coordinate where lo is subnormal)
   // and the product lo.lo
   const double sub = 3e-8 * sqrt((double)A.N);
-  const double rest = A.nseg == 1 ? nq * rx + rq * (xm + rx)
-                                  : (nq + rq) * (rx / 2048 + sub) + (xm + rx) * (rq / 2048 + sub) + rx * rq;
-  // roundings of the accumulation: one segment takes the worst case, all of
-  // them one way; with three that would be larger than all the rest, and
-  // four times their root mean square is taken instead
-  const double n = (double)A.nseg * A.nk * FK, steps = A.nseg == 1 ? n + 16 : 4 * sqrt(n) + 16;
-  return up * rest + steps * u23 * (0.5 * xm * xm + (nq + rq) * (xm + rx))                         // accumulation
-         + 0.5 * nerr * xm * xm;                                                                  // the start value
+  const double rest = A.nseg == 1 ? B.nq * rx + B.rq * (x + rx)
+                                  : (B.nq + B.rq) * (rx / 2048 + sub) + (x + rx) * (B.rq / 2048 + sub) + rx * B.rq;
+  // roundings of the accumulation, all of them one way: one to a product, of
+  // no more than 2^-23 of the largest partial sum
+  const double steps = (double)A.nseg * A.nk * FK + 16;
+  const double err = kUp * rest + steps * kU23 * (0.5 * x * x + (B.nq + 2 * B.rq) * (x + 2 * rx))   // accumulation
+                     + 0.5 * B.nerr * x * x;                                                       // the start value
+  return err == err ? err : INFINITY;
 }
 
 // KP lanes per query: merge the ranges' lists, exact FP32 distances of the
@@ -710,10 +736,12 @@ __global__ void __launch_bounds__(256) knn_finish_kernel(FinishArgs A) {
   }
   const bool have = mine != 0;
   const int64_t orig = on ? (A.map ? (int64_t)A.map[q] : q) : 0;
-  const double sc2 = (double)A.scale * A.scale, u23 = 1.1920928955078125e-7;
-  const double nerr = (A.N / 16 + 16) * u23;   // relative error of an FP32 squared norm (16 lanes, then a tree)
-  const double n2 = on ? (double)A.qnorm[orig] * sc2 : 0.0;
-  double xm = 0.0, err = 0.0;
+  const double sc2 = (double)A.scale * A.scale;
+  QueryBound B;
+  B.nerr = (A.N / 16 + 16) * kU23;   // 16 lanes, then a tree
+  const double n2 = on ? (double)A.qnorm[orig] : 0.0;
+  B.nq = sqrt(n2 * (1 + B.nerr)) * kUp;
+  B.rq = on ? sqrt((double)A.qres[orig] * (1 + B.nerr)) * kUp : 0.0;
   int rank = 0, found = 0;
   uint64_t last = ~0ull, kth = 0;
 #pragma unroll 4
@@ -724,20 +752,32 @@ __global__ void __launch_bounds__(256) knn_finish_kernel(FinishArgs A) {
     last = m < last ? m : last;
   }
   uint64_t nth[3] = {0, 0, 0};   // the 8th, 16th and 32nd best
+  for (int j = 0; j < KP; ++j) {
+    const uint64_t m = __shfl(mine, g0 + j, 64);
+    const int rj = __shfl(rank, g0 + j, 64);
+    kth = rj == A.k - 1 && m ? m : kth;
+#pragma unroll
+    for (int l = 0; l < 3; ++l) nth[l] = rj == (8 << l) - 1 ? m : nth[l];
+  }
+  // A candidate whose norm exceeds the query's by more than the k-th distance is
+  // farther than that, whatever its value: only norms up to `reach` matter, and a
+  // row far from all others spoils no bound but its own.  The k best values bound
+  // the k-th distance from above with the error that goes with the reach so far.
   bool near = have;   // may be among the k nearest
-  if (A.fails) {
-    err = value_error(A, n2, nerr, xm);
+  double reach = sqrt((double)__uint_as_float(A.xs->norm2) * (1 + B.nerr)) * kUp;
+  if (kth != 0) {
+    double err = value_error(A, B, reach);
+    for (int it = 0; it < 4; ++it) {
+      const double far2 = n2 * (1 + B.nerr) - 2.0 * ((double)key_value(kth) - err);
+      const double r = (B.nq + sqrt(far2 > 0 ? far2 : 0.0)) * kUp;
+      if (!(r < 0.75 * reach)) break;
+      reach = r;
+      err = value_error(A, B, reach);
+    }
     // a value more than two errors below the k-th best cannot be (the slack
     // covers the rounding of the distances themselves)
-    for (int j = 0; j < KP; ++j) {
-      const uint64_t m = __shfl(mine, g0 + j, 64);
-      const int rj = __shfl(rank, g0 + j, 64);
-      kth = rj == A.k - 1 && m ? m : kth;
-#pragma unroll
-      for (int l = 0; l < 3; ++l) nth[l] = rj == (8 << l) - 1 ? m : nth[l];
-    }
-    const double slack = (A.N + 16) * u23 * (n2 + xm * xm);
-    near = have && (kth == 0 || (double)key_value(mine) >= (double)key_value(kth) - 2.0 * err - slack);
+    const double slack = (A.N + 16) * kU23 * (n2 + reach * reach);
+    near = have && !((double)key_value(mine) < (double)key_value(kth) - 2.0 * err - slack);
   }
   float d = FLT_MAX;
   if (near)
@@ -754,22 +794,30 @@ __global__ void __launch_bounds__(256) knn_finish_kernel(FinishArgs A) {
     A.out_idx[orig * A.k + rank] = near ? id : -1;
     if (A.out_dist) A.out_dist[orig * A.k + rank] = d;
   }
-  // The least squared distance of a candidate that is not among the first L of
-  // the list, between the centred rows and (their rounding: 2^-24 of each
-  // row) between the given ones, must lie above the k-th distance.
-  if (A.fails && on && rank == A.k - 1) {
-    const double top = (double)d * sc2 * (1 + (A.N + 16) * u23);
+  if (on && rank == A.k - 1) {
+    // The least squared distance of a candidate that is not among the first L of
+    // the list, between the centred rows and (their rounding: 2^-24 of each
+    // row) between the given ones, must lie above the k-th distance (FP32, and
+    // subnormal squares).
+    const double top = ((double)d * (1 + (A.N + 16) * kU23) + A.N * 1.5e-45) * sc2;
+    const double r = (B.nq + sqrt(top)) * kUp;
+    const double x = r < reach ? r : reach, err = value_error(A, B, x);
     auto certified = [&](uint64_t last) {
-      const double least = n2 * (1 - nerr) - 2.0 * ((double)key_value(last) + err);
-      const double moved = sqrt(least > 0 ? least : 0.0) - 0.5 * u23 * (sqrt(n2 * (1 + nerr)) + xm);
+      const double least = n2 * (1 - B.nerr) - 2.0 * ((double)key_value(last) + err);
+      const double moved = sqrt(least > 0 ? least : 0.0) - 0.5 * kU23 * (B.nq + x);
       return top < (moved > 0 ? moved * moved : 0.0) * (1 - 1e-12);
+    };
+    // a list that is not full is the answer if it holds all there are
+    auto complete = [&]() {
+      const int64_t own = A.self_mode == 1 ? orig : (A.self_mode == 2 ? (int64_t)A.self[orig] : -1);
+      return found >= A.M - (own >= 0 && own < A.M ? 1 : 0);
     };
     if (A.pilot) {
       for (int l = 0; l < 3; ++l) {
         const int len = 8 << l;
-        if (len <= KP && found >= len && (len < A.k || !certified(nth[l]))) atomicAdd(&A.pilot[l], 1);
+        if (len <= KP && (found < len ? !complete() : len < A.k || !certified(nth[l]))) atomicAdd(&A.pilot[l], 1);
       }
-    } else if (found == KP && !certified(last)) {
+    } else if (found < KP ? !complete() : !certified(last)) {
       A.fails[1 + atomicAdd(&A.fails[0], 1)] = (int32_t)orig;
     }
   }
@@ -901,15 +949,28 @@ int64_t knn_image_halves(int64_t M, int N) { return (M + FT - 1) / FT * FT * (in
 
 // (an image without room for the rows is refused)
 hipError_t launch_knn_split(const float *X, int64_t M, int N, const int32_t *map, const float *mean, float scale,
-                            const KnnImage &hi, const KnnImage &lo, float *norms, float *start, KnnStats *stats,
-                            hipStream_t s) {
+                            const KnnImage &hi, const KnnImage &lo, float *norms, float *res, float *start,
+                            KnnStats *stats, hipStream_t s) {
   const int64_t need = knn_image_halves(M, N);
   if ((hi.p && need > hi.halves) || (lo.p && need > lo.halves)) return hipErrorInvalidValue;
   const bool vec = N % 4 == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0;
   const int64_t groups = (M + FT - 1) / FT * (FT / 16);
-  knn_split_kernel<<<(unsigned)(groups < 4096 ? groups : 4096), 256, 0, s>>>(X, M, N, (N + FK - 1) / FK, map, mean,
-                                                                             scale, hi.p, lo.p, norms, start, stats, vec);
+  knn_split_kernel<<<(unsigned)(groups < 4096 ? groups : 4096), 256, 0, s>>>(
+      X, M, N, (N + FK - 1) / FK, map, mean, scale, hi.p, lo.p, norms, res, start, stats, vec);
   return hipGetLastError();
+}
+
+// Power of two for a sample of that spread: it below 2^8, so that values 256 times
+// as large are in range and values 2^-22 of it on the normal FP16 grid; |s| <= 126, so that the scale and its
+// inverse are normal floats.  spread 0: any finite magnitude in range.
+float sample_scale(float spread, float absmax) {
+  if (!(absmax > 0.f)) return 1.f;
+  const bool some = spread > 0.f && std::isfinite(spread);
+  int e;
+  (void)frexpf(some ? spread : absmax, &e);   // m 2^e, 0.5 <= m < 1
+  int sh = (some ? 8 : 14) - e;
+  sh = sh > 126 ? 126 : (sh < -126 ? -126 : sh);
+  return ldexpf(1.f, sh);
 }
 
 // Segments and list length: the pilot runs kPilotTiles query tiles spread over
@@ -935,14 +996,14 @@ constexpr int64_t kFewTiles = 16;
 
 }  // namespace
 
-int KnnSearch::open(int64_t M_, int N_, const float *Q_, int64_t nq_, bool same_, int k_, float scale_, hipStream_t s_) {
+int KnnSearch::open(int64_t M_, int N_, const float *Q_, int64_t nq_, const float *sample, int64_t sample_rows,
+                    bool same_, int k_, float absmax, hipStream_t s_) {
   M = M_;
   N = N_;
   Q = Q_;
   nq = nq_;
   same = same_;
   k = k_;
-  scale = scale_;
   s = s_;
   S.stream = s_;
   few = (M + FT - 1) / FT < kFewTiles;
@@ -952,22 +1013,22 @@ int KnnSearch::open(int64_t M_, int N_, const float *Q_, int64_t nq_, bool same_
     V.add(&im->p, halves);
     im->halves = halves;
   };
+  uint32_t *spread = nullptr;
   image(&ch, nx);
-  V.add(&norms, M);
   V.add(&start, tiles * FT);
   V.add(&xstats, 1);
-  V.add(&qstats, 1);
   V.add(&fails, nq + 1);
   V.add(&pilot, 3);
   V.add(&mean, N);
-  V.add(&mean_part, (int64_t)kMeanParts * N);
+  V.add(&spread, 1);
+  V.add(&qnorm, nq);
+  V.add(&qres, nq);
   if (few) {
     image(&cl, nx);
     V.add(&rest, nq + 1);
   }
   if (!same) {
     image(&qh, nqi);
-    V.add(&qnorm, nq);
     if (few) image(&ql, nqi);
   }
   const int rc = V.get(S, "operands of the search");
@@ -975,9 +1036,16 @@ int KnnSearch::open(int64_t M_, int N_, const float *Q_, int64_t nq_, bool same_
   if (same) {
     qh = ch;
     ql = cl;
-    qnorm = norms;
-    qstats = xstats;
   }
+  uint32_t bits = 0;
+  HIPCHK(launch_fill_i32((int32_t *)spread, 1, 0, s));
+  knn_sample_kernel<<<(unsigned)N, 256, 0, s>>>(sample, sample_rows, N, mean, spread);
+  HIPCHK(hipGetLastError());
+  HIPCHK(hipMemcpyAsync(&bits, spread, sizeof bits, hipMemcpyDeviceToHost, s));
+  HIPCHK(hipStreamSynchronize(s));
+  float spread_h;
+  std::memcpy(&spread_h, &bits, sizeof bits);
+  scale = sample_scale(spread_h, absmax);
   return IVHD_OK;
 }
 
@@ -986,18 +1054,14 @@ int KnnSearch::run(const float *X, int self_mode, const int32_t *self, int32_t *
   const int64_t tiles = (M + FT - 1) / FT, nqb = (nq + FT - 1) / FT;
   int kp = list_length(k), rc;
   bool three = few;   // few candidates: three segments from the start, both halves made at once
-  float *centre = few ? nullptr : mean;
-  if (!few) {
-    knn_mean_parts_kernel<<<kMeanParts, 256, 0, s>>>(X, M, N, mean_part);
-    knn_mean_kernel<<<grid_for(N, 256), 256, 0, s>>>(mean_part, M, N, mean);
-    HIPCHK(hipGetLastError());
-  }
   HIPCHK(launch_fill_i32((int32_t *)xstats, sizeof(KnnStats) / 4, 0, s));
-  HIPCHK(launch_knn_split(X, M, N, nullptr, centre, scale, ch, cl, norms, start, xstats, s));
+  HIPCHK(launch_knn_split(X, M, N, nullptr, mean, scale, ch, cl, same ? qnorm : nullptr, same ? qres : nullptr, start,
+                          xstats, s));
+  knn_classes_kernel<<<1, kNormClasses, 0, s>>>(xstats);
+  HIPCHK(hipGetLastError());
   if (!same && !queries_ready) {
-    HIPCHK(launch_fill_i32((int32_t *)qstats, sizeof(KnnStats) / 4, 0, s));
-    HIPCHK(launch_knn_split(Q, nq, N, nullptr, centre, scale, qh, ql, qnorm, nullptr, qstats, s));
-    queries_ready = few;   // their images do not depend on the candidates then
+    HIPCHK(launch_knn_split(Q, nq, N, nullptr, mean, scale, qh, ql, qnorm, qres, nullptr, nullptr, s));
+    queries_ready = true;   // their images do not depend on the candidates
   }
 
   FilterArgs f{};
@@ -1008,7 +1072,6 @@ int KnnSearch::run(const float *X, int self_mode, const int32_t *self, int32_t *
   f.nk = nk;
   f.nseg = 1;
   f.nq = nq;
-  f.M = M;
   f.tiles = tiles;
   f.self_mode = self_mode;
   f.self = self;
@@ -1019,12 +1082,15 @@ int KnnSearch::run(const float *X, int self_mode, const int32_t *self, int32_t *
   g.nk = nk;
   g.k = k;
   g.nq = nq;
+  g.M = M;
+  g.self_mode = self_mode;
+  g.self = self;
   g.out_idx = idx;
   g.out_dist = dist;
   g.nseg = 1;
   g.qnorm = qnorm;
+  g.qres = qres;
   g.xs = xstats;
-  g.qs = qstats;
   g.scale = scale;
 
   auto sweep = [&](int64_t qb0, int64_t step, int64_t n) -> int {
@@ -1105,14 +1171,15 @@ int KnnSearch::run(const float *X, int self_mode, const int32_t *self, int32_t *
     };
     if ((rc = R.get(&left, nq + 1, "uncertified queries (three segments)"))) return rc;
     if ((rc = image(&low_c, M, "candidate operands (low)"))) return rc;
-    HIPCHK(launch_knn_split(X, M, N, nullptr, centre, scale, KnnImage{}, low_c, nullptr, nullptr, nullptr, s));
+    HIPCHK(launch_knn_split(X, M, N, nullptr, mean, scale, KnnImage{}, low_c, nullptr, nullptr, nullptr, nullptr,
+                            s));
     if (three && same) {
       low_q = low_c;
     } else {
       if ((rc = image(&low_q, n3, "query operands (low)"))) return rc;
       if (!three && (rc = image(&qi, n3, "query operands"))) return rc;
-      HIPCHK(launch_knn_split(Q, n3, N, map, centre, scale, three ? KnnImage{} : qi, low_q, nullptr, nullptr, nullptr,
-                              s));
+      HIPCHK(launch_knn_split(Q, n3, N, map, mean, scale, three ? KnnImage{} : qi, low_q, nullptr, nullptr, nullptr,
+                              nullptr, s));
     }
   }
   kp = list_length(k);

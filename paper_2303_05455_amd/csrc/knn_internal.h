@@ -46,10 +46,12 @@ struct Carve {
   }
 };
 
-// largest squared norm and squared rounding residual of a set of rows, as
-// float bits (non-negative floats compare as integers); zero before use
+// What a set of rows has at most, as float bits (non-negative floats compare as
+// integers; zero before use): the squared norm, and for each class of squared
+// norms (by their exponents) the squared rounding residual of a row up to it
+constexpr int kNormClasses = 256;
 struct KnnStats {
-  uint32_t norm2, res2;
+  uint32_t norm2, res2[kNormClasses];
 };
 // operand images of whole tiles of rows, and the room that was allocated
 struct KnnImage {
@@ -61,13 +63,14 @@ struct KnnImage {
 // replaced; what a run needs beyond that, for the queries that it repeats, is
 // the run's own.
 struct KnnSearch {
-  // allocates; scale from knn_split_scale over every coordinate
-  int open(int64_t M, int N, const float *Q, int64_t nq, bool same, int k, float scale, hipStream_t s);
+  // allocates, and takes the centre and the scale of all operands from a sample
+  // of the rows `sample`; absmax: the largest |coordinate| of all.  Synchronises.
+  int open(int64_t M, int N, const float *Q, int64_t nq, const float *sample, int64_t sample_rows, bool same, int k,
+           float absmax, hipStream_t s);
   // the answers for the candidates X [M][N]; self_mode: 0 = none, 1 = query q
   // excludes candidate q, 2 = query q excludes self[q].  Synchronises the
-  // stream.  It may be called again with other candidates, as many and at the
-  // same scale, and the same queries: against few candidates (few), where the
-  // queries' images do not depend on the candidates, those are prepared once.
+  // stream.  It may be called again with as many other candidates and the same
+  // queries, which are prepared once.
   int run(const float *X, int self_mode, const int32_t *self, int32_t *idx, float *dist);
 
   Scratch S;
@@ -78,8 +81,8 @@ struct KnnSearch {
   float scale = 1.f;
   hipStream_t s = nullptr;
   KnnImage ch, cl, qh, ql;   // operands, high and low; the low ones only with few
-  float *norms = nullptr, *start = nullptr, *qnorm = nullptr, *mean = nullptr, *mean_part = nullptr;
-  KnnStats *xstats = nullptr, *qstats = nullptr;
+  float *start = nullptr, *qnorm = nullptr, *qres = nullptr, *mean = nullptr;
+  KnnStats *xstats = nullptr;
   int32_t *fails = nullptr, *rest = nullptr, *pilot = nullptr;   // rest: only with few
   uint64_t *part = nullptr;
   int64_t part_cap = 0;

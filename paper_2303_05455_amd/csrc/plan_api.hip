@@ -330,7 +330,7 @@ static int knn_common(const float *d_x, int64_t M, int32_t N, const float *d_q, 
   int rc = largest_magnitude(d_x, M * (int64_t)N, same ? nullptr : d_q, Q * (int64_t)N, &amx, s);
   if (rc) return rc;
   KnnSearch K;
-  if ((rc = K.open(M, N, d_q, Q, same, k, knn_split_scale(amx), s))) return rc;
+  if ((rc = K.open(M, N, d_q, Q, d_x, M, same, k, amx, s))) return rc;
   return K.run(d_x, self_mode, d_self, d_idx, d_dist);
 }
 
@@ -394,10 +394,10 @@ int ivhd_ivf_train(const float *d_x, int64_t M, int32_t N, int32_t nlist, int32_
   float amx = 0.f;
   if ((rc = largest_magnitude(d_x, M * (int64_t)N, nullptr, 0, &amx, s))) return rc;
   HIPCHK(launch_init_centroids(d_x, M, N, nlist, d_centroids, s));
-  // the points are prepared once for all assignments; a mean is no larger
-  // than its points, so one scale holds throughout
+  // the points are prepared once for all assignments; means lie among the
+  // points, so their centre and scale hold throughout
   KnnSearch K;
-  if ((rc = K.open(nlist, N, d_x, M, false, 1, knn_split_scale(amx), s))) return rc;
+  if ((rc = K.open(nlist, N, d_x, M, d_x, M, false, 1, amx, s))) return rc;
   for (int it = 0; it <= n_iter; ++it) {
     if ((rc = K.run(d_centroids, 0, nullptr, d_assign, nullptr))) return rc;
     if (it == n_iter) break;
