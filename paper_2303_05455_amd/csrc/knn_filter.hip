@@ -115,24 +115,31 @@ constexpr int kSampleRows = 255;
 
 __global__ void __launch_bounds__(256) knn_sample_kernel(const float *__restrict__ X, int64_t M, int N,
                                                          float *__restrict__ mean, uint32_t *__restrict__ spread) {
-  __shared__ float v[256], quartile, most;
+  __shared__ __attribute__((aligned(16))) float v[256];
+  __shared__ float quartile, most;
   const int n = blockIdx.x, p = threadIdx.x;
   const int rows = M < kSampleRows ? (int)M : kSampleRows;
-  auto rank_of = [&](float x) {   // place of the thread's value among the sample's, in v
+  const bool on = p < rows;
+  auto rank_of = [&](float x) {   // place of the thread's value among the sample's, in v (no other is below infinity)
     int rank = 0;
-    for (int e = 0; e < rows; ++e) rank += v[e] < x || (v[e] == x && e < p) ? 1 : 0;
+#pragma unroll 8
+    for (int e = 0; e < 256; e += 4) {
+      const floatx4 w = *reinterpret_cast<const floatx4 *>(v + e);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) rank += w[u] < x || (w[u] == x && e + u < p) ? 1 : 0;
+    }
     return rank;
   };
-  const float x = p < rows ? X[(int64_t)p * M / rows * N + n] : 0.f;
+  const float x = on ? X[(int64_t)p * M / rows * N + n] : INFINITY;
   v[p] = x;
   __syncthreads();
-  if (p < rows && rank_of(x) == rows / 2) mean[n] = most = x;
+  if (on && rank_of(x) == rows / 2) mean[n] = most = x;
   __syncthreads();
-  const float far = fabsf(x - most);
+  const float far = on ? fabsf(x - most) : INFINITY;
   __syncthreads();
   v[p] = far;
   __syncthreads();
-  const int rank = p < rows ? rank_of(far) : -1;
+  const int rank = on ? rank_of(far) : -1;
   if (rank == rows * 3 / 4) quartile = far;
   if (rank == (rows > 4 ? rows - 4 : rows - 1)) most = far;
   __syncthreads();
@@ -221,29 +228,34 @@ __global__ void __launch_bounds__(256) knn_split_kernel(const float *__restrict_
   __syncthreads();
   if (threadIdx.x == 0)   // non-negative floats compare as integers
     atomicMax(&stats->norm2, __float_as_uint(fmaxf(fmaxf(smax[0], smax[1]), fmaxf(smax[2], smax[3]))));
-  if (cls[threadIdx.x]) atomicMax(&stats->res2[threadIdx.x], cls[threadIdx.x]);
+  if (cls[threadIdx.x]) atomicMax(&stats->res[threadIdx.x], cls[threadIdx.x]);
 }
 
-// res2[c] <- the largest of classes 0..c
-__global__ void __launch_bounds__(kNormClasses) knn_classes_kernel(KnnStats *stats) {
+constexpr double kUp = 1.0 + 1e-6, kU23 = 1.1920928955078125e-7;
+
+// relative error of an FP32 sum of N squares: 16 lanes, then a tree
+__host__ __device__ __forceinline__ double sum_error(int N) { return (N / 16 + 16) * kU23; }
+
+// res[c] <- the largest of classes 0..c, as a residual and not its square, rounded up
+__global__ void __launch_bounds__(kNormClasses) knn_classes_kernel(KnnStats *stats, int N) {
   __shared__ uint32_t m[kNormClasses];
   const int t = threadIdx.x;
-  m[t] = stats->res2[t];
+  m[t] = stats->res[t];
   for (int o = 1; o < kNormClasses; o *= 2) {
     __syncthreads();
     const uint32_t w = t >= o ? m[t - o] : 0u;
     __syncthreads();
     m[t] = w > m[t] ? w : m[t];
   }
-  stats->res2[t] = m[t];
+  stats->res[t] = __float_as_uint((float)(sqrt((double)__uint_as_float(m[t]) * (1 + sum_error(N))) * (kUp * kUp)));
 }
 
 // ---- the filter -------------------------------------------------------------
 
 struct FilterArgs {
-  const _Float16 *Qh, *Ql, *Ch, *Cl;   // stage images; the lo ones only with nseg = 3
+  const _Float16 *Qh, *Ql, *Ch, *Cl;   // stage images; the lo ones only with three segments
   const float *start;                  // [tiles * FT]
-  int nk, nseg;                        // stages per segment, segments
+  int nk;                              // stages per segment
   int64_t nq;
   int64_t qb0, qb_step;                // query tile of item row r: qb0 + r qb_step
   int64_t nqb;                         // query tiles of this launch
@@ -253,6 +265,10 @@ struct FilterArgs {
   int self_mode;                       // 0 none, 1 the query's own row, 2 self[]
   const int32_t *self, *map;           // map: original row of query q (NULL: q)
   uint64_t *part;                      // [launch query][splits][KP]
+  // band: hits of launch query t, those with values from limits[q] up
+  const float *limits;                 // by query
+  int32_t *count, *ids;                // [t], [t][cap]; count goes on past cap
+  int cap;
 };
 
 // block barrier that waits for this wave's LDS operations only: the stage
@@ -335,9 +351,12 @@ __device__ __forceinline__ void cut_lists(uint32_t todo, int q0, uint64_t *lists
   }
 }
 
-template <int KP>
+// KP: length of the lists.  SEG3: three segments, the small ones first, so that
+// only the last one's additions round at the size of the value.  BAND: no lists;
+// every value from the query's limit up is a hit.
+template <int KP, bool SEG3, bool BAND>
 __global__ void __launch_bounds__(kFilterThreads, kFilterWaves / 4) knn_filter_kernel(FilterArgs A) {
-  constexpr int C = kListPlaces, RING = kRing;
+  constexpr int C = kListPlaces, RING = kRing, SEGS = SEG3 ? 3 : 1;
   constexpr int AREA = (C - KP) / kOwners;
   static_assert(C <= 64 && (C - KP) % kOwners == 0 && C % 2 == 0 && KP <= 32, "list shape");
   constexpr int kTrigger = AREA - (AREA > 4 ? 2 : 1);   // an area this full has the lists cut
@@ -372,10 +391,10 @@ __global__ void __launch_bounds__(kFilterThreads, kFilterWaves / 4) knn_filter_k
   const int64_t q0 = qb * FT;
   const int t0 = (int)(split * A.tiles_per_split);
   const int t1 = (int)(t0 + A.tiles_per_split < A.tiles ? t0 + A.tiles_per_split : A.tiles);
-  const int per_tile = A.nk * A.nseg;
+  const int per_tile = A.nk * SEGS;
   // the tiles of this block in order: `lead` of them for the starting
   // thresholds, then all
-  const int lead = t1 > t0 ? min(A.lead, t1 - t0) : 0;
+  const int lead = !BAND && t1 > t0 ? min(A.lead, t1 - t0) : 0;
   const int ntiles = t1 > t0 ? lead + (t1 - t0) : 0;
   const int64_t nstages = (int64_t)ntiles * per_tile;
 
@@ -387,13 +406,16 @@ __global__ void __launch_bounds__(kFilterThreads, kFilterWaves / 4) knn_filter_k
   if (tid < FT) {
     const int64_t q = q0 + tid;
     const int64_t orig = q < A.nq ? (A.map ? (int64_t)A.map[q] : q) : 0;
-    sThr[tid] = q < A.nq ? kNoValue : INFINITY;   // padding queries keep nothing
-    sThrId[tid] = INT32_MAX;
+    // padding queries, and those without a limit, keep nothing
+    sThr[tid] = q < A.nq ? (BAND ? (A.limits[q] > -INFINITY ? A.limits[q] : INFINITY) : kNoValue) : INFINITY;
+    if (!BAND) sThrId[tid] = INT32_MAX;
     sSelf[tid] = A.self_mode == 1 ? (int32_t)orig : (A.self_mode == 2 && q < A.nq ? A.self[orig] : -1);
   }
-  if (tid < 2) sFlag[tid] = -1;
-  for (int e = tid; e < FT * kOwners; e += kFilterThreads) sCnt[e] = 0;
-  for (int e = tid; e < FT * C; e += kFilterThreads) sList[e] = 0;
+  if constexpr (!BAND) {
+    if (tid < 2) sFlag[tid] = -1;
+    for (int e = tid; e < FT * kOwners; e += kFilterThreads) sCnt[e] = 0;
+    for (int e = tid; e < FT * C; e += kFilterThreads) sList[e] = 0;
+  }
   __syncthreads();
   if (lead > 0)
     for (int e = tid; e < 32 * GP; e += kFilterThreads) gm[e] = kNoValue;
@@ -403,8 +425,8 @@ __global__ void __launch_bounds__(kFilterThreads, kFilterWaves / 4) knn_filter_k
   const uint32_t load_at = tid * 16;
   auto issue = [&]() __attribute__((always_inline)) {
     const int64_t i_tile = i_seq < lead ? t0 + i_seq : t0 + i_seq - lead;
-    const _Float16 *c = (i_seg == 1 ? A.Cl : A.Ch) + (i_tile * A.nk + i_k) * kTileHalves;
-    const _Float16 *q = (i_seg == 2 ? A.Ql : A.Qh) + (qb * A.nk + i_k) * kTileHalves;
+    const _Float16 *c = (SEG3 && i_seg == 0 ? A.Cl : A.Ch) + (i_tile * A.nk + i_k) * kTileHalves;
+    const _Float16 *q = (SEG3 && i_seg == 1 ? A.Ql : A.Qh) + (qb * A.nk + i_k) * kTileHalves;
     _Float16 *dst = ring + i_slot * 2 * kTileHalves;
     if (i_seg == 0 && i_k == 0) {   // the tile's start values, ahead of its first stage
       if (wave == 0)
@@ -424,7 +446,7 @@ __global__ void __launch_bounds__(kFilterThreads, kFilterWaves / 4) knn_filter_k
     i_slot = i_slot == RING - 1 ? 0 : i_slot + 1;
     if (++i_k == A.nk) {
       i_k = 0;
-      if (++i_seg == A.nseg) {
+      if (++i_seg == SEGS) {
         i_seg = 0;
         ++i_seq;
       }
@@ -477,12 +499,7 @@ __global__ void __launch_bounds__(kFilterThreads, kFilterWaves / 4) knn_filter_k
   // waits for its operands, and a wait after the reads would be for them too.
   auto finish_stage = [&]() __attribute__((always_inline)) {
     __builtin_amdgcn_sched_barrier(0);
-    if (RING == 3 && issued - st >= 3) {
-      if (kFilterWaves == 8) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-      else asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
-    } else {
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     lds_barrier();
     at = at == (RING - 1) * kSlot ? 0 : at + kSlot;
     acc[0][0] = mfma(a1[0], b1[0], acc[0][0]);
@@ -506,27 +523,38 @@ __global__ void __launch_bounds__(kFilterThreads, kFilterWaves / 4) knn_filter_k
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   lds_barrier();
   read0();
+  // the start values of a 32 x 32 block's rows
+  auto starts = [&](int i) __attribute__((always_inline)) {
+    const float *sv = sStart + c_start * FT + wc + 4 * (lane >> 5);
+    floatx16 v;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const floatx4 w = *reinterpret_cast<const floatx4 *>(sv + 32 * i + 8 * g);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) v[4 * g + r] = w[r];
+    }
+    return v;
+  };
   for (int seq = 0; seq < ntiles; ++seq) {
-    {
-      const float *sv = sStart + c_start * FT + wc + 4 * (lane >> 5);
 #pragma unroll
-      for (int i = 0; i < NI; ++i) {
-        floatx16 v;
+    for (int i = 0; i < NI; ++i) {
+      floatx16 v = {};
+      if (!SEG3) v = starts(i);
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const floatx4 w = *reinterpret_cast<const floatx4 *>(sv + 32 * i + 8 * g);
-#pragma unroll
-          for (int r = 0; r < 4; ++r) v[4 * g + r] = w[r];
-        }
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = mfma(a0[i], b0[j], v);
-      }
-      c_start = c_start == 2 ? 0 : c_start + 1;
+      for (int j = 0; j < 2; ++j) acc[i][j] = mfma(a0[i], b0[j], v);
     }
     read1();
     finish_stage();
 #pragma unroll 1
     for (int ks = 1; ks < per_tile; ++ks) {
+      if (SEG3 && ks == 2 * A.nk) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+          const floatx16 v = starts(i);
+#pragma unroll
+          for (int j = 0; j < 2; ++j) acc[i][j] += v;
+        }
+      }
       acc[0][0] = mfma(a0[0], b0[0], acc[0][0]);
       __builtin_amdgcn_sched_barrier(0);
       read1();
@@ -536,6 +564,41 @@ __global__ void __launch_bounds__(kFilterThreads, kFilterWaves / 4) knn_filter_k
 #pragma unroll
         for (int j = 0; j < 2; ++j) acc[i][j] = mfma(a0[i], b0[j], acc[i][j]);
       finish_stage();
+    }
+    c_start = c_start == 2 ? 0 : c_start + 1;
+    if constexpr (BAND) {
+      // a lane's hits of the tile counted, then one atomic for their places; a
+      // query that has too many is given up
+      const int32_t c0 = (t0 + seq) * FT + wc + 4 * (lane >> 5);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        auto hits = [&](auto take) __attribute__((always_inline)) {
+#pragma unroll
+          for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+              const floatx16 &v = acc[i][j];
+              if (!__any(fmaxf(fmaxf(v[4 * g], v[4 * g + 1]), fmaxf(v[4 * g + 2], v[4 * g + 3])) >= thr[j])) continue;
+#pragma unroll
+              for (int r = 0; r < 4; ++r) {
+                const int32_t id = c0 + 32 * i + 8 * g + r;
+                if (v[4 * g + r] >= thr[j] && id != self[j]) take(id);
+              }
+            }
+        };
+        int n = 0;
+        hits([&](int32_t) { ++n; });
+        if (!__any(n > 0)) continue;
+        const int64_t t = qrow * FT + ql[j];
+        int at = n > 0 ? atomicAdd(&A.count[t], n) : 0;
+        if (n > 0 && at + n > A.cap) {
+          thr[j] = INFINITY;
+          n = 0;
+        }
+        int32_t *to = A.ids + t * A.cap;
+        if (n > 0) hits([&](int32_t id) { to[at++] = id; });
+      }
+      continue;
     }
     if (seq < lead) {
       // a lead tile (a query's own row is not a candidate, so its tile is
@@ -646,6 +709,7 @@ __global__ void __launch_bounds__(kFilterThreads, kFilterWaves / 4) knn_filter_k
       if (!again) break;
     }
   }
+  if constexpr (BAND) return;
   __syncthreads();
   static_assert(FT / kFilterWaves == 32, "a wave's lists in one mask");
   cut_lists<KP, C>(~0u, wave * 32, sList, sCnt, sThr, sThrId, lane);
@@ -672,9 +736,11 @@ struct FinishArgs {
   // certificate; norms and residuals in scaled units, centred
   const float *qnorm, *qres;     // [rows of Q] squared norm, squared residual
   const KnnStats *xs;            // of the candidates, after knn_classes_kernel
+  double sub;                    // norm of the low parts' errors where they are subnormal
   float scale;
   int nseg;
   int32_t *fails;                // [0] count, then query ids
+  float *limits;                 // of the fails: the least value of a candidate of the answer (-inf: none)
   int32_t *pilot;                // [3]: answers that lists of 8, 16, 32 would not certify (NULL: no pilot)
 };
 
@@ -683,24 +749,30 @@ struct FinishArgs {
 struct QueryBound {
   double nq, rq, nerr;   // norm, residual, relative error of an FP32 sum of N squares
 };
-constexpr double kUp = 1.0 + 1e-6, kU23 = 1.1920928955078125e-7;
 
-// Bound on the error of a against any candidate of norm up to x (infinite when
-// the rows' figures give none)
-__device__ __forceinline__ double value_error(const FinishArgs &A, const QueryBound &B, double x) {
+// Bound on the error of a, of nseg segments, against any candidate of norm up to
+// x at a distance of up to dist (infinite when the rows' figures give none)
+__device__ __forceinline__ double value_error(const FinishArgs &A, const QueryBound &B, double x, double dist,
+                                              int nseg) {
   const float limit = (float)(x * x * (1 + B.nerr) * kUp);
-  const double rx = sqrt((double)__uint_as_float(A.xs->res2[norm_class(limit) & (kNormClasses - 1)]) * (1 + B.nerr)) * kUp;
-  // what the segments leave out of q.c: with hi + lo, the rounding of lo
-  // (2^-11 of the residual, or 2^-25 per coordinate where lo is subnormal)
-  // and the product lo.lo
-  const double sub = 3e-8 * sqrt((double)A.N);
-  const double rest = A.nseg == 1 ? B.nq * rx + B.rq * (x + rx)
-                                  : (B.nq + B.rq) * (rx / 2048 + sub) + (x + rx) * (B.rq / 2048 + sub) + rx * B.rq;
-  // roundings of the accumulation, all of them one way: one to a product, of
-  // no more than 2^-23 of the largest partial sum
-  const double steps = (double)A.nseg * A.nk * FK + 16;
-  const double err = kUp * rest + steps * kU23 * (0.5 * x * x + (B.nq + 2 * B.rq) * (x + 2 * rx))   // accumulation
-                     + 0.5 * B.nerr * x * x;                                                       // the start value
+  const double rx = __uint_as_float(A.xs->res[norm_class(limit) & (kNormClasses - 1)]);
+  const double cross = B.nq * rx + B.rq * (x + rx);   // q.c less its high parts' product
+  // the largest partial sum: some of q.c's terms, those of |c|^2 and the rest of
+  // no more than dist |c|, and the start value, of the other sign
+  const double any = 0.5 * x * x + B.nq * x, close = x * x + dist * x;
+  const double sum = (close < any ? close : any) + 2 * cross;
+  // one rounding to a product, of no more than 2^-23 of that, all of them one way
+  const double n = (double)A.nk * FK + 17;
+  double err = n * kU23 * sum + 0.5 * B.nerr * x * x;   // (and the start value's own)
+  if (nseg == 1) {
+    err += kUp * cross;
+  } else {
+    // with hi + lo: the rounding of lo (2^-11 of the residual, or 2^-25 per
+    // coordinate where lo is subnormal), the product lo.lo, and the additions
+    // that come before the large ones
+    const double sub = A.sub, low = 1.5 * cross + (B.nq + x) * sub;
+    err += kUp * ((B.nq + B.rq) * (rx / 2048 + sub) + (x + rx) * (B.rq / 2048 + sub) + rx * B.rq) + 3 * n * kU23 * low;
+  }
   return err == err ? err : INFINITY;
 }
 
@@ -738,7 +810,7 @@ __global__ void __launch_bounds__(256) knn_finish_kernel(FinishArgs A) {
   const int64_t orig = on ? (A.map ? (int64_t)A.map[q] : q) : 0;
   const double sc2 = (double)A.scale * A.scale;
   QueryBound B;
-  B.nerr = (A.N / 16 + 16) * kU23;   // 16 lanes, then a tree
+  B.nerr = sum_error(A.N);
   const double n2 = on ? (double)A.qnorm[orig] : 0.0;
   B.nq = sqrt(n2 * (1 + B.nerr)) * kUp;
   B.rq = on ? sqrt((double)A.qres[orig] * (1 + B.nerr)) * kUp : 0.0;
@@ -766,13 +838,14 @@ __global__ void __launch_bounds__(256) knn_finish_kernel(FinishArgs A) {
   bool near = have;   // may be among the k nearest
   double reach = sqrt((double)__uint_as_float(A.xs->norm2) * (1 + B.nerr)) * kUp;
   if (kth != 0) {
-    double err = value_error(A, B, reach);
-    for (int it = 0; it < 4; ++it) {
+    double err = value_error(A, B, reach, INFINITY, A.nseg);
+    for (int it = 0; it < 4 && reach > 2 * B.nq; ++it) {   // (not far off: little to gain)
       const double far2 = n2 * (1 + B.nerr) - 2.0 * ((double)key_value(kth) - err);
-      const double r = (B.nq + sqrt(far2 > 0 ? far2 : 0.0)) * kUp;
-      if (!(r < 0.75 * reach)) break;
-      reach = r;
-      err = value_error(A, B, reach);
+      const double far = sqrt(far2 > 0 ? far2 : 0.0) * kUp, r = (B.nq + far) * kUp;
+      const bool less = r < 0.75 * reach;
+      if (r < reach) reach = r;
+      err = value_error(A, B, reach, far + 2 * kU23 * (B.nq + reach), A.nseg);
+      if (!less) break;
     }
     // a value more than two errors below the k-th best cannot be (the slack
     // covers the rounding of the distances themselves)
@@ -800,11 +873,12 @@ __global__ void __launch_bounds__(256) knn_finish_kernel(FinishArgs A) {
     // row) between the given ones, must lie above the k-th distance (FP32, and
     // subnormal squares).
     const double top = ((double)d * (1 + (A.N + 16) * kU23) + A.N * 1.5e-45) * sc2;
-    const double r = (B.nq + sqrt(top)) * kUp;
-    const double x = r < reach ? r : reach, err = value_error(A, B, x);
+    const double r = (B.nq + sqrt(top)) * kUp, x = r < reach ? r : reach;
+    const double shift = 0.5 * kU23 * (B.nq + x), dist = (sqrt(top) + shift) * kUp;
+    const double err = value_error(A, B, x, dist, A.nseg);
     auto certified = [&](uint64_t last) {
       const double least = n2 * (1 - B.nerr) - 2.0 * ((double)key_value(last) + err);
-      const double moved = sqrt(least > 0 ? least : 0.0) - 0.5 * kU23 * (B.nq + x);
+      const double moved = sqrt(least > 0 ? least : 0.0) - shift;
       return top < (moved > 0 ? moved * moved : 0.0) * (1 - 1e-12);
     };
     // a list that is not full is the answer if it holds all there are
@@ -818,30 +892,88 @@ __global__ void __launch_bounds__(256) knn_finish_kernel(FinishArgs A) {
         if (len <= KP && (found < len ? !complete() : len < A.k || !certified(nth[l]))) atomicAdd(&A.pilot[l], 1);
       }
     } else if (found < KP ? !complete() : !certified(last)) {
-      A.fails[1 + atomicAdd(&A.fails[0], 1)] = (int32_t)orig;
+      const int32_t at = atomicAdd(&A.fails[0], 1);
+      A.fails[1 + at] = (int32_t)orig;
+      // what three segments give a candidate as near as the k-th here, at least
+      const double low = 0.5 * (n2 * (1 - B.nerr) - dist * dist) - value_error(A, B, x, dist, 3);
+      const float f = (float)(low - 1.2e-7 * fabs(low));
+      A.limits[at] = f > kNoValue ? f : -INFINITY;
     }
   }
 }
 
-// ---- every candidate, for the queries that no certificate covers --------------
+// ---- answers from exact distances of many candidates ---------------------------
 
-// A block takes kBruteQ queries over one range of the candidates: thread t
-// computes the FP32 distances of candidate c0 + t (a tile of 256 at a time);
-// the four waves then offer the tile's keys (distance above, id below) to two
-// queries each, whose best 64 a wave holds sorted over its lanes.  Bound by
-// the vector ALU (2 instructions per query, candidate and feature); rare.
-constexpr int kBruteQ = 8;
-
+// best: a wavefront's 64 best keys (distance above, id below) sorted over its
+// lanes, of which the first k count
 __device__ __forceinline__ void offer_sorted(uint64_t &best, uint64_t key, int lane, int k) {
   uint64_t mask = __ballot(key < __shfl(best, k - 1, 64));
   while (mask) {
     const uint64_t in = __shfl(key, __builtin_ctzll(mask), 64);
-    mask &= mask - 1;
     const int pos = __popcll(__ballot(best < in));
     const uint64_t up = __shfl_up(best, 1, 64);
     best = lane < pos ? best : (lane == pos ? in : up);
+    mask &= mask - 1;
+    mask &= __ballot(key < __shfl(best, k - 1, 64));   // those that still can be among them
   }
 }
+
+__device__ __forceinline__ void put_answer(uint64_t best, int64_t q, int lane, int k, int32_t *out_idx,
+                                           float *out_dist) {
+  if (lane >= k) return;
+  out_idx[q * k + lane] = best == ~0ull ? -1 : (int32_t)(uint32_t)best;
+  if (out_dist) out_dist[q * k + lane] = best == ~0ull ? FLT_MAX : __uint_as_float((uint32_t)(best >> 32));
+}
+
+// Query rows[blockIdx.x]: the k nearest of its hits (count, ids); one without a
+// limit, or with more hits than were kept, goes to `left` ([0] count).  Bound by
+// the latency of the hits' rows, which come from L2 and the memory-side cache, so
+// the four waves of a block share a query (a wave to a query: 100,000 x 100 points
+// with 5,000 hits each 28 ms).
+__global__ void __launch_bounds__(256) knn_band_rank_kernel(const float *__restrict__ X, int N,
+                                                            const float *__restrict__ Q,
+                                                            const int32_t *__restrict__ rows,
+                                                            const float *__restrict__ limits,
+                                                            const int32_t *__restrict__ count,
+                                                            const int32_t *__restrict__ ids, int cap, int k,
+                                                            int32_t *__restrict__ out_idx,
+                                                            float *__restrict__ out_dist, int32_t *__restrict__ left) {
+  __shared__ uint64_t lists[4][32];
+  static_assert(sizeof lists / sizeof lists[0][0] == 4 * 32, "k is at most 28");
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t t = blockIdx.x, q = rows[t];
+  const int32_t hits = count[t];
+  if (!(limits[t] > -INFINITY) || hits > cap) {
+    if (threadIdx.x == 0) left[1 + atomicAdd(&left[0], 1)] = (int32_t)q;
+    return;
+  }
+  const bool vec4 = rows_are_vec4(X, Q, N);
+  uint64_t best = ~0ull;
+  for (int32_t base = 64 * wave; base < hits; base += 256) {
+    uint64_t key = ~0ull;
+    if (base + lane < hits) {
+      const int32_t c = ids[t * cap + base + lane];
+      key = (uint64_t)__float_as_uint(exact_distance(Q + q * N, X + (int64_t)c * N, N, vec4)) << 32 | (uint32_t)c;
+    }
+    offer_sorted(best, key, lane, k);
+  }
+  if (lane < 32) lists[wave][lane] = best;
+  __syncthreads();
+  if (wave > 0) return;
+  for (int w = 1; w < 4; ++w) offer_sorted(best, lane < k ? lists[w][lane] : ~0ull, lane, k);
+  put_answer(best, q, lane, k, out_idx, out_dist);
+}
+
+// Every candidate.  A block takes kBruteQ queries over one range of the
+// candidates: thread t computes the FP32 distances of candidate c0 + t (a tile of
+// 256 at a time) to all of them, 32 features of its row in registers and the
+// queries' through the scalar cache; the four waves then offer the tile's keys to
+// two queries each.  Bound by the vector ALU (2 instructions per query, candidate
+// and feature).  A range ends when k candidates of distance 0 are found for each
+// query: those that follow have higher ids.
+constexpr int kBruteQ = 8;
+
+typedef const __attribute__((address_space(4))) float *ScalarRow;   // read-only, at an address the wavefront shares
 
 __global__ void __launch_bounds__(256) knn_brute_kernel(const float *__restrict__ X, int64_t M, int N,
                                                         const float *__restrict__ Q, int64_t nq,
@@ -851,27 +983,62 @@ __global__ void __launch_bounds__(256) knn_brute_kernel(const float *__restrict_
   __shared__ uint64_t keys[kBruteQ][256];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t f0 = (int64_t)blockIdx.x * kBruteQ;
+  const int nf = nq - f0 < kBruteQ ? (int)(nq - f0) : kBruteQ;
   const int64_t per = ((M + splits - 1) / splits + 255) / 256 * 256;
   const int64_t b = blockIdx.y * per, e = b + per < M ? b + per : M;
   const bool vec4 = rows_are_vec4(X, Q, N);
+  ScalarRow qrow[kBruteQ];
+  int64_t own[kBruteQ];
+#pragma unroll
+  for (int f = 0; f < kBruteQ; ++f) {
+    const int64_t at = f0 + (f < nf ? f : 0), q = rows ? (int64_t)rows[at] : at;
+    qrow[f] = (ScalarRow)(Q + q * N);
+    own[f] = self_mode == 1 ? q : (self_mode == 2 ? (int64_t)self[q] : -1);
+  }
   uint64_t best[2] = {~0ull, ~0ull};
   for (int64_t c0 = b; c0 < e; c0 += 256) {
     const int64_t c = c0 + tid;
-    for (int f = 0; f < kBruteQ; ++f) {
-      uint64_t key = ~0ull;
-      if (c < e && f0 + f < nq) {
-        const int64_t q = rows[f0 + f];
-        const int64_t own = self_mode == 1 ? q : (self_mode == 2 ? (int64_t)self[q] : -1);
-        if (c != own)
-          key = (uint64_t)__float_as_uint(exact_distance(Q + q * N, X + c * N, N, vec4)) << 32 | (uint32_t)c;
-      }
-      keys[f][tid] = key;
-    }
-    __syncthreads();
+    const float *x = X + (c < e ? c : e - 1) * N;
+    float d[kBruteQ];
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
-      for (int g = 0; g < 4; ++g) offer_sorted(best[h], keys[2 * wave + h][64 * g + lane], lane, k);
+    for (int f = 0; f < kBruteQ; ++f) d[f] = 0.f;
+    // (the additions of exact_distance, in its order)
+    auto add = [&](int f, float u, float v) {
+      const float w = u - v;
+      d[f] = fmaf(w, w, d[f]);
+    };
+    int kk = 0;
+    if (vec4)
+      for (; kk + 32 <= N; kk += 32) {
+        float4 v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = *reinterpret_cast<const float4 *>(x + kk + 4 * j);
+#pragma unroll
+        for (int f = 0; f < kBruteQ; ++f)
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            add(f, qrow[f][kk + 4 * j], v[j].x);
+            add(f, qrow[f][kk + 4 * j + 1], v[j].y);
+            add(f, qrow[f][kk + 4 * j + 2], v[j].z);
+            add(f, qrow[f][kk + 4 * j + 3], v[j].w);
+          }
+      }
+    for (; kk < N; ++kk) {
+      const float v = x[kk];
+#pragma unroll
+      for (int f = 0; f < kBruteQ; ++f) add(f, qrow[f][kk], v);
+    }
+#pragma unroll
+    for (int f = 0; f < kBruteQ; ++f)
+      keys[f][tid] = c < e && f < nf && c != own[f] ? (uint64_t)__float_as_uint(d[f]) << 32 | (uint32_t)c : ~0ull;
     __syncthreads();
+    bool done = true;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      for (int g = 0; g < 4; ++g) offer_sorted(best[h], keys[2 * wave + h][64 * g + lane], lane, k);
+      done = done && (2 * wave + h >= nf || __shfl(best[h], k - 1, 64) >> 32 == 0);
+    }
+    if (__syncthreads_and(done)) break;
   }
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
@@ -892,15 +1059,12 @@ __global__ void __launch_bounds__(256) knn_brute_merge_kernel(const uint64_t *__
   const uint64_t *P = part + f * splits * k;
   for (int base = 0; base < splits * k; base += 64)
     offer_sorted(best, base + lane < splits * k ? P[base + lane] : ~0ull, lane, k);
-  if (lane >= k) return;
-  const int64_t q = rows[f];
-  out_idx[q * k + lane] = best == ~0ull ? -1 : (int32_t)(uint32_t)best;
-  if (out_dist) out_dist[q * k + lane] = best == ~0ull ? FLT_MAX : __uint_as_float((uint32_t)(best >> 32));
+  put_answer(best, rows ? (int64_t)rows[f] : f, lane, k, out_idx, out_dist);
 }
 
-template <int KP>
+template <int KP, bool SEG3>
 hipError_t launch_filter_kp(const FilterArgs &f, const FinishArgs &g, hipStream_t s) {
-  knn_filter_kernel<KP><<<(unsigned)(f.nqb * f.splits), kFilterThreads, 0, s>>>(f);
+  knn_filter_kernel<KP, SEG3, false><<<(unsigned)(f.nqb * f.splits), kFilterThreads, 0, s>>>(f);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   knn_finish_kernel<KP><<<grid_for(g.n_launch * KP, 256), 256, 0, s>>>(g);
@@ -932,10 +1096,11 @@ int lead_tiles(int64_t tiles) {
 }
 
 hipError_t run_filter(const FilterArgs &f, const FinishArgs &g, int kp, hipStream_t s) {
+  const bool three = g.nseg == 3;
   switch (kp) {
-    case 8: return launch_filter_kp<8>(f, g, s);
-    case 16: return launch_filter_kp<16>(f, g, s);
-    default: return launch_filter_kp<32>(f, g, s);
+    case 8: return three ? launch_filter_kp<8, true>(f, g, s) : launch_filter_kp<8, false>(f, g, s);
+    case 16: return three ? launch_filter_kp<16, true>(f, g, s) : launch_filter_kp<16, false>(f, g, s);
+    default: return three ? launch_filter_kp<32, true>(f, g, s) : launch_filter_kp<32, false>(f, g, s);
   }
 }
 
@@ -973,31 +1138,34 @@ float sample_scale(float spread, float absmax) {
   return ldexpf(1.f, sh);
 }
 
-// Segments and list length: the pilot runs kPilotTiles query tiles spread over
-// the call with one segment and counts the answers that lists of 8, 16 and
-// (when k asks for those anyway) 32 would not certify.  A failed answer costs
-// three times its share of the sweep, a longer list more hits (at 400,000 x
-// 100 lists of 8, 16 and 32 sweep in 62, 74 and about 90 ms, against 45 ms
-// without any hit): 8 while at most one answer in 16 fails, then 16 while at
-// most one in 6 does, then 32.  When half of them fail with 16, or a quarter
-// with 32, repeating them would cost more than the two segments saved, and the
-// call uses three from the start.  Calls of fewer query tiles than CUs go
-// without a pilot, which takes as long as it takes a block to fill its lists
-// (1.4 ms with lists of 32) and leaves most CUs idle: 50,000 x 128, k 2 / 5 /
-// 10 / 20: 2.8 / 3.4 / 5.0 / 7.3 ms with one, 2.4 / 2.7 / 3.9 / 5.9 without.
-// Wide rows keep it from 4 kPilotTiles tiles on, as their failed answers cost
-// more than the pilot (20,000 x 500, k 10: 2.9 ms with it, 3.6 without).  With
-// fewer than kFewTiles candidate tiles (a coarse quantizer's centroids) the
-// lists cost more than the products, so short lists and three segments are
-// best (200,000 queries against 512 centroids of width 100).
+// List length: the pilot runs kPilotTiles query tiles spread over the call and
+// counts the answers that lists of 8, 16 and (when k asks for those anyway) 32
+// would not certify.  A failed answer costs three times its share of the sweep, a
+// longer list more hits (at 400,000 x 100 lists of 8, 16 and 32 sweep in 62, 74
+// and about 90 ms, against 45 ms without any hit): 8 while at most one answer in 16
+// fails, then 16 while at most one in 6 does, then 32; and where half of them fail
+// with 16, the shortest, as a longer list would not help them.  Calls of fewer
+// query tiles than CUs go without a pilot, which takes as long as it takes a block
+// to fill its lists (1.4 ms with lists of 32) and leaves most CUs idle: 50,000 x
+// 128, k 2 / 5 / 10 / 20: 2.8 / 3.4 / 5.0 / 7.3 ms with one, 2.4 / 2.7 / 3.9 / 5.9
+// without.  Wide rows keep it from 4 kPilotTiles tiles on, as their failed answers
+// cost more than the pilot (20,000 x 500, k 10: 2.9 ms with it, 3.6 without).  With
+// fewer than kFewTiles candidate tiles (a coarse quantizer's centroids) the lists
+// cost more than the products, so short lists and three segments are best (200,000
+// queries against 512 centroids of width 100).
 constexpr int kWidePilot = 256;
 constexpr int64_t kPilotTiles = 8;
 constexpr int64_t kFewTiles = 16;
 
+// The band's hits: so many are kept of a query, and so many ids in all (they fit
+// a buffer that the library keeps)
+constexpr int64_t kBandHits = 16384;
+constexpr int64_t kBandIds = int64_t{32} << 20;
+
 }  // namespace
 
 int KnnSearch::open(int64_t M_, int N_, const float *Q_, int64_t nq_, const float *sample, int64_t sample_rows,
-                    bool same_, int k_, float absmax, hipStream_t s_) {
+                    bool same_, int k_, hipStream_t s_) {
   M = M_;
   N = N_;
   Q = Q_;
@@ -1013,20 +1181,18 @@ int KnnSearch::open(int64_t M_, int N_, const float *Q_, int64_t nq_, const floa
     V.add(&im->p, halves);
     im->halves = halves;
   };
-  uint32_t *spread = nullptr;
+  uint32_t *spread = nullptr;   // of the sample, then the largest |coordinate|
   image(&ch, nx);
   V.add(&start, tiles * FT);
   V.add(&xstats, 1);
   V.add(&fails, nq + 1);
+  V.add(&limits, nq);
   V.add(&pilot, 3);
   V.add(&mean, N);
-  V.add(&spread, 1);
+  V.add(&spread, 2);
   V.add(&qnorm, nq);
   V.add(&qres, nq);
-  if (few) {
-    image(&cl, nx);
-    V.add(&rest, nq + 1);
-  }
+  if (few) image(&cl, nx);
   if (!same) {
     image(&qh, nqi);
     if (few) image(&ql, nqi);
@@ -1037,15 +1203,18 @@ int KnnSearch::open(int64_t M_, int N_, const float *Q_, int64_t nq_, const floa
     qh = ch;
     ql = cl;
   }
-  uint32_t bits = 0;
-  HIPCHK(launch_fill_i32((int32_t *)spread, 1, 0, s));
+  uint32_t bits[2];
+  float seen[2];
+  HIPCHK(launch_fill_i32((int32_t *)spread, 2, 0, s));
+  HIPCHK(launch_absmax(sample, sample_rows * N, spread + 1, s));
+  if (Q != sample || nq != sample_rows) HIPCHK(launch_absmax(Q, nq * N, spread + 1, s));
   knn_sample_kernel<<<(unsigned)N, 256, 0, s>>>(sample, sample_rows, N, mean, spread);
   HIPCHK(hipGetLastError());
-  HIPCHK(hipMemcpyAsync(&bits, spread, sizeof bits, hipMemcpyDeviceToHost, s));
+  HIPCHK(hipMemcpyAsync(bits, spread, sizeof bits, hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
-  float spread_h;
-  std::memcpy(&spread_h, &bits, sizeof bits);
-  scale = sample_scale(spread_h, absmax);
+  std::memcpy(seen, bits, sizeof bits);
+  if (!std::isfinite(seen[1])) return fail(IVHD_EINVAL, "the points hold a non-finite coordinate");
+  scale = sample_scale(seen[0], seen[1]);
   return IVHD_OK;
 }
 
@@ -1053,11 +1222,10 @@ int KnnSearch::run(const float *X, int self_mode, const int32_t *self, int32_t *
   const int nk = (N + FK - 1) / FK;
   const int64_t tiles = (M + FT - 1) / FT, nqb = (nq + FT - 1) / FT;
   int kp = list_length(k), rc;
-  bool three = few;   // few candidates: three segments from the start, both halves made at once
   HIPCHK(launch_fill_i32((int32_t *)xstats, sizeof(KnnStats) / 4, 0, s));
   HIPCHK(launch_knn_split(X, M, N, nullptr, mean, scale, ch, cl, same ? qnorm : nullptr, same ? qres : nullptr, start,
                           xstats, s));
-  knn_classes_kernel<<<1, kNormClasses, 0, s>>>(xstats);
+  knn_classes_kernel<<<1, kNormClasses, 0, s>>>(xstats, N);
   HIPCHK(hipGetLastError());
   if (!same && !queries_ready) {
     HIPCHK(launch_knn_split(Q, nq, N, nullptr, mean, scale, qh, ql, qnorm, qres, nullptr, nullptr, s));
@@ -1065,12 +1233,12 @@ int KnnSearch::run(const float *X, int self_mode, const int32_t *self, int32_t *
   }
 
   FilterArgs f{};
-  KnnImage qi = qh;   // of the queries that are swept
-  f.Qh = qi.p;
+  f.Qh = qh.p;
+  f.Ql = ql.p;
   f.Ch = ch.p;
+  f.Cl = cl.p;
   f.start = start;
   f.nk = nk;
-  f.nseg = 1;
   f.nq = nq;
   f.tiles = tiles;
   f.self_mode = self_mode;
@@ -1087,26 +1255,34 @@ int KnnSearch::run(const float *X, int self_mode, const int32_t *self, int32_t *
   g.self = self;
   g.out_idx = idx;
   g.out_dist = dist;
-  g.nseg = 1;
+  g.nseg = few ? 3 : 1;   // few candidates: both halves are made at once
   g.qnorm = qnorm;
   g.qres = qres;
   g.xs = xstats;
+  g.sub = 3e-8 * std::sqrt((double)N);
   g.scale = scale;
+  g.fails = fails;
+  g.limits = limits;
 
-  auto sweep = [&](int64_t qb0, int64_t step, int64_t n) -> int {
+  // the query tiles qb0, qb0 + step, .., of images `images`
+  auto shape = [&](int64_t qb0, int64_t step, int64_t n, int nseg, int list, const KnnImage &images) -> int {
     f.qb0 = g.qb0 = qb0;
     f.qb_step = g.qb_step = step;
     f.nqb = n;
-    f.splits = g.splits = choose_splits(n, tiles, nk * f.nseg, kp);
+    f.splits = g.splits = choose_splits(n, tiles, nk * nseg, list);
     f.tiles_per_split = (tiles + f.splits - 1) / f.splits;
     f.lead = lead_tiles(f.tiles_per_split);
     g.n_launch = n * FT;
-    if ((qb0 + (n - 1) * step + 1) * nk * kTileHalves > qi.halves || tiles * nk * kTileHalves > ch.halves)
+    if ((qb0 + (n - 1) * step + 1) * nk * kTileHalves > images.halves || tiles * nk * kTileHalves > ch.halves)
       return fail(IVHD_ESTATE, "kNN: query tiles outside their operands");
+    return IVHD_OK;
+  };
+  auto sweep = [&](int64_t qb0, int64_t step, int64_t n) -> int {
+    int r = shape(qb0, step, n, g.nseg, kp, qh);
+    if (r) return r;
     const int64_t need = n * FT * f.splits * kp;
     if (need > part_cap) {   // (a larger launch is queued behind the smaller: both lists stay)
-      const int r = S.get(&part, need, "candidate lists");
-      if (r) return r;
+      if ((r = S.get(&part, need, "candidate lists"))) return r;
       part_cap = need;
     }
     f.part = part;
@@ -1114,25 +1290,7 @@ int KnnSearch::run(const float *X, int self_mode, const int32_t *self, int32_t *
     HIPCHK(run_filter(f, g, kp, s));
     return IVHD_OK;
   };
-  // all query tiles: whole rounds of the CUs take the candidates in one range,
-  // which costs the fewest hits; the rest is split to fill the CUs once more
-  // (few candidates: one launch, a second would last as long as a round)
-  auto sweep_all = [&](int64_t n) -> int {
-    const int64_t whole = few ? n : n / kCus * kCus;
-    for (int64_t b = 0; b < whole; b += kBatchTiles) {
-      const int r = sweep(b, 1, whole - b < kBatchTiles ? whole - b : kBatchTiles);
-      if (r) return r;
-    }
-    return n > whole ? sweep(whole, 1, n - whole) : IVHD_OK;
-  };
-  int32_t failed = 0;
-  auto read_failed = [&](const int32_t *list) -> int {
-    HIPCHK(hipMemcpyAsync(&failed, list, sizeof failed, hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
-    return IVHD_OK;
-  };
-  g.fails = fails;
-  if (!three && nqb >= (N > kWidePilot ? 4 * kPilotTiles : kCus)) {
+  if (!few && nqb >= (N > kWidePilot ? 4 * kPilotTiles : kCus)) {
     int32_t bad[3];
     HIPCHK(launch_fill_i32(pilot, 3, 0, s));
     g.pilot = pilot;
@@ -1143,56 +1301,73 @@ int KnnSearch::run(const float *X, int self_mode, const int32_t *self, int32_t *
     HIPCHK(hipMemcpyAsync(bad, pilot, sizeof bad, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
     const int32_t all = (int32_t)(kPilotTiles * FT);
-    if (kp == 32) {
-      three = bad[2] > all / 4;
-    } else {
-      three = bad[1] > all / 2;
-      if (want == 8 && bad[0] <= all / 16) kp = 8;
+    if (kp == 16) {
+      if (bad[1] > all / 2) kp = want;
+      else if (want == 8 && bad[0] <= all / 16) kp = 8;
       else if (bad[1] > all / 6) kp = 32;
     }
-  } else if (!three && kp == 8) {
+  } else if (!few && kp == 8) {
     kp = 16;
   }
-  if (!three) {
-    HIPCHK(launch_fill_i32(fails, 1, 0, s));
-    if ((rc = sweep_all(nqb)) || (rc = read_failed(fails))) return rc;
-    if (failed == 0) return IVHD_OK;
-  }
-  // three segments: everything, or the queries that were not certified
-  const int64_t n3 = three ? nq : failed;
-  const int32_t *map = three ? nullptr : fails + 1;
+  HIPCHK(launch_fill_i32(fails, 1, 0, s));
+  // all query tiles: whole rounds of the CUs take the candidates in one range,
+  // which costs the fewest hits; the rest is split to fill the CUs once more
+  // (few candidates: one launch, a second would last as long as a round)
+  const int64_t whole = few ? nqb : nqb / kCus * kCus;
+  for (int64_t b = 0; b < whole; b += kBatchTiles)
+    if ((rc = sweep(b, 1, whole - b < kBatchTiles ? whole - b : kBatchTiles))) return rc;
+  if (nqb > whole && (rc = sweep(whole, 1, nqb - whole))) return rc;
+  auto read_count = [&](const int32_t *list, int32_t *n) -> int {
+    HIPCHK(hipMemcpyAsync(n, list, sizeof *n, hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+    return IVHD_OK;
+  };
+  int32_t failed = 0;
+  if ((rc = read_count(fails, &failed)) || failed == 0) return rc;
+
+  // The answers that are not certified: all candidates whose value, of three
+  // segments, may be an answer's are ranked by their FP32 distances, a batch of
+  // queries at a time
   Scratch R(s);   // of this run
-  KnnImage low_c = cl, low_q = ql;
-  int32_t *left = rest;
-  if (!few) {
-    auto image = [&](KnnImage *im, int64_t rows, const char *what) -> int {
-      im->halves = knn_image_halves(rows, N);
-      return R.get(&im->p, im->halves, what);
-    };
-    if ((rc = R.get(&left, nq + 1, "uncertified queries (three segments)"))) return rc;
-    if ((rc = image(&low_c, M, "candidate operands (low)"))) return rc;
-    HIPCHK(launch_knn_split(X, M, N, nullptr, mean, scale, KnnImage{}, low_c, nullptr, nullptr, nullptr, nullptr,
-                            s));
-    if (three && same) {
-      low_q = low_c;
-    } else {
-      if ((rc = image(&low_q, n3, "query operands (low)"))) return rc;
-      if (!three && (rc = image(&qi, n3, "query operands"))) return rc;
-      HIPCHK(launch_knn_split(Q, n3, N, map, mean, scale, three ? KnnImage{} : qi, low_q, nullptr, nullptr, nullptr,
-                              nullptr, s));
-    }
-  }
-  kp = list_length(k);
-  f.Qh = qi.p;
+  const int32_t *again = fails + 1;
+  KnnImage low_c = cl, high_q, low_q;
+  auto image = [&](KnnImage *im, int64_t rows, const char *what) -> int {
+    im->halves = knn_image_halves(rows, N);
+    return R.get(&im->p, im->halves, what);
+  };
+  const int64_t cap = M < kBandHits ? M : kBandHits, all_rows = (failed + FT - 1) / FT * (int64_t)FT;
+  int64_t batch = kBandIds / cap / FT * FT;
+  batch = batch < all_rows ? batch : all_rows;
+  int32_t *left, *count, *ids;
+  if ((rc = image(&high_q, failed, "query operands (high)")) || (rc = image(&low_q, failed, "query operands (low)")) ||
+      (!few && (rc = image(&low_c, M, "candidate operands (low)"))) ||
+      (rc = R.get(&left, (int64_t)failed + 1, "queries left")) || (rc = R.get(&count, batch, "hits of a query")) ||
+      (rc = R.get(&ids, batch * cap, "hits")))
+    return rc;
+  if (!few)
+    HIPCHK(launch_knn_split(X, M, N, nullptr, mean, scale, KnnImage{}, low_c, nullptr, nullptr, nullptr, nullptr, s));
+  HIPCHK(launch_knn_split(Q, failed, N, again, mean, scale, high_q, low_q, nullptr, nullptr, nullptr, nullptr, s));
+  HIPCHK(launch_fill_i32(left, 1, 0, s));
+  f.Qh = high_q.p;
   f.Ql = low_q.p;
   f.Cl = low_c.p;
-  f.nseg = g.nseg = 3;
-  f.nq = g.nq = n3;
-  f.map = g.map = map;
-  HIPCHK(launch_fill_i32(left, 1, 0, s));
-  g.fails = left;
-  if ((rc = sweep_all((n3 + FT - 1) / FT)) || (rc = read_failed(left))) return rc;
-  if (failed == 0) return IVHD_OK;
+  f.nq = failed;
+  f.map = again;
+  f.limits = limits;
+  f.count = count;
+  f.ids = ids;
+  f.cap = (int)cap;
+  for (int64_t q0 = 0; q0 < failed; q0 += batch) {
+    const int64_t n = failed - q0 < batch ? failed - q0 : batch;
+    if ((rc = shape(q0 / FT, 1, (n + FT - 1) / FT, 3, 0, high_q))) return rc;
+    HIPCHK(launch_fill_i32(count, n, 0, s));
+    knn_filter_kernel<8, true, true><<<(unsigned)(f.nqb * f.splits), kFilterThreads, 0, s>>>(f);
+    knn_band_rank_kernel<<<(unsigned)n, 256, 0, s>>>(X, N, Q, again + q0, limits + q0, count, ids, (int)cap, k, idx, dist,
+                                                     left);
+    HIPCHK(hipGetLastError());
+  }
+  if ((rc = read_count(left, &failed)) || failed == 0) return rc;
+
   const int64_t groups = (failed + kBruteQ - 1) / kBruteQ;
   int64_t splits = 4 * kCus / groups;
   splits = splits < 1 ? 1 : (splits > 64 ? 64 : splits);

@@ -48,10 +48,11 @@ struct Carve {
 
 // What a set of rows has at most, as float bits (non-negative floats compare as
 // integers; zero before use): the squared norm, and for each class of squared
-// norms (by their exponents) the squared rounding residual of a row up to it
+// norms (by their exponents) the squared rounding residual of a row, in the end
+// the residual of a row up to that class
 constexpr int kNormClasses = 256;
 struct KnnStats {
-  uint32_t norm2, res2[kNormClasses];
+  uint32_t norm2, res[kNormClasses];
 };
 // operand images of whole tiles of rows, and the room that was allocated
 struct KnnImage {
@@ -64,9 +65,9 @@ struct KnnImage {
 // the run's own.
 struct KnnSearch {
   // allocates, and takes the centre and the scale of all operands from a sample
-  // of the rows `sample`; absmax: the largest |coordinate| of all.  Synchronises.
+  // of the rows `sample` (IVHD_EINVAL when they or Q are not finite).  Synchronises.
   int open(int64_t M, int N, const float *Q, int64_t nq, const float *sample, int64_t sample_rows, bool same, int k,
-           float absmax, hipStream_t s);
+           hipStream_t s);
   // the answers for the candidates X [M][N]; self_mode: 0 = none, 1 = query q
   // excludes candidate q, 2 = query q excludes self[q].  Synchronises the
   // stream.  It may be called again with as many other candidates and the same
@@ -83,7 +84,8 @@ struct KnnSearch {
   KnnImage ch, cl, qh, ql;   // operands, high and low; the low ones only with few
   float *start = nullptr, *qnorm = nullptr, *qres = nullptr, *mean = nullptr;
   KnnStats *xstats = nullptr;
-  int32_t *fails = nullptr, *rest = nullptr, *pilot = nullptr;   // rest: only with few
+  float *limits = nullptr;
+  int32_t *fails = nullptr, *pilot = nullptr;
   uint64_t *part = nullptr;
   int64_t part_cap = 0;
 };

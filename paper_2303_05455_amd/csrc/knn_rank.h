@@ -40,31 +40,31 @@ __device__ __forceinline__ float exact_distance(const float *__restrict__ qr, co
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         float e = u[j].x - v[j].x;
-        d += e * e;
+        d = fmaf(e, e, d);
         e = u[j].y - v[j].y;
-        d += e * e;
+        d = fmaf(e, e, d);
         e = u[j].z - v[j].z;
-        d += e * e;
+        d = fmaf(e, e, d);
         e = u[j].w - v[j].w;
-        d += e * e;
+        d = fmaf(e, e, d);
       }
     }
     for (; kk < N; kk += 4) {
       const float4 u = *reinterpret_cast<const float4 *>(qr + kk);
       const float4 v = *reinterpret_cast<const float4 *>(xr + kk);
       float e = u.x - v.x;
-      d += e * e;
+      d = fmaf(e, e, d);
       e = u.y - v.y;
-      d += e * e;
+      d = fmaf(e, e, d);
       e = u.z - v.z;
-      d += e * e;
+      d = fmaf(e, e, d);
       e = u.w - v.w;
-      d += e * e;
+      d = fmaf(e, e, d);
     }
   } else {
     for (int kk = 0; kk < N; ++kk) {
       const float e = qr[kk] - xr[kk];
-      d += e * e;
+      d = fmaf(e, e, d);
     }
   }
   return d;

@@ -297,16 +297,15 @@ int ivhd_grad_edges(const float *d_y, int64_t M, const int32_t *d_nn_idx, int32_
   return rc ? rc : rc2;
 }
 
-// the largest |x| of one or two arrays (IVHD_EINVAL when it is not finite); synchronises s
-static int largest_magnitude(const float *x, int64_t nx, const float *y, int64_t ny, float *out, hipStream_t s) {
+// the largest |x| (IVHD_EINVAL when it is not finite); synchronises s
+static int largest_magnitude(const float *x, int64_t n, float *out, hipStream_t s) {
   Scratch S(s);
   uint32_t *amax = nullptr;
   const int rc = S.get(&amax, 1, "largest magnitude");
   if (rc) return rc;
   uint32_t bits = 0;
   HIPCHK(launch_fill_i32((int32_t *)amax, 1, 0, s));
-  HIPCHK(launch_absmax(x, nx, amax, s));
-  if (y) HIPCHK(launch_absmax(y, ny, amax, s));
+  HIPCHK(launch_absmax(x, n, amax, s));
   HIPCHK(hipMemcpyAsync(&bits, amax, sizeof bits, hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
   std::memcpy(out, &bits, sizeof bits);
@@ -326,11 +325,9 @@ static int knn_common(const float *d_x, int64_t M, int32_t N, const float *d_q, 
   if (Q == 0) return IVHD_OK;
   hipStream_t s = (hipStream_t)stream;
   const bool same = d_q == d_x && Q == M;
-  float amx = 0.f;
-  int rc = largest_magnitude(d_x, M * (int64_t)N, same ? nullptr : d_q, Q * (int64_t)N, &amx, s);
-  if (rc) return rc;
   KnnSearch K;
-  if ((rc = K.open(M, N, d_q, Q, d_x, M, same, k, amx, s))) return rc;
+  const int rc = K.open(M, N, d_q, Q, d_x, M, same, k, s);
+  if (rc) return rc;
   return K.run(d_x, self_mode, d_self, d_idx, d_dist);
 }
 
@@ -391,13 +388,11 @@ int ivhd_ivf_train(const float *d_x, int64_t M, int32_t N, int32_t nlist, int32_
   int32_t *flags;
   int rc = S.get(&flags, FLAG_SLOTS, "device flags");
   if (rc) return rc;
-  float amx = 0.f;
-  if ((rc = largest_magnitude(d_x, M * (int64_t)N, nullptr, 0, &amx, s))) return rc;
-  HIPCHK(launch_init_centroids(d_x, M, N, nlist, d_centroids, s));
   // the points are prepared once for all assignments; means lie among the
   // points, so their centre and scale hold throughout
   KnnSearch K;
-  if ((rc = K.open(nlist, N, d_x, M, d_x, M, false, 1, amx, s))) return rc;
+  if ((rc = K.open(nlist, N, d_x, M, d_x, M, false, 1, s))) return rc;
+  HIPCHK(launch_init_centroids(d_x, M, N, nlist, d_centroids, s));
   for (int it = 0; it <= n_iter; ++it) {
     if ((rc = K.run(d_centroids, 0, nullptr, d_assign, nullptr))) return rc;
     if (it == n_iter) break;
@@ -408,7 +403,8 @@ int ivhd_ivf_train(const float *d_x, int64_t M, int32_t N, int32_t nlist, int32_
     HIPCHK(hipStreamSynchronize(s));   // before L frees the lists
   }
   // (a sum of huge coordinates can overflow)
-  return largest_magnitude(d_centroids, (int64_t)nlist * N, nullptr, 0, &amx, s);
+  float amx = 0.f;
+  return largest_magnitude(d_centroids, (int64_t)nlist * N, &amx, s);
 }
 
 int ivhd_ivf_search(const float *d_x, int64_t M, int32_t N, const float *d_centroids, int32_t nlist,
