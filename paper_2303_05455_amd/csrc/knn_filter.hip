@@ -55,6 +55,7 @@
 #include <cfloat>
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 
 #include "knn_internal.h"
 #include "knn_rank.h"
@@ -64,6 +65,7 @@ namespace {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) void lds_void;
 
@@ -115,31 +117,33 @@ constexpr int kSampleRows = 255;
 
 __global__ void __launch_bounds__(256) knn_sample_kernel(const float *__restrict__ X, int64_t M, int N,
                                                          float *__restrict__ mean, uint32_t *__restrict__ spread) {
-  __shared__ __attribute__((aligned(16))) float v[256];
+  __shared__ __attribute__((aligned(16))) uint32_t v[256];
   __shared__ float quartile, most;
   const int n = blockIdx.x, p = threadIdx.x;
   const int rows = M < kSampleRows ? (int)M : kSampleRows;
   const bool on = p < rows;
-  auto rank_of = [&](float x) {   // place of the thread's value among the sample's, in v (no other is below infinity)
+  // place of the thread's value among the sample's: by the top 24 bits of its
+  // order, then by row (256 comparisons, of keys that differ)
+  auto rank_of = [&](float x) {
+    const uint32_t u = __float_as_uint(x);
+    const uint32_t key = on ? ((u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u)) & ~255u) | (uint32_t)p : ~0u;
+    v[p] = key;
+    __syncthreads();
     int rank = 0;
 #pragma unroll 8
     for (int e = 0; e < 256; e += 4) {
-      const floatx4 w = *reinterpret_cast<const floatx4 *>(v + e);
+      const u32x4 w = *reinterpret_cast<const u32x4 *>(v + e);
 #pragma unroll
-      for (int u = 0; u < 4; ++u) rank += w[u] < x || (w[u] == x && e + u < p) ? 1 : 0;
+      for (int u = 0; u < 4; ++u) rank += w[u] < key ? 1 : 0;
     }
-    return rank;
+    __syncthreads();
+    return on ? rank : -1;
   };
-  const float x = on ? X[(int64_t)p * M / rows * N + n] : INFINITY;
-  v[p] = x;
+  const float x = on ? X[(int64_t)p * M / rows * N + n] : 0.f;
+  if (rank_of(x) == rows / 2) mean[n] = most = x;
   __syncthreads();
-  if (on && rank_of(x) == rows / 2) mean[n] = most = x;
-  __syncthreads();
-  const float far = on ? fabsf(x - most) : INFINITY;
-  __syncthreads();
-  v[p] = far;
-  __syncthreads();
-  const int rank = on ? rank_of(far) : -1;
+  const float far = fabsf(x - most);
+  const int rank = rank_of(far);   // (every thread has read most)
   if (rank == rows * 3 / 4) quartile = far;
   if (rank == (rows > 4 ? rows - 4 : rows - 1)) most = far;
   __syncthreads();
@@ -148,7 +152,9 @@ __global__ void __launch_bounds__(256) knn_sample_kernel(const float *__restrict
 }
 
 // Class of a row by its squared norm: a factor of two to a class
-__device__ __forceinline__ int norm_class(float norm2) { return (int)(__float_as_uint(norm2) >> 23); }
+__device__ __forceinline__ int norm_class(float norm2) {
+  return (int)(__float_as_uint(norm2) >> 23 & (kNormClasses - 1));   // (a NaN's sign aside)
+}
 
 __device__ __forceinline__ float clamp_half(float t) { return fminf(fmaxf(t, -65504.f), 65504.f); }
 
@@ -741,7 +747,8 @@ struct FinishArgs {
   int nseg;
   int32_t *fails;                // [0] count, then query ids
   float *limits;                 // of the fails: the least value of a candidate of the answer (-inf: none)
-  int32_t *pilot;                // [3]: answers that lists of 8, 16, 32 would not certify (NULL: no pilot)
+  int32_t *pilot;                // [2][3]: answers that lists of 8, 16, 32 would not certify with one and
+                                 // (by these values) three segments (NULL: no pilot)
 };
 
 // The rows' own figures that bound the error of a query's values, in FP64 and
@@ -755,14 +762,14 @@ struct QueryBound {
 __device__ __forceinline__ double value_error(const FinishArgs &A, const QueryBound &B, double x, double dist,
                                               int nseg) {
   const float limit = (float)(x * x * (1 + B.nerr) * kUp);
-  const double rx = __uint_as_float(A.xs->res[norm_class(limit) & (kNormClasses - 1)]);
+  const double rx = __uint_as_float(A.xs->res[norm_class(limit)]);
   const double cross = B.nq * rx + B.rq * (x + rx);   // q.c less its high parts' product
   // the largest partial sum: some of q.c's terms, those of |c|^2 and the rest of
   // no more than dist |c|, and the start value, of the other sign
   const double any = 0.5 * x * x + B.nq * x, close = x * x + dist * x;
   const double sum = (close < any ? close : any) + 2 * cross;
-  // one rounding to a product, of no more than 2^-23 of that, all of them one way
-  const double n = (double)A.nk * FK + 17;
+  // one rounding to a feature, of no more than 2^-23 of that, all of them one way
+  const double n = (double)A.N + 17;
   double err = n * kU23 * sum + 0.5 * B.nerr * x * x;   // (and the start value's own)
   if (nseg == 1) {
     err += kUp * cross;
@@ -876,7 +883,7 @@ __global__ void __launch_bounds__(256) knn_finish_kernel(FinishArgs A) {
     const double r = (B.nq + sqrt(top)) * kUp, x = r < reach ? r : reach;
     const double shift = 0.5 * kU23 * (B.nq + x), dist = (sqrt(top) + shift) * kUp;
     const double err = value_error(A, B, x, dist, A.nseg);
-    auto certified = [&](uint64_t last) {
+    auto certified = [&](uint64_t last, double err) {
       const double least = n2 * (1 - B.nerr) - 2.0 * ((double)key_value(last) + err);
       const double moved = sqrt(least > 0 ? least : 0.0) - shift;
       return top < (moved > 0 ? moved * moved : 0.0) * (1 - 1e-12);
@@ -887,11 +894,14 @@ __global__ void __launch_bounds__(256) knn_finish_kernel(FinishArgs A) {
       return found >= A.M - (own >= 0 && own < A.M ? 1 : 0);
     };
     if (A.pilot) {
+      const double err3 = value_error(A, B, x, dist, 3);
       for (int l = 0; l < 3; ++l) {
         const int len = 8 << l;
-        if (len <= KP && (found < len ? !complete() : len < A.k || !certified(nth[l]))) atomicAdd(&A.pilot[l], 1);
+        if (len > KP) continue;
+        if (found < len ? !complete() : len < A.k || !certified(nth[l], err)) atomicAdd(&A.pilot[l], 1);
+        if (found < len ? !complete() : len < A.k || !certified(nth[l], err3)) atomicAdd(&A.pilot[3 + l], 1);
       }
-    } else if (found < KP ? !complete() : !certified(last)) {
+    } else if (found < KP ? !complete() : !certified(last, err)) {
       const int32_t at = atomicAdd(&A.fails[0], 1);
       A.fails[1 + at] = (int32_t)orig;
       // what three segments give a candidate as near as the k-th here, at least
@@ -979,7 +989,8 @@ __global__ void __launch_bounds__(256) knn_brute_kernel(const float *__restrict_
                                                         const float *__restrict__ Q, int64_t nq,
                                                         const int32_t *__restrict__ rows, int self_mode,
                                                         const int32_t *__restrict__ self, int k, int splits,
-                                                        uint64_t *__restrict__ part) {
+                                                        uint64_t *__restrict__ part, int32_t *__restrict__ out_idx,
+                                                        float *__restrict__ out_dist) {
   __shared__ uint64_t keys[kBruteQ][256];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t f0 = (int64_t)blockIdx.x * kBruteQ;
@@ -1007,26 +1018,35 @@ __global__ void __launch_bounds__(256) knn_brute_kernel(const float *__restrict_
       const float w = u - v;
       d[f] = fmaf(w, w, d[f]);
     };
-    int kk = 0;
-    if (vec4)
-      for (; kk + 32 <= N; kk += 32) {
-        float4 v[8];
+    // CH features at a time, their loads on their way together
+    auto chunk = [&](int kk, auto ch, auto vec) __attribute__((always_inline)) {
+      constexpr int CH = decltype(ch)::value;
+      float v[CH];
+      if constexpr (decltype(vec)::value) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = *reinterpret_cast<const float4 *>(x + kk + 4 * j);
+        for (int j = 0; j < CH; j += 4) {
+          const float4 w = *reinterpret_cast<const float4 *>(x + kk + j);
+          v[j] = w.x;
+          v[j + 1] = w.y;
+          v[j + 2] = w.z;
+          v[j + 3] = w.w;
+        }
+      } else {
 #pragma unroll
-        for (int f = 0; f < kBruteQ; ++f)
-#pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            add(f, qrow[f][kk + 4 * j], v[j].x);
-            add(f, qrow[f][kk + 4 * j + 1], v[j].y);
-            add(f, qrow[f][kk + 4 * j + 2], v[j].z);
-            add(f, qrow[f][kk + 4 * j + 3], v[j].w);
-          }
+        for (int j = 0; j < CH; ++j) v[j] = x[kk + j];
       }
-    for (; kk < N; ++kk) {
-      const float v = x[kk];
 #pragma unroll
-      for (int f = 0; f < kBruteQ; ++f) add(f, qrow[f][kk], v);
+      for (int f = 0; f < kBruteQ; ++f)
+#pragma unroll
+        for (int j = 0; j < CH; ++j) add(f, qrow[f][kk + j], v[j]);
+    };
+    int kk = 0;
+    if (vec4) {
+      for (; kk + 32 <= N; kk += 32) chunk(kk, std::integral_constant<int, 32>{}, std::true_type{});
+      for (; kk < N; kk += 4) chunk(kk, std::integral_constant<int, 4>{}, std::true_type{});
+    } else {
+      for (; kk + 8 <= N; kk += 8) chunk(kk, std::integral_constant<int, 8>{}, std::false_type{});
+      for (; kk < N; ++kk) chunk(kk, std::integral_constant<int, 1>{}, std::false_type{});
     }
 #pragma unroll
     for (int f = 0; f < kBruteQ; ++f)
@@ -1043,7 +1063,9 @@ __global__ void __launch_bounds__(256) knn_brute_kernel(const float *__restrict_
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     const int64_t f = f0 + 2 * wave + h;
-    if (f < nq && lane < k) part[(f * splits + blockIdx.y) * k + lane] = best[h];
+    if (f >= nq) continue;
+    if (splits == 1) put_answer(best[h], rows ? (int64_t)rows[f] : f, lane, k, out_idx, out_dist);
+    else if (lane < k) part[(f * splits + blockIdx.y) * k + lane] = best[h];
   }
 }
 
@@ -1138,24 +1160,57 @@ float sample_scale(float spread, float absmax) {
   return ldexpf(1.f, sh);
 }
 
-// List length: the pilot runs kPilotTiles query tiles spread over the call and
-// counts the answers that lists of 8, 16 and (when k asks for those anyway) 32
-// would not certify.  A failed answer costs three times its share of the sweep, a
-// longer list more hits (at 400,000 x 100 lists of 8, 16 and 32 sweep in 62, 74
-// and about 90 ms, against 45 ms without any hit): 8 while at most one answer in 16
-// fails, then 16 while at most one in 6 does, then 32; and where half of them fail
-// with 16, the shortest, as a longer list would not help them.  Calls of fewer
-// query tiles than CUs go without a pilot, which takes as long as it takes a block
-// to fill its lists (1.4 ms with lists of 32) and leaves most CUs idle: 50,000 x
-// 128, k 2 / 5 / 10 / 20: 2.8 / 3.4 / 5.0 / 7.3 ms with one, 2.4 / 2.7 / 3.9 / 5.9
-// without.  Wide rows keep it from 4 kPilotTiles tiles on, as their failed answers
-// cost more than the pilot (20,000 x 500, k 10: 2.9 ms with it, 3.6 without).  With
-// fewer than kFewTiles candidate tiles (a coarse quantizer's centroids) the lists
-// cost more than the products, so short lists and three segments are best (200,000
-// queries against 512 centroids of width 100).
+// List length and segments: the pilot runs kPilotTiles query tiles spread over the
+// call with one segment and counts the answers that lists of 8, 16 and (when k asks
+// for those anyway) 32 would not certify with its error and with that of three.  A
+// tile costs its products (as in choose_splits; the band's for the share that
+// fails) and, more for a longer list, its hits: kListCost, in the same us (at
+// 400,000 x 100 lists of 8, 16 and 32 sweep in 62, 74 and about 90 ms, against 45
+// ms without any hit); the cheapest is taken.  Three segments pay where they certify what one
+// does not: 200,000 x 100, k 28: 46 ms against 64; 200,000 x 3, k 2: 13 against 18.
+// Calls of fewer query tiles than CUs go without a pilot, which takes as long as it
+// takes a block to fill its lists (1.4 ms with lists of 32) and leaves most CUs
+// idle: 50,000 x 128, k 2 / 5 / 10 / 20: 2.8 / 3.4 / 5.0 / 7.3 ms with one, 2.4 / 2.7
+// / 3.9 / 5.9 without.  Wide rows keep it from 4 kPilotTiles tiles on, as their
+// failed answers cost more than the pilot (20,000 x 500, k 10: 2.9 ms with it, 3.6
+// without).  With fewer than kFewTiles candidate tiles (a coarse quantizer's
+// centroids) the lists cost more than the products, so short lists and three
+// segments are best (200,000 queries against 512 centroids of width 100).
+constexpr double kListCost[3] = {1.6, 2.8, 4.3};
 constexpr int kWidePilot = 256;
 constexpr int64_t kPilotTiles = 8;
 constexpr int64_t kFewTiles = 16;
+
+// Ranges of the candidates, for blocks of kBruteQ queries: to fill the chip
+int64_t brute_splits(int64_t nq, int64_t M) {
+  const int64_t groups = (nq + kBruteQ - 1) / kBruteQ, tiles = (M + 255) / 256;
+  int64_t splits = 4 * kCus / groups;
+  splits = splits < 1 ? 1 : (splits > 256 ? 256 : splits);
+  return splits < tiles ? splits : tiles;
+}
+
+// Whether a call's exact distances take no longer than the filter and what goes
+// with it.  In us, fitted to calls of 100 to 200,000 candidates, 1 to 200,000
+// queries, 2 to 784 features and k 1, 5 and 28, so that it errs towards the filter:
+// the filter takes 310 (600 with lists of 32) against few candidates, else 520
+// (1,500), for a query's list 2 to 11 ns, for the operands 12 ps a feature of a
+// query and 6 of a candidate, and for a pair of tiles as in choose_splits; the
+// distances take 110, 64 fs a pair and feature (81 % of the vector ALU) and as much
+// as 17 features for a pair's way through the lists.  300 x 3, k 2: 273 -> 97 us
+// (195 with the search before the filter); 128 x 64 and 50,000 queries: 356 -> 228
+// (252); 1,000 x 20: 307 -> 104.
+bool direct_pays(int64_t M, int N, int64_t nq, int k, bool few, bool same) {
+  const double pairs = (double)((nq + kBruteQ - 1) / kBruteQ * kBruteQ) * (double)((M + 255) / 256 * 256);
+  const double blocks = (double)((nq + kBruteQ - 1) / kBruteQ) * (double)brute_splits(nq, M);
+  const double idle = blocks < 4 * kCus ? 4 * kCus / blocks : 1.0;
+  const double stages = (double)((N + FK - 1) / FK) * (few ? 3 : 1);
+  const double filter = (few ? (k > 12 ? 600.0 : 310.0) : (k > 12 ? 1500.0 : 520.0)) +
+                        (double)nq * (k > 12 ? 1.1e-2 : (k > 4 ? 3e-3 : 1.9e-3)) + 1.2e-5 * (double)nq * N +
+                        (same ? 0.0 : 6e-6 * (double)M * N) +
+                        pairs * (0.9 * stages + 0.7) / (FT * FT * (double)kCus);
+  const double direct = 110.0 + 6.4e-8 * pairs * (N + 17) * idle + 2.7e-6 * (double)nq * N;
+  return direct <= filter;
+}
 
 // The band's hits: so many are kept of a query, and so many ids in all (they fit
 // a buffer that the library keeps)
@@ -1175,6 +1230,7 @@ int KnnSearch::open(int64_t M_, int N_, const float *Q_, int64_t nq_, const floa
   s = s_;
   S.stream = s_;
   few = (M + FT - 1) / FT < kFewTiles;
+  direct = direct_pays(M, N, nq, k, few, same);
   const int64_t tiles = (M + FT - 1) / FT, nx = knn_image_halves(M, N), nqi = knn_image_halves(nq, N);
   Carve V;
   auto image = [&](KnnImage *im, int64_t halves) {
@@ -1182,20 +1238,22 @@ int KnnSearch::open(int64_t M_, int N_, const float *Q_, int64_t nq_, const floa
     im->halves = halves;
   };
   uint32_t *spread = nullptr;   // of the sample, then the largest |coordinate|
-  image(&ch, nx);
-  V.add(&start, tiles * FT);
-  V.add(&xstats, 1);
-  V.add(&fails, nq + 1);
-  V.add(&limits, nq);
-  V.add(&pilot, 3);
-  V.add(&mean, N);
   V.add(&spread, 2);
-  V.add(&qnorm, nq);
-  V.add(&qres, nq);
-  if (few) image(&cl, nx);
-  if (!same) {
-    image(&qh, nqi);
-    if (few) image(&ql, nqi);
+  if (!direct) {
+    image(&ch, nx);
+    V.add(&start, tiles * FT);
+    V.add(&xstats, 1);
+    V.add(&fails, nq + 1);
+    V.add(&limits, nq);
+    V.add(&pilot, 6);
+    V.add(&mean, N);
+    V.add(&qnorm, nq);
+    V.add(&qres, nq);
+    if (few) image(&cl, nx);
+    if (!same) {
+      image(&qh, nqi);
+      if (few) image(&ql, nqi);
+    }
   }
   const int rc = V.get(S, "operands of the search");
   if (rc) return rc;
@@ -1208,7 +1266,7 @@ int KnnSearch::open(int64_t M_, int N_, const float *Q_, int64_t nq_, const floa
   HIPCHK(launch_fill_i32((int32_t *)spread, 2, 0, s));
   HIPCHK(launch_absmax(sample, sample_rows * N, spread + 1, s));
   if (Q != sample || nq != sample_rows) HIPCHK(launch_absmax(Q, nq * N, spread + 1, s));
-  knn_sample_kernel<<<(unsigned)N, 256, 0, s>>>(sample, sample_rows, N, mean, spread);
+  if (!direct) knn_sample_kernel<<<(unsigned)N, 256, 0, s>>>(sample, sample_rows, N, mean, spread);
   HIPCHK(hipGetLastError());
   HIPCHK(hipMemcpyAsync(bits, spread, sizeof bits, hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
@@ -1219,6 +1277,7 @@ int KnnSearch::open(int64_t M_, int N_, const float *Q_, int64_t nq_, const floa
 }
 
 int KnnSearch::run(const float *X, int self_mode, const int32_t *self, int32_t *idx, float *dist) {
+  if (direct) return rank_all(X, nullptr, nq, self_mode, self, idx, dist);
   const int nk = (N + FK - 1) / FK;
   const int64_t tiles = (M + FT - 1) / FT, nqb = (nq + FT - 1) / FT;
   int kp = list_length(k), rc;
@@ -1264,6 +1323,12 @@ int KnnSearch::run(const float *X, int self_mode, const int32_t *self, int32_t *
   g.fails = fails;
   g.limits = limits;
 
+  Scratch R(s);   // of this run
+  KnnImage low_c = cl;
+  auto image = [&](KnnImage *im, int64_t rows, const char *what) -> int {
+    im->halves = knn_image_halves(rows, N);
+    return R.get(&im->p, im->halves, what);
+  };
   // the query tiles qb0, qb0 + step, .., of images `images`
   auto shape = [&](int64_t qb0, int64_t step, int64_t n, int nseg, int list, const KnnImage &images) -> int {
     f.qb0 = g.qb0 = qb0;
@@ -1291,8 +1356,8 @@ int KnnSearch::run(const float *X, int self_mode, const int32_t *self, int32_t *
     return IVHD_OK;
   };
   if (!few && nqb >= (N > kWidePilot ? 4 * kPilotTiles : kCus)) {
-    int32_t bad[3];
-    HIPCHK(launch_fill_i32(pilot, 3, 0, s));
+    int32_t bad[6];
+    HIPCHK(launch_fill_i32(pilot, 6, 0, s));
     g.pilot = pilot;
     const int want = kp;
     kp = kp < 16 ? 16 : kp;
@@ -1300,11 +1365,32 @@ int KnnSearch::run(const float *X, int self_mode, const int32_t *self, int32_t *
     g.pilot = nullptr;
     HIPCHK(hipMemcpyAsync(bad, pilot, sizeof bad, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
-    const int32_t all = (int32_t)(kPilotTiles * FT);
-    if (kp == 16) {
-      if (bad[1] > all / 2) kp = want;
-      else if (want == 8 && bad[0] <= all / 16) kp = 8;
-      else if (bad[1] > all / 6) kp = 32;
+    double least = 1e300;
+    int segs = 1;
+    for (int l = want == 8 ? 0 : (want == 16 ? 1 : 2); l < 3; ++l)
+      for (int three = 0; three < 2; ++three) {
+        const bool seen = (8 << l) <= (want == 32 ? 32 : 16);   // else, of 32: a third, or as many if half fail with 16
+        const double share = bad[3 * three + (seen ? l : 1)] / (double)(kPilotTiles * FT);
+        const double fails = seen || share > 0.5 ? share : share / 3;
+        const double one = 0.9 * nk + 0.7, all = 2.7 * nk + 0.7;   // a tile's products and values
+        const double cost = kListCost[l] + (three ? all : one) + all * fails;
+        if (cost < least) {
+          least = cost;
+          kp = 8 << l;
+          segs = three ? 3 : 1;
+        }
+      }
+    if (segs == 3) {
+      if ((rc = image(&low_c, M, "candidate operands (low)"))) return rc;
+      HIPCHK(launch_knn_split(X, M, N, nullptr, mean, scale, KnnImage{}, low_c, nullptr, nullptr, nullptr, nullptr, s));
+      KnnImage low = low_c;
+      if (!same) {
+        if ((rc = image(&low, nq, "query operands (low)"))) return rc;
+        HIPCHK(launch_knn_split(Q, nq, N, nullptr, mean, scale, KnnImage{}, low, nullptr, nullptr, nullptr, nullptr, s));
+      }
+      f.Cl = low_c.p;
+      f.Ql = low.p;
+      g.nseg = 3;
     }
   } else if (!few && kp == 8) {
     kp = 16;
@@ -1328,23 +1414,19 @@ int KnnSearch::run(const float *X, int self_mode, const int32_t *self, int32_t *
   // The answers that are not certified: all candidates whose value, of three
   // segments, may be an answer's are ranked by their FP32 distances, a batch of
   // queries at a time
-  Scratch R(s);   // of this run
   const int32_t *again = fails + 1;
-  KnnImage low_c = cl, high_q, low_q;
-  auto image = [&](KnnImage *im, int64_t rows, const char *what) -> int {
-    im->halves = knn_image_halves(rows, N);
-    return R.get(&im->p, im->halves, what);
-  };
+  KnnImage high_q, low_q;
   const int64_t cap = M < kBandHits ? M : kBandHits, all_rows = (failed + FT - 1) / FT * (int64_t)FT;
   int64_t batch = kBandIds / cap / FT * FT;
   batch = batch < all_rows ? batch : all_rows;
   int32_t *left, *count, *ids;
+  const bool made = low_c.p != nullptr;
   if ((rc = image(&high_q, failed, "query operands (high)")) || (rc = image(&low_q, failed, "query operands (low)")) ||
-      (!few && (rc = image(&low_c, M, "candidate operands (low)"))) ||
+      (!made && (rc = image(&low_c, M, "candidate operands (low)"))) ||
       (rc = R.get(&left, (int64_t)failed + 1, "queries left")) || (rc = R.get(&count, batch, "hits of a query")) ||
       (rc = R.get(&ids, batch * cap, "hits")))
     return rc;
-  if (!few)
+  if (!made)
     HIPCHK(launch_knn_split(X, M, N, nullptr, mean, scale, KnnImage{}, low_c, nullptr, nullptr, nullptr, nullptr, s));
   HIPCHK(launch_knn_split(Q, failed, N, again, mean, scale, high_q, low_q, nullptr, nullptr, nullptr, nullptr, s));
   HIPCHK(launch_fill_i32(left, 1, 0, s));
@@ -1368,15 +1450,19 @@ int KnnSearch::run(const float *X, int self_mode, const int32_t *self, int32_t *
   }
   if ((rc = read_count(left, &failed)) || failed == 0) return rc;
 
-  const int64_t groups = (failed + kBruteQ - 1) / kBruteQ;
-  int64_t splits = 4 * kCus / groups;
-  splits = splits < 1 ? 1 : (splits > 64 ? 64 : splits);
-  if (splits > tiles) splits = tiles;
-  uint64_t *bp;
-  if ((rc = R.get(&bp, failed * splits * k, "candidate lists (all candidates)"))) return rc;
-  knn_brute_kernel<<<dim3((unsigned)groups, (unsigned)splits), 256, 0, s>>>(X, M, N, Q, failed, left + 1, self_mode, self,
-                                                                            k, (int)splits, bp);
-  knn_brute_merge_kernel<<<grid_for(failed, 4), 256, 0, s>>>(bp, failed, left + 1, k, (int)splits, idx, dist);
+  return rank_all(X, left + 1, failed, self_mode, self, idx, dist);
+}
+
+int KnnSearch::rank_all(const float *X, const int32_t *rows, int64_t n, int self_mode, const int32_t *self, int32_t *idx,
+                        float *dist) {
+  const int64_t groups = (n + kBruteQ - 1) / kBruteQ, splits = brute_splits(n, M);
+  Scratch R(s);
+  uint64_t *bp = nullptr;
+  int rc;
+  if (splits > 1 && (rc = R.get(&bp, n * splits * k, "candidate lists (all candidates)"))) return rc;
+  knn_brute_kernel<<<dim3((unsigned)groups, (unsigned)splits), 256, 0, s>>>(X, M, N, Q, n, rows, self_mode, self, k,
+                                                                            (int)splits, bp, idx, dist);
+  if (splits > 1) knn_brute_merge_kernel<<<grid_for(n, 4), 256, 0, s>>>(bp, n, rows, k, (int)splits, idx, dist);
   HIPCHK(hipGetLastError());
   HIPCHK(hipStreamSynchronize(s));
   return IVHD_OK;

@@ -73,12 +73,15 @@ struct KnnSearch {
   // stream.  It may be called again with as many other candidates and the same
   // queries, which are prepared once.
   int run(const float *X, int self_mode, const int32_t *self, int32_t *idx, float *dist);
+  // the answers of queries rows[0..n) (NULL: all) from all exact distances
+  int rank_all(const float *X, const int32_t *rows, int64_t n, int self_mode, const int32_t *self, int32_t *idx,
+               float *dist);
 
   Scratch S;
   int64_t M = 0, nq = 0;
   int N = 0, k = 0;
   const float *Q = nullptr;
-  bool same = false, few = false, queries_ready = false;
+  bool same = false, few = false, direct = false, queries_ready = false;
   float scale = 1.f;
   hipStream_t s = nullptr;
   KnnImage ch, cl, qh, ql;   // operands, high and low; the low ones only with few
