@@ -323,8 +323,9 @@ int ivhd_enc_embed(ivhd_enc *e, const uint16_t *d_x16, int64_t rows, float *d_z)
   if (!enc_live(e)) return fail(IVHD_ESTATE, "invalid encoder");
   if (rows < 0) return fail(IVHD_EINVAL, "rows = %lld < 0", (long long)rows);
   if (rows > 0 && (!d_x16 || !d_z)) return fail(IVHD_EINVAL, "d_x16 and d_z must not be NULL");
-  // the fused pass needs no room for activations: all rows at once
-  const int64_t step = mlp_ok(e->n_in, e->h1, e->h2) ? (int64_t)1 << 30 : e->r_cap;
+  // the fused pass needs no room for activations: as many rows as one launch
+  // takes (fewer than 2^32 threads, of which a block has 512 for 32 rows at least)
+  const int64_t step = mlp_ok(e->n_in, e->h1, e->h2) ? (int64_t)1 << 27 : e->r_cap;
   for (int64_t r0 = 0; r0 < rows; r0 += step) {
     const int64_t R = rows - r0 < step ? rows - r0 : step;
     int rc = forward_rows(e, d_x16 + r0 * e->n_in, e->n_in, R, d_z + 2 * r0, false);
