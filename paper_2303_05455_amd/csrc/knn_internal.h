@@ -2,6 +2,7 @@
 // the stateless calls.  Not part of the public ABI.
 #pragma once
 
+#include <new>
 #include <vector>
 
 #include "ivhd_internal.h"
@@ -18,6 +19,12 @@ struct Scratch {
   ~Scratch() { dev_free_all(bufs.data(), bufs.size(), stream); }
   template <typename T>
   int get(T **p, size_t n, const char *what) {
+    *p = nullptr;
+    try {   // room for it first: nothing is thrown across the ABI
+      bufs.reserve(bufs.size() + 1);
+    } catch (const std::bad_alloc &) {
+      return fail(IVHD_ENOMEM, "host memory for the buffer list (%s)", what);
+    }
     int rc = dev_alloc(p, n, what);
     if (!rc) bufs.push_back(*p);
     return rc;
@@ -26,22 +33,25 @@ struct Scratch {
 
 // several buffers out of one allocation (each on a 256-byte boundary)
 struct Carve {
+  static constexpr int kMost = 16;
   struct Part {
     void **p;
     size_t at;
-  };
-  std::vector<Part> parts;
+  } parts[kMost];
+  int n_parts = 0;
   size_t bytes = 0;
   template <typename T>
   void add(T **p, size_t n) {
-    parts.push_back({reinterpret_cast<void **>(p), bytes});
+    if (n_parts < kMost) parts[n_parts] = {reinterpret_cast<void **>(p), bytes};
+    ++n_parts;
     bytes += (n * sizeof(T) + 255) / 256 * 256;
   }
   int get(Scratch &S, const char *what) {
+    if (n_parts > kMost) return fail(IVHD_ESTATE, "%d buffers in one allocation (%s)", n_parts, what);
     unsigned char *base;
     const int rc = S.get(&base, bytes, what);
     if (!rc)
-      for (const Part &q : parts) *q.p = base + q.at;
+      for (int i = 0; i < n_parts; ++i) *parts[i].p = base + parts[i].at;
     return rc;
   }
 };

@@ -176,7 +176,16 @@ void dev_free_all(void *const *bufs, size_t n, hipStream_t stream) {
   if (!any) return;
   try {
     put(bufs, n, stream);
-  } catch (const std::bad_alloc &) {   // nothing was moved: they stay allocated
+  } catch (const std::bad_alloc &) {   // nothing was moved: back to the device, which needs no memory
+    Pool &P = pool();
+    for (size_t i = 0; i < n; ++i) {
+      if (!bufs[i]) continue;
+      {
+        std::lock_guard<std::mutex> lk(P.mu);
+        P.used.erase(bufs[i]);
+      }
+      (void)hipFree(bufs[i]);
+    }
   }
 }
 

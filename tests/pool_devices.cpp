@@ -1,16 +1,19 @@
 // Host check of the device buffer pool (pool.hip) against a stand-in for the
 // HIP runtime with two devices: a buffer that work still uses must not be
-// handed out.  Built and run by test_pool_devices.py.
+// handed out; and without host memory nothing is thrown or lost.  Built and run
+// by test_pool_devices.py.
 #include <cstdio>
 #include <cstdlib>
 #include <map>
+#include <new>
 #include <set>
 
-#include "ivhd_internal.h"
+#include "knn_internal.h"
 
 namespace {
 int g_device = 0;
 bool g_capturing = false;
+bool g_no_memory = false;   // operator new throws
 std::map<void *, int> g_of;                              // allocation -> device
 std::map<std::pair<int, hipStream_t>, std::set<void *>> g_busy;   // (device, stream): what queued work uses
 
@@ -27,7 +30,20 @@ bool busy(void *p) {
 hipStream_t stream_no(int k) { return reinterpret_cast<hipStream_t>(static_cast<uintptr_t>(k)); }
 }  // namespace
 
+void *operator new(size_t n) {
+  void *p = g_no_memory ? nullptr : std::malloc(n);
+  if (!p) throw std::bad_alloc();
+  return p;
+}
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, size_t) noexcept { std::free(p); }
+
+namespace ivhd {
+int fail(int code, const char *, ...) { return code; }
+}  // namespace ivhd
+
 extern "C" {
+const char *hipGetErrorString(hipError_t) { return ""; }
 hipError_t hipGetDevice(int *d) {
   *d = g_device;
   return hipSuccess;
@@ -38,8 +54,11 @@ hipError_t hipSetDevice(int d) {
   return hipSuccess;
 }
 hipError_t hipMalloc(void **p, size_t bytes) {
+  const bool none = g_no_memory;   // the device has memory of its own
+  g_no_memory = false;
   *p = std::malloc(bytes);
   g_of[*p] = g_device;
+  g_no_memory = none;
   return hipSuccess;
 }
 hipError_t hipFree(void *p) {   // waits for the device of the buffer
@@ -91,6 +110,28 @@ int main() {
   g_capturing = true;
   ivhd::dev_free(p, stream_no(16));
   check(g_of.count(p) == 0, "freed while a capture is on");
+  g_capturing = false;
+  // no host memory: a failure code, and a release that gives the buffer back
+  {
+    ivhd::Scratch S(stream_no(16));
+    float *q = nullptr, *r = nullptr;
+    check(S.get(&q, 3000000, "a buffer") == IVHD_OK, "allocates");
+    const size_t had = g_of.size();
+    g_no_memory = true;
+    check(S.get(&r, 100, "another") == IVHD_ENOMEM && r == nullptr && g_of.size() == had, "refuses without host memory");
+    S.~Scratch();
+    g_no_memory = false;
+    new (&S) ivhd::Scratch(stream_no(16));
+    check(g_of.count(q) == 0, "released without host memory");
+    void *again = nullptr;
+    check(ivhd::pool_get(&again, 12000000) == hipSuccess && g_of.count(again) == 1, "allocates again");
+    ivhd::dev_free(again, stream_no(16));
+  }
+  ivhd::Carve many;
+  void *parts[20];
+  for (void *&part : parts) many.add(reinterpret_cast<unsigned char **>(&part), 10);
+  ivhd::Scratch S;
+  check(many.get(S, "too many") == IVHD_ESTATE, "more parts than there is room for");
   std::printf("ok\n");
   return 0;
 }
