@@ -476,6 +476,14 @@ int ivhd_gemm_bf16(const uint16_t *d_a, const uint16_t *d_b, int64_t M, int64_t 
                    const float *d_bias, const uint16_t *d_mask, int64_t ldm, void *d_c, int64_t ldc,
                    int32_t splits, float *d_work, void *stream);
 
+/* ivhd_trim: gives the device memory that waits inside the library back to
+ * the device.  Buffers of destroyed objects and of finished calls wait for
+ * the next one: at most 512 MiB on all devices together, none above 128 MiB,
+ * and each until 64 objects or calls have ended without a request for its
+ * size.  Another allocator in the process that runs out of memory can have
+ * them this way.  Live objects keep theirs.                                */
+int ivhd_trim(void);
+
 /* ivhd_last_error: message of the last failure on this thread ("" if none). */
 const char *ivhd_last_error(void);
 

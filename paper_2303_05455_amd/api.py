@@ -26,7 +26,7 @@ __all__ = [
     "ivhd_grad_edges_noalloc", "ivhd_set_adaptive",
     "ivhd_get_adaptive", "ivhd_rnn_mask", "ivhd_set_adam", "ivhd_ivf_train", "ivhd_ivf_search",
     "ivf_knn_graph", "ivhd_eval_neighbours", "ivhd_eval_ranks", "ivhd_eval_scores", "ivhd_probe_gather",
-    "ivhd_probe_atomic",
+    "ivhd_probe_atomic", "ivhd_trim",
 ]
 
 
@@ -333,6 +333,12 @@ def ivf_knn_graph(x: torch.Tensor, k: int, nlist: int, nprobe: int, n_iter: int 
     C, a = ivhd_ivf_train(x, nlist, n_iter)
     self_idx = torch.arange(x.shape[0], dtype=torch.int32, device=x.device)
     return ivhd_ivf_search(x, C, a, x, k, nprobe, self_idx=self_idx)
+
+
+def ivhd_trim() -> None:
+    """Give the device memory that waits inside the library back to the device
+    (at most 512 MiB of destroyed objects and finished calls)."""
+    check(_lib.load().ivhd_trim())
 
 
 def ivhd_last_error() -> str:

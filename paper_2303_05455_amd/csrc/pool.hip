@@ -16,8 +16,8 @@
 // whole device: hipDeviceSynchronize breaks
 // the graph captures of other threads.  What waits is bounded (kMaxIdle),
 // buffers above kMaxBlock never wait, a buffer that was not asked for again
-// during kMaxAge releases is given back to the device, and when an allocation
-// fails all of them are before it is tried again.
+// during kMaxAge releases is given back to the device, when an allocation
+// fails all of them are before it is tried again, and so they are by ivhd_trim.
 #include <algorithm>
 #include <mutex>
 #include <new>
@@ -65,6 +65,13 @@ void give_back(const std::vector<Block> &blocks) {
   for (const Block &b : blocks) (void)hipFree(b.p);
 }
 
+// what waits, out of the pool
+void take_idle(Pool &P, std::vector<Block> &idle) {
+  std::lock_guard<std::mutex> lk(P.mu);
+  idle.swap(P.idle);
+  P.idle_bytes = 0;
+}
+
 // the calls below without their guards against std::bad_alloc
 
 hipError_t get(void **p, size_t bytes) {
@@ -89,11 +96,7 @@ hipError_t get(void **p, size_t bytes) {
   if (e == hipErrorOutOfMemory) {
     (void)hipGetLastError();
     std::vector<Block> idle;
-    {
-      std::lock_guard<std::mutex> lk(P.mu);
-      idle.swap(P.idle);
-      P.idle_bytes = 0;
-    }
+    take_idle(P, idle);
     if (idle.empty()) return e;
     give_back(idle);
     e = hipMalloc(p, bytes);
@@ -190,3 +193,10 @@ void dev_free_all(void *const *bufs, size_t n, hipStream_t stream) {
 }
 
 }  // namespace ivhd
+
+extern "C" int ivhd_trim(void) {
+  std::vector<ivhd::Block> idle;
+  ivhd::take_idle(ivhd::pool(), idle);
+  ivhd::give_back(idle);
+  return IVHD_OK;
+}

@@ -127,6 +127,14 @@ int main() {
     check(ivhd::pool_get(&again, 12000000) == hipSuccess && g_of.count(again) == 1, "allocates again");
     ivhd::dev_free(again, stream_no(16));
   }
+  // trimmed: what waits goes back, what is in use does not
+  void *held = nullptr, *idle = nullptr;
+  (void)hipSetDevice(1);
+  check(ivhd::pool_get(&held, 4000) == hipSuccess && ivhd::pool_get(&idle, 9000) == hipSuccess, "allocates");
+  ivhd::dev_free(idle, nullptr);
+  check(g_of.count(idle) == 1, "a released buffer waits");
+  check(ivhd_trim() == IVHD_OK && g_of.size() == 1 && g_of.count(held) == 1, "only the buffer in use is left");
+  ivhd::dev_free(held, nullptr);
   ivhd::Carve many;
   void *parts[20];
   for (void *&part : parts) many.add(reinterpret_cast<unsigned char **>(&part), 10);
