@@ -55,6 +55,7 @@
 #include <cfloat>
 #include <cmath>
 #include <cstring>
+#include <numeric>
 #include <type_traits>
 
 #include "knn_internal.h"
@@ -149,6 +150,16 @@ __global__ void __launch_bounds__(256) knn_sample_kernel(const float *__restrict
   __syncthreads();
   const float q = quartile > 0.f ? quartile : most;
   if (p == 0 && q > 0.f) atomicMax(spread, __float_as_uint(q));   // non-negative floats compare as integers
+}
+
+// The order in which candidates are swept: place p holds row p stride mod M, the
+// stride about 0.618 M and prime to M, so that every stretch of places is spread
+// evenly over the rows.  Rows as they come may lie along a path (a series in time),
+// and then every candidate on the way to a query is nearer than all before it: each
+// a hit (100,000 x 100 points along a line: 402 ms as they come).
+__global__ void knn_order_kernel(int64_t M, int64_t stride, int32_t *__restrict__ order) {
+  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (p < M) order[p] = (int32_t)(p * stride % M);
 }
 
 // Class of a row by its squared norm: a factor of two to a class
@@ -268,6 +279,7 @@ struct FilterArgs {
   int splits;                          // candidate ranges
   int64_t tiles, tiles_per_split;
   int lead;                            // tiles that set the starting thresholds
+  int64_t M, place_of;                 // row r is candidate r place_of mod M
   int self_mode;                       // 0 none, 1 the query's own row, 2 self[]
   const int32_t *self, *map;           // map: original row of query q (NULL: q)
   uint64_t *part;                      // [launch query][splits][KP]
@@ -415,7 +427,8 @@ __global__ void __launch_bounds__(kFilterThreads, kFilterWaves / 4) knn_filter_k
     // padding queries, and those without a limit, keep nothing
     sThr[tid] = q < A.nq ? (BAND ? (A.limits[q] > -INFINITY ? A.limits[q] : INFINITY) : kNoValue) : INFINITY;
     if (!BAND) sThrId[tid] = INT32_MAX;
-    sSelf[tid] = A.self_mode == 1 ? (int32_t)orig : (A.self_mode == 2 && q < A.nq ? A.self[orig] : -1);
+    const int64_t own = q >= A.nq ? -1 : (A.self_mode == 1 ? orig : (A.self_mode == 2 ? (int64_t)A.self[orig] : -1));
+    sSelf[tid] = own >= 0 && own < A.M ? (int32_t)(own * A.place_of % A.M) : -1;
   }
   if constexpr (!BAND) {
     if (tid < 2) sFlag[tid] = -1;
@@ -734,13 +747,14 @@ struct FinishArgs {
   int64_t nq, M;                 // queries of the call (compact ids), candidates
   int64_t qb0, qb_step, n_launch;   // launch query t is query (qb0 + t / FT qb_step) FT + t % FT
   const int32_t *map;            // original row of query q (NULL: q)
+  const int32_t *order;          // row of candidate c
   int self_mode;                 // 0 none, 1 the query's own row, 2 self[]
   const int32_t *self;
   const uint64_t *part;
   int32_t *out_idx;
   float *out_dist;
   // certificate; norms and residuals in scaled units, centred
-  const float *qnorm, *qres;     // [rows of Q] squared norm, squared residual
+  const float *qnorm, *qres;     // [query] squared norm, squared residual
   const KnnStats *xs;            // of the candidates, after knn_classes_kernel
   double sub;                    // norm of the low parts' errors where they are subnormal
   float scale;
@@ -818,9 +832,9 @@ __global__ void __launch_bounds__(256) knn_finish_kernel(FinishArgs A) {
   const double sc2 = (double)A.scale * A.scale;
   QueryBound B;
   B.nerr = sum_error(A.N);
-  const double n2 = on ? (double)A.qnorm[orig] : 0.0;
+  const double n2 = on ? (double)A.qnorm[q] : 0.0;
   B.nq = sqrt(n2 * (1 + B.nerr)) * kUp;
-  B.rq = on ? sqrt((double)A.qres[orig] * (1 + B.nerr)) * kUp : 0.0;
+  B.rq = on ? sqrt((double)A.qres[q] * (1 + B.nerr)) * kUp : 0.0;
   int rank = 0, found = 0;
   uint64_t last = ~0ull, kth = 0;
 #pragma unroll 4
@@ -860,9 +874,8 @@ __global__ void __launch_bounds__(256) knn_finish_kernel(FinishArgs A) {
     near = have && !((double)key_value(mine) < (double)key_value(kth) - 2.0 * err - slack);
   }
   float d = FLT_MAX;
-  if (near)
-    d = exact_distance(A.Q + orig * A.N, A.X + (int64_t)key_id(mine) * A.N, A.N, rows_are_vec4(A.X, A.Q, A.N));
-  const int32_t id = near ? key_id(mine) : INT32_MAX;
+  const int32_t id = near ? A.order[key_id(mine)] : INT32_MAX;
+  if (near) d = exact_distance(A.Q + orig * A.N, A.X + (int64_t)id * A.N, A.N, rows_are_vec4(A.X, A.Q, A.N));
   rank = 0;
 #pragma unroll 4
   for (int j = 0; j < KP; ++j) {
@@ -945,7 +958,8 @@ __global__ void __launch_bounds__(256) knn_band_rank_kernel(const float *__restr
                                                             const int32_t *__restrict__ rows,
                                                             const float *__restrict__ limits,
                                                             const int32_t *__restrict__ count,
-                                                            const int32_t *__restrict__ ids, int cap, int k,
+                                                            const int32_t *__restrict__ ids, int cap,
+                                                            const int32_t *__restrict__ order, int k,
                                                             int32_t *__restrict__ out_idx,
                                                             float *__restrict__ out_dist, int32_t *__restrict__ left) {
   __shared__ uint64_t lists[4][32];
@@ -962,7 +976,7 @@ __global__ void __launch_bounds__(256) knn_band_rank_kernel(const float *__restr
   for (int32_t base = 64 * wave; base < hits; base += 256) {
     uint64_t key = ~0ull;
     if (base + lane < hits) {
-      const int32_t c = ids[t * cap + base + lane];
+      const int32_t c = order[ids[t * cap + base + lane]];
       key = (uint64_t)__float_as_uint(exact_distance(Q + q * N, X + (int64_t)c * N, N, vec4)) << 32 | (uint32_t)c;
     }
     offer_sorted(best, key, lane, k);
@@ -1219,6 +1233,19 @@ constexpr int64_t kBandIds = int64_t{32} << 20;
 
 }  // namespace
 
+// x with a x = 1 mod m (a prime to m)
+static int64_t inverse_mod(int64_t a, int64_t m) {
+  int64_t r0 = m, r1 = a % m, x0 = 0, x1 = 1;
+  while (r1) {
+    const int64_t q = r0 / r1, r = r0 - q * r1, x = x0 - q * x1;
+    r0 = r1;
+    r1 = r;
+    x0 = x1;
+    x1 = x;
+  }
+  return (x0 % m + m) % m;
+}
+
 int KnnSearch::open(int64_t M_, int N_, const float *Q_, int64_t nq_, const float *sample, int64_t sample_rows,
                     bool same_, int k_, hipStream_t s_) {
   M = M_;
@@ -1249,6 +1276,7 @@ int KnnSearch::open(int64_t M_, int N_, const float *Q_, int64_t nq_, const floa
     V.add(&mean, N);
     V.add(&qnorm, nq);
     V.add(&qres, nq);
+    V.add(&order, M);
     if (few) image(&cl, nx);
     if (!same) {
       image(&qh, nqi);
@@ -1266,7 +1294,13 @@ int KnnSearch::open(int64_t M_, int N_, const float *Q_, int64_t nq_, const floa
   HIPCHK(launch_fill_i32((int32_t *)spread, 2, 0, s));
   HIPCHK(launch_absmax(sample, sample_rows * N, spread + 1, s));
   if (Q != sample || nq != sample_rows) HIPCHK(launch_absmax(Q, nq * N, spread + 1, s));
-  if (!direct) knn_sample_kernel<<<(unsigned)N, 256, 0, s>>>(sample, sample_rows, N, mean, spread);
+  if (!direct) {
+    int64_t stride = (int64_t)((double)M * 0.6180339887498949);
+    while (stride < 1 || std::gcd(stride, M) != 1) ++stride;
+    place_of = inverse_mod(stride, M);
+    knn_order_kernel<<<grid_for(M), kBlock, 0, s>>>(M, stride, order);
+    knn_sample_kernel<<<(unsigned)N, 256, 0, s>>>(sample, sample_rows, N, mean, spread);
+  }
   HIPCHK(hipGetLastError());
   HIPCHK(hipMemcpyAsync(bits, spread, sizeof bits, hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
@@ -1282,7 +1316,7 @@ int KnnSearch::run(const float *X, int self_mode, const int32_t *self, int32_t *
   const int64_t tiles = (M + FT - 1) / FT, nqb = (nq + FT - 1) / FT;
   int kp = list_length(k), rc;
   HIPCHK(launch_fill_i32((int32_t *)xstats, sizeof(KnnStats) / 4, 0, s));
-  HIPCHK(launch_knn_split(X, M, N, nullptr, mean, scale, ch, cl, same ? qnorm : nullptr, same ? qres : nullptr, start,
+  HIPCHK(launch_knn_split(X, M, N, order, mean, scale, ch, cl, same ? qnorm : nullptr, same ? qres : nullptr, start,
                           xstats, s));
   knn_classes_kernel<<<1, kNormClasses, 0, s>>>(xstats, N);
   HIPCHK(hipGetLastError());
@@ -1300,6 +1334,9 @@ int KnnSearch::run(const float *X, int self_mode, const int32_t *self, int32_t *
   f.nk = nk;
   f.nq = nq;
   f.tiles = tiles;
+  f.M = M;
+  f.place_of = place_of;
+  f.map = same ? order : nullptr;
   f.self_mode = self_mode;
   f.self = self;
   FinishArgs g{};
@@ -1310,6 +1347,8 @@ int KnnSearch::run(const float *X, int self_mode, const int32_t *self, int32_t *
   g.k = k;
   g.nq = nq;
   g.M = M;
+  g.map = f.map;
+  g.order = order;
   g.self_mode = self_mode;
   g.self = self;
   g.out_idx = idx;
@@ -1382,7 +1421,7 @@ int KnnSearch::run(const float *X, int self_mode, const int32_t *self, int32_t *
       }
     if (segs == 3) {
       if ((rc = image(&low_c, M, "candidate operands (low)"))) return rc;
-      HIPCHK(launch_knn_split(X, M, N, nullptr, mean, scale, KnnImage{}, low_c, nullptr, nullptr, nullptr, nullptr, s));
+      HIPCHK(launch_knn_split(X, M, N, order, mean, scale, KnnImage{}, low_c, nullptr, nullptr, nullptr, nullptr, s));
       KnnImage low = low_c;
       if (!same) {
         if ((rc = image(&low, nq, "query operands (low)"))) return rc;
@@ -1427,7 +1466,7 @@ int KnnSearch::run(const float *X, int self_mode, const int32_t *self, int32_t *
       (rc = R.get(&ids, batch * cap, "hits")))
     return rc;
   if (!made)
-    HIPCHK(launch_knn_split(X, M, N, nullptr, mean, scale, KnnImage{}, low_c, nullptr, nullptr, nullptr, nullptr, s));
+    HIPCHK(launch_knn_split(X, M, N, order, mean, scale, KnnImage{}, low_c, nullptr, nullptr, nullptr, nullptr, s));
   HIPCHK(launch_knn_split(Q, failed, N, again, mean, scale, high_q, low_q, nullptr, nullptr, nullptr, nullptr, s));
   HIPCHK(launch_fill_i32(left, 1, 0, s));
   f.Qh = high_q.p;
@@ -1444,7 +1483,8 @@ int KnnSearch::run(const float *X, int self_mode, const int32_t *self, int32_t *
     if ((rc = shape(q0 / FT, 1, (n + FT - 1) / FT, 3, 0, high_q))) return rc;
     HIPCHK(launch_fill_i32(count, n, 0, s));
     knn_filter_kernel<8, true, true><<<(unsigned)(f.nqb * f.splits), kFilterThreads, 0, s>>>(f);
-    knn_band_rank_kernel<<<(unsigned)n, 256, 0, s>>>(X, N, Q, again + q0, limits + q0, count, ids, (int)cap, k, idx, dist,
+    knn_band_rank_kernel<<<(unsigned)n, 256, 0, s>>>(X, N, Q, again + q0, limits + q0, count, ids, (int)cap, order, k, idx,
+                                                     dist,
                                                      left);
     HIPCHK(hipGetLastError());
   }

@@ -98,7 +98,8 @@ struct KnnSearch {
   float *start = nullptr, *qnorm = nullptr, *qres = nullptr, *mean = nullptr;
   KnnStats *xstats = nullptr;
   float *limits = nullptr;
-  int32_t *fails = nullptr, *pilot = nullptr;
+  int32_t *fails = nullptr, *pilot = nullptr, *order = nullptr;
+  int64_t place_of = 1;
   uint64_t *part = nullptr;
   int64_t part_cap = 0;
 };
