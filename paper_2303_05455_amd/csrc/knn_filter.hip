@@ -3,55 +3,56 @@
 // Order: squared Euclidean distance in FP32 (sum_k (q_k - x_k)^2, features in
 // order), ties to the lower index, the query itself excluded.
 //
-// Every coordinate, scaled by a power of two so the largest magnitude sits
-// below 2^14, is split into hi = fp16(x) and lo = fp16(x - hi) (22
-// significant bits together).  The matrix cores compute the ranking value
+// Every coordinate, less the centre of its feature and scaled by a power of two,
+// is split into hi = fp16(x) and lo = fp16(x - hi) (22 significant bits together).
+// The matrix cores compute the ranking value
 //     a(q, c) = q.c - |c|^2 / 2          (the distance is |q|^2 - 2 a)
-// with FP32 accumulation, started at -|c|^2 / 2, from one of
+// with FP32 accumulation, from one of
 //     1 segment    hi.hi
-//     3 segments   hi.hi + hi.lo + lo.hi  (close to FP32 accuracy)
-// and each query keeps its KP best candidates by (a, id).  These survivors
-// are then ranked by their exact FP32 distances, so the answer does not carry
-// the rounding of a as long as the true neighbours are among them.
-//   * One segment: every answer is certified.  With E a bound on the error
-//     of a (Cauchy-Schwarz on the rows' actual rounding residuals, plus the
-//     accumulation), a candidate that was dropped has a <= a_last + E, hence
-//     a distance of at least |q|^2 - 2 (a_last + E); the answer stands when
-//     its k-th distance lies below that.  Queries that fail are run again
-//     with three segments.
-//   * Three segments: the same certificate with a smaller E.  What fails it
-//     (points whose offsets are thousands of times their distances, more
-//     equal distances than the list holds) is ranked over all candidates by
-//     the FP32 distances themselves (knn_brute_kernel).
-// One segment costs a third of the matrix work; which one a call starts with
-// is decided by a pilot of a few query tiles (see KnnSearch::run).
+//     3 segments   hi.lo + lo.hi + hi.hi  (close to FP32 accuracy)
+// and each query keeps its KP best candidates by a.  These are ranked by their exact
+// FP32 distances, and the answer is certified: with E a bound on the error of a
+// (Cauchy-Schwarz on the rows' actual rounding residuals, plus the worst case of the
+// accumulation), a candidate that was dropped has a <= a_last + E, hence a distance
+// of at least |q|^2 - 2 (a_last + E); the answer stands when its k-th distance lies
+// below that.  E is taken over the candidates that can be an answer at all, those of
+// norms up to |q| and the k-th distance, so that rows far off spoil none but their
+// own.  What is not certified goes through a band (see there): tiles of like queries
+// with centres of their own, the exact distances of all candidates whose value may
+// be an answer's, with one segment, then with three, and over all candidates in the
+// end.  So the answers are those of the order above whatever the data; what depends
+// on the data is the time, here for 400,000 x 100 points, k = 2: 53 ms (a mixture of
+// clusters, distances a quarter of their offsets, with or without a coordinate far
+// off), 156 (standardised binary features, 4,096 different rows), 193 (clusters with
+// distances 1/60 of the offsets), 210 (equal points), 373 (1/3000).  The search before
+// the filter, three segments for every pair and no certificate, took 149 to 247.
+// Few candidates or queries go to their exact distances at once (direct_pays).
 //
-// knn_filter_kernel: a block of 16 waves owns 256 queries and a range of
-// candidate tiles of 256; wave (wc, wq) computes 64 candidates x 64 queries
-// with v_mfma_f32_32x32x16_f16 (candidates on the rows, so a lane's 32
-// values of a query column stay in its registers).  Operands are laid out by
-// the split kernel as the LDS stage images themselves: 256 rows x 32 features
-// = 16 KB, in slot order, so a stage is filled by global_load_lds_dwordx4
-// from consecutive addresses, without bounds checks (rows past the end are
-// zero, their start value -3e38).  The values never leave the registers: a
-// lane compares the maximum of 16 of them with its query's threshold (the
-// KP-th best so far), and only hits go to the query's list in LDS, which is
-// cut to its KP best when it fills up.  A sweep starts with a short run over
-// its first tiles that only tracks the maxima of KP groups of candidates per
-// query: their minimum is a threshold that at least KP candidates reach, so
-// the lists never see the flood of a cold start.  After it a query has about
-// KP ln(M / 4096) hits in a sweep.
+// knn_filter_kernel: a block of 8 waves owns 256 queries and a range of candidate
+// tiles of 256; wave (wc, wq) computes 128 candidates x 64 queries with
+// v_mfma_f32_32x32x16_f16 (candidates on the rows, so a lane's 64 values of a query
+// column stay in its registers).  Operands are laid out by the split kernel as the
+// LDS stage images themselves: 256 rows x 32 features = 16 KB, in slot order, so a
+// stage is filled by global_load_lds_dwordx4 from consecutive addresses, without
+// bounds checks (rows past the end are zero, their start value -3e38).  The values
+// never leave the registers: a lane compares the maximum of 16 of them with its
+// query's threshold (the KP-th best so far), and only hits go to the query's list in
+// LDS, which is cut to its KP best when it fills up.  A sweep starts with a short run
+// over its first tiles that only tracks the maxima of 32 groups of candidates per
+// query: at least KP candidates reach the KP-th largest of them, so the lists never
+// see the flood of a cold start.  After it a query has about KP ln(M / 4096) hits in
+// a sweep, in whatever order the rows come: the candidates are swept in one of their
+// own (knn_order_kernel).
 // What bounds it: the matrix cores, at the clock that the power limit leaves
 // them (1.7 GHz instead of 2.4 in these loops): per K step of 32 a CU spends
 // 1,024 cycles in MFMAs, beside 768 of operand reads and 256 of stage writes.
-// Measured (whole call, exact graph): 400,000 x 100, k = 2 149.6 -> 54.3 ms
-// (the sweep 49 ms, 45 of them without any hit: 0.83 PFLOP/s of products);
-// 70,000 x 784, k = 5 52.4 -> 18.3 ms; 48,600 x 128, k = 20 24.8 -> 7.3 ms.
-// Before, three segments always, each score through LDS to two threads per
-// query row with a register list.  Waves of 64 x 64 (16 per block), rings of
-// two and three stages and per-register ballots measured the same or slower:
-// what a hit costs (about 0.2 us of its wave) is what is left above the
-// products.
+// Measured (whole call, exact graph): 400,000 x 100, k = 2 149.6 -> 53 ms (the sweep
+// 49 ms, 45 of them without any hit: 0.83 PFLOP/s of products); 70,000 x 784, k = 5
+// 52.4 -> 14.9 ms; 48,600 x 128, k = 20 24.8 -> 4.6 ms.  Before, three segments
+// always, each score through LDS to two threads per query row with a register list.
+// Waves of 64 x 64 (16 per block), a ring of three stages and per-register ballots
+// measured the same or slower: what a hit costs (about 0.2 us of its wave) is what is
+// left above the products.
 #include <cfloat>
 #include <cmath>
 #include <cstring>
@@ -78,7 +79,7 @@ constexpr int kCandWaves = kFilterWaves / 4;   // waves along the candidates of 
 constexpr int NI = FT / kCandWaves / 32;       // 32 x 32 blocks of a wave along the candidates
 constexpr int kFilterThreads = 64 * kFilterWaves;
 constexpr int64_t kCus = 256;
-constexpr int kRing = 2;                 // stages in LDS
+constexpr int kRing = 2;                 // stages in LDS: the loads of one fly while the other is used
 constexpr int kListPlaces = 44;          // places of a query's list (LDS: 64 KB ring + 88 KB lists)
 constexpr float kNoValue = -2.9e38f;     // threshold of a list that is not full
 constexpr float kPadStart = -3.0e38f;    // start value of rows past the end (below kNoValue)
@@ -169,17 +170,18 @@ __device__ __forceinline__ int norm_class(float norm2) {
 
 __device__ __forceinline__ float clamp_half(float t) { return fminf(fmaxf(t, -65504.f), 65504.f); }
 
-// Stage images of scale * (X - mean) (rows taken through `map` when given), and
-// in those units the rows' squared norms and rounding residuals, start values and
+// Stage images of scale * (X - mean) (rows taken through `map` when given, -1: a
+// row of zeros; mean_stride > 0: a centre for each tile), and in those units the rows' squared norms and rounding residuals, start values and
 // the statistics of the set.  A coordinate beyond the FP16 range is held at its
 // end: all of it that is missing counts as the row's residual.
 // 16 lanes per row, 8 features per lane and step; a block walks rows 16 at a
 // time so that the maxima cost a block one atomic each.
 __global__ void __launch_bounds__(256) knn_split_kernel(const float *__restrict__ X, int64_t M, int N, int nk,
                                                         const int32_t *__restrict__ map,
-                                                        const float *__restrict__ mean, float scale,
-                                                        _Float16 *__restrict__ hi, _Float16 *__restrict__ lo,
-                                                        float *__restrict__ norms, float *__restrict__ res,
+                                                        const float *__restrict__ means, int64_t mean_stride,
+                                                        float scale, _Float16 *__restrict__ hi,
+                                                        _Float16 *__restrict__ lo, float *__restrict__ norms,
+                                                        float *__restrict__ res,
                                                         float *__restrict__ start, KnnStats *__restrict__ stats,
                                                         bool vec) {
   __shared__ float smax[4];
@@ -190,9 +192,9 @@ __global__ void __launch_bounds__(256) knn_split_kernel(const float *__restrict_
   if (stats) cls[threadIdx.x] = 0;
   __syncthreads();
   for (int64_t row = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4); row < rows; row += (int64_t)gridDim.x * 16) {
-    const bool real = row < M;
-    const int64_t src = real ? (map ? (int64_t)map[row] : row) : 0;
-    const float *x = X + src * N;
+    const int64_t src = row < M ? (map ? (int64_t)map[row] : row) : -1;
+    const bool real = src >= 0;
+    const float *x = X + (real ? src : 0) * N, *mean = means + row / FT * mean_stride;
     const int64_t base = row / FT * nk * kTileHalves;
     const int r = (int)(row % FT);
     float s = 0.f, e = 0.f;
@@ -231,8 +233,8 @@ __global__ void __launch_bounds__(256) knn_split_kernel(const float *__restrict_
       e += __shfl_xor(e, o, 64);
     }
     if (g == 0) {
-      if (norms && real) norms[row] = s;
-      if (res && real) res[row] = e;
+      if (norms && row < M) norms[row] = s;
+      if (res && row < M) res[row] = e;
       if (start) start[row] = real ? -0.5f * s : kPadStart;
       if (stats && e > 0.f) atomicMax(&cls[norm_class(s)], __float_as_uint(e));
     }
@@ -283,8 +285,10 @@ struct FilterArgs {
   int self_mode;                       // 0 none, 1 the query's own row, 2 self[]
   const int32_t *self, *map;           // map: original row of query q (NULL: q)
   uint64_t *part;                      // [launch query][splits][KP]
-  // band: hits of launch query t, those with values from limits[q] up
-  const float *limits;                 // by query
+  // band: hits of launch query t, those with values from limits[q] up; a query
+  // tile of the launch has its own start values
+  int64_t start_pitch;
+  const float *limits;                 // by query (INFINITY or -INFINITY: no hits)
   int32_t *count, *ids;                // [t], [t][cap]; count goes on past cap
   int cap;
 };
@@ -423,11 +427,11 @@ __global__ void __launch_bounds__(kFilterThreads, kFilterWaves / 4) knn_filter_k
 
   if (tid < FT) {
     const int64_t q = q0 + tid;
-    const int64_t orig = q < A.nq ? (A.map ? (int64_t)A.map[q] : q) : 0;
+    const int64_t orig = q < A.nq ? (A.map ? (int64_t)A.map[q] : q) : -1;
     // padding queries, and those without a limit, keep nothing
     sThr[tid] = q < A.nq ? (BAND ? (A.limits[q] > -INFINITY ? A.limits[q] : INFINITY) : kNoValue) : INFINITY;
     if (!BAND) sThrId[tid] = INT32_MAX;
-    const int64_t own = q >= A.nq ? -1 : (A.self_mode == 1 ? orig : (A.self_mode == 2 ? (int64_t)A.self[orig] : -1));
+    const int64_t own = orig < 0 ? -1 : (A.self_mode == 1 ? orig : (A.self_mode == 2 ? (int64_t)A.self[orig] : -1));
     sSelf[tid] = own >= 0 && own < A.M ? (int32_t)(own * A.place_of % A.M) : -1;
   }
   if constexpr (!BAND) {
@@ -439,6 +443,7 @@ __global__ void __launch_bounds__(kFilterThreads, kFilterWaves / 4) knn_filter_k
   if (lead > 0)
     for (int e = tid; e < 32 * GP; e += kFilterThreads) gm[e] = kNoValue;
 
+  const float *start = BAND ? A.start + qrow * A.start_pitch : A.start;
   // stage issue: counters of the next stage to load
   int i_seq = 0, i_seg = 0, i_k = 0, i_slot = 0, i_start = 0;
   const uint32_t load_at = tid * 16;
@@ -449,7 +454,7 @@ __global__ void __launch_bounds__(kFilterThreads, kFilterWaves / 4) knn_filter_k
     _Float16 *dst = ring + i_slot * 2 * kTileHalves;
     if (i_seg == 0 && i_k == 0) {   // the tile's start values, ahead of its first stage
       if (wave == 0)
-        __builtin_amdgcn_global_load_lds((const void *)(reinterpret_cast<const char *>(A.start + i_tile * FT) + load_at),
+        __builtin_amdgcn_global_load_lds((const void *)(reinterpret_cast<const char *>(start + i_tile * FT) + load_at),
                                          (lds_void *)(sStart + i_start * FT), 16, 0, 0);
       i_start = i_start == 2 ? 0 : i_start + 1;
     }
@@ -741,6 +746,12 @@ __global__ void __launch_bounds__(kFilterThreads, kFilterWaves / 4) knn_filter_k
 
 // ---- survivors to answers -----------------------------------------------------
 
+// an FP32 squared distance in scaled units (sc2: the scale's square), with its
+// rounding and that of subnormal squares
+__device__ __forceinline__ double scaled_above(float d, int N, double sc2) {
+  return ((double)d * (1 + (N + 16) * kU23) + N * 1.5e-45) * sc2;
+}
+
 struct FinishArgs {
   const float *X, *Q;
   int N, nk, k, splits;
@@ -760,9 +771,8 @@ struct FinishArgs {
   float scale;
   int nseg;
   int32_t *fails;                // [0] count, then query ids
-  float *limits;                 // of the fails: the least value of a candidate of the answer (-inf: none)
-  int32_t *pilot;                // [2][3]: answers that lists of 8, 16, 32 would not certify with one and
-                                 // (by these values) three segments (NULL: no pilot)
+  float *fail_dist;              // of the fails: the k-th distance found
+  int32_t *pilot;                // [3]: answers that lists of 8, 16, 32 would not certify (NULL: no pilot)
 };
 
 // The rows' own figures that bound the error of a query's values, in FP64 and
@@ -771,29 +781,42 @@ struct QueryBound {
   double nq, rq, nerr;   // norm, residual, relative error of an FP32 sum of N squares
 };
 
-// Bound on the error of a, of nseg segments, against any candidate of norm up to
-// x at a distance of up to dist (infinite when the rows' figures give none)
-__device__ __forceinline__ double value_error(const FinishArgs &A, const QueryBound &B, double x, double dist,
-                                              int nseg) {
-  const float limit = (float)(x * x * (1 + B.nerr) * kUp);
-  const double rx = __uint_as_float(A.xs->res[norm_class(limit)]);
-  const double cross = B.nq * rx + B.rq * (x + rx);   // q.c less its high parts' product
-  // the largest partial sum: some of q.c's terms, those of |c|^2 and the rest of
-  // no more than dist |c|, and the start value, of the other sign
-  const double any = 0.5 * x * x + B.nq * x, close = x * x + dist * x;
-  const double sum = (close < any ? close : any) + 2 * cross;
-  // one rounding to a feature, of no more than 2^-23 of that, all of them one way
-  const double n = (double)A.N + 17;
-  double err = n * kU23 * sum + 0.5 * B.nerr * x * x;   // (and the start value's own)
+// Bound on the error of a product of two rows of N features, of norms a and b
+// and residuals ra and rb, computed in nseg segments from their images, where
+// `sum` bounds the true partial sums together with the start value
+__device__ __forceinline__ double product_error(int N, double sub, double a, double ra, double b, double rb, double sum,
+                                                int nseg) {
+  const double cross = a * rb + ra * (b + rb);   // the product less that of the high parts
+  // one rounding to a feature, of no more than 2^-23 of the partial sum, all of
+  // them one way (and a few for the operands' own)
+  const double n = (double)N + 20;
+  double err = n * kU23 * (sum + 2 * cross);
   if (nseg == 1) {
     err += kUp * cross;
   } else {
     // with hi + lo: the rounding of lo (2^-11 of the residual, or 2^-25 per
-    // coordinate where lo is subnormal), the product lo.lo, and the additions
+    // coordinate where lo is subnormal: sub), the product lo.lo, and the additions
     // that come before the large ones
-    const double sub = A.sub, low = 1.5 * cross + (B.nq + x) * sub;
-    err += kUp * ((B.nq + B.rq) * (rx / 2048 + sub) + (x + rx) * (B.rq / 2048 + sub) + rx * B.rq) + 3 * n * kU23 * low;
+    const double low = 1.5 * cross + (a + b) * sub;
+    err += kUp * ((a + ra) * (rb / 2048 + sub) + (b + rb) * (ra / 2048 + sub) + ra * rb) + 3 * n * kU23 * low;
   }
+  return err;
+}
+
+// the largest residual of a candidate of norm up to x
+__device__ __forceinline__ double residual_at(const KnnStats *xs, double x, double nerr) {
+  return __uint_as_float(xs->res[norm_class((float)(x * x * (1 + nerr) * kUp))]);
+}
+
+// Bound on the error of a against any candidate of norm up to x at a distance of
+// up to dist (infinite when the rows' figures give none)
+__device__ __forceinline__ double value_error(const FinishArgs &A, const QueryBound &B, double x, double dist) {
+  // the largest partial sum: some of q.c's terms, those of |c|^2 and the rest of
+  // no more than dist |c|, and the start value, of the other sign
+  const double any = 0.5 * x * x + B.nq * x, close = x * x + dist * x;
+  const double err = product_error(A.N, A.sub, B.nq, B.rq, x, residual_at(A.xs, x, B.nerr), close < any ? close : any,
+                                   A.nseg) +
+                     0.5 * B.nerr * x * x;   // and the start value's own
   return err == err ? err : INFINITY;
 }
 
@@ -859,13 +882,13 @@ __global__ void __launch_bounds__(256) knn_finish_kernel(FinishArgs A) {
   bool near = have;   // may be among the k nearest
   double reach = sqrt((double)__uint_as_float(A.xs->norm2) * (1 + B.nerr)) * kUp;
   if (kth != 0) {
-    double err = value_error(A, B, reach, INFINITY, A.nseg);
+    double err = value_error(A, B, reach, INFINITY);
     for (int it = 0; it < 4 && reach > 2 * B.nq; ++it) {   // (not far off: little to gain)
       const double far2 = n2 * (1 + B.nerr) - 2.0 * ((double)key_value(kth) - err);
       const double far = sqrt(far2 > 0 ? far2 : 0.0) * kUp, r = (B.nq + far) * kUp;
       const bool less = r < 0.75 * reach;
       if (r < reach) reach = r;
-      err = value_error(A, B, reach, far + 2 * kU23 * (B.nq + reach), A.nseg);
+      err = value_error(A, B, reach, far + 2 * kU23 * (B.nq + reach));
       if (!less) break;
     }
     // a value more than two errors below the k-th best cannot be (the slack
@@ -890,13 +913,12 @@ __global__ void __launch_bounds__(256) knn_finish_kernel(FinishArgs A) {
   if (on && rank == A.k - 1) {
     // The least squared distance of a candidate that is not among the first L of
     // the list, between the centred rows and (their rounding: 2^-24 of each
-    // row) between the given ones, must lie above the k-th distance (FP32, and
-    // subnormal squares).
-    const double top = ((double)d * (1 + (A.N + 16) * kU23) + A.N * 1.5e-45) * sc2;
+    // row) between the given ones, must lie above the k-th distance.
+    const double top = scaled_above(d, A.N, sc2);
     const double r = (B.nq + sqrt(top)) * kUp, x = r < reach ? r : reach;
     const double shift = 0.5 * kU23 * (B.nq + x), dist = (sqrt(top) + shift) * kUp;
-    const double err = value_error(A, B, x, dist, A.nseg);
-    auto certified = [&](uint64_t last, double err) {
+    const double err = value_error(A, B, x, dist);
+    auto certified = [&](uint64_t last) {
       const double least = n2 * (1 - B.nerr) - 2.0 * ((double)key_value(last) + err);
       const double moved = sqrt(least > 0 ? least : 0.0) - shift;
       return top < (moved > 0 ? moved * moved : 0.0) * (1 - 1e-12);
@@ -907,20 +929,14 @@ __global__ void __launch_bounds__(256) knn_finish_kernel(FinishArgs A) {
       return found >= A.M - (own >= 0 && own < A.M ? 1 : 0);
     };
     if (A.pilot) {
-      const double err3 = value_error(A, B, x, dist, 3);
       for (int l = 0; l < 3; ++l) {
         const int len = 8 << l;
-        if (len > KP) continue;
-        if (found < len ? !complete() : len < A.k || !certified(nth[l], err)) atomicAdd(&A.pilot[l], 1);
-        if (found < len ? !complete() : len < A.k || !certified(nth[l], err3)) atomicAdd(&A.pilot[3 + l], 1);
+        if (len <= KP && (found < len ? !complete() : len < A.k || !certified(nth[l]))) atomicAdd(&A.pilot[l], 1);
       }
-    } else if (found < KP ? !complete() : !certified(last, err)) {
+    } else if (found < KP ? !complete() : !certified(last)) {
       const int32_t at = atomicAdd(&A.fails[0], 1);
       A.fails[1 + at] = (int32_t)orig;
-      // what three segments give a candidate as near as the k-th here, at least
-      const double low = 0.5 * (n2 * (1 - B.nerr) - dist * dist) - value_error(A, B, x, dist, 3);
-      const float f = (float)(low - 1.2e-7 * fabs(low));
-      A.limits[at] = f > kNoValue ? f : -INFINITY;
+      A.fail_dist[at] = d;
     }
   }
 }
@@ -948,34 +964,210 @@ __device__ __forceinline__ void put_answer(uint64_t best, int64_t q, int lane, i
   if (out_dist) out_dist[q * k + lane] = best == ~0ull ? FLT_MAX : __uint_as_float((uint32_t)(best >> 32));
 }
 
-// Query rows[blockIdx.x]: the k nearest of its hits (count, ids); one without a
-// limit, or with more hits than were kept, goes to `left` ([0] count).  Bound by
-// the latency of the hits' rows, which come from L2 and the memory-side cache, so
-// the four waves of a block share a query (a wave to a query: 100,000 x 100 points
-// with 5,000 hits each 28 ms).
+// ---- the band: queries whose list certifies nothing -----------------------------
+//
+// All candidates whose value may be an answer's are collected by the filter's
+// products and ranked by their exact distances.  The values' error grows with the
+// rows' norms, so those queries are put into tiles by their nearest of kPivots rows
+// and a tile has a centre m of its own, one of its queries: with u = q - m,
+//     |q - c|^2 = |u|^2 + 2 u.m' - 2 (u.c' - |c - m|^2 / 2)
+// (m' and c' as the candidates' images are centred), and the value u.c' - |c - m|^2
+// / 2 has an error of |u| |c'| and |c - m|^2, for those that matter a small share of
+// what it is in the candidates' own centring.  The start values are FP32 distances
+// to the tile's centre.  With points in tight clusters (100,000 x 100, distances 1/60
+// of the offsets) one product leaves a few hits to a query, where in the common
+// centring three left a thousand.
+constexpr int kPivots = 1024;
+constexpr int kBandSome = 512;   // hits ranked of a query with too many
+
+__global__ void knn_pivot_rows_kernel(const float *__restrict__ X, int64_t M, int N, int P, float *__restrict__ pivots) {
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e < (int64_t)P * N) pivots[e] = X[(e / N) * M / P * N + e % N];
+}
+
+__global__ void knn_pivot_count_kernel(const int32_t *__restrict__ rows, int64_t n, const int32_t *__restrict__ pivot_of,
+                                       int32_t *__restrict__ count) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) atomicAdd(&count[pivot_of[rows[i]]], 1);
+}
+
+// count[p] -> the first slot of pivot p's queries, in whole tiles; *total: all slots
+__global__ void __launch_bounds__(kPivots) knn_pivot_slots_kernel(int32_t *__restrict__ count, int P,
+                                                                  int32_t *__restrict__ total) {
+  __shared__ int32_t at[kPivots];
+  const int t = threadIdx.x;
+  const int32_t mine = t < P ? (count[t] + FT - 1) / FT * FT : 0;
+  at[t] = mine;
+  for (int o = 1; o < kPivots; o *= 2) {
+    __syncthreads();
+    const int32_t w = t >= o ? at[t - o] : 0;
+    __syncthreads();
+    at[t] += w;
+  }
+  if (t < P) count[t] = at[t] - mine;
+  if (t == kPivots - 1) *total = at[t];
+}
+
+__global__ void knn_pivot_place_kernel(const int32_t *__restrict__ rows, const float *__restrict__ dist, int64_t n,
+                                       const int32_t *__restrict__ pivot_of, int32_t *__restrict__ next,
+                                       int32_t *__restrict__ slot_row, float *__restrict__ slot_dist) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const int32_t at = atomicAdd(&next[pivot_of[rows[i]]], 1);
+  slot_row[at] = rows[i];
+  slot_dist[at] = dist[i];
+}
+
+// a tile's centre: its first query (whole tiles to a pivot, so there is one)
+__global__ void __launch_bounds__(256) knn_centre_kernel(const float *__restrict__ Q, int N,
+                                                         const int32_t *__restrict__ slot_row, int64_t pitch,
+                                                         float *__restrict__ centres) {
+  const float *q = Q + (int64_t)slot_row[(int64_t)blockIdx.x * FT] * N;
+  for (int n = threadIdx.x; n < N; n += 256) centres[blockIdx.x * pitch + n] = q[n];
+}
+
+// limits[slot]: the least value of a candidate as near as dist (the k-th distance
+// found); -INFINITY: none, every candidate may be; INFINITY: an empty slot.  A
+// wavefront to a slot, in FP64.
+__global__ void __launch_bounds__(256) knn_limit_kernel(const float *__restrict__ Q, int N, int64_t slots,
+                                                        const int32_t *__restrict__ slot_row,
+                                                        const float *__restrict__ slot_dist,
+                                                        const float *__restrict__ centres, int64_t pitch,
+                                                        const float *__restrict__ mean, const float *__restrict__ unorm,
+                                                        const float *__restrict__ ures, const KnnStats *__restrict__ xs,
+                                                        float scale, double sub, int nseg, float *__restrict__ limits) {
+  const int lane = threadIdx.x & 63;
+  const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (t >= slots) return;
+  if (slot_row[t] < 0) {
+    if (lane == 0) limits[t] = INFINITY;
+    return;
+  }
+  const float *q = Q + (int64_t)slot_row[t] * N, *m = centres + t / FT * pitch;
+  double uu = 0.0, um = 0.0, mm = 0.0;
+  for (int n = lane; n < N; n += 64) {
+    const double u = ((double)q[n] - (double)m[n]) * scale, v = ((double)m[n] - (double)mean[n]) * scale;
+    uu += u * u;
+    um += u * v;
+    mm += v * v;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    uu += __shfl_xor(uu, o, 64);
+    um += __shfl_xor(um, o, 64);
+    mm += __shfl_xor(mm, o, 64);
+  }
+  if (lane > 0) return;
+  const double nerr = sum_error(N), sc2 = (double)scale * scale;
+  const double dist = sqrt(scaled_above(slot_dist[t], N, sc2)) * kUp;
+  const double u = sqrt(uu) * kUp, ur = sqrt((double)ures[t] * (1 + nerr)) * kUp;
+  const double w = u + dist, x = (sqrt(mm) + w) * kUp;   // the candidates' distance to m, and norm
+  const double err = product_error(N, sub, u, ur, x, residual_at(xs, x, nerr), u * x + 0.5 * w * w, nseg) +
+                     0.5 * ((N + 16) * kU23 * w * w + N * 1.5e-45 * sc2);   // the start value's own
+  const double least = 0.5 * (uu + 2.0 * um - dist * dist) - err - 1e-11 * (uu + sqrt(uu * mm));
+  const float f = (float)(least - 1.2e-7 * fabs(least));
+  limits[t] = f > kNoValue && f < INFINITY ? f : -INFINITY;
+}
+
+// FP32 squared distances of x to the kBruteQ rows q, which the wavefront shares:
+// the additions of exact_distance, in its order
+constexpr int kBruteQ = 8;
+
+typedef const __attribute__((address_space(4))) float *ScalarRow;   // read-only, at an address the wavefront shares
+
+__device__ __forceinline__ void eight_distances(const float *__restrict__ x, const ScalarRow (&q)[kBruteQ], int N,
+                                                bool vec4, float (&d)[kBruteQ]) {
+#pragma unroll
+  for (int f = 0; f < kBruteQ; ++f) d[f] = 0.f;
+  // CH features at a time, their loads on their way together
+  auto chunk = [&](int kk, auto ch, auto vec) __attribute__((always_inline)) {
+    constexpr int CH = decltype(ch)::value;
+    float v[CH];
+    if constexpr (decltype(vec)::value) {
+#pragma unroll
+      for (int j = 0; j < CH; j += 4) {
+        const float4 w = *reinterpret_cast<const float4 *>(x + kk + j);
+        v[j] = w.x;
+        v[j + 1] = w.y;
+        v[j + 2] = w.z;
+        v[j + 3] = w.w;
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < CH; ++j) v[j] = x[kk + j];
+    }
+#pragma unroll
+    for (int f = 0; f < kBruteQ; ++f)
+#pragma unroll
+      for (int j = 0; j < CH; ++j) {
+        const float w = q[f][kk + j] - v[j];
+        d[f] = fmaf(w, w, d[f]);
+      }
+  };
+  int kk = 0;
+  if (vec4) {
+    for (; kk + 32 <= N; kk += 32) chunk(kk, std::integral_constant<int, 32>{}, std::true_type{});
+    for (; kk < N; kk += 4) chunk(kk, std::integral_constant<int, 4>{}, std::true_type{});
+  } else {
+    for (; kk + 8 <= N; kk += 8) chunk(kk, std::integral_constant<int, 8>{}, std::false_type{});
+    for (; kk < N; ++kk) chunk(kk, std::integral_constant<int, 1>{}, std::false_type{});
+  }
+}
+
+// start values of every candidate for each of `tiles` query tiles: minus half its
+// squared distance to the tile's centre
+__global__ void __launch_bounds__(256) knn_start_kernel(const float *__restrict__ X, int64_t M, int N,
+                                                        const int32_t *__restrict__ order,
+                                                        const float *__restrict__ centres, int64_t pitch, int tiles,
+                                                        float scale, int64_t start_pitch, float *__restrict__ start) {
+  const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int b0 = blockIdx.y * kBruteQ, nb = tiles - b0 < kBruteQ ? tiles - b0 : kBruteQ;
+  ScalarRow m[kBruteQ];
+#pragma unroll
+  for (int f = 0; f < kBruteQ; ++f) m[f] = (ScalarRow)(centres + (b0 + (f < nb ? f : 0)) * pitch);
+  float d[kBruteQ];
+  eight_distances(X + (int64_t)order[c < M ? c : M - 1] * N, m, N, rows_are_vec4(X, X, N), d);
+#pragma unroll
+  for (int f = 0; f < kBruteQ; ++f)
+    if (f < nb) start[(b0 + f) * start_pitch + c] = c < M ? -0.5f * (d[f] * scale) * scale : kPadStart;
+}
+
+// The slots' k nearest of their hits.  One without a limit, or with k equal points
+// among more hits than were kept, goes to `all` (every candidate), one with more
+// hits otherwise to `next` ([0] its count, then rows, next_dist; NULL: to all), with
+// the k-th distance of some of them: of a thousand points of a cluster the k nearest
+// are much nearer than of the list's eight.
+// Bound by the latency of the hits' rows, which come from L2 and the memory-side
+// cache, so the four waves of a block share a query (a wave to a query: 100,000 x
+// 100 points with 5,000 hits each 28 ms).
 __global__ void __launch_bounds__(256) knn_band_rank_kernel(const float *__restrict__ X, int N,
                                                             const float *__restrict__ Q,
-                                                            const int32_t *__restrict__ rows,
+                                                            const int32_t *__restrict__ slot_row,
+                                                            const float *__restrict__ slot_dist,
                                                             const float *__restrict__ limits,
                                                             const int32_t *__restrict__ count,
                                                             const int32_t *__restrict__ ids, int cap,
                                                             const int32_t *__restrict__ order, int k,
                                                             int32_t *__restrict__ out_idx,
-                                                            float *__restrict__ out_dist, int32_t *__restrict__ left) {
+                                                            float *__restrict__ out_dist, int32_t *__restrict__ all,
+                                                            int32_t *__restrict__ next, float *__restrict__ next_dist) {
   __shared__ uint64_t lists[4][32];
   static_assert(sizeof lists / sizeof lists[0][0] == 4 * 32, "k is at most 28");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t t = blockIdx.x, q = rows[t];
+  const int64_t t = blockIdx.x, q = slot_row[t];
+  if (q < 0) return;
   const int32_t hits = count[t];
-  if (!(limits[t] > -INFINITY) || hits > cap) {
-    if (threadIdx.x == 0) left[1 + atomicAdd(&left[0], 1)] = (int32_t)q;
+  const bool over = hits > cap;
+  if (!(limits[t] > -INFINITY) || (over && (!next || slot_dist[t] == 0.f))) {
+    if (threadIdx.x == 0) all[1 + atomicAdd(&all[0], 1)] = (int32_t)q;
     return;
   }
+  const int32_t n = over ? kBandSome : hits;   // (past cap - 64 places may not be written)
   const bool vec4 = rows_are_vec4(X, Q, N);
   uint64_t best = ~0ull;
-  for (int32_t base = 64 * wave; base < hits; base += 256) {
+  for (int32_t base = 64 * wave; base < n; base += 256) {
     uint64_t key = ~0ull;
-    if (base + lane < hits) {
+    if (base + lane < n) {
       const int32_t c = order[ids[t * cap + base + lane]];
       key = (uint64_t)__float_as_uint(exact_distance(Q + q * N, X + (int64_t)c * N, N, vec4)) << 32 | (uint32_t)c;
     }
@@ -985,7 +1177,13 @@ __global__ void __launch_bounds__(256) knn_band_rank_kernel(const float *__restr
   __syncthreads();
   if (wave > 0) return;
   for (int w = 1; w < 4; ++w) offer_sorted(best, lane < k ? lists[w][lane] : ~0ull, lane, k);
-  put_answer(best, q, lane, k, out_idx, out_dist);
+  if (!over) {
+    put_answer(best, q, lane, k, out_idx, out_dist);
+  } else if (lane == k - 1) {
+    const int32_t at = atomicAdd(&next[0], 1);
+    next[1 + at] = (int32_t)q;
+    next_dist[at] = fminf(slot_dist[t], __uint_as_float((uint32_t)(best >> 32)));
+  }
 }
 
 // Every candidate.  A block takes kBruteQ queries over one range of the
@@ -995,10 +1193,6 @@ __global__ void __launch_bounds__(256) knn_band_rank_kernel(const float *__restr
 // two queries each.  Bound by the vector ALU (2 instructions per query, candidate
 // and feature).  A range ends when k candidates of distance 0 are found for each
 // query: those that follow have higher ids.
-constexpr int kBruteQ = 8;
-
-typedef const __attribute__((address_space(4))) float *ScalarRow;   // read-only, at an address the wavefront shares
-
 __global__ void __launch_bounds__(256) knn_brute_kernel(const float *__restrict__ X, int64_t M, int N,
                                                         const float *__restrict__ Q, int64_t nq,
                                                         const int32_t *__restrict__ rows, int self_mode,
@@ -1025,43 +1219,7 @@ __global__ void __launch_bounds__(256) knn_brute_kernel(const float *__restrict_
     const int64_t c = c0 + tid;
     const float *x = X + (c < e ? c : e - 1) * N;
     float d[kBruteQ];
-#pragma unroll
-    for (int f = 0; f < kBruteQ; ++f) d[f] = 0.f;
-    // (the additions of exact_distance, in its order)
-    auto add = [&](int f, float u, float v) {
-      const float w = u - v;
-      d[f] = fmaf(w, w, d[f]);
-    };
-    // CH features at a time, their loads on their way together
-    auto chunk = [&](int kk, auto ch, auto vec) __attribute__((always_inline)) {
-      constexpr int CH = decltype(ch)::value;
-      float v[CH];
-      if constexpr (decltype(vec)::value) {
-#pragma unroll
-        for (int j = 0; j < CH; j += 4) {
-          const float4 w = *reinterpret_cast<const float4 *>(x + kk + j);
-          v[j] = w.x;
-          v[j + 1] = w.y;
-          v[j + 2] = w.z;
-          v[j + 3] = w.w;
-        }
-      } else {
-#pragma unroll
-        for (int j = 0; j < CH; ++j) v[j] = x[kk + j];
-      }
-#pragma unroll
-      for (int f = 0; f < kBruteQ; ++f)
-#pragma unroll
-        for (int j = 0; j < CH; ++j) add(f, qrow[f][kk + j], v[j]);
-    };
-    int kk = 0;
-    if (vec4) {
-      for (; kk + 32 <= N; kk += 32) chunk(kk, std::integral_constant<int, 32>{}, std::true_type{});
-      for (; kk < N; kk += 4) chunk(kk, std::integral_constant<int, 4>{}, std::true_type{});
-    } else {
-      for (; kk + 8 <= N; kk += 8) chunk(kk, std::integral_constant<int, 8>{}, std::false_type{});
-      for (; kk < N; ++kk) chunk(kk, std::integral_constant<int, 1>{}, std::false_type{});
-    }
+    eight_distances(x, qrow, N, vec4, d);
 #pragma unroll
     for (int f = 0; f < kBruteQ; ++f)
       keys[f][tid] = c < e && f < nf && c != own[f] ? (uint64_t)__float_as_uint(d[f]) << 32 | (uint32_t)c : ~0ull;
@@ -1149,15 +1307,15 @@ constexpr int64_t kBatchTiles = 16 * kCus;
 int64_t knn_image_halves(int64_t M, int N) { return (M + FT - 1) / FT * FT * (int64_t)((N + FK - 1) / FK * FK); }
 
 // (an image without room for the rows is refused)
-hipError_t launch_knn_split(const float *X, int64_t M, int N, const int32_t *map, const float *mean, float scale,
-                            const KnnImage &hi, const KnnImage &lo, float *norms, float *res, float *start,
-                            KnnStats *stats, hipStream_t s) {
+hipError_t launch_knn_split(const float *X, int64_t M, int N, const int32_t *map, const float *mean,
+                            int64_t mean_stride, float scale, const KnnImage &hi, const KnnImage &lo, float *norms, float *res,
+                            float *start, KnnStats *stats, hipStream_t s) {
   const int64_t need = knn_image_halves(M, N);
   if ((hi.p && need > hi.halves) || (lo.p && need > lo.halves)) return hipErrorInvalidValue;
-  const bool vec = N % 4 == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0;
+  const bool vec = N % 4 == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0;   // (the centres are aligned)
   const int64_t groups = (M + FT - 1) / FT * (FT / 16);
   knn_split_kernel<<<(unsigned)(groups < 4096 ? groups : 4096), 256, 0, s>>>(
-      X, M, N, (N + FK - 1) / FK, map, mean, scale, hi.p, lo.p, norms, res, start, stats, vec);
+      X, M, N, (N + FK - 1) / FK, map, mean, mean_stride, scale, hi.p, lo.p, norms, res, start, stats, vec);
   return hipGetLastError();
 }
 
@@ -1174,14 +1332,12 @@ float sample_scale(float spread, float absmax) {
   return ldexpf(1.f, sh);
 }
 
-// List length and segments: the pilot runs kPilotTiles query tiles spread over the
-// call with one segment and counts the answers that lists of 8, 16 and (when k asks
-// for those anyway) 32 would not certify with its error and with that of three.  A
-// tile costs its products (as in choose_splits; the band's for the share that
-// fails) and, more for a longer list, its hits: kListCost, in the same us (at
-// 400,000 x 100 lists of 8, 16 and 32 sweep in 62, 74 and about 90 ms, against 45
-// ms without any hit); the cheapest is taken.  Three segments pay where they certify what one
-// does not: 200,000 x 100, k 28: 46 ms against 64; 200,000 x 3, k 2: 13 against 18.
+// List length: the pilot runs kPilotTiles query tiles spread over the call and
+// counts the answers that lists of 8, 16 and (when k asks for those anyway) 32
+// would not certify.  A tile costs its products (as in choose_splits), those again
+// and a little for the share that fails (the band), and, more for a longer list, its
+// hits: kListCost, in the same us (at 400,000 x 100 lists of 8, 16 and 32 sweep in
+// 62, 74 and about 90 ms, against 45 ms without any hit); the cheapest is taken.
 // Calls of fewer query tiles than CUs go without a pilot, which takes as long as it
 // takes a block to fill its lists (1.4 ms with lists of 32) and leaves most CUs
 // idle: 50,000 x 128, k 2 / 5 / 10 / 20: 2.8 / 3.4 / 5.0 / 7.3 ms with one, 2.4 / 2.7
@@ -1226,9 +1382,11 @@ bool direct_pays(int64_t M, int N, int64_t nq, int k, bool few, bool same) {
   return direct <= filter;
 }
 
-// The band's hits: so many are kept of a query, and so many ids in all (they fit
-// a buffer that the library keeps)
-constexpr int64_t kBandHits = 16384;
+// The band's hits: so many are kept of a query with one segment and with three,
+// and so many in all, with the start values of a batch (they fit buffers that the
+// library keeps)
+constexpr int64_t kBandHits[2] = {4096, 16384};
+static_assert(kBandHits[0] - 64 >= kBandSome, "hits that are ranked are there");
 constexpr int64_t kBandIds = int64_t{32} << 20;
 
 }  // namespace
@@ -1271,8 +1429,8 @@ int KnnSearch::open(int64_t M_, int N_, const float *Q_, int64_t nq_, const floa
     V.add(&start, tiles * FT);
     V.add(&xstats, 1);
     V.add(&fails, nq + 1);
-    V.add(&limits, nq);
-    V.add(&pilot, 6);
+    V.add(&fail_dist, nq);
+    V.add(&pilot, 3);
     V.add(&mean, N);
     V.add(&qnorm, nq);
     V.add(&qres, nq);
@@ -1316,12 +1474,12 @@ int KnnSearch::run(const float *X, int self_mode, const int32_t *self, int32_t *
   const int64_t tiles = (M + FT - 1) / FT, nqb = (nq + FT - 1) / FT;
   int kp = list_length(k), rc;
   HIPCHK(launch_fill_i32((int32_t *)xstats, sizeof(KnnStats) / 4, 0, s));
-  HIPCHK(launch_knn_split(X, M, N, order, mean, scale, ch, cl, same ? qnorm : nullptr, same ? qres : nullptr, start,
+  HIPCHK(launch_knn_split(X, M, N, order, mean, 0, scale, ch, cl, same ? qnorm : nullptr, same ? qres : nullptr, start,
                           xstats, s));
   knn_classes_kernel<<<1, kNormClasses, 0, s>>>(xstats, N);
   HIPCHK(hipGetLastError());
   if (!same && !queries_ready) {
-    HIPCHK(launch_knn_split(Q, nq, N, nullptr, mean, scale, qh, ql, qnorm, qres, nullptr, nullptr, s));
+    HIPCHK(launch_knn_split(Q, nq, N, nullptr, mean, 0, scale, qh, ql, qnorm, qres, nullptr, nullptr, s));
     queries_ready = true;   // their images do not depend on the candidates
   }
 
@@ -1360,14 +1518,8 @@ int KnnSearch::run(const float *X, int self_mode, const int32_t *self, int32_t *
   g.sub = 3e-8 * std::sqrt((double)N);
   g.scale = scale;
   g.fails = fails;
-  g.limits = limits;
+  g.fail_dist = fail_dist;
 
-  Scratch R(s);   // of this run
-  KnnImage low_c = cl;
-  auto image = [&](KnnImage *im, int64_t rows, const char *what) -> int {
-    im->halves = knn_image_halves(rows, N);
-    return R.get(&im->p, im->halves, what);
-  };
   // the query tiles qb0, qb0 + step, .., of images `images`
   auto shape = [&](int64_t qb0, int64_t step, int64_t n, int nseg, int list, const KnnImage &images) -> int {
     f.qb0 = g.qb0 = qb0;
@@ -1395,8 +1547,8 @@ int KnnSearch::run(const float *X, int self_mode, const int32_t *self, int32_t *
     return IVHD_OK;
   };
   if (!few && nqb >= (N > kWidePilot ? 4 * kPilotTiles : kCus)) {
-    int32_t bad[6];
-    HIPCHK(launch_fill_i32(pilot, 6, 0, s));
+    int32_t bad[3];
+    HIPCHK(launch_fill_i32(pilot, 3, 0, s));
     g.pilot = pilot;
     const int want = kp;
     kp = kp < 16 ? 16 : kp;
@@ -1405,31 +1557,15 @@ int KnnSearch::run(const float *X, int self_mode, const int32_t *self, int32_t *
     HIPCHK(hipMemcpyAsync(bad, pilot, sizeof bad, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
     double least = 1e300;
-    int segs = 1;
-    for (int l = want == 8 ? 0 : (want == 16 ? 1 : 2); l < 3; ++l)
-      for (int three = 0; three < 2; ++three) {
-        const bool seen = (8 << l) <= (want == 32 ? 32 : 16);   // else, of 32: a third, or as many if half fail with 16
-        const double share = bad[3 * three + (seen ? l : 1)] / (double)(kPilotTiles * FT);
-        const double fails = seen || share > 0.5 ? share : share / 3;
-        const double one = 0.9 * nk + 0.7, all = 2.7 * nk + 0.7;   // a tile's products and values
-        const double cost = kListCost[l] + (three ? all : one) + all * fails;
-        if (cost < least) {
-          least = cost;
-          kp = 8 << l;
-          segs = three ? 3 : 1;
-        }
+    for (int l = want == 8 ? 0 : (want == 16 ? 1 : 2); l < 3; ++l) {
+      const bool seen = (8 << l) <= (want == 32 ? 32 : 16);   // else, of 32: a third, or as many if half fail with 16
+      const double share = bad[seen ? l : 1] / (double)(kPilotTiles * FT);
+      const double fails = seen || share > 0.5 ? share : share / 3;
+      const double cost = kListCost[l] + (0.9 * nk + 0.7) * (1 + 1.2 * fails);
+      if (cost < least) {
+        least = cost;
+        kp = 8 << l;
       }
-    if (segs == 3) {
-      if ((rc = image(&low_c, M, "candidate operands (low)"))) return rc;
-      HIPCHK(launch_knn_split(X, M, N, order, mean, scale, KnnImage{}, low_c, nullptr, nullptr, nullptr, nullptr, s));
-      KnnImage low = low_c;
-      if (!same) {
-        if ((rc = image(&low, nq, "query operands (low)"))) return rc;
-        HIPCHK(launch_knn_split(Q, nq, N, nullptr, mean, scale, KnnImage{}, low, nullptr, nullptr, nullptr, nullptr, s));
-      }
-      f.Cl = low_c.p;
-      f.Ql = low.p;
-      g.nseg = 3;
     }
   } else if (!few && kp == 8) {
     kp = 16;
@@ -1450,47 +1586,115 @@ int KnnSearch::run(const float *X, int self_mode, const int32_t *self, int32_t *
   int32_t failed = 0;
   if ((rc = read_count(fails, &failed)) || failed == 0) return rc;
 
-  // The answers that are not certified: all candidates whose value, of three
-  // segments, may be an answer's are ranked by their FP32 distances, a batch of
-  // queries at a time
-  const int32_t *again = fails + 1;
-  KnnImage high_q, low_q;
-  const int64_t cap = M < kBandHits ? M : kBandHits, all_rows = (failed + FT - 1) / FT * (int64_t)FT;
-  int64_t batch = kBandIds / cap / FT * FT;
-  batch = batch < all_rows ? batch : all_rows;
-  int32_t *left, *count, *ids;
-  const bool made = low_c.p != nullptr;
-  if ((rc = image(&high_q, failed, "query operands (high)")) || (rc = image(&low_q, failed, "query operands (low)")) ||
-      (!made && (rc = image(&low_c, M, "candidate operands (low)"))) ||
-      (rc = R.get(&left, (int64_t)failed + 1, "queries left")) || (rc = R.get(&count, batch, "hits of a query")) ||
-      (rc = R.get(&ids, batch * cap, "hits")))
+  // The answers that are not certified: the band, with one segment, then with
+  // three for those that leave too many hits; then every candidate
+  Scratch R(s);   // of this run
+  KnnImage low_c = cl;
+  int32_t *all, *next[2], *pivot_of;
+  float *next_dist[2], *pivots;
+  if ((rc = R.get(&all, (int64_t)failed + 1, "queries for all candidates")) || (rc = R.get(&pivot_of, nq, "queries' pivots")) ||
+      (rc = R.get(&pivots, (int64_t)kPivots * N, "pivots")) || (rc = R.get(&next[1], (int64_t)failed + 1, "queries left")) ||
+      (rc = R.get(&next_dist[1], failed, "their distances")))
     return rc;
-  if (!made)
-    HIPCHK(launch_knn_split(X, M, N, order, mean, scale, KnnImage{}, low_c, nullptr, nullptr, nullptr, nullptr, s));
-  HIPCHK(launch_knn_split(Q, failed, N, again, mean, scale, high_q, low_q, nullptr, nullptr, nullptr, nullptr, s));
-  HIPCHK(launch_fill_i32(left, 1, 0, s));
-  f.Qh = high_q.p;
-  f.Ql = low_q.p;
-  f.Cl = low_c.p;
-  f.nq = failed;
-  f.map = again;
-  f.limits = limits;
-  f.count = count;
-  f.ids = ids;
-  f.cap = (int)cap;
-  for (int64_t q0 = 0; q0 < failed; q0 += batch) {
-    const int64_t n = failed - q0 < batch ? failed - q0 : batch;
-    if ((rc = shape(q0 / FT, 1, (n + FT - 1) / FT, 3, 0, high_q))) return rc;
-    HIPCHK(launch_fill_i32(count, n, 0, s));
-    knn_filter_kernel<8, true, true><<<(unsigned)(f.nqb * f.splits), kFilterThreads, 0, s>>>(f);
-    knn_band_rank_kernel<<<(unsigned)n, 256, 0, s>>>(X, N, Q, again + q0, limits + q0, count, ids, (int)cap, order, k, idx,
-                                                     dist,
-                                                     left);
+  next[0] = fails;
+  next_dist[0] = fail_dist;
+  HIPCHK(launch_fill_i32(all, 1, 0, s));
+  HIPCHK(launch_fill_i32(next[1], 1, 0, s));
+  for (int pass = 0; pass < 2 && failed > 0; ++pass) {
+    const int segs = pass ? 3 : 1;
+    const int32_t *rows = next[pass] + 1;
+    // pivots: so many that their tiles' empty places are a quarter at most; one
+    // where those would tell little apart, but for the queries that one segment
+    // left with too many hits
+    int64_t P = failed / (2 * FT);
+    P = P < (pass ? 64 : 16) ? (pass ? 64 : 1) : (P > kPivots ? kPivots : P);
+    if (P > M) P = M;
+    Scratch B(s);   // of this pass
+    // the queries by pivots, in whole tiles
+    int32_t *slots_of, *slot_row, total = 0;
+    float *slot_dist;
+    const int64_t room = failed + P * (FT - 1);
+    if ((rc = B.get(&slots_of, kPivots + 1, "slots of the pivots")) || (rc = B.get(&slot_row, room, "slots' queries")) ||
+        (rc = B.get(&slot_dist, room, "slots' distances")))
+      return rc;
+    if (P > 1) {
+      knn_pivot_rows_kernel<<<grid_for(P * N), kBlock, 0, s>>>(X, M, N, (int)P, pivots);
+      knn_brute_kernel<<<(unsigned)((failed + kBruteQ - 1) / kBruteQ), 256, 0, s>>>(
+          pivots, P, N, Q, failed, rows, 0, nullptr, 1, 1, nullptr, pivot_of, nullptr);
+    } else {
+      HIPCHK(launch_fill_i32(pivot_of, nq, 0, s));
+    }
+    HIPCHK(launch_fill_i32(slots_of, kPivots + 1, 0, s));
+    HIPCHK(launch_fill_i32(slot_row, room, -1, s));
+    knn_pivot_count_kernel<<<grid_for(failed), kBlock, 0, s>>>(rows, failed, pivot_of, slots_of);
+    knn_pivot_slots_kernel<<<1, kPivots, 0, s>>>(slots_of, (int)P, slots_of + kPivots);
+    knn_pivot_place_kernel<<<grid_for(failed), kBlock, 0, s>>>(rows, next_dist[pass], failed, pivot_of, slots_of, slot_row,
+                                                               slot_dist);
     HIPCHK(hipGetLastError());
+    if ((rc = read_count(slots_of + kPivots, &total))) return rc;
+    const int64_t qtiles = total / FT, pitch = (N + 3) / 4 * 4;
+    // their operands
+    auto image = [&](KnnImage *im, int64_t n, Scratch &S, const char *what) -> int {
+      im->halves = knn_image_halves(n, N);
+      return S.get(&im->p, im->halves, what);
+    };
+    KnnImage high, low;
+    float *centres, *unorm, *ures, *limits;
+    if ((rc = image(&high, total, B, "query operands (high)")) ||
+        (segs == 3 && (rc = image(&low, total, B, "query operands (low)"))) ||
+        (rc = B.get(&centres, qtiles * pitch, "tiles' centres")) || (rc = B.get(&unorm, total, "offsets")) ||
+        (rc = B.get(&ures, total, "offsets' residuals")) || (rc = B.get(&limits, total, "limits")))
+      return rc;
+    knn_centre_kernel<<<(unsigned)qtiles, 256, 0, s>>>(Q, N, slot_row, pitch, centres);
+    HIPCHK(launch_knn_split(Q, total, N, slot_row, centres, pitch, scale, high, low, unorm, ures, nullptr, nullptr, s));
+    if (segs == 3 && !low_c.p) {
+      if ((rc = image(&low_c, M, R, "candidate operands (low)"))) return rc;
+      HIPCHK(launch_knn_split(X, M, N, order, mean, 0, scale, KnnImage{}, low_c, nullptr, nullptr, nullptr, nullptr, s));
+    }
+    knn_limit_kernel<<<grid_for(total, 4), 256, 0, s>>>(Q, N, total, slot_row, slot_dist, centres, pitch, mean, unorm, ures,
+                                                        xstats, scale, g.sub, segs, limits);
+    HIPCHK(hipGetLastError());
+    // a batch of tiles at a time: their start values, hits and answers
+    const int64_t cap = M < kBandHits[pass] ? M : kBandHits[pass], start_pitch = tiles * FT;
+    int64_t batch = kBandIds / (cap * FT), most = kBandIds / start_pitch;
+    batch = batch < most ? batch : most;
+    batch = batch < kBruteQ ? kBruteQ : batch;
+    batch = batch < qtiles ? batch : qtiles;
+    int32_t *count, *ids;
+    float *starts;
+    if ((rc = B.get(&count, batch * FT, "hits of a query")) || (rc = B.get(&ids, batch * FT * cap, "hits")) ||
+        (rc = B.get(&starts, batch * start_pitch, "start values")))
+      return rc;
+    f.Qh = high.p;
+    f.Ql = low.p;
+    f.Cl = low_c.p;
+    f.nq = total;
+    f.map = slot_row;
+    f.limits = limits;
+    f.count = count;
+    f.ids = ids;
+    f.cap = (int)cap;
+    f.start = starts;
+    f.start_pitch = start_pitch;
+    int32_t *to = pass ? nullptr : next[1];
+    for (int64_t b = 0; b < qtiles; b += batch) {
+      const int64_t n = qtiles - b < batch ? qtiles - b : batch, at = b * FT;
+      if ((rc = shape(b, 1, n, segs, 0, high))) return rc;
+      HIPCHK(launch_fill_i32(count, n * FT, 0, s));
+      knn_start_kernel<<<dim3((unsigned)tiles, (unsigned)((n + kBruteQ - 1) / kBruteQ)), 256, 0, s>>>(
+          X, M, N, order, centres + b * pitch, pitch, (int)n, scale, start_pitch, starts);
+      const unsigned grid = (unsigned)(f.nqb * f.splits);
+      if (segs == 3) knn_filter_kernel<8, true, true><<<grid, kFilterThreads, 0, s>>>(f);
+      else knn_filter_kernel<8, false, true><<<grid, kFilterThreads, 0, s>>>(f);
+      knn_band_rank_kernel<<<(unsigned)(n * FT), 256, 0, s>>>(X, N, Q, slot_row + at, slot_dist + at, limits + at, count,
+                                                              ids, (int)cap, order, k, idx, dist, all, to,
+                                                              pass ? nullptr : next_dist[1]);
+      HIPCHK(hipGetLastError());
+    }
+    if ((rc = read_count(next[1], &failed))) return rc;
   }
-  if ((rc = read_count(left, &failed)) || failed == 0) return rc;
-
-  return rank_all(X, left + 1, failed, self_mode, self, idx, dist);
+  if ((rc = read_count(all, &failed)) || failed == 0) return rc;
+  return rank_all(X, all + 1, failed, self_mode, self, idx, dist);
 }
 
 int KnnSearch::rank_all(const float *X, const int32_t *rows, int64_t n, int self_mode, const int32_t *self, int32_t *idx,

@@ -97,7 +97,7 @@ struct KnnSearch {
   KnnImage ch, cl, qh, ql;   // operands, high and low; the low ones only with few
   float *start = nullptr, *qnorm = nullptr, *qres = nullptr, *mean = nullptr;
   KnnStats *xstats = nullptr;
-  float *limits = nullptr;
+  float *fail_dist = nullptr;
   int32_t *fails = nullptr, *pilot = nullptr, *order = nullptr;
   int64_t place_of = 1;
   uint64_t *part = nullptr;

@@ -50,15 +50,21 @@ def test_queries(ivhd, M, N, Q, k, shift):
         assert np.array_equal(dist[i], ((Xh[want] - qh[i]) ** 2).sum(1))
 
 
-def test_small_calls_are_not_slower_than_launches(ivhd):
-    """300 x 3, k 2: a fill, two scans of the points and one search."""
+def test_small_calls_take_a_few_launches(ivhd):
+    """300 x 3, k 2, beside a scan of the same points for their neighbours in FP64
+    (72 us): 99 us, 273 with the filter's lists."""
     import time
     X = torch.randn((300, 3), device="cuda")
-    ivhd.ivhd_knn_build(X, 2)
-    best = 1.0
-    for _ in range(20):
-        torch.cuda.synchronize()
-        t = time.perf_counter()
-        ivhd.ivhd_knn_build(X, 2)
-        best = min(best, time.perf_counter() - t)
-    assert best < 180e-6   # 95 us; 195 with the search before the filter, 273 with the filter's lists
+    rows = torch.arange(300, device="cuda", dtype=torch.int32)
+
+    def best(f):
+        f()
+        t = []
+        for _ in range(20):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            f()
+            t.append(time.perf_counter() - t0)
+        return min(t)
+
+    assert best(lambda: ivhd.ivhd_knn_build(X, 2)) < 2.5 * best(lambda: ivhd.ivhd_eval_neighbours(X, rows, 10))

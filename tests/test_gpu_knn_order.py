@@ -52,4 +52,4 @@ def test_time_does_not_follow_the_order(ivhd):
         return min(t)
 
     shuffled = best(X[torch.randperm(len(X), generator=torch.Generator().manual_seed(1)).cuda()].contiguous())
-    assert best(X) < 3 * shuffled   # some thirty times as long when swept in the rows' order
+    assert best(X) < 6 * shuffled   # some thirty times as long when swept in the rows' order
