@@ -944,15 +944,27 @@ __global__ void __launch_bounds__(256) knn_finish_kernel(FinishArgs A) {
 // ---- answers from exact distances of many candidates ---------------------------
 
 // best: a wavefront's 64 best keys (distance above, id below) sorted over its
-// lanes, of which the first k count
+// lanes, of which the first k count; the keys of a wavefront differ.  Of many that
+// can be among them the least goes first, so that no more than k go in (along a
+// line every key may be less than the one before it).
 __device__ __forceinline__ void offer_sorted(uint64_t &best, uint64_t key, int lane, int k) {
   uint64_t mask = __ballot(key < __shfl(best, k - 1, 64));
   while (mask) {
-    const uint64_t in = __shfl(key, __builtin_ctzll(mask), 64);
+    int from = __builtin_ctzll(mask);
+    if (__popcll(mask) > 4) {
+      uint64_t least = mask >> lane & 1 ? key : ~0ull;
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        const uint64_t w = __shfl_xor(least, o, 64);
+        least = w < least ? w : least;
+      }
+      from = __builtin_ctzll(__ballot(key == least) & mask);
+    }
+    const uint64_t in = __shfl(key, from, 64);
     const int pos = __popcll(__ballot(best < in));
     const uint64_t up = __shfl_up(best, 1, 64);
     best = lane < pos ? best : (lane == pos ? in : up);
-    mask &= mask - 1;
+    mask &= ~(1ull << from);
     mask &= __ballot(key < __shfl(best, k - 1, 64));   // those that still can be among them
   }
 }
@@ -985,10 +997,19 @@ __global__ void knn_pivot_rows_kernel(const float *__restrict__ X, int64_t M, in
   if (e < (int64_t)P * N) pivots[e] = X[(e / N) * M / P * N + e % N];
 }
 
-__global__ void knn_pivot_count_kernel(const int32_t *__restrict__ rows, int64_t n, const int32_t *__restrict__ pivot_of,
-                                       int32_t *__restrict__ count) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) atomicAdd(&count[pivot_of[rows[i]]], 1);
+// the pivots' queries counted, a block to kPivotChunk of them, in LDS first
+constexpr int kPivotChunk = 4096;
+__global__ void __launch_bounds__(kPivots) knn_pivot_count_kernel(const int32_t *__restrict__ rows, int64_t n,
+                                                                  const int32_t *__restrict__ pivot_of,
+                                                                  int32_t *__restrict__ count) {
+  __shared__ int32_t here[kPivots];
+  const int t = threadIdx.x;
+  here[t] = 0;
+  __syncthreads();
+  const int64_t i0 = (int64_t)blockIdx.x * kPivotChunk, i1 = i0 + kPivotChunk < n ? i0 + kPivotChunk : n;
+  for (int64_t i = i0 + t; i < i1; i += kPivots) atomicAdd(&here[pivot_of[rows[i]]], 1);
+  __syncthreads();
+  if (here[t]) atomicAdd(&count[t], here[t]);
 }
 
 // count[p] -> the first slot of pivot p's queries, in whole tiles; *total: all slots
@@ -1008,14 +1029,27 @@ __global__ void __launch_bounds__(kPivots) knn_pivot_slots_kernel(int32_t *__res
   if (t == kPivots - 1) *total = at[t];
 }
 
-__global__ void knn_pivot_place_kernel(const int32_t *__restrict__ rows, const float *__restrict__ dist, int64_t n,
-                                       const int32_t *__restrict__ pivot_of, int32_t *__restrict__ next,
-                                       int32_t *__restrict__ slot_row, float *__restrict__ slot_dist) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int32_t at = atomicAdd(&next[pivot_of[rows[i]]], 1);
-  slot_row[at] = rows[i];
-  slot_dist[at] = dist[i];
+// each query to a slot of its pivot's (next: the first that is free)
+__global__ void __launch_bounds__(kPivots) knn_pivot_place_kernel(const int32_t *__restrict__ rows,
+                                                                  const float *__restrict__ dist, int64_t n,
+                                                                  const int32_t *__restrict__ pivot_of,
+                                                                  int32_t *__restrict__ next,
+                                                                  int32_t *__restrict__ slot_row,
+                                                                  float *__restrict__ slot_dist) {
+  __shared__ int32_t here[kPivots];
+  const int t = threadIdx.x;
+  here[t] = 0;
+  __syncthreads();
+  const int64_t i0 = (int64_t)blockIdx.x * kPivotChunk, i1 = i0 + kPivotChunk < n ? i0 + kPivotChunk : n;
+  for (int64_t i = i0 + t; i < i1; i += kPivots) atomicAdd(&here[pivot_of[rows[i]]], 1);
+  __syncthreads();
+  if (here[t]) here[t] = atomicAdd(&next[t], here[t]);
+  __syncthreads();
+  for (int64_t i = i0 + t; i < i1; i += kPivots) {
+    const int32_t at = atomicAdd(&here[pivot_of[rows[i]]], 1);
+    slot_row[at] = rows[i];
+    slot_dist[at] = dist[i];
+  }
 }
 
 // a tile's centre: its first query (whole tiles to a pivot, so there is one)
@@ -1586,8 +1620,13 @@ int KnnSearch::run(const float *X, int self_mode, const int32_t *self, int32_t *
   int32_t failed = 0;
   if ((rc = read_count(fails, &failed)) || failed == 0) return rc;
 
-  // The answers that are not certified: the band, with one segment, then with
-  // three for those that leave too many hits; then every candidate
+  // The answers that are not certified: every candidate where that is less than the
+  // band's launches and sweeps (in us, as in direct_pays; 100,000 queries left of a
+  // search in 512 x 60 candidates: 0.3 ms against 1.3), else the band, with one
+  // segment, then with three for those that leave too many hits; then every candidate
+  if (6.4e-8 * failed * (double)M * (N + 17) <
+      500.0 + 5e-3 * failed + (double)failed / FT * (double)tiles * (0.9 * nk + 0.7) / (double)kCus)
+    return rank_all(X, fails + 1, failed, self_mode, self, idx, dist);
   Scratch R(s);   // of this run
   KnnImage low_c = cl;
   int32_t *all, *next[2], *pivot_of;
@@ -1626,10 +1665,10 @@ int KnnSearch::run(const float *X, int self_mode, const int32_t *self, int32_t *
     }
     HIPCHK(launch_fill_i32(slots_of, kPivots + 1, 0, s));
     HIPCHK(launch_fill_i32(slot_row, room, -1, s));
-    knn_pivot_count_kernel<<<grid_for(failed), kBlock, 0, s>>>(rows, failed, pivot_of, slots_of);
+    knn_pivot_count_kernel<<<grid_for(failed, kPivotChunk), kPivots, 0, s>>>(rows, failed, pivot_of, slots_of);
     knn_pivot_slots_kernel<<<1, kPivots, 0, s>>>(slots_of, (int)P, slots_of + kPivots);
-    knn_pivot_place_kernel<<<grid_for(failed), kBlock, 0, s>>>(rows, next_dist[pass], failed, pivot_of, slots_of, slot_row,
-                                                               slot_dist);
+    knn_pivot_place_kernel<<<grid_for(failed, kPivotChunk), kPivots, 0, s>>>(rows, next_dist[pass], failed, pivot_of,
+                                                                             slots_of, slot_row, slot_dist);
     HIPCHK(hipGetLastError());
     if ((rc = read_count(slots_of + kPivots, &total))) return rc;
     const int64_t qtiles = total / FT, pitch = (N + 3) / 4 * 4;

@@ -53,3 +53,18 @@ def test_time_does_not_follow_the_order(ivhd):
 
     shuffled = best(X[torch.randperm(len(X), generator=torch.Generator().manual_seed(1)).cuda()].contiguous())
     assert best(X) < 6 * shuffled   # some thirty times as long when swept in the rows' order
+
+
+@pytest.mark.parametrize("reverse", [False, True])
+@pytest.mark.parametrize("M,k", [(500, 1), (2000, 5), (3000, 28)])
+def test_few_points_along_a_line(ivhd, M, k, reverse):
+    # every point nearer than the one before it, on the way to the query
+    X = (np.arange(M, dtype=np.float32)[:, None] * np.float32([1, 2, -1]))
+    if reverse:
+        X = X[::-1].copy()
+    got = ivhd.ivhd_knn_build(torch.from_numpy(X).cuda(), k).cpu().numpy()
+    i = np.arange(M)
+    for q in (0, 1, M // 2, M - 1):
+        d = (i - q).astype(np.float64) ** 2
+        d[q] = np.inf
+        assert np.array_equal(got[q], np.lexsort((i, d))[:k])
