@@ -795,19 +795,15 @@ __global__ void __launch_bounds__(kColsumThreads) head_backward_kernel(const flo
   }
 }
 
-// column sums over row chunks: part[c][j] = sum_{r in chunk c} f(r, j) for
-//   mode 0: BF16 matrix X[R][J]
-//   mode 1: dZ (FP32 [R][2]) x H (BF16 [R][K]): j = o*K + k -> dZ[r][o] H[r][k]  (dW3)
-//   mode 2: FP32 matrix [R][J]            (bias gradient of the head, later levels)
+// column sums of the FP32 matrix X [R][J] over row chunks (the head's bias
+// gradient, and the later levels of a sum): part[c][j] = sum_{r in chunk c} X[r][j]
 // A block of kColsumLanes x 32 threads covers 32 V-column groups of one chunk
 // of kColsumRows rows: row lane ty sums rows ty, ty + kColsumLanes, ... in
 // order, then the lane sums are added in order of ty (deterministic).  V = 4
-// needs J (and K) multiples of 4 and a 16-byte aligned source; eight rows in
-// flight, as with four and V = 8 57,344 x 512 took 24 us.
+// needs J a multiple of 4 and a 16-byte aligned source; eight rows in flight.
 template <int V>
-__global__ void __launch_bounds__(kColsumThreads) colsum_kernel(int mode, const void *__restrict__ Xp,
-                                                    const float *__restrict__ dZ, int64_t R, int64_t J, int64_t K,
-                                                    float *__restrict__ part) {
+__global__ void __launch_bounds__(kColsumThreads) colsum_kernel(const float *__restrict__ X, int64_t R, int64_t J,
+                                                                float *__restrict__ part) {
   __shared__ float red[kColsumLanes][32 * V + 1];
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
   const int64_t j0 = ((int64_t)blockIdx.x * 32 + tx) * V;
@@ -817,32 +813,16 @@ __global__ void __launch_bounds__(kColsumThreads) colsum_kernel(int mode, const 
 #pragma unroll
   for (int e = 0; e < V; ++e) acc[e] = 0.f;
   if (j0 < J) {
-    const int64_t half = mode == 1 ? j0 / K : 0, col = mode == 1 ? j0 % K : j0, ld = mode == 1 ? K : J;
 #pragma unroll 8
     for (int64_t r = r0 + ty; r < r1; r += kColsumLanes) {
-      float x[V];
-      if (mode == 2) {
-        const float *X = static_cast<const float *>(Xp) + r * J + j0;
-        if (V == 4) {
-          const floatx4 v = *reinterpret_cast<const floatx4 *>(X);
+      const float *x = X + r * J + j0;
+      if (V == 4) {
+        const floatx4 v = *reinterpret_cast<const floatx4 *>(x);
 #pragma unroll
-          for (int e = 0; e < V; ++e) x[e] = v[e];
-        } else {
-          x[0] = X[0];
-        }
+        for (int e = 0; e < V; ++e) acc[e] += v[e];
       } else {
-        const uint16_t *X = static_cast<const uint16_t *>(Xp) + r * ld + col;
-        const float w = mode == 1 ? dZ[2 * r + half] : 1.f;
-        if (V == 4) {
-          const U16x4 v = *reinterpret_cast<const U16x4 *>(X);
-#pragma unroll
-          for (int e = 0; e < V; ++e) x[e] = mode == 1 ? w * bf2f(v.v[e]) : bf2f(v.v[e]);
-        } else {
-          x[0] = mode == 1 ? w * bf2f(X[0]) : bf2f(X[0]);
-        }
+        acc[0] += x[0];
       }
-#pragma unroll
-      for (int e = 0; e < V; ++e) acc[e] += x[e];
     }
   }
 #pragma unroll
@@ -889,11 +869,6 @@ __global__ void glorot_kernel(float *__restrict__ w, int64_t n, int fan_in, int 
   const float u = (float)(z >> 40) * (1.0f / 16777216.0f);   // [0, 1)
   const float s = sqrtf(6.0f / (float)(fan_in + fan_out));
   w[e] = (2.f * u - 1.f) * s;
-}
-
-__global__ void scale_dz_kernel(float *__restrict__ dz, int64_t n, const float *__restrict__ s) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < n) dz[e] *= *s;
 }
 
 }  // namespace
@@ -988,24 +963,20 @@ int64_t colsum_workspace(int64_t R, int64_t J) {
 // Column sums as a tree: each level sums kColsumRows consecutive rows into
 // partials [ceil(rows / kColsumRows)][J], until one row is left (written to
 // out).  Levels ping-pong between two regions of ws.
-hipError_t launch_colsum(int mode, const void *X, const float *dZ, int64_t R, int64_t J, int64_t K, float *ws,
-                         float *out, hipStream_t s) {
+hipError_t launch_colsum(const float *X, int64_t R, int64_t J, float *ws, float *out, hipStream_t s) {
   if (R < 1 || (R + kColsumRows - 1) / kColsumRows > 65535) return hipErrorInvalidValue;
   const int64_t c0 = (R + kColsumRows - 1) / kColsumRows;
   float *buf[2] = {ws, ws + c0 * J};
-  const void *src = X;
+  const float *src = X;
   int64_t rows = R;
   for (int level = 0;; ++level) {
-    const int m = level == 0 ? mode : 2;
     const int64_t chunks = (rows + kColsumRows - 1) / kColsumRows;
     float *dst = chunks == 1 ? out : buf[level & 1];
-    const bool vec4 = J % 4 == 0 && (m != 1 || K % 4 == 0) && (reinterpret_cast<uintptr_t>(src) & 15) == 0;
+    const bool vec4 = J % 4 == 0 && (reinterpret_cast<uintptr_t>(src) & 15) == 0;
     if (vec4)
-      colsum_kernel<4><<<dim3((unsigned)((J / 4 + 31) / 32), (unsigned)chunks), kColsumThreads, 0, s>>>(m, src, dZ, rows, J,
-                                                                                           K, dst);
+      colsum_kernel<4><<<dim3((unsigned)((J / 4 + 31) / 32), (unsigned)chunks), kColsumThreads, 0, s>>>(src, rows, J, dst);
     else
-      colsum_kernel<1><<<dim3((unsigned)((J + 31) / 32), (unsigned)chunks), kColsumThreads, 0, s>>>(m, src, dZ, rows, J, K,
-                                                                                       dst);
+      colsum_kernel<1><<<dim3((unsigned)((J + 31) / 32), (unsigned)chunks), kColsumThreads, 0, s>>>(src, rows, J, dst);
     if (chunks == 1) break;
     src = dst;
     rows = chunks;
@@ -1032,7 +1003,7 @@ hipError_t launch_head_backward(const float *dZ, const uint16_t *W3, const uint1
                                                                                                       dH, part);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess || chunks == 1) return e;
-  return launch_colsum(2, part, nullptr, chunks, J, J, ws + chunks * J, out, s);
+  return launch_colsum(part, chunks, J, ws + chunks * J, out, s);
 }
 
 hipError_t launch_adam(float *w, const float *g, float *m, float *v, uint16_t *w16, int64_t n, float lr, float b1,
@@ -1045,11 +1016,6 @@ hipError_t launch_adam(float *w, const float *g, float *m, float *v, uint16_t *w
 hipError_t launch_glorot(float *w, int64_t n, int fan_in, int fan_out, uint64_t seed, uint64_t offset,
                          hipStream_t s) {
   glorot_kernel<<<grid_for(n), kBlock, 0, s>>>(w, n, fan_in, fan_out, seed, offset);
-  return hipGetLastError();
-}
-
-hipError_t launch_scale_dz(float *dz, int64_t n, const float *scale, hipStream_t s) {
-  scale_dz_kernel<<<grid_for(n), kBlock, 0, s>>>(dz, n, scale);
   return hipGetLastError();
 }
 

@@ -11,10 +11,10 @@
 //   dH1  = (dH2 W2) . [H1 > 0]            dW2 = dH2^T H1     db2 = sum dH2
 //                                         dW1 = dH1^T X_b    db1 = sum dH1
 //   Adam on all parameters with the gradients scaled by s, then BF16 copies.
-// The backward GEMMs read feature-major copies ([features][rows], rows
-// padded to a multiple of 8 with zeros) of X_b, H1 and dH2 and produce dH1
-// feature-major, so both operands of every GEMM are K-contiguous; db1 and
-// db2 are row sums of those copies.
+// The weight gradients multiply the row-major activations and gradients as they
+// are (both operands K-major); dH1 reads a transposed copy of W2, so that both its
+// operands are K-contiguous; db1 and db2 are column sums of the gradients.  A batch
+// whose width is not a multiple of 8 is copied to rows padded with zeros.
 #include <cmath>
 #include <mutex>
 #include <new>
@@ -171,7 +171,7 @@ int train_step_rows(ivhd_enc *e, const uint16_t *X, int64_t R, ivhd_edges *plan,
   }
   // head: its input gradient d2, and the sums over the rows of dz x a2 (dW3)
   HIPCHK(launch_head_backward(e->dz, e->w16 + e->oW3, e->a2, R, e->h2, e->d2, e->ws, e->g + e->oW3, s));
-  HIPCHK(launch_colsum(2, e->dz, nullptr, R, 2, 2, e->ws, e->g + e->ob3, s));
+  HIPCHK(launch_colsum(e->dz, R, 2, e->ws, e->g + e->ob3, s));
   HIPCHK(launch_bias_sum(e->d2, R, e->h2, e->ws, e->g + e->ob2, s));
   // layer 2: d1 = (d2 W2) * relu'(a1)
   GemmArgs gd = gemm(e->d2, e->w2T, R, e->h1, e->h2, e->h2, e->h2, e->d1, e->h1);

@@ -40,17 +40,15 @@ hipError_t launch_head_backward(const float *dZ, const uint16_t *W3, const uint1
 // column sums of the BF16 matrix X [R][J] (fixed order); ws: [bias_workspace(J)]
 int64_t bias_workspace(int64_t J);
 hipError_t launch_bias_sum(const uint16_t *X, int64_t R, int64_t J, float *ws, float *out, hipStream_t s);
-// column sums over R rows as a fixed-order tree of kColsumRows-row partial
-// sums (deterministic); see colsum_kernel for the modes.  ws must hold
-// colsum_workspace(R, J) floats.
+// column sums of the FP32 matrix X [R][J] as a fixed-order tree of kColsumRows-row
+// partial sums (deterministic).  ws must hold colsum_workspace(R, J) floats.
 constexpr int kColsumRows = 256;
 int64_t colsum_workspace(int64_t R, int64_t J);
+hipError_t launch_colsum(const float *X, int64_t R, int64_t J, float *ws, float *out, hipStream_t s);
 // out [C][ldo] = transpose of the BF16 matrix in [R][C], entries r >= R of
 // each out row zero (ldo >= R)
 hipError_t launch_transpose_bf16(const uint16_t *in, int64_t R, int64_t C, uint16_t *out, int64_t ldo,
                                  hipStream_t s);
-hipError_t launch_colsum(int mode, const void *X, const float *dZ, int64_t R, int64_t J, int64_t K, float *ws,
-                         float *out, hipStream_t s);
 hipError_t launch_adam(float *w, const float *g, float *m, float *v, uint16_t *w16, int64_t n, float lr, float b1,
                        float b2, float eps, int64_t t, float gscale, hipStream_t s);
 hipError_t launch_glorot(float *w, int64_t n, int fan_in, int fan_out, uint64_t seed, uint64_t offset,
