@@ -299,8 +299,15 @@ int ivhd_grad_edges_noalloc(const float *d_y, int64_t M, const int32_t *d_nn_idx
  * the row itself excluded.
  *   d_x    float32 [M][N], row-major (read only)
  *   d_idx  int32 [M][k] output, nearest first
- * 1 <= k <= min(28, M-1), N >= 1.  Allocates a temporary [M] float buffer
- * and synchronises the stream.                                              */
+ * 1 <= k <= min(28, M-1), N >= 1.  The rows are those of the order (FP32
+ * squared distance, the features summed in order; ties to the lower index):
+ * every answer is certified by a bound on the error of what found it, or ranked
+ * by the distances themselves.  The time grows where one product of 11-bit
+ * operands does not tell the neighbours apart (tight clusters far from each
+ * other, many equal rows).
+ * Temporaries: operands of 2 N_pad bytes a row (N_pad: N rounded up to 32;
+ * three times that, and the same for the queries, where answers are repeated),
+ * and lists and hits of some 100 to 400 MB.  Synchronises the stream.       */
 int ivhd_knn_build(const float *d_x, int64_t M, int32_t N, int32_t k, int32_t *d_idx,
                    void *stream);
 
@@ -361,7 +368,8 @@ int ivhd_rnn_mask(const int32_t *d_nn_idx, int64_t M, int32_t nn, const int32_t 
  *   d_q     float32 [Q][N] queries;  d_self int32 [Q] or NULL: row d_self[q]
  *           of X is excluded for query q (-1 = none)
  *   d_idx   int32 [Q][k];  d_dist float32 [Q][k] squared distances, or NULL
- * 1 <= k <= min(28, M-1).  Synchronises the stream.                         */
+ * 1 <= k <= min(28, M-1).  Order and temporaries as ivhd_knn_build.
+ * Synchronises the stream.                                                  */
 int ivhd_knn_query(const float *d_x, int64_t M, int32_t N, const float *d_q, int64_t Q,
                    const int32_t *d_self, int32_t k, int32_t *d_idx, float *d_dist,
                    void *stream);
