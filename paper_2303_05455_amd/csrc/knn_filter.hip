@@ -1404,8 +1404,8 @@ int64_t brute_splits(int64_t nq, int64_t M) {
 // query and 6 of a candidate, and for a pair of tiles as in choose_splits; the
 // distances take 110, 64 fs a pair and feature (81 % of the vector ALU) and as much
 // as 17 features for a pair's way through the lists.  300 x 3, k 2: 273 -> 97 us
-// (195 with the search before the filter); 128 x 64 and 50,000 queries: 356 -> 228
-// (252); 1,000 x 20: 307 -> 104.
+// (195 with the search before the filter); 128 x 64 and 50,000 queries: 356 -> 194
+// (252); 1,000 x 20, k 5: 307 -> 109 (764).
 bool direct_pays(int64_t M, int N, int64_t nq, int k, bool few, bool same) {
   const double pairs = (double)((nq + kBruteQ - 1) / kBruteQ * kBruteQ) * (double)((M + 255) / 256 * 256);
   const double blocks = (double)((nq + kBruteQ - 1) / kBruteQ) * (double)brute_splits(nq, M);
